@@ -1,5 +1,5 @@
-// GEMM kernels for gfx950: bf16 MFMA (LDS-tiled, fp32 accumulate) and a plain
-// fp32 kernel, both with the same fused epilogues (bias, residual, GELU,
+// GEMM kernels for gfx950: bf16 MFMA (LDS-tiled, fp32 accumulate) and an fp32 MFMA
+// kernel, both with the same fused epilogues (bias, residual, GELU,
 // GELU', scale) and the same causal short-cuts for attention operands.
 //
 // The linear layers of a block (y = x*W + b), their input gradients
@@ -790,77 +790,260 @@ static hipError_t launch_bf16_big(const GemmArgs &a, int ta, int tb, int ntiles,
 }
 
 // ---------------------------------------------------------------------------
-// fp32 kernel (no reduced-precision matrix path exists for fp32 on gfx950
-// other than real fp32): 64x64 tile, 16-wide K slices, 4x4 outputs per thread,
-// contraction accumulated in ascending k.
+// fp32 kernel: v_mfma_f32_32x32x2_f32 (full fp32 products and sums, no
+// reduced-precision split).  That instruction needs 64 clocks for 4096 flop, so
+// LDS and the load path are far from binding (a 32x32 result per wavefront
+// reads 16 bytes of LDS per clock and CU); what costs is everything that keeps
+// the matrix pipes waiting: too few tiles for 256 CUs and trips to memory.
+// Hence small tiles, operands requested two slices ahead (16-byte loads into
+// registers where alignment allows), two LDS buffers and one barrier per slice.
+//   64x64 tiles: 2x2 wavefronts, 32 contraction steps per slice
+//   32x32 tiles: the four wavefronts split every slice's 64 contraction steps
+//                and are summed through LDS at the end - four times the tiles
+//                where 64x64 ones would leave CUs idle
+// An operand sits in LDS as it sits in memory: [row][k] when its contraction
+// index is contiguous, else [k][row].  A lane feeds row L%32 and contraction
+// steps (L/32)*4 + s of every group of eight, s = 0..3, one step pair per MFMA;
+// both operands use the same assignment, so the pairing is immaterial.
+// Measured against the former vector-ALU kernel (64x64 tiles, 4-byte loads, no
+// prefetch): 1000x3072x768 265 -> 49 us, 128x128x512 34 -> 7 us, 4096^3 at 133-137
+// TFLOP/s of the 157 the matrix pipes offer; error against 64 bits 1.0e-6 -> 3.5e-7.
 // ---------------------------------------------------------------------------
-constexpr int FBM = 64, FBN = 64, FBK = 16;
+// descriptor of 2 GB from p on (offsets are 32 bits wide: the base moves with the slice)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void *p) {
+  return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 0x7ffffff0, 0x00020000);
+}
+constexpr int BUF_OUT = 0x7ffffff8;  // offset past the descriptor's range: the load returns zero and touches no memory
 
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs g, int ta, int tb) {
-  __shared__ float As[FBK][FBM + 4];
-  __shared__ float Bs[FBK][FBN + 4];
-  const int tid = threadIdx.x;
-  const int tile = blockIdx.x;
-  const int tm = tile / g.tiles_n, tn = tile % g.tiles_n;
-  const int m0 = tm * FBM, n0 = tn * FBN;
-  if (g.causal == CAUSAL_SKIP_UPPER && n0 > m0 + FBM - 1) return;
-  const int z = blockIdx.y, z1 = z / g.nb2, z2 = z % g.nb2;
-  const float *A = (const float *)g.A + z1 * g.sA1 + z2 * g.sA2;
-  const float *B = (const float *)g.B + z1 * g.sB1 + z2 * g.sB2;
-  const int64_t coff = z1 * g.sC1 + z2 * g.sC2;
-  int kbeg = 0, kend = g.K;
-  if (g.causal == CAUSAL_K_END) kend = min(g.K, m0 + FBM);
-  if (g.causal == CAUSAL_K_BEGIN) kbeg = (m0 / FBK) * FBK;
-
-  const int ty = tid / 16, tx = tid % 16;
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-
-  for (int k0 = kbeg; k0 < kend; k0 += FBK) {
-    // 64x16 elements per operand, 4 per thread; index so that the contiguous
-    // dimension of the source runs along consecutive threads
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int id = tid + i * 256;
-      int r, k;
-      if (ta) { r = id % FBM; k = id / FBM; } else { k = id % FBK; r = id / FBK; }
-      float v = 0.f;
-      if (m0 + r < g.M && k0 + k < kend)
-        v = ta ? A[(int64_t)(k0 + k) * g.lda + m0 + r] : A[(int64_t)(m0 + r) * g.lda + k0 + k];
-      As[k][r] = v;
-      if (tb) { r = id % FBN; k = id / FBN; } else { k = id % FBK; r = id / FBK; }
-      v = 0.f;
-      if (n0 + r < g.N && k0 + k < kend)
-        v = tb ? B[(int64_t)(k0 + k) * g.ldb + n0 + r] : B[(int64_t)(n0 + r) * g.ldb + k0 + k];
-      Bs[k][r] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < FBK; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+// Global -> registers -> LDS mover of one operand: R rows x BKF contraction steps per slice.  Buffer loads, so that
+// elements outside the operand are fetched from an out-of-range offset (zero) instead of behind a branch: a register
+// that is cleared under a condition makes the compiler wait for every load in flight before it reuses the register.
+// LD_VEC: 16-byte loads; LD_SCALAR: 4-byte loads for operands whose alignment does not allow them; LD_WIDE: leading
+// dimensions that a 32-bit offset within a slice cannot hold
+enum { LD_VEC = 0, LD_SCALAR = 1, LD_WIDE = 2 };
+template <int R, int BKF, int RC, int MODE>
+struct MoverF {
+  static constexpr int LEN = RC ? R : BKF;           // elements per line of memory (row of [row][k] / [k][row])
+  static constexpr int PITCH = LEN + 4;              // LDS pitch in floats: 16 bytes of padding spread the banks
+  static constexpr int SIZE = (RC ? BKF : R) * PITCH;
+  static constexpr int W = MODE == LD_VEC ? 4 : 1;   // elements per load
+  static constexpr int NL = R * BKF / 256 / W;       // loads per thread and slice
+  static constexpr int N = R * BKF / 256 / 4;        // 4-element registers per thread and slice
+  static constexpr int LS = 256 * W / LEN;           // lines between a thread's loads
+  static_assert(NL >= 1 && NL * 256 * W == R * BKF && 256 * W % LEN == 0, "the slice divides evenly over the threads");
+  const float *base;  // the tile's first row, contraction step 0
+  int64_t ld;
+  int rows, line, c;  // rows from the tile's first to the matrix's end; this thread's first line and its place in a line
+  __device__ __forceinline__ void init(const float *mat, int64_t ld_, int row0, int rows_, int tid) {
+    ld = ld_;
+    base = RC ? mat + row0 : mat + (int64_t)row0 * ld;
+    rows = rows_ - row0;
+    line = tid / (LEN / W);
+    c = (tid % (LEN / W)) * W;
   }
+  // contraction steps k0 .. k0 + BKF - 1; steps from kend on and rows past the matrix read as zero
+  __device__ __forceinline__ void load(f32x4_t (&r)[N], int k0, int kend) const {
+    const float *const b = base + (RC ? k0 * ld : (int64_t)k0);
+    const __amdgpu_buffer_rsrc_t rs = buffer_at(b);
+    const int off = (int)((line * ld + c) * 4);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = m0 + ty * 4 + i, col = n0 + tx * 4 + j;
-      if (row < g.M && col < g.N) epilogue_store<float>(g, coff, row, col, acc[i][j]);
+    for (int j = 0; j < NL; ++j) {
+      const int l = line + j * LS;
+      const bool in = (RC ? c : l) < rows && k0 + (RC ? l : c) < kend;
+      if (MODE == LD_VEC) {
+        union { u32x4_t u; f32x4_t f; } x;
+        x.u = __builtin_amdgcn_raw_buffer_load_b128(rs, in ? off + (int)(j * LS * ld * 4) : BUF_OUT, 0, 0);
+        r[j] = x.f;
+      } else if (MODE == LD_SCALAR) {
+        r[j / 4][j % 4] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, in ? off + (int)(j * LS * ld * 4) : BUF_OUT, 0, 0));
+      } else {
+        r[j / 4][j % 4] = in ? b[l * ld + c] : 0.f;
+      }
     }
+  }
+  __device__ __forceinline__ void store(const f32x4_t (&r)[N], float *lds) const {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      float *const p = lds + (line + j * LS) * PITCH + c;
+      if (MODE == LD_VEC) *(f32x4_t *)p = r[j];
+      else *p = r[j / 4][j % 4];
+    }
+  }
+  // the lane's four steps of the eight that start at k, of row
+  static __device__ __forceinline__ f32x4_t frag(const float *lds, int row, int k) {
+    if (!RC) return *(const f32x4_t *)(lds + row * PITCH + k);
+    f32x4_t v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = lds[(k + e) * PITCH + row];
+    return v;
+  }
+};
+
+// four consecutive columns of one row of C
+__device__ __forceinline__ void epilogue_store4_f32(const GemmArgs &g, int64_t coff, int row, int col, const f32x4_t acc,
+                                                    bool vec) {
+  if (!vec || col + 3 >= g.N) {
+#pragma unroll 1
+    for (int e = 0; e < 4; ++e) {
+      const float x = e == 0 ? acc[0] : e == 1 ? acc[1] : e == 2 ? acc[2] : acc[3];  // see epilogue_store4
+      if (col + e < g.N) epilogue_store<float>(g, coff, row, col + e, x);
+    }
+    return;
+  }
+  const int64_t idx = coff + (int64_t)row * g.ldc + col;
+  f32x4_t v = acc * g.alpha;
+  if (g.bias) v += *(const f32x4_t *)(g.bias + col);
+  if (g.epi == EPI_GELU) {
+    const f32x4_t h = {gelu_f(v[0]), gelu_f(v[1]), gelu_f(v[2]), gelu_f(v[3])};
+    *(f32x4_t *)((float *)g.out_act + idx) = v;
+    *(f32x4_t *)((float *)g.out_act2 + idx) = h;
+    return;
+  }
+  if (g.epi == EPI_DGELU) {
+    const f32x4_t a = *(const f32x4_t *)((const float *)g.aux + idx);
+    const f32x4_t dg = {dgelu_f(a[0]), dgelu_f(a[1]), dgelu_f(a[2]), dgelu_f(a[3])};
+    v *= dg;
+  }
+  if (g.resid) v += *(const f32x4_t *)(g.resid + idx);
+  if (g.out_f32) *(f32x4_t *)(g.out_f32 + idx) = v;
+  if (g.out_act) *(f32x4_t *)((float *)g.out_act + idx) = v;
 }
 
+template <int BM, int BN, int BKF, int WM, int WN, int KW, int TA, int TB, int MODE>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs g) {
+  static_assert(WM * WN * KW == 4 && BM == 32 * WM && BN == 32 * WN, "four wavefronts, one 32x32 result each");
+  typedef MoverF<BM, BKF, TA, MODE> MA;
+  typedef MoverF<BN, BKF, TB, MODE> MB;
+  constexpr int STAGE = MA::SIZE + MB::SIZE;
+  constexpr int KS = BKF / KW;  // contraction steps of a slice that one wavefront multiplies
+  static_assert(KS % 8 == 0 && (KW == 1 || 2 * STAGE >= 4 * 1024), "groups of eight steps; the exchange fits the buffers");
+  __shared__ __attribute__((aligned(16))) float lds[2 * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int kg = wave / (WM * WN), wm = (wave / WN) % WM, wn = wave % WN;
+  // tile numbering as in the bf16 kernels: contiguous runs per XCD, groups of g.grp tile rows walked column by column
+  const int nt = gridDim.x, bid = blockIdx.x, xcd = bid & 7, per = nt >> 3, rem = nt & 7;
+  const int tile = xcd * per + min(xcd, rem) + (bid >> 3);
+  const int gsz = g.grp * g.tiles_n;
+  const int grp = tile / gsz, in_grp = tile - grp * gsz;
+  const int rows_in_grp = min(g.grp, g.tiles_m - grp * g.grp);
+  const int m0 = (grp * g.grp + in_grp % rows_in_grp) * BM, n0 = (in_grp / rows_in_grp) * BN;
+  if (g.causal == CAUSAL_SKIP_UPPER && n0 > m0 + BM - 1) return;
+  const int z = blockIdx.y, z1 = z / g.nb2, z2 = z % g.nb2;
+  const int64_t coff = z1 * g.sC1 + z2 * g.sC2;
+  int kbeg = 0, kend = g.K;
+  if (g.causal == CAUSAL_K_END) kend = min(g.K, m0 + BM);
+  if (g.causal == CAUSAL_K_BEGIN) kbeg = m0;
+  const int nk = kend > kbeg ? (kend - kbeg + BKF - 1) / BKF : 0;
+
+  MA ma;
+  MB mb;
+  ma.init((const float *)g.A + z1 * g.sA1 + z2 * g.sA2, g.lda, m0, g.M, tid);
+  mb.init((const float *)g.B + z1 * g.sB1 + z2 * g.sB2, g.ldb, n0, g.N, tid);
+  f32x4_t ra[2][MA::N], rb[2][MB::N];
+  f32x16_t acc[2];  // even and odd MFMAs of a group: two independent chains
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.f;
+
+  const int arow = wm * 32 + (lane & 31), brow = wn * 32 + (lane & 31), klane = kg * KS + (lane >> 5) * 4;
+  auto compute = [&](const float *as, const float *bs) {
+#pragma unroll
+    for (int k = 0; k < KS; k += 8) {
+      const f32x4_t a = MA::frag(as, arow, klane + k), b = MB::frag(bs, brow, klane + k);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        acc[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[e], a[e], acc[e & 1], 0, 0, 0);
+    }
+  };
+  // slice t travels in register set t & 1 and LDS buffer t & 1
+  auto step = [&](int t, auto setc) {
+    constexpr int S = decltype(setc)::value;
+    ma.load(ra[S], kbeg + (t + 2) * BKF, kend);  // past the end: zeros, without a memory access
+    mb.load(rb[S], kbeg + (t + 2) * BKF, kend);
+    compute(lds + S * STAGE, lds + S * STAGE + MA::SIZE);
+    if (t + 1 < nk) {
+      ma.store(ra[S ^ 1], lds + (S ^ 1) * STAGE);
+      mb.store(rb[S ^ 1], lds + (S ^ 1) * STAGE + MA::SIZE);
+    }
+    __syncthreads();
+  };
+  if (nk > 0) {
+    ma.load(ra[0], kbeg, kend);
+    mb.load(rb[0], kbeg, kend);
+    ma.load(ra[1], kbeg + BKF, kend);
+    mb.load(rb[1], kbeg + BKF, kend);
+    ma.store(ra[0], lds);
+    mb.store(rb[0], lds + MA::SIZE);
+  }
+  __syncthreads();
+  for (int t = 0; t < nk; t += 2) {
+    step(t, std::integral_constant<int, 0>());
+    if (t + 1 < nk) step(t + 1, std::integral_constant<int, 1>());
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][r] += acc[1][r];
+
+  const bool vec = ((g.ldc & 3) == 0) && ((coff & 3) == 0) &&
+                   ((((uintptr_t)g.out_f32 | (uintptr_t)g.resid | (uintptr_t)g.bias | (uintptr_t)g.out_act |
+                      (uintptr_t)g.out_act2 | (uintptr_t)g.aux) & 15) == 0);
+  const int row = m0 + wm * 32 + (lane & 31), col = n0 + wn * 32 + (lane >> 5) * 4;
+  if constexpr (KW == 1) {
+    if (row < g.M) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4_t v = {acc[0][q * 4 + 0], acc[0][q * 4 + 1], acc[0][q * 4 + 2], acc[0][q * 4 + 3]};
+        epilogue_store4_f32(g, coff, row, col + q * 8, v, vec);
+      }
+    }
+  } else {
+    // wavefront w writes out column group w of the tile: the sum of the four partial results, in a fixed order
+    f32x4_t *const xch = (f32x4_t *)lds;  // [wavefront][column group][lane]; every wavefront is past the last barrier
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4_t v = {acc[0][q * 4 + 0], acc[0][q * 4 + 1], acc[0][q * 4 + 2], acc[0][q * 4 + 3]};
+      xch[(wave * 4 + q) * 64 + lane] = v;
+    }
+    __syncthreads();
+    if (row < g.M) {
+      const f32x4_t v = (xch[(0 + kg) * 64 + lane] + xch[(4 + kg) * 64 + lane]) +
+                        (xch[(8 + kg) * 64 + lane] + xch[(12 + kg) * 64 + lane]);
+      epilogue_store4_f32(g, coff, row, col + kg * 8, v, vec);
+    }
+  }
+}
+
+template <int BM, int BN, int BKF, int WM, int WN, int KW, int MODE>
+static hipError_t launch_f32_cfg(GemmArgs &a, int ta, int tb, int nbatch, hipStream_t s) {
+  a.tiles_m = (a.M + BM - 1) / BM;
+  a.tiles_n = (a.N + BN - 1) / BN;
+  a.grp = xcd_group_rows(a.tiles_m, a.tiles_n, BM, BN);
+  dim3 grid(a.tiles_m * a.tiles_n, nbatch);
+  if (ta == 0 && tb == 0) hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BKF, WM, WN, KW, 0, 0, MODE>), grid, dim3(256), 0, s, a);
+  else if (ta == 0 && tb == 1) hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BKF, WM, WN, KW, 0, 1, MODE>), grid, dim3(256), 0, s, a);
+  else if (ta == 1 && tb == 1) hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BKF, WM, WN, KW, 1, 1, MODE>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BKF, WM, WN, KW, 1, 0, MODE>), grid, dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+// 16-byte loads of an fp32 operand: aligned rows and no chunk that straddles the end of the contiguous extent (rows
+// of a row-contiguous operand, contraction range of the other kind - a causal range ends at a multiple of 32 or at K)
+static bool f32_vec_ok(const void *p, int64_t ld, int64_t s1, int64_t s2, int extent) {
+  return (((uintptr_t)p) & 15) == 0 && !((ld | s1 | s2 | extent) & 3);
+}
+
+constexpr int64_t F32_LD_MAX = 0x70000000 / (64 * 4);  // 64 lines of a slice stay below 2 GB
+static hipError_t launch_gemm_f32(GemmArgs &a, const GemmDesc &d, int nbatch, hipStream_t s) {
+  const bool vec = f32_vec_ok(d.A, d.lda, d.sA1, d.sA2, d.ta ? d.M : d.K) && f32_vec_ok(d.B, d.ldb, d.sB1, d.sB2, d.tb ? d.N : d.K);
+  const long t64 = (long)((d.M + 63) / 64) * ((d.N + 63) / 64) * nbatch;
+  if (d.lda >= F32_LD_MAX || d.ldb >= F32_LD_MAX) return launch_f32_cfg<32, 32, 64, 1, 1, 4, LD_WIDE>(a, d.ta, d.tb, nbatch, s);
+  // 64x64 tiles once they go round the 256 CUs two and a half times: below that the last round leaves too many idle
+  // (us, 64x64 / 32x32 tiles: 192 tiles 72 / 51 at 1000x768x3072, 384 tiles 83 / 69 at 2048x768x2304, 576 tiles
+  // 58 / 56 at 768x3072x1000, 768 tiles 49 / 56 at 1000x3072x768, 4096 tiles 1032 / 1192 at 4096^3 = 133 TFLOP/s)
+  if (t64 >= 640)
+    return vec ? launch_f32_cfg<64, 64, 32, 2, 2, 1, LD_VEC>(a, d.ta, d.tb, nbatch, s)
+               : launch_f32_cfg<64, 64, 32, 2, 2, 1, LD_SCALAR>(a, d.ta, d.tb, nbatch, s);
+  return vec ? launch_f32_cfg<32, 32, 64, 1, 1, 4, LD_VEC>(a, d.ta, d.tb, nbatch, s)
+             : launch_f32_cfg<32, 32, 64, 1, 1, 4, LD_SCALAR>(a, d.ta, d.tb, nbatch, s);
+}
 
 template <int BM, int BN, int WM, int WN, int D>
 static hipError_t launch_bf16_cfg(const GemmArgs &a, int ta, int tb, dim3 grid, hipStream_t s) {
@@ -883,7 +1066,6 @@ static const char *gemm_name(int dtype, int bn, int ta, int tb) {
   static const char *n128[4] = {"gemm_bf16_128x128_nt", "gemm_bf16_128x128_nn", "gemm_bf16_128x128_tt",
                                 "gemm_bf16_128x128_tn"};
   static const char *n64[4] = {"gemm_bf16_x64_nt", "gemm_bf16_x64_nn", "gemm_bf16_x64_tt", "gemm_bf16_x64_tn"};
-  if (dtype == DT_F32) return "gemm_f32_64x64";
   return (bn == 128 ? n128 : n64)[ta * 2 + tb];
 }
 
@@ -900,12 +1082,8 @@ hipError_t launch_gemm(const GemmDesc &d, hipStream_t s) {
   a.grp = 8;
   const int nbatch = d.nb1 * d.nb2;
   if (d.dtype == DT_F32) {
-    a.tiles_m = (d.M + FBM - 1) / FBM;
-    a.tiles_n = (d.N + FBN - 1) / FBN;
-    dim3 grid(a.tiles_m * a.tiles_n, nbatch);
-    ProfScope ps(gemm_name(DT_F32, 0, 0, 0), s, gemm_flops(d), 0);
-    hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, s, a, d.ta, d.tb);
-    return hipGetLastError();
+    ProfScope ps("gemm_f32", s, gemm_flops(d), 0);
+    return launch_gemm_f32(a, d, nbatch, s);
   }
   // operand alignment the vector loads rely on
   if ((d.lda & 7) || (d.ldb & 7) || (((uintptr_t)d.A) & 15) || (((uintptr_t)d.B) & 15)) return hipErrorInvalidValue;
