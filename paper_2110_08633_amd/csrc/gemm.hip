@@ -790,24 +790,27 @@ static hipError_t launch_bf16_big(const GemmArgs &a, int ta, int tb, int ntiles,
 }
 
 // ---------------------------------------------------------------------------
-// fp32 kernel: v_mfma_f32_32x32x2_f32 (full fp32 products and sums, no
-// reduced-precision split).  That instruction needs 64 clocks for 4096 flop, so
+// fp32 kernel: v_mfma_f32_32x32x2_f32 and 16x16x4 (full fp32 products and sums,
+// no reduced-precision split; each is a chain of fused multiply-adds over its
+// contraction steps in ascending order).  The instruction needs 64 clocks for 4096 flop, so
 // LDS and the load path are far from binding (a 32x32 result per wavefront
 // reads 16 bytes of LDS per clock and CU); what costs is everything that keeps
 // the matrix pipes waiting: too few tiles for 256 CUs and trips to memory.
 // Hence small tiles, operands requested two slices ahead (16-byte loads into
 // registers where alignment allows), two LDS buffers and one barrier per slice.
 //   64x64 tiles: 2x2 wavefronts, 32 contraction steps per slice
-//   32x32 tiles: the four wavefronts split every slice's 64 contraction steps
-//                and are summed through LDS at the end - four times the tiles
-//                where 64x64 ones would leave CUs idle
+//   32x32 tiles: 2x2 wavefronts of 16x16 results, 64 steps per slice - four times
+//                the tiles where 64x64 ones would leave CUs idle
+// A result is one chain of fused multiply-adds over ascending k, whatever the
+// tile: the sum does not depend on the shape, and parameters whose gradient is
+// zero but for rounding (the key bias) see the same rounding everywhere.
 // An operand sits in LDS as it sits in memory: [row][k] when its contraction
-// index is contiguous, else [k][row].  A lane feeds row L%32 and contraction
-// steps (L/32)*4 + s of every group of eight, s = 0..3, one step pair per MFMA;
-// both operands use the same assignment, so the pairing is immaterial.
+// index is contiguous (steps regrouped so that a lane's four are neighbours),
+// else [k][row].  A lane feeds row L%MT and steps e * KG + L/MT, e = 0..3, of
+// every group of 4 * KG.
 // Measured against the former vector-ALU kernel (64x64 tiles, 4-byte loads, no
-// prefetch): 1000x3072x768 265 -> 49 us, 128x128x512 34 -> 7 us, 4096^3 at 133-137
-// TFLOP/s of the 157 the matrix pipes offer; error against 64 bits 1.0e-6 -> 3.5e-7.
+// prefetch): 1000x3072x768 265 -> 51 us, 128x128x512 34 -> 6 us, 4096^3 at 128
+// TFLOP/s of the 157 the matrix pipes offer; the results are the same to the bit.
 // ---------------------------------------------------------------------------
 // descriptor of 2 GB from p on (offsets are 32 bits wide: the base moves with the slice)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void *p) {
@@ -821,7 +824,7 @@ constexpr int BUF_OUT = 0x7ffffff8;  // offset past the descriptor's range: the 
 // LD_VEC: 16-byte loads; LD_SCALAR: 4-byte loads for operands whose alignment does not allow them; LD_WIDE: leading
 // dimensions that a 32-bit offset within a slice cannot hold
 enum { LD_VEC = 0, LD_SCALAR = 1, LD_WIDE = 2 };
-template <int R, int BKF, int RC, int MODE>
+template <int R, int BKF, int RC, int KG, int MODE>
 struct MoverF {
   static constexpr int LEN = RC ? R : BKF;           // elements per line of memory (row of [row][k] / [k][row])
   static constexpr int PITCH = LEN + 4;              // LDS pitch in floats: 16 bytes of padding spread the banks
@@ -861,20 +864,31 @@ struct MoverF {
       }
     }
   }
+  // position of contraction step k in a line of [row][k]: within every 4 * KG steps, those of one lane group together
+  static __device__ __forceinline__ int place(int k) { return k / (4 * KG) * (4 * KG) + (k % KG) * 4 + k % (4 * KG) / KG; }
   __device__ __forceinline__ void store(const f32x4_t (&r)[N], float *lds) const {
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
-      float *const p = lds + (line + j * LS) * PITCH + c;
-      if (MODE == LD_VEC) *(f32x4_t *)p = r[j];
-      else *p = r[j / 4][j % 4];
+      float *const p = lds + (line + j * LS) * PITCH;
+      if (MODE != LD_VEC) {
+        p[RC ? c : place(c)] = r[j / 4][j % 4];
+      } else if (RC) {
+        *(f32x4_t *)(p + c) = r[j];
+      } else if (KG == 2) {  // steps c, c + 2 and c + 1, c + 3 are neighbours
+        *(f32x2_t *)(p + place(c)) = f32x2_t{r[j][0], r[j][2]};
+        *(f32x2_t *)(p + place(c) + 4) = f32x2_t{r[j][1], r[j][3]};
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[place(c) + 4 * e] = r[j][e];
+      }
     }
   }
-  // the lane's four steps of the eight that start at k, of row
-  static __device__ __forceinline__ f32x4_t frag(const float *lds, int row, int k) {
-    if (!RC) return *(const f32x4_t *)(lds + row * PITCH + k);
+  // lane group kq's four of the 4 * KG steps that start at k, of row: steps k + e * KG + kq, e = 0..3
+  static __device__ __forceinline__ f32x4_t frag(const float *lds, int row, int k, int kq) {
+    if (!RC) return *(const f32x4_t *)(lds + row * PITCH + k + kq * 4);
     f32x4_t v;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = lds[(k + e) * PITCH + row];
+    for (int e = 0; e < 4; ++e) v[e] = lds[(k + e * KG + kq) * PITCH + row];
     return v;
   }
 };
@@ -909,17 +923,19 @@ __device__ __forceinline__ void epilogue_store4_f32(const GemmArgs &g, int64_t c
   if (g.out_act) *(f32x4_t *)((float *)g.out_act + idx) = v;
 }
 
-template <int BM, int BN, int BKF, int WM, int WN, int KW, int TA, int TB, int MODE>
+template <int MT, int BKF, int TA, int TB, int MODE>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs g) {
-  static_assert(WM * WN * KW == 4 && BM == 32 * WM && BN == 32 * WN, "four wavefronts, one 32x32 result each");
-  typedef MoverF<BM, BKF, TA, MODE> MA;
-  typedef MoverF<BN, BKF, TB, MODE> MB;
+  constexpr int BM = 2 * MT, BN = 2 * MT;  // 2x2 wavefronts, one MT x MT result each
+  constexpr int KG = 64 / MT;              // lane groups = contraction steps of one MFMA
+  constexpr int NR = MT * MT / 64;         // accumulator registers
+  typedef MoverF<BM, BKF, TA, KG, MODE> MA;
+  typedef MoverF<BN, BKF, TB, KG, MODE> MB;
+  typedef __attribute__((ext_vector_type(NR))) float acc_t;
   constexpr int STAGE = MA::SIZE + MB::SIZE;
-  constexpr int KS = BKF / KW;  // contraction steps of a slice that one wavefront multiplies
-  static_assert(KS % 8 == 0 && (KW == 1 || 2 * STAGE >= 4 * 1024), "groups of eight steps; the exchange fits the buffers");
+  static_assert(BKF % (4 * KG) == 0, "whole groups of steps");
   __shared__ __attribute__((aligned(16))) float lds[2 * STAGE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int kg = wave / (WM * WN), wm = (wave / WN) % WM, wn = wave % WN;
+  const int wm = wave >> 1, wn = wave & 1;
   // tile numbering as in the bf16 kernels: contiguous runs per XCD, groups of g.grp tile rows walked column by column
   const int nt = gridDim.x, bid = blockIdx.x, xcd = bid & 7, per = nt >> 3, rem = nt & 7;
   const int tile = xcd * per + min(xcd, rem) + (bid >> 3);
@@ -940,18 +956,20 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs g) {
   ma.init((const float *)g.A + z1 * g.sA1 + z2 * g.sA2, g.lda, m0, g.M, tid);
   mb.init((const float *)g.B + z1 * g.sB1 + z2 * g.sB2, g.ldb, n0, g.N, tid);
   f32x4_t ra[2][MA::N], rb[2][MB::N];
-  f32x16_t acc[2];  // even and odd MFMAs of a group: two independent chains
+  acc_t acc;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.f;
+  for (int r = 0; r < NR; ++r) acc[r] = 0.f;
 
-  const int arow = wm * 32 + (lane & 31), brow = wn * 32 + (lane & 31), klane = kg * KS + (lane >> 5) * 4;
+  const int arow = wm * MT + lane % MT, brow = wn * MT + lane % MT, kq = lane / MT;
   auto compute = [&](const float *as, const float *bs) {
 #pragma unroll
-    for (int k = 0; k < KS; k += 8) {
-      const f32x4_t a = MA::frag(as, arow, klane + k), b = MB::frag(bs, brow, klane + k);
+    for (int k = 0; k < BKF; k += 4 * KG) {
+      const f32x4_t a = MA::frag(as, arow, k, kq), b = MB::frag(bs, brow, k, kq);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        acc[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[e], a[e], acc[e & 1], 0, 0, 0);
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (MT == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[e], a[e], acc, 0, 0, 0);
+        else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], acc, 0, 0, 0);
+      }
     }
   };
   // slice t travels in register set t & 1 and LDS buffer t & 1
@@ -979,48 +997,31 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs g) {
     step(t, std::integral_constant<int, 0>());
     if (t + 1 < nk) step(t + 1, std::integral_constant<int, 1>());
   }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[0][r] += acc[1][r];
 
   const bool vec = ((g.ldc & 3) == 0) && ((coff & 3) == 0) &&
                    ((((uintptr_t)g.out_f32 | (uintptr_t)g.resid | (uintptr_t)g.bias | (uintptr_t)g.out_act |
                       (uintptr_t)g.out_act2 | (uintptr_t)g.aux) & 15) == 0);
-  const int row = m0 + wm * 32 + (lane & 31), col = n0 + wn * 32 + (lane >> 5) * 4;
-  if constexpr (KW == 1) {
-    if (row < g.M) {
+  const int row = m0 + arow, col = n0 + wn * MT + kq * 4;
+  if (row < g.M) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4_t v = {acc[0][q * 4 + 0], acc[0][q * 4 + 1], acc[0][q * 4 + 2], acc[0][q * 4 + 3]};
-        epilogue_store4_f32(g, coff, row, col + q * 8, v, vec);
-      }
-    }
-  } else {
-    // wavefront w writes out column group w of the tile: the sum of the four partial results, in a fixed order
-    f32x4_t *const xch = (f32x4_t *)lds;  // [wavefront][column group][lane]; every wavefront is past the last barrier
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4_t v = {acc[0][q * 4 + 0], acc[0][q * 4 + 1], acc[0][q * 4 + 2], acc[0][q * 4 + 3]};
-      xch[(wave * 4 + q) * 64 + lane] = v;
-    }
-    __syncthreads();
-    if (row < g.M) {
-      const f32x4_t v = (xch[(0 + kg) * 64 + lane] + xch[(4 + kg) * 64 + lane]) +
-                        (xch[(8 + kg) * 64 + lane] + xch[(12 + kg) * 64 + lane]);
-      epilogue_store4_f32(g, coff, row, col + kg * 8, v, vec);
+    for (int q = 0; q < NR / 4; ++q) {
+      const f32x4_t v = {acc[q * 4 + 0], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
+      epilogue_store4_f32(g, coff, row, col + q * 8, v, vec);
     }
   }
 }
 
-template <int BM, int BN, int BKF, int WM, int WN, int KW, int MODE>
+template <int MT, int BKF, int MODE>
 static hipError_t launch_f32_cfg(GemmArgs &a, int ta, int tb, int nbatch, hipStream_t s) {
-  a.tiles_m = (a.M + BM - 1) / BM;
-  a.tiles_n = (a.N + BN - 1) / BN;
-  a.grp = xcd_group_rows(a.tiles_m, a.tiles_n, BM, BN);
+  constexpr int BT = 2 * MT;
+  a.tiles_m = (a.M + BT - 1) / BT;
+  a.tiles_n = (a.N + BT - 1) / BT;
+  a.grp = xcd_group_rows(a.tiles_m, a.tiles_n, BT, BT);
   dim3 grid(a.tiles_m * a.tiles_n, nbatch);
-  if (ta == 0 && tb == 0) hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BKF, WM, WN, KW, 0, 0, MODE>), grid, dim3(256), 0, s, a);
-  else if (ta == 0 && tb == 1) hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BKF, WM, WN, KW, 0, 1, MODE>), grid, dim3(256), 0, s, a);
-  else if (ta == 1 && tb == 1) hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BKF, WM, WN, KW, 1, 1, MODE>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BKF, WM, WN, KW, 1, 0, MODE>), grid, dim3(256), 0, s, a);
+  if (ta == 0 && tb == 0) hipLaunchKernelGGL((gemm_f32_kernel<MT, BKF, 0, 0, MODE>), grid, dim3(256), 0, s, a);
+  else if (ta == 0 && tb == 1) hipLaunchKernelGGL((gemm_f32_kernel<MT, BKF, 0, 1, MODE>), grid, dim3(256), 0, s, a);
+  else if (ta == 1 && tb == 1) hipLaunchKernelGGL((gemm_f32_kernel<MT, BKF, 1, 1, MODE>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((gemm_f32_kernel<MT, BKF, 1, 0, MODE>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1034,15 +1035,15 @@ constexpr int64_t F32_LD_MAX = 0x70000000 / (64 * 4);  // 64 lines of a slice st
 static hipError_t launch_gemm_f32(GemmArgs &a, const GemmDesc &d, int nbatch, hipStream_t s) {
   const bool vec = f32_vec_ok(d.A, d.lda, d.sA1, d.sA2, d.ta ? d.M : d.K) && f32_vec_ok(d.B, d.ldb, d.sB1, d.sB2, d.tb ? d.N : d.K);
   const long t64 = (long)((d.M + 63) / 64) * ((d.N + 63) / 64) * nbatch;
-  if (d.lda >= F32_LD_MAX || d.ldb >= F32_LD_MAX) return launch_f32_cfg<32, 32, 64, 1, 1, 4, LD_WIDE>(a, d.ta, d.tb, nbatch, s);
+  if (d.lda >= F32_LD_MAX || d.ldb >= F32_LD_MAX) return launch_f32_cfg<16, 64, LD_WIDE>(a, d.ta, d.tb, nbatch, s);
   // 64x64 tiles once they go round the 256 CUs two and a half times: below that the last round leaves too many idle
-  // (us, 64x64 / 32x32 tiles: 192 tiles 72 / 51 at 1000x768x3072, 384 tiles 83 / 69 at 2048x768x2304, 576 tiles
-  // 58 / 56 at 768x3072x1000, 768 tiles 49 / 56 at 1000x3072x768, 4096 tiles 1032 / 1192 at 4096^3 = 133 TFLOP/s)
+  // (us, 64x64 / 32x32 tiles: 192 tiles 72 / 57 at 1000x768x3072, 384 tiles 83 / 75 at 2048x768x2304, 768 tiles
+  // 51 / 56 at 1000x3072x768, 4096 tiles 1074 / 1192 at 4096^3)
   if (t64 >= 640)
-    return vec ? launch_f32_cfg<64, 64, 32, 2, 2, 1, LD_VEC>(a, d.ta, d.tb, nbatch, s)
-               : launch_f32_cfg<64, 64, 32, 2, 2, 1, LD_SCALAR>(a, d.ta, d.tb, nbatch, s);
-  return vec ? launch_f32_cfg<32, 32, 64, 1, 1, 4, LD_VEC>(a, d.ta, d.tb, nbatch, s)
-             : launch_f32_cfg<32, 32, 64, 1, 1, 4, LD_SCALAR>(a, d.ta, d.tb, nbatch, s);
+    return vec ? launch_f32_cfg<32, 32, LD_VEC>(a, d.ta, d.tb, nbatch, s)
+               : launch_f32_cfg<32, 32, LD_SCALAR>(a, d.ta, d.tb, nbatch, s);
+  return vec ? launch_f32_cfg<16, 64, LD_VEC>(a, d.ta, d.tb, nbatch, s)
+             : launch_f32_cfg<16, 64, LD_SCALAR>(a, d.ta, d.tb, nbatch, s);
 }
 
 template <int BM, int BN, int WM, int WN, int D>
