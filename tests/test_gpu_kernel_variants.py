@@ -53,3 +53,40 @@ def test_gemm_f32_variants(H, ta, tb, M, N, K, extra, shift):
     bound = (K + 2) * U32 * (0.5 * (A.double().abs() @ B.double().abs()) + resid.double().abs())
     assert ((out[:, :N].double() - ref).abs() <= bound).all()
     assert (out[:, N:] == 7.0).all()
+
+
+# bf16 products, one matrix each: sizes for which the launcher takes each of its tile shapes - 64x64 with the contraction
+# split over two groups, 64x64, 64x96, 128x64, 128x128 (both kinds), 128x192, 128x256, 256x256 - with ragged last rows,
+# columns and contractions (shorter than a slice, one step into the next slice, an odd length)
+PLAIN_CASES = [(1, 1, 8), (33, 40, 72), (201, 2304, 768), (520, 264, 200), (513, 1024, 1001), (2050, 776, 2056),
+               (1100, 1608, 600), (900, 3300, 776), (1030, 4104, 1000), (2000, 3000, 520), (1000, 6408, 1608),
+               (4100, 4104, 72), (1000, 16392, 4096)]
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", PLAIN_CASES)
+def test_gemm_bf16_tile_shapes(H, ta, tb, M, N, K):
+    r8 = lambda n: (n + 7) // 8 * 8
+    if not (ta and tb):
+        K = r8(K)  # a contraction-contiguous operand is read in chunks of eight steps
+    A, B = randn(M + K, M, K).bfloat16(), randn(N + K + 1, K, N).bfloat16()
+    bias, resid = randn(N, N), randn(M + N + 2, M, N)
+    As, Bs = A.t().contiguous() if ta else A, B if tb else B.t().contiguous()
+    lda, ldb, ldc = r8(As.shape[1]) + 8, r8(Bs.shape[1]), N + 1
+    dA, dB = stored(As, lda, 0), stored(Bs, ldb, 8)
+    if M * N * K < 1 << 30:  # once with everything the epilogue can do, unaligned; large ones plain and aligned
+        out, act = torch.full((M, ldc), 7.0, device="cuda"), torch.full((M, ldc), 7.0, device="cuda").bfloat16()
+        H.hydra_op_gemm(1, ta, tb, M, N, K, 0.5, dA, lda, dB, ldb, bias, stored(resid, ldc, 0), out, act, ldc)
+        ref = 0.5 * (A.double() @ B.double()) + bias.double() + resid.double()
+        mag = 0.5 * (A.double().abs() @ B.double().abs()) + bias.double().abs() + resid.double().abs()
+        assert (out[:, N:] == 7.0).all() and (act[:, N:] == 7.0).all()
+        out, act = out[:, :N], act[:, :N]
+        # bf16 copy: half a unit in the last place of 8 bits on top
+        assert ((act.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2 * (K + 4) * U32 * mag).all()
+    else:
+        out = torch.empty((M, N), device="cuda")
+        H.hydra_op_gemm(1, ta, tb, M, N, K, 1.0, dA, lda, dB, ldb, None, None, out, None, N)
+        ref, mag = A.double() @ B.double(), A.double().abs() @ B.double().abs()
+    # products of bf16 values are exact in fp32; each of the K + 4 additions and scalings errs by at most a unit in the
+    # last place of the sum of magnitudes (the matrix instruction may truncate)
+    assert ((out.double() - ref).abs() <= 2 * (K + 4) * U32 * mag).all()
