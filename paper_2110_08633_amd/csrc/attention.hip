@@ -8,28 +8,29 @@
 // per row, only the log-sum-exp L_i = log sum_j exp(s[i,j]); the backward
 // kernels rebuild p[i,j] = exp(s[i,j] - L_i) from q and k.
 //
-// Operand conventions are those of the GEMM kernels: v_mfma_f32_32x32x16_bf16
-// with the column operand first, so a lane holds row L%32 of a 32x32 result and
-// columns (r/4)*8 + (L/32)*4 + r%4 for r = 0..15.  K and V tiles of 64 keys
-// are staged in LDS with the GEMM movers (K contraction-contiguous, V read with
-// the transposing LDS read); probabilities go through a per-wavefront LDS patch
-// to become the row operand of the second product.
-#include "kernels.h"
-#include "tile_ops.h"
+// Operand conventions: v_mfma_f32_32x32x16_bf16 with the column operand first, so a
+// lane holds row L%32 of a 32x32 result and columns (r/4)*8 + (L/32)*4 + r%4 for
+// r = 0..15.  Tiles of 64 rows go straight to LDS (one copy, read both along the
+// head dimension and, transposing, along the rows); probabilities stay in the
+// registers they are computed in.
+#include "gemm_common.h"
 
 namespace hydra {
 
 namespace {
 
-constexpr int AQ = 128;      // query rows per block, 32 per wavefront
-constexpr int AK = 64;       // keys per tile (= BK)
-constexpr int PP = AK + 8;   // pitch of the probability patch (bf16 elements): 144 bytes, conflict-free 16-byte reads
+constexpr int AQ = 128;  // rows (queries, or keys in the dK/dV kernel) per block and wavefront group, 32 per wavefront
+constexpr int AK = 64;   // rows of a tile that is walked over (keys, or queries in the dK/dV kernel)
 constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
 
-__device__ __forceinline__ float xor32(float x) { return __shfl_xor(x, 32, 64); }
-
-// column (within a 32-wide tile) of accumulator register r of this lane
-__device__ __forceinline__ int acc_col(int r, int lane) { return (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3); }
+// value of the lane 32 away and the lane's own, in either order
+__device__ __forceinline__ void halves(float x, float &a, float &b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float sum_halves(float x) { float a, b; halves(x, a, b); return a + b; }
+__device__ __forceinline__ float max_halves(float x) { float a, b; halves(x, a, b); return __builtin_fmaxf(a, b); }
 
 __device__ __forceinline__ bf16x8_t load_frag_global(const bf16_t *p) {
   union { u32x4_t u; bf16x8_t f; } x;
@@ -37,66 +38,67 @@ __device__ __forceinline__ bf16x8_t load_frag_global(const bf16_t *p) {
   return x.f;
 }
 
-// A [64 rows][DH] bf16 tile of a row-major matrix, fetched once from global memory (16 bytes per lane, rows past
-// the end of the sequence read as zero) and written to LDS in one or both of the operand layouts of tile_ops.h:
-//   layout 0: DH/64 slices [row][64], contraction (head dimension) contiguous - operand of products over dh
-//   layout 1: [row][DH] as a slice of 64 contraction steps (= rows)       - operand of products over the rows
-template <int DH, int SETS = 2>
+// Results r = 8*s .. 8*s + 7 of a lane (row L%32, columns (r/4)*8 + (L/32)*4 + r%4) as the row operand of a product
+// that contracts over those columns: rounded to bf16, they already sit in the right lane - lane half h holds steps
+// 4h .. 4h+3 and 8+4h .. 11+4h of the sixteen, and RowTile::tr feeds the other operand's steps in the same order.  So
+// probabilities never leave the registers.
+__device__ __forceinline__ bf16x8_t row_operand(const float (&p)[16], int s) {
+  union { uint32_t u[4]; bf16x8_t f; } x;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) x.u[e] = pack_bf16(p[s * 8 + 2 * e], p[s * 8 + 2 * e + 1]);
+  return x.f;
+}
+
+// A [64 rows][DH] bf16 tile of a row-major matrix in LDS: DH/64 slices [row][64] whose 16-byte chunks are swizzled so
+// that both ways of reading it are free of bank conflicts - as operand of a product over the head dimension (16 bytes
+// per lane: rows of one parity need distinct slots) and, through the transposing read, of a product over the rows (32
+// bytes of rows k..k+3 each, two column groups at a time).  One copy serves both.
+template <int DH>
 struct RowTile {
-  static constexpr int CPT = DH / 8;            // 16-byte chunks per row
-  static constexpr int N = 64 * CPT / 256;      // chunks per thread
-  uint32_t off[N];
-  int row[N], slot0[N], slot1[N];
-  u32x4_t r[SETS][N];  // up to two tiles in flight: tile t travels in set t & 1 (always indexed by compile-time constants)
-  __device__ __forceinline__ void init(int64_t ld, int tid) {
+  static constexpr int SIZE = AK * DH;            // elements
+  static constexpr int N = SIZE / 8 / 256;        // 16-byte loads per lane for four wavefronts
+  int off, row;  // byte offset and row of this lane's first chunk; the others are 32 rows and 64 columns further on
+  int64_t ld;
+  static __device__ __forceinline__ int swz(int r) { return ((r >> 1) & 1) << 2 | ((r >> 2) & 1) << 1 | ((r >> 3) & 1); }
+  __device__ __forceinline__ void init(int64_t ld_, int tid) {  // tid within the four wavefronts
+    ld = ld_;
+    row = tid >> 3;
+    off = (int)((row * ld + ((tid & 7) ^ swz(row)) * 8) * 2);
+  }
+  // base: element (first row of the tile, first column of the head), uniform; rows from `valid` on read as zero
+  __device__ __forceinline__ void load(const bf16_t *base, int valid, uint32_t lds, int wave) const {
+    const int o0 = row < valid ? off : BUF_OUT, o1 = row + 32 < valid ? off : BUF_OUT;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int id = tid + i * 256;
-      const int rw = id / CPT, c = id % CPT;
-      row[i] = rw;
-      off[i] = (uint32_t)(rw * ld + c * 8);
-      slot0[i] = (c / 8) * AK * BK + (rw * CPR + ((c % 8) ^ kc_swz(rw))) * 8;
-      slot1[i] = (rw * CPT + (c ^ rc_swz<DH>(rw))) * 8;
+    for (int i = 0; i < N; ++i)
+      load_to_lds(base + (i & 1) * 32 * ld + (i >> 1) * 64, i & 1 ? o1 : o0, lds + (i * 256 + wave * 64) * 16);
+  }
+};
+template <int DH>
+struct RowFrag {
+  int kc[4], t0[2], t1[2];
+  __device__ __forceinline__ void init(int lane) {
+    const int r = lane & 31, hi = lane >> 5;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) kc[kk] = r * 64 + ((kk * 2 + hi) ^ RowTile<DH>::swz(r)) * 8;
+    const int G = lane >> 4, sl = lane & 15, k = 4 * hi + (sl >> 2);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int m = q * 32 + 16 * (G & 1) + 4 * (sl & 3);
+      t0[q] = k * 64 + ((m >> 3) ^ RowTile<DH>::swz(k)) * 8 + ((m >> 2) & 1) * 4;
+      t1[q] = (k + 8) * 64 + ((m >> 3) ^ RowTile<DH>::swz(k + 8)) * 8 + ((m >> 2) & 1) * 4;
     }
   }
-  // base: element (first row of the tile, first column of the head); rows_valid: rows of the tile inside the sequence
-  template <int S>
-  __device__ __forceinline__ void load(const bf16_t *base, int rows_valid) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      u32x4_t v = {0u, 0u, 0u, 0u};
-      if (row[i] < rows_valid) v = *(gvec_ptr)(base + off[i]);
-      r[S][i] = v;
-    }
+  // rows 32*nt .. +31, head dimensions 16*kk .. +15
+  __device__ __forceinline__ bf16x8_t rows(const bf16_t *t, int nt, int kk) const {
+    return *(const bf16x8_t *)(t + (kk >> 2) * 4096 + nt * 2048 + kc[kk & 3]);
   }
-  template <int S>
-  __device__ __forceinline__ void store0(bf16_t *lds) const {
-#pragma unroll
-    for (int i = 0; i < N; ++i) *(u32x4_t *)(lds + slot0[i]) = r[S][i];
-  }
-  template <int S>
-  __device__ __forceinline__ void store1(bf16_t *lds) const {
-#pragma unroll
-    for (int i = 0; i < N; ++i) *(u32x4_t *)(lds + slot1[i]) = r[S][i];
+  // rows 16*kk .. +15 (in the order of row_operand) as contraction steps, head dimensions 32*nd .. +31
+  __device__ __forceinline__ bf16x8_t tr(const bf16_t *t, int nd, int kk) const {
+    const int c = (nd >> 1) * 4096 + kk * 1024;
+    return fragment<1>(t, c + t0[nd & 1], c + t1[nd & 1]);
   }
 };
 
-template <int V> struct IntC { static constexpr int value = V; };
-
-// four consecutive results of a lane's row -> bf16 -> the wavefront's patch [32][PP]
-__device__ __forceinline__ void patch_put(bf16_t *patch, int lane, int nt, int q, const float (&w)[4]) {
-  u32x2_t v;
-  v.x = pack_bf16(w[0], w[1]);
-  v.y = pack_bf16(w[2], w[3]);
-  *(u32x2_t *)(patch + (lane & 31) * PP + nt * 32 + q * 8 + (lane >> 5) * 4) = v;
-}
-__device__ __forceinline__ bf16x8_t patch_get(const bf16_t *patch, int lane, int kk) {
-  return *(const bf16x8_t *)(patch + (lane & 31) * PP + kk * 16 + (lane >> 5) * 8);
-}
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wavefront's LDS traffic has completed
-  __builtin_amdgcn_wave_barrier();
-}
 // a lane's 32x32 result tile (row L%32) -> bf16 row segment at dst (already offset to the row and the tile)
 __device__ __forceinline__ void store_tile_row(bf16_t *dst, int lane, const f32x16_t &a) {
 #pragma unroll
@@ -108,65 +110,74 @@ __device__ __forceinline__ void store_tile_row(bf16_t *dst, int lane, const f32x
   }
 }
 
+__device__ __forceinline__ void landed_barrier() {
+  wait_loads_le<0>();  // this wavefront's tiles have landed and its LDS traffic is done
+  block_barrier();
+}
+__device__ __forceinline__ uint32_t lds_addr(const void *p) {
+  return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p);
+}
+
+// Block -> (sample and head, row block): all pairs' row blocks of one index before those of the next, the ones with the
+// most tiles first (the longest ones would otherwise be started last and run alone).  Consecutive block ids go
+// round-robin to the 8 XCDs, so with a multiple of 8 pairs a pair's keys and values stay in one XCD's L2.
+__device__ __forceinline__ void block_place(int pairs, int &z, int &rb) {
+  rb = blockIdx.x / pairs;
+  z = blockIdx.x - rb * pairs;
+}
+
 // ---------------------------------------------------------------------------
-// forward: one block = 128 query rows of one (sample, head); wavefront w owns
+// forward: four wavefronts = 128 query rows of one (sample, head); wavefront w owns
 // rows r0 = q0 + 32 w .. + 31 and keeps its Q fragments in registers.  One
 // sweep over the key tiles up to the diagonal with a running row maximum and
 // sum (the output is rescaled when the maximum grows and divided by the sum at
-// the end).  K and V tiles are requested from global memory two tiles ahead
-// (one tile's arithmetic is shorter than a trip to memory), rest in registers,
-// and move into one of two LDS buffers one tile ahead; one barrier per tile.
+// the end).  Tiles go straight from global memory to LDS, one ahead; one barrier
+// per tile.  KW groups of four wavefronts share the rows: group g takes key
+// tiles g, g + KW, ... and the partial results are merged through LDS at the end
+// (launches that would leave CUs without work).
+// Bound: per tile and wavefront 1024 clocks of MFMAs at head width 128 (512 at 64) and 960 of vector ALU, which overlap
+// only between the two or more wavefronts of a SIMD; counters at B 4, H 16, T 2048, dh 128: matrix pipes 0.40 busy,
+// vector ALU 0.43, LDS 0.20.  That launch: 255 us with one wavefront per SIMD, register-staged tiles and probabilities
+// through LDS; 103 us without these; 79 us with the long blocks first.  Measured without gain: tiles two and three
+// ahead, raised wavefront priority around the MFMAs, MFMAs and exponentials interleaved by scheduling directives (spills).
 // ---------------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(256) void attn_fwd_kernel(const bf16_t *__restrict__ qkv, bf16_t *__restrict__ o,
-                                                       float *__restrict__ lse, int T, int H, int d,
-                                                       float scale_log2e) {
-  constexpr int NS = DH / 64;  // 64-wide slices of the head dimension
+template <int DH, int KW>
+__global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__restrict__ qkv, bf16_t *__restrict__ o,
+                                                               float *__restrict__ lse, int T, int H, int d, int nb, int pairs,
+                                                               float scale_log2e) {
   constexpr int ND = DH / 32;  // 32-wide column tiles of the output
-  constexpr int TILE = AK * DH;
-  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-  bf16_t *const Ks = smem;              // [2][TILE] layout 0
-  bf16_t *const Vs = Ks + 2 * TILE;     // [2][TILE] layout 1
-  bf16_t *const Ps = Vs + 2 * TILE;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int qb = gridDim.x - 1 - blockIdx.x;  // blocks with the most keys first
-  const int z = blockIdx.y, b = z / H, h = z % H;
+  constexpr int TILE = RowTile<DH>::SIZE, STAGE = 2 * TILE * KW;
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];  // [2 stages][KW][K, V]
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+  int z, qb;
+  block_place(pairs, z, qb);
+  qb = nb - 1 - qb;
+  const int b = z / H, h = z % H;
   const int q0 = qb * AQ, r0 = q0 + wave * 32;
   const int64_t ld = 3 * (int64_t)d;
   const bf16_t *qp = qkv + (int64_t)b * T * ld + h * DH, *kp = qp + d, *vp = qp + 2 * d;
   const int myrow = r0 + (lane & 31);
   const int ldrow = min(myrow, T - 1);  // rows past the sequence compute on a valid row and store nothing
 
+  RowTile<DH> tile;
+  tile.init(ld, tid);
+  const uint32_t lds0 = lds_addr(smem) + grp * 2 * TILE * 2;
+  const int kend = min(T, q0 + AQ);  // keys any row of the block can see
+  const int nstep = (kend + AK * KW - 1) / (AK * KW);
+  const int my_last = r0 + 31;       // tiles starting beyond it hold nothing for this wavefront
+  auto load = [&](int it) {
+    const int j0 = (it * KW + grp) * AK;
+    const uint32_t s = lds0 + (it & 1) * STAGE * 2;
+    tile.load(kp + (int64_t)j0 * ld, T - j0, s, wave);
+    tile.load(vp + (int64_t)j0 * ld, T - j0, s + TILE * 2, wave);
+  };
+  load(0);
   bf16x8_t qf[DH / 16];
 #pragma unroll
   for (int kk = 0; kk < DH / 16; ++kk) qf[kk] = load_frag_global(qp + ldrow * ld + kk * 16 + (lane >> 5) * 8);
-
-  int ko[2][4], vo[ND][4][2];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    int unused;
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) fragment_offsets<AK, 0>(nt * 32, kk, lane, ko[nt][kk], unused);
-#pragma unroll
-    for (int nd = 0; nd < ND; ++nd) fragment_offsets<DH, 1>(nd * 32, kk, lane, vo[nd][kk][0], vo[nd][kk][1]);
-  }
-  bf16_t *const patch = Ps + wave * 32 * PP;
-  const int kend = min(T, q0 + AQ);  // keys any row of the block can see
-  const int ntile = (kend + AK - 1) / AK;
-  const int my_last = r0 + 31;       // tiles starting beyond it hold nothing for this wavefront
-
-  RowTile<DH> tk, tv;
-  tk.init(ld, tid);
-  tv.init(ld, tid);
-  tk.template load<0>(kp, T);
-  tv.template load<0>(vp, T);
-  if (ntile > 1) {
-    tk.template load<1>(kp + (int64_t)AK * ld, T - AK);
-    tv.template load<1>(vp + (int64_t)AK * ld, T - AK);
-  }
-  tk.template store0<0>(Ks);
-  tv.template store1<0>(Vs);
-  __syncthreads();
+  RowFrag<DH> fr;
+  fr.init(lane);
 
   float m = -INFINITY, l = 0.f;
   f32x16_t acc[ND];
@@ -175,97 +186,97 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(const bf16_t *__restrict_
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[nd][r] = 0.f;
 
-  // one key tile; SET = jt & 1 is the register set tile jt travelled in (free again: tile jt is in LDS)
-  auto tile_step = [&](int jt, auto setc) {
-    constexpr int SET = decltype(setc)::value;
-    const int j0 = jt * AK;
-    const bf16_t *ks = Ks + SET * TILE, *vs = Vs + SET * TILE;
-    if (jt + 2 < ntile) {  // tile jt + 2: global -> registers, in flight during this tile's and the next one's products
-      tk.template load<SET>(kp + (int64_t)(j0 + 2 * AK) * ld, T - j0 - 2 * AK);
-      tv.template load<SET>(vp + (int64_t)(j0 + 2 * AK) * ld, T - j0 - 2 * AK);
+  for (int it = 0; it < nstep; ++it) {
+    landed_barrier();
+    if (it + 1 < nstep) load(it + 1);
+    const int j0 = (it * KW + grp) * AK;
+    const bf16_t *const ks = smem + (it & 1) * STAGE + grp * 2 * TILE, *const vs = ks + TILE;
+    if (j0 > my_last) continue;
+    f32x16_t s[2];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[nt][r] = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < DH / 16; ++kk)
+        s[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.rows(ks, nt, kk), qf[kk], s[nt], 0, 0, 0);
     }
-    if (j0 <= my_last) {
-      f32x16_t s[2];
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[nt][r] = 0.f;
-#pragma unroll
-        for (int sl = 0; sl < NS; ++sl)
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk)
-            s[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment<0>(ks + sl * AK * BK, ko[nt][kk], 0),
-                                                            qf[sl * 4 + kk], s[nt], 0, 0, 0);
-      }
-      // Vector-ALU work per score is what bounds this kernel (a wavefront instruction takes four clocks), so it is
-      // kept to a maximum, a fused multiply-add, an exponential, an add and half a conversion: the scores stay
-      // unscaled (the scale is positive, so it commutes with the maximum and is folded into the exponent's
-      // multiply-add), and the causal mask is applied only in tiles that reach above the wavefront's first row.
-      if (j0 + AK - 1 > r0) {
-        const int over = j0 + (lane >> 5) * 4 - myrow;  // key - row of this lane's first column
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (over + nt * 32 + (r >> 2) * 8 + (r & 3) > 0) s[nt][r] = -INFINITY;
-      }
-      float tmax = s[0][0];
+    // Vector-ALU work per score is kept to a maximum, a fused multiply-add, an exponential, an add and half a
+    // conversion: the scores stay unscaled (the scale is positive, so it commutes with the maximum and is folded into
+    // the exponent's multiply-add), and the causal mask is applied only in tiles that reach above the wavefront's
+    // first row.
+    if (j0 + AK - 1 > r0) {
+      const int over = j0 + (lane >> 5) * 4 - myrow;  // key - row of this lane's first column
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) tmax = __builtin_fmaxf(tmax, s[nt][r]);
-      tmax = __builtin_fmaxf(tmax, xor32(tmax));
-      // The reference maximum m of a row (log2 domain) only has to keep the exponentials in range, so it is moved -
-      // and the sum and the output rescaled - only when some row's maximum has outgrown it by more than 2^8; the
-      // result does not depend on which reference is used.  Finite from the first tile on: key 0 is visible to
-      // every row.
-      const float tm = tmax * scale_log2e;
-      if (__builtin_amdgcn_ballot_w64(tm > m + 8.f)) {
-        const float mn = __builtin_fmaxf(m, tm);
-        const float alpha = __builtin_amdgcn_exp2f(m - mn);
-        m = mn;
-        l *= alpha;
-#pragma unroll
-        for (int nd = 0; nd < ND; ++nd)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[nd][r] *= alpha;
-      }
-      float sum = 0.f;
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float p[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[nt][q * 4 + e], scale_log2e, -m));
-            sum += p[e];
-          }
-          patch_put(patch, lane, nt, q, p);
-        }
-      l += sum;
-      wave_lds_fence();
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const bf16x8_t pf = patch_get(patch, lane, kk);
-#pragma unroll
-        for (int nd = 0; nd < ND; ++nd)
-          acc[nd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment<1>(vs, vo[nd][kk][0], vo[nd][kk][1]), pf, acc[nd], 0,
-                                                            0, 0);
-      }
-      wave_lds_fence();  // the patch has been read before the next tile overwrites it
+        for (int r = 0; r < 16; ++r)
+          if (over + nt * 32 + (r >> 2) * 8 + (r & 3) > 0) s[nt][r] = -INFINITY;
     }
-    if (jt + 1 < ntile) {
-      tk.template store0<SET ^ 1>(Ks + (SET ^ 1) * TILE);
-      tv.template store1<SET ^ 1>(Vs + (SET ^ 1) * TILE);
+    float tmax = s[0][0];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) tmax = __builtin_fmaxf(tmax, s[nt][r]);
+    tmax = max_halves(tmax);
+    // The reference maximum m of a row (log2 domain) only has to keep the exponentials in range, so it is moved -
+    // and the sum and the output rescaled - only when some row's maximum has outgrown it by more than 2^8; the
+    // result does not depend on which reference is used.  Finite from a
+    // wavefront's first tile on: a tile that it does not skip starts at or before its first row.
+    const float tm = tmax * scale_log2e;
+    if (__builtin_amdgcn_ballot_w64(tm > m + 8.f)) {
+      const float mn = __builtin_fmaxf(m, tm);
+      const float alpha = __builtin_amdgcn_exp2f(m - mn);
+      m = mn;
+      l *= alpha;
+#pragma unroll
+      for (int nd = 0; nd < ND; ++nd)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[nd][r] *= alpha;
+    }
+    float sum = 0.f;
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+      float p[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[nt][r], scale_log2e, -m));
+        sum += p[r];
+      }
+#pragma unroll
+      for (int k2 = 0; k2 < 2; ++k2) {
+        const bf16x8_t pf = row_operand(p, k2);
+#pragma unroll
+        for (int nd = 0; nd < ND; ++nd)
+          acc[nd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.tr(vs, nd, nt * 2 + k2), pf, acc[nd], 0, 0, 0);
+      }
+    }
+    l += sum;
+  }
+  l = sum_halves(l);
+  if constexpr (KW == 2) {
+    // group 1 hands its maximum, sum and output over; [value][wavefront][lane]
+    float *const x = (float *)smem + wave * 64 + lane;
+    __syncthreads();
+    if (grp == 1) {
+      x[0] = m;
+      x[256] = l;
+#pragma unroll
+      for (int nd = 0; nd < ND; ++nd)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) x[(2 + nd * 16 + r) * 256] = acc[nd][r];
     }
     __syncthreads();
-  };
-  for (int jt = 0; jt < ntile; jt += 2) {
-    tile_step(jt, IntC<0>());
-    if (jt + 1 < ntile) tile_step(jt + 1, IntC<1>());
+    if (grp == 1) return;
+    const float m1 = x[0], mn = __builtin_fmaxf(m, m1);
+    const float a0 = __builtin_amdgcn_exp2f(m - mn), a1 = __builtin_amdgcn_exp2f(m1 - mn);
+    m = mn;
+    l = l * a0 + x[256] * a1;
+#pragma unroll
+    for (int nd = 0; nd < ND; ++nd)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[nd][r] = acc[nd][r] * a0 + x[(2 + nd * 16 + r) * 256] * a1;
   }
-  l += xor32(l);
   const float inv_l = 1.f / l;
   if (myrow < T) {
     if (lane < 32) lse[(int64_t)z * T + myrow] = (m + log2f(l)) * LN2;
@@ -279,33 +290,65 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(const bf16_t *__restrict_
   }
 }
 
+// adds what group 1 of a two-group block holds to group 0's accumulators; false for the wavefronts of group 1
+template <int NA>
+__device__ __forceinline__ bool merge_groups(f32x16_t (&acc)[NA], int grp, float *smem, int wave, int lane) {
+  float *const x = smem + wave * 64 + lane;
+  __syncthreads();
+  if (grp == 1) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) x[(i * 16 + r) * 256] = acc[i][r];
+  }
+  __syncthreads();
+  if (grp == 1) return false;
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] += x[(i * 16 + r) * 256];
+  return true;
+}
+
 // ---------------------------------------------------------------------------
-// backward, part 1: dQ.  Same decomposition as the forward kernel (128 query
-// rows per block, 32 per wavefront, key tiles up to the diagonal).  Per tile:
+// backward, part 1: dQ.  Same decomposition as the forward kernel.  Per tile:
 // p = exp(s - L), dP = dO V^T, dS = p (dP - D) / sqrt(dh) with
-// D_i = sum_c dO[i,c] O[i,c] (written out for part 2), dQ += dS K.
+// D_i = sum_c dO[i,c] O[i,c] (written out for part 2), dQ += dS K.  Both backward
+// kernels together at B 4, H 16, T 2048, dh 128: 830 -> 280 us; at B 4, H 12, T 512, dh 64: 41 -> 28 us.
 // ---------------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
-                                                          const bf16_t *__restrict__ d_o, const float *__restrict__ lse,
-                                                          float *__restrict__ dsum, bf16_t *__restrict__ dqkv, int T,
-                                                          int H, int d, float scale) {
-  constexpr int NS = DH / 64, ND = DH / 32;
-  constexpr int TILE = AK * DH;
+template <int DH, int KW>
+__global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
+                                                                  const bf16_t *__restrict__ d_o, const float *__restrict__ lse,
+                                                                  float *__restrict__ dsum, bf16_t *__restrict__ dqkv, int T,
+                                                                  int H, int d, int nb, int pairs, float scale) {
+  constexpr int ND = DH / 32;
+  constexpr int TILE = RowTile<DH>::SIZE, STAGE = 2 * TILE * KW;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-  bf16_t *const Ks0 = smem;              // [2][TILE] K, layout 0 (scores)
-  bf16_t *const Ks1 = Ks0 + 2 * TILE;    // [2][TILE] K, layout 1 (dQ += dS K contracts over keys)
-  bf16_t *const Vs0 = Ks1 + 2 * TILE;    // [2][TILE] V, layout 0 (dP = dO V^T)
-  bf16_t *const Ps = Vs0 + 2 * TILE;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int qb = gridDim.x - 1 - blockIdx.x;
-  const int z = blockIdx.y, b = z / H, h = z % H;
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+  int z, qb;
+  block_place(pairs, z, qb);
+  qb = nb - 1 - qb;
+  const int b = z / H, h = z % H;
   const int q0 = qb * AQ, r0 = q0 + wave * 32;
   const int64_t ld = 3 * (int64_t)d;
   const bf16_t *qp = qkv + (int64_t)b * T * ld + h * DH, *kp = qp + d, *vp = qp + 2 * d;
   const int myrow = r0 + (lane & 31);
   const int ldrow = min(myrow, T - 1);
 
+  RowTile<DH> tile;
+  tile.init(ld, tid);
+  const uint32_t lds0 = lds_addr(smem) + grp * 2 * TILE * 2;
+  const int kend = min(T, q0 + AQ);
+  const int nstep = (kend + AK * KW - 1) / (AK * KW);
+  const int my_last = r0 + 31;
+  auto load = [&](int it) {
+    const int j0 = (it * KW + grp) * AK;
+    const uint32_t s = lds0 + (it & 1) * STAGE * 2;
+    tile.load(kp + (int64_t)j0 * ld, T - j0, s, wave);
+    tile.load(vp + (int64_t)j0 * ld, T - j0, s + TILE * 2, wave);
+  };
+  load(0);
   bf16x8_t qf[DH / 16], dof[DH / 16];
   float dsum_part = 0.f;
   {
@@ -320,39 +363,13 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16_t *__restri
       for (int e = 0; e < 8; ++e) dsum_part += (float)dof[kk][e] * (float)of[e];
     }
   }
-  const float Di = dsum_part + xor32(dsum_part);
+  const float Di = sum_halves(dsum_part);
   const float L2 = lse[(int64_t)z * T + ldrow] * LOG2E;
-  if (lane < 32 && myrow < T) dsum[(int64_t)z * T + myrow] = Di;
-
-  int ko[2][4], vo[ND][4][2];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    int unused;
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) fragment_offsets<AK, 0>(nt * 32, kk, lane, ko[nt][kk], unused);
-#pragma unroll
-    for (int nd = 0; nd < ND; ++nd) fragment_offsets<DH, 1>(nd * 32, kk, lane, vo[nd][kk][0], vo[nd][kk][1]);
-  }
-  bf16_t *const patch = Ps + wave * 32 * PP;
-  const int kend = min(T, q0 + AQ);
-  const int ntile = (kend + AK - 1) / AK;
-  const int my_last = r0 + 31;
+  if (grp == 0 && lane < 32 && myrow < T) dsum[(int64_t)z * T + myrow] = Di;
   const float scale_log2e = scale * LOG2E;
   const float nL2 = -L2, nDs = -Di * scale;
-
-  RowTile<DH> tk, tv;
-  tk.init(ld, tid);
-  tv.init(ld, tid);
-  tk.template load<0>(kp, T);
-  tv.template load<0>(vp, T);
-  if (ntile > 1) {
-    tk.template load<1>(kp + (int64_t)AK * ld, T - AK);
-    tv.template load<1>(vp + (int64_t)AK * ld, T - AK);
-  }
-  tk.template store0<0>(Ks0);
-  tk.template store1<0>(Ks1);
-  tv.template store0<0>(Vs0);
-  __syncthreads();
+  RowFrag<DH> fr;
+  fr.init(lane);
 
   f32x16_t acc[ND];
 #pragma unroll
@@ -360,70 +377,48 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16_t *__restri
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[nd][r] = 0.f;
 
-  // staging as in the forward kernel: tiles requested two ahead, SET = jt & 1
-  auto tile_step = [&](int jt, auto setc) {
-    constexpr int SET = decltype(setc)::value;
-    const int j0 = jt * AK, cur = SET * TILE, nxt = (SET ^ 1) * TILE;
-    if (jt + 2 < ntile) {
-      tk.template load<SET>(kp + (int64_t)(j0 + 2 * AK) * ld, T - j0 - 2 * AK);
-      tv.template load<SET>(vp + (int64_t)(j0 + 2 * AK) * ld, T - j0 - 2 * AK);
-    }
-    if (j0 <= my_last) {
+  for (int it = 0; it < nstep; ++it) {
+    landed_barrier();
+    if (it + 1 < nstep) load(it + 1);
+    const int j0 = (it * KW + grp) * AK;
+    const bf16_t *const ks = smem + (it & 1) * STAGE + grp * 2 * TILE, *const vs = ks + TILE;
+    if (j0 > my_last) continue;
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        f32x16_t s, dp;
+    for (int nt = 0; nt < 2; ++nt) {
+      f32x16_t s, dp;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+      for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
 #pragma unroll
-        for (int sl = 0; sl < NS; ++sl)
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk) {
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment<0>(Ks0 + cur + sl * AK * BK, ko[nt][kk], 0),
-                                                        qf[sl * 4 + kk], s, 0, 0, 0);
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment<0>(Vs0 + cur + sl * AK * BK, ko[nt][kk], 0),
-                                                         dof[sl * 4 + kk], dp, 0, 0, 0);
-          }
-        // as in the forward kernel the vector-ALU work per score is kept minimal: the mask only where the tile
-        // reaches above the wavefront's first row (a masked score of -inf gives p = 0 exactly), the scale folded
-        // into two fused multiply-adds
-        if (j0 + nt * 32 + 31 > r0) {
-          const int over = j0 + nt * 32 + (lane >> 5) * 4 - myrow;
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (over + (r >> 2) * 8 + (r & 3) > 0) s[r] = -INFINITY;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float ds[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[q * 4 + e], scale_log2e, nL2));
-            ds[e] = p * __builtin_fmaf(dp[q * 4 + e], scale, nDs);
-          }
-          patch_put(patch, lane, nt, q, ds);
-        }
+      for (int kk = 0; kk < DH / 16; ++kk) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.rows(ks, nt, kk), qf[kk], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.rows(vs, nt, kk), dof[kk], dp, 0, 0, 0);
       }
-      wave_lds_fence();
+      // as in the forward kernel the vector-ALU work per score is kept minimal: the mask only where the tile
+      // reaches above the wavefront's first row (a masked score of -inf gives p = 0 exactly), the scale folded
+      // into two fused multiply-adds
+      if (j0 + nt * 32 + 31 > r0) {
+        const int over = j0 + nt * 32 + (lane >> 5) * 4 - myrow;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const bf16x8_t df = patch_get(patch, lane, kk);
+        for (int r = 0; r < 16; ++r)
+          if (over + (r >> 2) * 8 + (r & 3) > 0) s[r] = -INFINITY;
+      }
+      float ds[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2e, nL2));
+        ds[r] = p * __builtin_fmaf(dp[r], scale, nDs);
+      }
+#pragma unroll
+      for (int k2 = 0; k2 < 2; ++k2) {
+        const bf16x8_t df = row_operand(ds, k2);
 #pragma unroll
         for (int nd = 0; nd < ND; ++nd)
-          acc[nd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment<1>(Ks1 + cur, vo[nd][kk][0], vo[nd][kk][1]), df,
-                                                            acc[nd], 0, 0, 0);
+          acc[nd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.tr(ks, nd, nt * 2 + k2), df, acc[nd], 0, 0, 0);
       }
-      wave_lds_fence();
     }
-    if (jt + 1 < ntile) {
-      tk.template store0<SET ^ 1>(Ks0 + nxt);
-      tk.template store1<SET ^ 1>(Ks1 + nxt);
-      tv.template store0<SET ^ 1>(Vs0 + nxt);
-    }
-    __syncthreads();
-  };
-  for (int jt = 0; jt < ntile; jt += 2) {
-    tile_step(jt, IntC<0>());
-    if (jt + 1 < ntile) tile_step(jt + 1, IntC<1>());
+  }
+  if constexpr (KW == 2) {
+    if (!merge_groups(acc, grp, (float *)smem, wave, lane)) return;
   }
   if (myrow < T) {
     bf16_t *dq = dqkv + ((int64_t)b * T + myrow) * ld + h * DH;
@@ -433,31 +428,28 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16_t *__restri
 }
 
 // ---------------------------------------------------------------------------
-// backward, part 2: dK and dV.  One block = 128 keys of one (sample, head),
+// backward, part 2: dK and dV.  Four wavefronts = 128 keys of one (sample, head),
 // wavefront w owns keys kr0 = k0 + 32 w .. + 31 and keeps their K and V
 // fragments in registers.  It walks the query tiles (64 rows) from the diagonal
 // to the end of the sequence, computing the transposed quantities directly:
 // s^T = K Q^T, p^T = exp(s^T - L), dP^T = V dO^T, dS^T = p^T (dP^T - D)/sqrt(dh),
 // dV += p^T dO, dK += dS^T Q.  No atomics: every key row has one owner.
 // ---------------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
-                                                           const bf16_t *__restrict__ d_o,
-                                                           const float *__restrict__ lse,
-                                                           const float *__restrict__ dsum, bf16_t *__restrict__ dqkv,
-                                                           int T, int H, int d, float scale) {
-  constexpr int NS = DH / 64, ND = DH / 32;
-  constexpr int TILE = AK * DH;
-  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-  bf16_t *const Qs0 = smem;              // [2][TILE] Q, layout 0 (s^T)
-  bf16_t *const Qs1 = Qs0 + 2 * TILE;    // [2][TILE] Q, layout 1 (dK += dS^T Q contracts over queries)
-  bf16_t *const Os0 = Qs1 + 2 * TILE;    // [2][TILE] dO, layout 0 (dP^T)
-  bf16_t *const Os1 = Os0 + 2 * TILE;    // [2][TILE] dO, layout 1 (dV += p^T dO)
-  bf16_t *const Ps = Os1 + 2 * TILE;
-  float *const Ls = (float *)(Ps + 4 * 32 * PP);  // [2][128]: -log-sum-exp (log2 domain) and -D / sqrt(dh) of the tile's 64 queries
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int kb = blockIdx.x;
-  const int z = blockIdx.y, b = z / H, h = z % H;
+template <int DH, int KW>
+__global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
+                                                                   const bf16_t *__restrict__ d_o,
+                                                                   const float *__restrict__ lse,
+                                                                   const float *__restrict__ dsum, bf16_t *__restrict__ dqkv,
+                                                                   int T, int H, int d, int nb, int pairs, float scale) {
+  constexpr int ND = DH / 32;
+  constexpr int TILE = RowTile<DH>::SIZE, STAGE = 2 * TILE * KW;
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];  // [2 stages][KW][Q, dO], then the statistics
+  float *const Ls = (float *)(smem + 2 * STAGE);  // [2][KW][128]: -log-sum-exp (log2 domain) and -D / sqrt(dh) of a tile's 64 queries
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+  int z, kb;
+  block_place(pairs, z, kb);
+  const int b = z / H, h = z % H;
   const int k0 = kb * AQ, kr0 = k0 + wave * 32;
   const int64_t ld = 3 * (int64_t)d;
   const bf16_t *qp = qkv + (int64_t)b * T * ld + h * DH, *kp = qp + d, *vp = qp + 2 * d;
@@ -465,6 +457,25 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const bf16_t *__restr
   const int mykey = kr0 + (lane & 31);
   const int ldkey = min(mykey, T - 1);
 
+  RowTile<DH> tq, to;
+  tq.init(ld, tid);
+  to.init(d, tid);
+  const uint32_t lds0 = lds_addr(smem) + grp * 2 * TILE * 2;
+  const int nstep = (T - k0 + AK * KW - 1) / (AK * KW);
+  auto first = [&](int it) { return k0 + (it * KW + grp) * AK; };  // first query of this group's tile
+  auto load = [&](int it) {
+    const int i0 = first(it);
+    const uint32_t s = lds0 + (it & 1) * STAGE * 2;
+    tq.load(qp + (int64_t)i0 * ld, T - i0, s, wave);
+    to.load(dop + (int64_t)i0 * d, T - i0, s + TILE * 2, wave);
+  };
+  auto load_stat = [&](int i0) -> float {
+    const int qi = i0 + (tid & 63);
+    if (tid >= 128 || qi >= T) return 0.f;
+    return tid < 64 ? -lse[(int64_t)z * T + qi] * LOG2E : -dsum[(int64_t)z * T + qi] * scale;
+  };
+  load(0);
+  float stat = load_stat(first(0));
   bf16x8_t kf[DH / 16], vf[DH / 16];
 #pragma unroll
   for (int kk = 0; kk < DH / 16; ++kk) {
@@ -472,163 +483,81 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const bf16_t *__restr
     kf[kk] = load_frag_global(kp + ldkey * ld + c);
     vf[kk] = load_frag_global(vp + ldkey * ld + c);
   }
-  int ko[2][4], vo[ND][4][2];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    int unused;
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) fragment_offsets<AK, 0>(nt * 32, kk, lane, ko[nt][kk], unused);
-#pragma unroll
-    for (int nd = 0; nd < ND; ++nd) fragment_offsets<DH, 1>(nd * 32, kk, lane, vo[nd][kk][0], vo[nd][kk][1]);
-  }
-  bf16_t *const patch = Ps + wave * 32 * PP;
+  if (tid < 128) Ls[grp * 128 + tid] = stat;
   const float scale_log2e = scale * LOG2E;
+  RowFrag<DH> fr;
+  fr.init(lane);
 
-  f32x16_t dk[ND], dv[ND];
+  f32x16_t acc[2 * ND];  // dK, dV
 #pragma unroll
-  for (int nd = 0; nd < ND; ++nd)
+  for (int nd = 0; nd < 2 * ND; ++nd)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) dk[nd][r] = dv[nd][r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[nd][r] = 0.f;
 
-  // head width 128 has no registers left for a second tile in flight (it would spill): one tile ahead there
-  constexpr bool FAR = DH <= 64;
-  RowTile<DH, FAR ? 2 : 1> tq, to;
-  tq.init(ld, tid);
-  to.init(d, tid);
-  const int ibeg = (k0 / AK) * AK;
-  float stat0 = 0.f, stat1 = 0.f;  // this thread's entry of the statistics of the two tiles in flight
-  auto load_stat = [&](int i0) -> float {
-    float st = 0.f;
-    if (tid < 128) {
-      const int qi = i0 + (tid & 63);
-      if (qi < T) st = tid < 64 ? -lse[(int64_t)z * T + qi] * LOG2E : -dsum[(int64_t)z * T + qi] * scale;
+  for (int it = 0; it < nstep; ++it) {
+    landed_barrier();
+    const bool more = it + 1 < nstep;
+    if (more) {
+      stat = load_stat(first(it + 1));
+      load(it + 1);
     }
-    return st;
-  };
-  tq.template load<0>(qp + (int64_t)ibeg * ld, T - ibeg);
-  to.template load<0>(dop + (int64_t)ibeg * d, T - ibeg);
-  stat0 = load_stat(ibeg);
-  if (FAR && ibeg + AK < T) {
-    tq.template load<FAR ? 1 : 0>(qp + (int64_t)(ibeg + AK) * ld, T - ibeg - AK);
-    to.template load<FAR ? 1 : 0>(dop + (int64_t)(ibeg + AK) * d, T - ibeg - AK);
-    stat1 = load_stat(ibeg + AK);
-  }
-  tq.template store0<0>(Qs0);
-  tq.template store1<0>(Qs1);
-  to.template store0<0>(Os0);
-  to.template store1<0>(Os1);
-  if (tid < 128) Ls[tid] = stat0;
-  __syncthreads();
-
-  // one query tile; SET = it & 1.  Tiles are requested from global memory two ahead, as in the other two kernels.
-  // (par = parity of the tile's index = its LDS buffer; with FAR it equals SET, otherwise only set 0 is used)
-  auto tile_step = [&](int i0, int par, auto setc) {
-    constexpr int SET = decltype(setc)::value;
-    const int cur = par * TILE, nxt = (par ^ 1) * TILE;
-    const float *ls = Ls + par * 128;
-    const bool more = i0 + AK < T;
-    if (FAR && i0 + 2 * AK < T) {
-      tq.template load<FAR ? SET : 0>(qp + (int64_t)(i0 + 2 * AK) * ld, T - i0 - 2 * AK);
-      to.template load<FAR ? SET : 0>(dop + (int64_t)(i0 + 2 * AK) * d, T - i0 - 2 * AK);
-      (SET ? stat1 : stat0) = load_stat(i0 + 2 * AK);
-    }
-    if (!FAR && more) {
-      tq.template load<0>(qp + (int64_t)(i0 + AK) * ld, T - i0 - AK);
-      to.template load<0>(dop + (int64_t)(i0 + AK) * d, T - i0 - AK);
-      stat0 = load_stat(i0 + AK);
-    }
-    if (i0 + AK - 1 >= kr0) {  // else every query of the tile precedes every key of this wavefront
-      f32x16_t s[2], dp[2];
+    const int i0 = first(it);
+    const bf16_t *const qs = smem + (it & 1) * STAGE + grp * 2 * TILE, *const os = qs + TILE;
+    const float *const ls = Ls + ((it & 1) * KW + grp) * 128;
+    if (i0 + AK - 1 >= kr0 && i0 < T) {  // else no query of the tile comes after a key of this wavefront
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt) {
+        f32x16_t s, dp;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[nt][r] = dp[nt][r] = 0.f;
+        for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
 #pragma unroll
-        for (int sl = 0; sl < NS; ++sl)
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk) {
-            s[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment<0>(Qs0 + cur + sl * AK * BK, ko[nt][kk], 0),
-                                                            kf[sl * 4 + kk], s[nt], 0, 0, 0);
-            dp[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment<0>(Os0 + cur + sl * AK * BK, ko[nt][kk], 0),
-                                                             vf[sl * 4 + kk], dp[nt], 0, 0, 0);
-          }
-        // p^T into the patch; dS^T replaces s in registers for the second round.  The mask is needed only where
-        // the tile holds queries that precede keys of this wavefront; queries past the end of the sequence need
-        // none (their Q and dO rows are zero-filled and their statistics zero, so they contribute exact zeros).
-        // ls holds -L (log2 domain) and -D / sqrt(dh) of the tile's queries.
+        for (int kk = 0; kk < DH / 16; ++kk) {
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.rows(qs, nt, kk), kf[kk], s, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.rows(os, nt, kk), vf[kk], dp, 0, 0, 0);
+        }
+        // The mask is needed only where the tile holds queries that precede keys of this wavefront; queries past the
+        // end of the sequence need none (their Q and dO rows are zero-filled and their statistics zero, so they
+        // contribute exact zeros).
         if (i0 + nt * 32 < kr0 + 31) {
           const int under = mykey - (i0 + nt * 32 + (lane >> 5) * 4);  // key - query of this lane's first column
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            if (under - ((r >> 2) * 8 + (r & 3)) > 0) s[nt][r] = -INFINITY;
+            if (under - ((r >> 2) * 8 + (r & 3)) > 0) s[r] = -INFINITY;
         }
+        float p[16], ds[16];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int qc = nt * 32 + q * 8 + (lane >> 5) * 4;  // first of this lane's four queries within the tile
           const f32x4_t nl = *(const f32x4_t *)(ls + qc), nd4 = *(const f32x4_t *)(ls + 64 + qc);
-          float p4[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[nt][q * 4 + e], scale_log2e, nl[e]));
-            p4[e] = p;
-            s[nt][q * 4 + e] = p * __builtin_fmaf(dp[nt][q * 4 + e], scale, nd4[e]);
+            const int r = q * 4 + e;
+            p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2e, nl[e]));
+            ds[r] = p[r] * __builtin_fmaf(dp[r], scale, nd4[e]);
           }
-          patch_put(patch, lane, nt, q, p4);
+        }
+#pragma unroll
+        for (int k2 = 0; k2 < 2; ++k2) {
+          const bf16x8_t pf = row_operand(p, k2), df = row_operand(ds, k2);
+#pragma unroll
+          for (int nd = 0; nd < ND; ++nd) {
+            acc[ND + nd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.tr(os, nd, nt * 2 + k2), pf, acc[ND + nd], 0, 0, 0);
+            acc[nd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.tr(qs, nd, nt * 2 + k2), df, acc[nd], 0, 0, 0);
+          }
         }
       }
-      wave_lds_fence();
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const bf16x8_t pf = patch_get(patch, lane, kk);
-#pragma unroll
-        for (int nd = 0; nd < ND; ++nd)
-          dv[nd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment<1>(Os1 + cur, vo[nd][kk][0], vo[nd][kk][1]), pf,
-                                                           dv[nd], 0, 0, 0);
-      }
-      wave_lds_fence();
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float w4[4] = {s[nt][q * 4 + 0], s[nt][q * 4 + 1], s[nt][q * 4 + 2], s[nt][q * 4 + 3]};
-          patch_put(patch, lane, nt, q, w4);
-        }
-      wave_lds_fence();
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const bf16x8_t pf = patch_get(patch, lane, kk);
-#pragma unroll
-        for (int nd = 0; nd < ND; ++nd)
-          dk[nd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment<1>(Qs1 + cur, vo[nd][kk][0], vo[nd][kk][1]), pf,
-                                                           dk[nd], 0, 0, 0);
-      }
-      wave_lds_fence();
     }
-    if (more) {
-      constexpr int NS_ = FAR ? (SET ^ 1) : 0;  // register set the next tile travelled in
-      tq.template store0<NS_>(Qs0 + nxt);
-      tq.template store1<NS_>(Qs1 + nxt);
-      to.template store0<NS_>(Os0 + nxt);
-      to.template store1<NS_>(Os1 + nxt);
-      if (tid < 128) Ls[(par ^ 1) * 128 + tid] = NS_ ? stat1 : stat0;
-    }
-    __syncthreads();
-  };
-  if (FAR) {
-    for (int i0 = ibeg; i0 < T; i0 += 2 * AK) {
-      tile_step(i0, 0, IntC<0>());
-      if (i0 + AK < T) tile_step(i0 + AK, 1, IntC<1>());
-    }
-  } else {
-    int it = 0;
-    for (int i0 = ibeg; i0 < T; i0 += AK, ++it) tile_step(i0, it & 1, IntC<0>());
+    if (more && tid < 128) Ls[(((it + 1) & 1) * KW + grp) * 128 + tid] = stat;
+  }
+  if constexpr (KW == 2) {
+    if (!merge_groups(acc, grp, (float *)smem, wave, lane)) return;
   }
   if (mykey < T) {
     bf16_t *dkp = dqkv + ((int64_t)b * T + mykey) * ld + d + h * DH, *dvp = dkp + d;
 #pragma unroll
     for (int nd = 0; nd < ND; ++nd) {
-      store_tile_row(dkp + nd * 32, lane, dk[nd]);
-      store_tile_row(dvp + nd * 32, lane, dv[nd]);
+      store_tile_row(dkp + nd * 32, lane, acc[nd]);
+      store_tile_row(dvp + nd * 32, lane, acc[ND + nd]);
     }
   }
 }
@@ -637,56 +566,70 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const bf16_t *__restr
 
 bool attention_fused_supported(int dtype, int dh) { return dtype == DT_BF16 && (dh == 64 || dh == 128); }
 
-template <typename K>
-static hipError_t set_lds(K kern, size_t bytes) {
-  return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+// bytes of LDS: two stages of two tiles per group, and room for the merge of two groups (nacc 32-column accumulators
+// and `extra` values per row)
+static constexpr size_t attn_lds(int dh, int kw, int nacc, int extra, size_t stats) {
+  const size_t tiles = (size_t)2 * kw * 2 * AK * dh * 2 + stats, merge = kw == 2 ? (size_t)(nacc * 16 + extra) * 256 * 4 : 0;
+  return tiles > merge ? tiles : merge;
 }
 
+#define HYDRA_ATTN(KERN_, LDS_, ...)                                                                             \
+  do {                                                                                                           \
+    auto kern = KERN_;                                                                                           \
+    static hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, \
+                                                 (int)(LDS_));                                                   \
+    if (attr != hipSuccess) return attr;                                                                         \
+    hipLaunchKernelGGL(kern, dim3(nb * B * H), dim3(256 * KW), LDS_, s, __VA_ARGS__);                            \
+  } while (0)
+
+template <int DH, int KW>
+static hipError_t attn_fwd(const bf16_t *qkv, bf16_t *o, float *lse, int B, int H, int T, hipStream_t s) {
+  const int nb = (T + AQ - 1) / AQ, d = H * DH;
+  HYDRA_ATTN((attn_fwd_kernel<DH, KW>), attn_lds(DH, KW, DH / 32, 2, 0), qkv, o, lse, T, H, d, nb, B * H,
+             LOG2E / sqrtf((float)DH));
+  return hipGetLastError();
+}
+
+template <int DH, int KW>
+static hipError_t attn_bwd(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o, const float *lse, float *dsum, bf16_t *dqkv,
+                           int B, int H, int T, hipStream_t s) {
+  const int nb = (T + AQ - 1) / AQ, d = H * DH;
+  const float scale = 1.0f / sqrtf((float)DH);
+  HYDRA_ATTN((attn_bwd_dq_kernel<DH, KW>), attn_lds(DH, KW, DH / 32, 0, 0), qkv, o, d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale);
+  HYDRA_ATTN((attn_bwd_dkv_kernel<DH, KW>), attn_lds(DH, KW, DH / 16, 0, KW * 256 * 4), qkv, d_o, lse, dsum, dqkv, T, H, d, nb, B * H,
+             scale);
+  return hipGetLastError();
+}
+#undef HYDRA_ATTN
+
+// Two groups of wavefronts per block while the row blocks of a launch leave wavefront slots empty (two blocks of four
+// wavefronts per CU make 512): us with one / two groups, forward, then backward -
+//   B 4, H 12, T 512, dh 64 (192 blocks) 10.8 / 10.1, 29.9 / 28.0;   B 2, H 12, T 2048, dh 64 (384) 33 / 27, 93 / 76;
+//   B 1, H 32, T 1024, dh 128 (256) 27 / 23, 91 / 76;   B 5, H 12, T 1024, dh 64 (480) 19.9 / 19.3, 55 / 59;
+//   B 3, H 25, T 1000, dh 64 (600) 23 / 25, 67 / 80;   B 4, H 16, T 2048, dh 128 (1024) 79 / 98, 280 / 325.
+// Sequences of one or two tiles have nothing to share out.
+static bool two_groups(int B, int H, int T, int limit) { return T > 4 * AK && (long)((T + AQ - 1) / AQ) * B * H <= limit; }
+
 hipError_t launch_attention_fwd(const void *qkv, void *o, float *lse, int B, int H, int T, int dh, hipStream_t s) {
-  const int d = H * dh;
-  const float scale_log2e = LOG2E / sqrtf((float)dh);
-  dim3 grid((T + AQ - 1) / AQ, B * H);
-  const size_t lds = (size_t)(4 * AK * dh + 4 * 32 * PP) * 2;
   // causal half of both products
   ProfScope ps("attention_fwd", s, 2.0 * B * H * dh * ((double)T * (T + 1.0)), 0);
-#define HYDRA_ATTN_FWD(DH_)                                                                                     \
-  do {                                                                                                           \
-    static hipError_t a1 = set_lds(attn_fwd_kernel<DH_>, lds);                                                   \
-    if (a1 != hipSuccess) return a1;                                                                             \
-    hipLaunchKernelGGL(attn_fwd_kernel<DH_>, grid, dim3(256), lds, s, (const bf16_t *)qkv, (bf16_t *)o, lse, T, H, \
-                       d, scale_log2e);                                                                          \
-  } while (0)
-  if (dh == 64) HYDRA_ATTN_FWD(64);
-  else if (dh == 128) HYDRA_ATTN_FWD(128);
-  else return hipErrorInvalidValue;
-#undef HYDRA_ATTN_FWD
-  return hipGetLastError();
+  const bool two = two_groups(B, H, T, 512);
+  const bf16_t *in = (const bf16_t *)qkv;
+  if (dh == 64) return two ? attn_fwd<64, 2>(in, (bf16_t *)o, lse, B, H, T, s) : attn_fwd<64, 1>(in, (bf16_t *)o, lse, B, H, T, s);
+  if (dh == 128) return two ? attn_fwd<128, 2>(in, (bf16_t *)o, lse, B, H, T, s) : attn_fwd<128, 1>(in, (bf16_t *)o, lse, B, H, T, s);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_attention_bwd(const void *qkv, const void *o, const void *d_o, const float *lse, float *dsum,
                                 void *dqkv, int B, int H, int T, int dh, hipStream_t s) {
-  const int d = H * dh;
-  const float scale = 1.0f / sqrtf((float)dh);
-  dim3 grid((T + AQ - 1) / AQ, B * H);
-  const size_t lds_dq = (size_t)(6 * AK * dh + 4 * 32 * PP) * 2;
-  const size_t lds_dkv = (size_t)(8 * AK * dh + 4 * 32 * PP) * 2 + 256 * 4;
   // five causal products of T x T x dh each (s and dP in both kernels count once: the recomputation is overhead)
   ProfScope ps("attention_bwd", s, 5.0 * B * H * dh * ((double)T * (T + 1.0)), 0);
-#define HYDRA_ATTN_BWD(DH_)                                                                                        \
-  do {                                                                                                              \
-    static hipError_t a1 = set_lds(attn_bwd_dq_kernel<DH_>, lds_dq), a2 = set_lds(attn_bwd_dkv_kernel<DH_>, lds_dkv); \
-    if (a1 != hipSuccess) return a1;                                                                                \
-    if (a2 != hipSuccess) return a2;                                                                                \
-    hipLaunchKernelGGL(attn_bwd_dq_kernel<DH_>, grid, dim3(256), lds_dq, s, (const bf16_t *)qkv, (const bf16_t *)o, \
-                       (const bf16_t *)d_o, lse, dsum, (bf16_t *)dqkv, T, H, d, scale);                             \
-    hipLaunchKernelGGL(attn_bwd_dkv_kernel<DH_>, grid, dim3(256), lds_dkv, s, (const bf16_t *)qkv,                  \
-                       (const bf16_t *)d_o, lse, dsum, (bf16_t *)dqkv, T, H, d, scale);                             \
-  } while (0)
-  if (dh == 64) HYDRA_ATTN_BWD(64);
-  else if (dh == 128) HYDRA_ATTN_BWD(128);
-  else return hipErrorInvalidValue;
-#undef HYDRA_ATTN_BWD
-  return hipGetLastError();
+  const bool two = two_groups(B, H, T, 400);
+  const bf16_t *a = (const bf16_t *)qkv, *b = (const bf16_t *)o, *c = (const bf16_t *)d_o;
+  bf16_t *out = (bf16_t *)dqkv;
+  if (dh == 64) return two ? attn_bwd<64, 2>(a, b, c, lse, dsum, out, B, H, T, s) : attn_bwd<64, 1>(a, b, c, lse, dsum, out, B, H, T, s);
+  if (dh == 128) return two ? attn_bwd<128, 2>(a, b, c, lse, dsum, out, B, H, T, s) : attn_bwd<128, 1>(a, b, c, lse, dsum, out, B, H, T, s);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace hydra

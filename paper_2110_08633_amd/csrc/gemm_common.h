@@ -290,7 +290,6 @@ __device__ __forceinline__ void store_patch(const GemmArgs &g, int64_t coff, con
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void *p) {
   return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 0x7ffffff0, 0x00020000);
 }
-constexpr int BUF_OUT = 0x7ffffff8;  // offset past the descriptor's range: the load returns zero and touches no memory
 
 template <int n> __device__ __forceinline__ void wait_loads_le() {
   // vmcnt (outstanding vector-memory loads) is split over bits 3:0 and 15:14; lgkmcnt(0): this wavefront's LDS

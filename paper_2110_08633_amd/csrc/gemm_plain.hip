@@ -38,16 +38,6 @@ namespace hydra {
 // What bounds the large ones now: with loads, LDS reads and MFMAs switched off in turn, 1024x16384x4096 takes 71 us of
 // loads alone (25 bytes per clock and CU), 73 us of MFMAs alone at the clock the chip holds for them, 100 us together.
 // ---------------------------------------------------------------------------
-// 16 bytes per lane from p + off (bytes; BUF_OUT writes zeros) to LDS, lane l at byte dst + 16*l.  Written out because the
-// compiler, when it sees such a load, puts a wait for every load in flight in front of each transposing LDS read; the
-// instruction has no destination register, and the kernel waits for it by count before the barrier that hands a
-// stage over.  (p and dst are uniform.)
-__device__ __forceinline__ void load_to_lds(const bf16_t *p, int off, uint32_t dst) {
-  const uint64_t a = (uint64_t)p;
-  const u32x4_t rsrc = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, 0x7ffffff0u, 0x00020000u};
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rsrc)
-               : "memory");  // m0 is reserved: the compiler keeps nothing in it
-}
 // 16-byte chunk position within a line of LDS.  [row][BK]: 16 rows at one chunk index must fall into distinct slots
 // of the 256-byte bank period.  [k][R]: a read takes two neighbouring chunks of lines k..k+3 and k+8..k+11.
 template <int BK_> __device__ __forceinline__ int swz_kc(int row) { return (BK_ >= 128 ? row : row >> 1) & (BK_ >= 64 ? 7 : 3); }
@@ -170,7 +160,7 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
   // loads than the others waits for a little more than it has to)
   constexpr int NLMIN = NL - (MA::NCH % (64 * NW) ? 1 : 0) - (MB::NCH % (64 * NW) ? 1 : 0);
   wait_loads_le<(S - 1) * NLMIN>();
-  __builtin_amdgcn_s_barrier();
+  block_barrier();
   bf16x8_t af[2][MI], bfr[2][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i) af[0][i] = fa.get(lds, i, 0);
@@ -191,7 +181,7 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
       if (kk + 1 == KS) {
         // slice t + 1 has landed, and this wavefront's reads of slice t are complete before anybody overwrites it
         wait_loads_le<(S - 2) * NLMIN>();
-        __builtin_amdgcn_s_barrier();
+        block_barrier();
         na = lds + st_next * STAGE;
       }
       const bf16_t *const nb = na + BM * BK_;
@@ -237,7 +227,7 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
     if (t < nk) slice(t, st, std::integral_constant<int, 0>());
   }
   wait_loads_le<0>();
-  __builtin_amdgcn_s_barrier();  // the write-out reuses the stages
+  block_barrier();  // the write-out reuses the stages
 
   const bool vec = ((g.ldc & 3) == 0) &&
                    ((((uintptr_t)g.out_f32 | (uintptr_t)g.resid | (uintptr_t)g.bias) & 15) == 0) &&

@@ -146,4 +146,22 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   x.h = __builtin_convertvector(v, bf16x2_t);
   return x.u;
 }
+constexpr int BUF_OUT = 0x7ffffff8;  // offset past the descriptor's range: the load returns zero and touches no memory
+
+// 16 bytes per lane from p + off (bytes; BUF_OUT writes zeros) to LDS, lane l at byte dst + 16*l.  Written out because the
+// compiler, when it sees such a load, puts a wait for every load in flight in front of each transposing LDS read; the
+// instruction has no destination register, and the kernel waits for it by count before the barrier that hands a
+// stage over.  (p and dst are uniform.)
+__device__ __forceinline__ void load_to_lds(const bf16_t *p, int off, uint32_t dst) {
+  const uint64_t a = (uint64_t)p;
+  const u32x4_t rsrc = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, 0x7ffffff0u, 0x00020000u};
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rsrc)
+               : "memory");  // m0 is reserved: the compiler keeps nothing in it
+}
+// a bare barrier (the caller has waited for what it needs) that no memory access moves across
+__device__ __forceinline__ void block_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 }  // namespace hydra

@@ -90,3 +90,45 @@ def test_gemm_bf16_tile_shapes(H, ta, tb, M, N, K):
     # products of bf16 values are exact in fp32; each of the K + 4 additions and scalings errs by at most a unit in the
     # last place of the sum of magnitudes (the matrix instruction may truncate)
     assert ((out.double() - ref).abs() <= 2 * (K + 4) * U32 * mag).all()
+
+
+# one group of wavefronts per block (short sequences, or many row blocks) and two (few row blocks); last tiles and row
+# blocks partly empty; an odd number of tiles for two groups to share; peaked scores, for which the running maximum moves
+ATT_CASES = [(1, 1, 8, 64, 1.0), (2, 3, 72, 128, 1.0), (1, 3, 256, 64, 1.0), (1, 2, 264, 64, 6.0), (3, 5, 328, 128, 1.0),
+             (1, 7, 1000, 64, 1.0), (1, 2, 1096, 128, 6.0), (9, 13, 584, 64, 1.0), (5, 17, 776, 128, 1.0),
+             (7, 16, 520, 64, 6.0)]
+
+
+@pytest.mark.parametrize("B,Hn,T,dh,peak", ATT_CASES)
+def test_attention_variants(H, B, Hn, T, dh, peak):
+    d = Hn * dh
+    qkv = randn(B * T + Hn, B * T, 3 * d)
+    qkv[:, :d] *= peak
+    qkv, d_o = qkv.bfloat16(), randn(T + dh, B * T, d).bfloat16()
+    o, dqkv = (torch.full((B * T + 1, n * d), 7.0, device="cuda").bfloat16() for n in (1, 3))  # a row past the end
+    lse, dsum = (torch.empty(B * Hn * T, device="cuda") for _ in range(2))
+    H.hydra_op_attention_fwd(qkv, o, lse, B, Hn, T, dh)
+    H.hydra_op_attention_bwd(qkv, o, d_o, lse, dsum, dqkv, B, Hn, T, dh)
+    torch.cuda.synchronize()
+    assert (o[-1] == 7.0).all() and (dqkv[-1] == 7.0).all()
+    x = qkv.double().requires_grad_()
+    q, k, v = (x[:, j * d:(j + 1) * d].reshape(B, T, Hn, dh).transpose(1, 2) for j in range(3))
+    s = (q @ k.transpose(2, 3).contiguous()) / dh ** 0.5
+    s = s.masked_fill(torch.ones(T, T, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+    ref_lse = torch.logsumexp(s, -1)
+    p = torch.exp(s - ref_lse[..., None])
+    ref = (p @ v).transpose(1, 2).reshape(B * T, d)
+    mag = (p @ v.abs()).transpose(1, 2).reshape(B * T, d).detach()
+    ref.backward(d_o.double())
+    ref = ref.detach()
+    # the result is rounded to 8 bits and so is every probability (half a unit each); 2^-12 for the exponentials' and the
+    # sums' fp32 rounding
+    assert ((o[:-1].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + (2.0 ** -8 + 2.0 ** -12) * mag).all()
+    # scores are sums of dh products
+    tol = (dh + 8) * U32 * (q.abs().amax() * k.abs().amax()).detach() * dh ** 0.5 + 1e-5
+    assert ((lse.double() - ref_lse.detach().reshape(-1)).abs() <= tol).all()
+    # gradients: the operands p, dS and dP's input o are rounded to 8 bits, 2^-9 / sqrt(3) rms each; D = sum dO * O and the
+    # differences dP - D can double that
+    for j in range(3):
+        g, r = dqkv[:-1, j * d:(j + 1) * d].double(), x.grad[:, j * d:(j + 1) * d]
+        assert (g - r).norm() <= 2.0 ** -7 * r.norm() + 1e-12
