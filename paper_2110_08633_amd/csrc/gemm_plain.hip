@@ -34,7 +34,8 @@ namespace hydra {
 // Measured, us, the kernels this one replaced / now (MxNxK; n: operand contraction-contiguous, t: not):
 //   nt 201x768x2304 13.4 / 9.4, 2048x2304x768 14.7 / 12.7, 1000x3072x768 11.1 / 9.9, 1024x16384x4096 115 / 100,
 //   4096^3 116 / 104; tn 768x2304x2048 20.1 / 17.1, 3072x768x2048 28.8 / 19.0, 1600x6400x1000 41 / 34,
-//   4096x4096x1024 53 / 40, 4096^3 204 / 124; nn 2048x768x50257 437 / 345, 4096^3 188 / 106.
+//   4096x4096x1024 53 / 40, 4096^3 204 / 124; nn 2048x768x50257 437 / 272, 4096^3 188 / 111;
+//   tn 768x50257x2048 270 / 208.
 // What bounds the large ones now: with loads, LDS reads and MFMAs switched off in turn, 1024x16384x4096 takes 71 us of
 // loads alone (25 bytes per clock and CU), 73 us of MFMAs alone at the clock the chip holds for them, 100 us together.
 // ---------------------------------------------------------------------------
@@ -361,30 +362,36 @@ static hipError_t launch_shape(const GemmDesc *d, int n, hipStream_t s) {
 // The tile shapes, and what a launch of each costs in us:
 //   t0 + rounds * (nk * a + c) + tiles / 256 * (nk * b + e)
 // with nk = contraction / 64 (rounded up) and rounds = tiles / 256 rounded up: the tiles of the busiest CU one after the
-// other, plus what all of them take from the caches and from memory together.  The constants are least-squares fits
-// (rms error 3-14 %) to 200 products of the four models' widths at 201 to 4096 tokens, LM heads included, one set for
-// operands that are both contraction-contiguous and one for products with a transposing LDS read.  Taking the cheapest
-// shape by this estimate is within 1.3 % / 1.7 % of the fastest shape on average, and 15 % / 31 % faster than the
-// kernels it replaces.
+// other, plus what all of them take from the caches and from memory together.  With transposing LDS reads of both a block of four
+// wavefronts alone leaves its CU half idle, so there a round is as many tiles as the CUs hold blocks.  The constants are
+// least-squares fits (weighted towards the products for which a shape is among the fastest) to 200 products of the four
+// models' widths at 201 to 4096 tokens, LM heads included: one set for operands that are both contraction-contiguous and
+// one for products that read both through the transposing LDS read; products with one of each take the middle.  The
+// cheapest shape by this estimate is within 1.1 % of the fastest one on average, and 1.35 times as fast as the kernels
+// it replaces (210 random products).
 struct PlainShape {
-  int bm, bn;
+  int bm, bn, occ;  // tile, blocks per CU
   float t0[2], a[2], b[2], c[2], e[2];
 };
 static const PlainShape plain_shapes[] = {
-    {256, 256, {0.f, 0.f}, {1.009f, 1.418f}, {0.302f, 0.272f}, {7.66f, 6.60f}, {5.24f, 7.60f}},
-    {128, 256, {0.72f, 3.24f}, {0.575f, 0.672f}, {0.166f, 0.148f}, {4.95f, 1.95f}, {2.78f, 4.33f}},
-    {128, 192, {0.46f, 4.56f}, {0.488f, 0.541f}, {0.116f, 0.111f}, {4.42f, 0.f}, {2.42f, 5.15f}},
-    {128, 128, {0.45f, 2.60f}, {0.336f, 0.383f}, {0.116f, 0.121f}, {3.75f, 1.30f}, {0.76f, 2.47f}},
-    {128, 64, {3.37f, 4.31f}, {0.265f, 0.262f}, {0.012f, 0.036f}, {0.f, 0.f}, {1.01f, 1.13f}},
-    {64, 96, {3.74f, 3.76f}, {0.231f, 0.246f}, {0.f, 0.011f}, {0.f, 0.f}, {0.88f, 1.33f}},
-    {64, 64, {3.72f, 3.70f}, {0.187f, 0.191f}, {0.f, 0.f}, {0.f, 0.f}, {0.50f, 0.60f}},
-    {64, 64, {1.58f, 1.60f}, {0.145f, 0.174f}, {0.032f, 0.f}, {2.46f, 2.62f}, {0.10f, 0.f}},  // slices split over two groups
-    {128, 128, {1e9f, 4.81f}, {0.f, 0.545f}, {0.f, 0.f}, {0.f, 0.f}, {0.f, 1.43f}},           // two blocks of four wavefronts
+    {256, 256, 1, {0.f, 0.f}, {0.830f, 1.272f}, {0.538f, 0.538f}, {7.196f, 7.679f}, {5.990f, 5.423f}},
+    {128, 256, 1, {0.700f, 2.841f}, {0.542f, 0.588f}, {0.215f, 0.251f}, {4.376f, 2.872f}, {3.607f, 3.663f}},
+    {128, 192, 1, {0.698f, 4.614f}, {0.470f, 0.506f}, {0.150f, 0.154f}, {3.797f, 0.f}, {2.403f, 4.969f}},
+    {128, 128, 1, {1.171f, 2.835f}, {0.323f, 0.332f}, {0.137f, 0.171f}, {3.051f, 1.382f}, {0.878f, 2.316f}},
+    {128, 64, 2, {3.621f, 3.814f}, {0.258f, 0.307f}, {0.025f, 0.135f}, {0.f, 0.f}, {0.751f, 1.514f}},
+    {64, 96, 2, {3.906f, 3.841f}, {0.231f, 0.272f}, {0.012f, 0.112f}, {0.f, 0.f}, {0.578f, 1.421f}},
+    {64, 64, 3, {3.788f, 3.715f}, {0.193f, 0.124f}, {0.f, 0.147f}, {0.f, 0.f}, {0.500f, 0.668f}},
+    {64, 64, 1, {1.535f, 1.619f}, {0.147f, 0.166f}, {0.027f, 0.f}, {2.522f, 2.463f}, {0.088f, 0.294f}},  // slices split over two groups of wavefronts
+    {128, 64, 1, {1.761f, 2.516f}, {0.215f, 0.222f}, {0.071f, 0.075f}, {3.127f, 2.300f}, {0.f, 0.936f}},  // the same
+    {64, 96, 1, {2.014f, 2.093f}, {0.186f, 0.186f}, {0.043f, 0.075f}, {2.271f, 2.622f}, {0.677f, 0.415f}},  // the same
+    {128, 128, 2, {0.f, 3.209f}, {0.f, 0.432f}, {0.f, 0.223f}, {0.f, 0.879f}, {0.f, 2.244f}},  // two blocks of four wavefronts: see best_shape
 };
 constexpr int N_SHAPES = sizeof(plain_shapes) / sizeof(plain_shapes[0]);
 
 static float shape_cost(const PlainShape &p, const GemmDesc *d, int n) {
-  const int l = d->ta || d->tb;
+  // one transposed operand: half way between the two
+  const float x = d->ta == d->tb ? (float)(d->ta != 0) : 0.5f;
+  auto at = [x](const float (&v)[2]) { return v[0] + x * (v[1] - v[0]); };
   float tiles = 0.f;
   int K = 0;
   for (int i = 0; i < n; ++i) {
@@ -392,12 +399,17 @@ static float shape_cost(const PlainShape &p, const GemmDesc *d, int n) {
     K = d[i].K > K ? d[i].K : K;
   }
   const float nk = (float)((K + 63) / 64), u = tiles * (1.f / 256.f);
-  return p.t0[l] + ceilf(u) * (nk * p.a[l] + p.c[l]) + u * (nk * p.b[l] + p.e[l]);
+  const float rounds = ceilf(x == 1.f ? u / (float)p.occ : u);
+  return at(p.t0) + rounds * (nk * at(p.a) + at(p.c)) + u * (nk * at(p.b) + at(p.e));
 }
 
 static int best_shape(const GemmDesc *d, int n, float *cost) {
+  // the last shape gains where two blocks write out and multiply in turn, which needs many tiles, transposing reads and
+  // vector stores (768x50257x2048 with its odd rows: 256 us against 208 with 128x256)
+  bool last = true;
+  for (int i = 0; i < n; ++i) last = last && d[i].ta && d[i].tb && !(d[i].ldc & 3);
   int best = 0;
-  for (int i = 0; i < N_SHAPES; ++i) {
+  for (int i = 0; i < N_SHAPES - (last ? 0 : 1); ++i) {
     const float c = shape_cost(plain_shapes[i], d, n);
     if (i == 0 || c < *cost) { best = i; *cost = c; }
   }
@@ -408,7 +420,7 @@ static hipError_t launch_best(const GemmDesc *d, int n, int shape, hipStream_t s
   static const char *const names[N_SHAPES][4] = {
 #define HYDRA_N(X) {"gemm_bf16_" X "_nt", "gemm_bf16_" X "_nn", "gemm_bf16_" X "_tt", "gemm_bf16_" X "_tn"}
       HYDRA_N("256x256"), HYDRA_N("128x256"), HYDRA_N("128x192"), HYDRA_N("128x128"), HYDRA_N("128x64"),
-      HYDRA_N("64x96"), HYDRA_N("64x64"), HYDRA_N("64x64k2"), HYDRA_N("128x128x2")};
+      HYDRA_N("64x96"), HYDRA_N("64x64"), HYDRA_N("64x64k2"), HYDRA_N("128x64k2"), HYDRA_N("64x96k2"), HYDRA_N("128x128x2")};
 #undef HYDRA_N
   double flops = 0;
   for (int i = 0; i < n; ++i) flops += gemm_flops(d[i]);
@@ -422,6 +434,8 @@ static hipError_t launch_best(const GemmDesc *d, int n, int shape, hipStream_t s
     case 5: return launch_shape<64, 96, 2, 2, 1, 64, 3, 2>(d, n, s);
     case 6: return launch_shape<64, 64, 2, 2, 1, 64, 3, 3>(d, n, s);
     case 7: return launch_shape<64, 64, 2, 2, 2, 128, 4, 1>(d, n, s);
+    case 8: return launch_shape<128, 64, 2, 2, 2, 128, 3, 1>(d, n, s);
+    case 9: return launch_shape<64, 96, 2, 2, 2, 128, 3, 1>(d, n, s);
     default: return launch_shape<128, 128, 2, 2, 1, 64, 2, 2>(d, n, s);
   }
 }
