@@ -426,115 +426,113 @@ hipError_t launch_layernorm_bwd_params(const float *dy, const float *x, const fl
 // One pass over the rows gives everything a LayerNorm's backward produces: dx
 // (fp32, optionally a bf16 copy) and, per block of LNB_ROWS rows, the partial
 // column sums of dy * xhat (-> dgamma), of dy (-> dbeta) and of dx (-> the bias
-// gradient of the linear layer whose output gradient dx is).  A wavefront walks
-// LNB_ROWS / 4 rows with its column partials in registers; the four
-// wavefronts of a block are added in a fixed order through LDS.  The partials
-// [gridDim.x][3][d] are summed by colsum_finish_kernel.  NR = float4 per lane
-// that cover a row (d <= 256 * NR).
+// gradient of the linear layer whose output gradient dx is).  A wavefront owns one
+// row, with x, dy and the residual gradient requested together and then held in
+// registers: the kernel is bound by memory (18 bytes per element) and by how much
+// of it is in flight.  (With two rows per wavefront and the partial sums in
+// registers only eight wavefronts fitted on a CU: 4096 x 1600 took 36 us, now 24.)
+// The block's rows are added in a fixed order through LDS: rows w and w + 4, then
+// w = 0..3 in ascending order.  The partials [gridDim.x][3][d] are summed by
+// colsum_finish_kernel.  NR = float4 per lane that cover a row (d <= 256 * NR).
 constexpr int LNB_ROWS = 8;
 int layernorm_bwd_fused_blocks(int M) { return (M + LNB_ROWS - 1) / LNB_ROWS; }
 bool layernorm_bwd_fused_supported(int d) { return d % 4 == 0 && d <= 256 * LN_R; }
 
 template <int NR>
-__global__ __launch_bounds__(256) void layernorm_bwd_fused_kernel(const float *__restrict__ dy, const float *__restrict__ x,
-                                                                  const float *__restrict__ mean,
-                                                                  const float *__restrict__ rstd,
-                                                                  const float *__restrict__ gamma,
-                                                                  const float *__restrict__ dres, float *__restrict__ dx,
-                                                                  bf16_t *__restrict__ dx_bf16, float *__restrict__ part,
-                                                                  int M, int d) {
-  __shared__ float red[3][NR * 256];
+__global__ __launch_bounds__(512, NR <= 7 ? 4 : 2) void layernorm_bwd_fused_kernel(const float *__restrict__ dy, const float *__restrict__ x,
+                                                                     const float *__restrict__ mean,
+                                                                     const float *__restrict__ rstd,
+                                                                     const float *__restrict__ gamma,
+                                                                     const float *__restrict__ dres, float *__restrict__ dx,
+                                                                     bf16_t *__restrict__ dx_bf16, float *__restrict__ part,
+                                                                     int M, int d) {
+  // which products are fused into a sum is written out, so that results do not depend on the compiler's choice
+#pragma clang fp contract(off)
+  __shared__ float red[2][4][NR * 256];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  float4 gm[NR], ag[NR], ab[NR], ax[NR];
+  const int row = blockIdx.x * LNB_ROWS + wave;
+  const bool in = row < M;  // uniform over the wavefront
+  float4 xh[NR], g[NR], o[NR];
+  if (in) {
+    const float *xr = x + (int64_t)row * d, *dyr = dy + (int64_t)row * d, *rr = dres + (int64_t)row * d;
 #pragma unroll
-  for (int i = 0; i < NR; ++i) {
-    const int c = lane * 4 + i * 256;
-    gm[i] = c < d ? *(const float4 *)(gamma + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-    ag[i] = ab[i] = ax[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  constexpr int RPW = LNB_ROWS / 4;
-#pragma unroll 1
-  for (int rr = 0; rr < RPW; ++rr) {
-    const int row = blockIdx.x * LNB_ROWS + rr * 4 + wave;  // ascending rows within a wavefront
-    if (row >= M) break;
-    const float *xr = x + (int64_t)row * d, *dyr = dy + (int64_t)row * d;
+    for (int i = 0; i < NR; ++i) {
+      const int c = lane * 4 + i * 256;
+      xh[i] = g[i] = o[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (c < d) {
+        xh[i] = *(const float4 *)(xr + c);
+        g[i] = *(const float4 *)(dyr + c);
+        if (dres) o[i] = *(const float4 *)(rr + c);
+      }
+    }
     const float mu = mean[row], rs = rstd[row];
-    float4 xh[NR], g[NR], h[NR];
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       const int c = lane * 4 + i * 256;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      g[i] = v;
-      if (c < d) {
-        v = *(const float4 *)(xr + c);
-        g[i] = *(const float4 *)(dyr + c);
-      }
+      const float4 gm = c < d ? *(const float4 *)(gamma + c) : make_float4(0.f, 0.f, 0.f, 0.f), v = xh[i];
       xh[i] = c < d ? make_float4((v.x - mu) * rs, (v.y - mu) * rs, (v.z - mu) * rs, (v.w - mu) * rs) : v;
-      h[i] = make_float4(g[i].x * gm[i].x, g[i].y * gm[i].y, g[i].z * gm[i].z, g[i].w * gm[i].w);
-      s1 += (h[i].x + h[i].y) + (h[i].z + h[i].w);
-      s2 += (h[i].x * xh[i].x + h[i].y * xh[i].y) + (h[i].z * xh[i].z + h[i].w * xh[i].w);
+      const float4 h = make_float4(g[i].x * gm.x, g[i].y * gm.y, g[i].z * gm.z, g[i].w * gm.w);
+      s1 += fmaf(gm.y, g[i].y, h.x) + fmaf(gm.w, g[i].w, h.z);
+      s2 += fmaf(h.x, xh[i].x, h.y * xh[i].y) + fmaf(h.z, xh[i].z, h.w * xh[i].w);
     }
     const float m1 = wave_sum(s1) / (float)d, m2 = wave_sum(s2) / (float)d;
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       const int c = lane * 4 + i * 256;
       if (c < d) {
-        float4 o;
-        o.x = rs * (h[i].x - m1 - xh[i].x * m2);
-        o.y = rs * (h[i].y - m1 - xh[i].y * m2);
-        o.z = rs * (h[i].z - m1 - xh[i].z * m2);
-        o.w = rs * (h[i].w - m1 - xh[i].w * m2);
-        if (dres) {
-          const float4 r = *(const float4 *)(dres + (int64_t)row * d + c);
-          o.x += r.x; o.y += r.y; o.z += r.z; o.w += r.w;
-        }
-        *(float4 *)(dx + (int64_t)row * d + c) = o;
-        if (dx_bf16) {
-          uint2 p;
-          p.x = (uint32_t)f2bf(o.x) | ((uint32_t)f2bf(o.y) << 16);
-          p.y = (uint32_t)f2bf(o.z) | ((uint32_t)f2bf(o.w) << 16);
-          *(uint2 *)(dx_bf16 + (int64_t)row * d + c) = p;
-        }
-        ag[i].x += g[i].x * xh[i].x; ag[i].y += g[i].y * xh[i].y; ag[i].z += g[i].z * xh[i].z; ag[i].w += g[i].w * xh[i].w;
-        ab[i].x += g[i].x; ab[i].y += g[i].y; ab[i].z += g[i].z; ab[i].w += g[i].w;
-        ax[i].x += o.x; ax[i].y += o.y; ax[i].z += o.z; ax[i].w += o.w;
+        const float4 gm = *(const float4 *)(gamma + c), r = o[i];
+        const float4 h = make_float4(g[i].x * gm.x, g[i].y * gm.y, g[i].z * gm.z, g[i].w * gm.w);
+        float4 t;
+        t.x = rs * fmaf(-xh[i].x, m2, h.x - m1);
+        t.y = rs * fmaf(-xh[i].y, m2, h.y - m1);
+        t.z = rs * fmaf(-xh[i].z, m2, h.z - m1);
+        t.w = rs * fmaf(-xh[i].w, m2, h.w - m1);
+        if (dres) { t.x += r.x; t.y += r.y; t.z += r.z; t.w += r.w; }
+        *(float4 *)(dx + (int64_t)row * d + c) = t;
+        if (dx_bf16) st4(dx_bf16 + (int64_t)row * d + c, t.x, t.y, t.z, t.w);
+        o[i] = t;
       }
     }
   }
-  // wavefronts 1..3 add to what wavefront 0 holds, one after the other (fixed order)
   float *out = part + (int64_t)blockIdx.x * 3 * d;
-  for (int w = 1; w < 4; ++w) {
-    if (wave == w) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {  // dy * xhat, dy, dx
+    float(*const buf)[NR * 256] = red[q & 1];
+    if (wave < 4) {
 #pragma unroll
       for (int i = 0; i < NR; ++i) {
-        *(float4 *)&red[0][lane * 4 + i * 256] = ag[i];
-        *(float4 *)&red[1][lane * 4 + i * 256] = ab[i];
-        *(float4 *)&red[2][lane * 4 + i * 256] = ax[i];
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (in)
+          v = q == 0 ? make_float4(g[i].x * xh[i].x, g[i].y * xh[i].y, g[i].z * xh[i].z, g[i].w * xh[i].w) : q == 1 ? g[i] : o[i];
+        *(float4 *)&buf[wave][lane * 4 + i * 256] = v;
       }
     }
     __syncthreads();
-    if (wave == 0) {
+    if (wave >= 4 && in) {
 #pragma unroll
       for (int i = 0; i < NR; ++i) {
-        const float4 a = *(const float4 *)&red[0][lane * 4 + i * 256], b = *(const float4 *)&red[1][lane * 4 + i * 256],
-                     c4 = *(const float4 *)&red[2][lane * 4 + i * 256];
-        ag[i].x += a.x; ag[i].y += a.y; ag[i].z += a.z; ag[i].w += a.w;
-        ab[i].x += b.x; ab[i].y += b.y; ab[i].z += b.z; ab[i].w += b.w;
-        ax[i].x += c4.x; ax[i].y += c4.y; ax[i].z += c4.z; ax[i].w += c4.w;
+        float4 *const p = (float4 *)&buf[wave - 4][lane * 4 + i * 256];
+        float4 v = *p;
+        if (q == 0) {
+          v.x = fmaf(g[i].x, xh[i].x, v.x); v.y = fmaf(g[i].y, xh[i].y, v.y);
+          v.z = fmaf(g[i].z, xh[i].z, v.z); v.w = fmaf(g[i].w, xh[i].w, v.w);
+        } else {
+          const float4 a = q == 1 ? g[i] : o[i];
+          v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+        }
+        *p = v;
       }
     }
-    __syncthreads();
-  }
-  if (wave == 0) {
+    __syncthreads();  // (the buffer is written again two quantities later, after the barriers of the one between)
+    for (int c = threadIdx.x * 4; c < d; c += 2048) {
+      float4 t = *(const float4 *)&buf[0][c];
 #pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      const int c = lane * 4 + i * 256;
-      if (c < d) {
-        *(float4 *)(out + c) = ag[i];
-        *(float4 *)(out + d + c) = ab[i];
-        *(float4 *)(out + 2 * d + c) = ax[i];
+      for (int k = 1; k < 4; ++k) {
+        const float4 a = *(const float4 *)&buf[k][c];
+        t.x += a.x; t.y += a.y; t.z += a.z; t.w += a.w;
       }
+      *(float4 *)(out + (int64_t)q * d + c) = t;
     }
   }
 }
@@ -544,7 +542,7 @@ hipError_t launch_layernorm_bwd_fused(const float *dy, const float *x, const flo
                                       int d, hipStream_t s) {
   if (!layernorm_bwd_fused_supported(d)) return hipErrorInvalidValue;
   const int nr = (d + 255) / 256;
-  dim3 grid(layernorm_bwd_fused_blocks(M)), block(256);
+  dim3 grid(layernorm_bwd_fused_blocks(M)), block(512);
   ProfScope ps("layernorm_bwd", s, 0, (double)M * d * ((dres ? 16.0 : 12.0) + (dx_bf16 ? 2.0 : 0.0)) + 12.0 * grid.x * d);
 #define HYDRA_LNB(NR_)                                                                                                  \
   hipLaunchKernelGGL(layernorm_bwd_fused_kernel<NR_>, grid, block, 0, s, dy, x, mean, rstd, gamma, dres, dx,             \
@@ -553,7 +551,9 @@ hipError_t launch_layernorm_bwd_fused(const float *dy, const float *x, const flo
   else if (nr <= 2) HYDRA_LNB(2);
   else if (nr <= 3) HYDRA_LNB(3);
   else if (nr <= 4) HYDRA_LNB(4);
+  else if (nr <= 5) HYDRA_LNB(5);
   else if (nr <= 6) HYDRA_LNB(6);
+  else if (nr <= 7) HYDRA_LNB(7);
   else HYDRA_LNB(8);
 #undef HYDRA_LNB
   return hipGetLastError();
@@ -718,12 +718,12 @@ hipError_t launch_colsum2_pass1(int dtype, const void *in0, int N0, float *part0
 }
 
 // Last pass of several column sums in one launch: segment i adds its nch partial rows (stride elements apart) into
-// out[0..N) (added to what out holds when acc is set).  A block takes 32 columns of one segment with 32 row lanes of
+// out[0..N) (added to what out holds when acc is set).  A block takes 32 columns of one segment with 64 row lanes of
 // 8 threads, four columns each (one 16-byte load per row where the segment allows it, else four 4-byte loads): lane r
-// adds rows r, r + 32, ... in ascending order in double, eight loads in flight at a time (256 partial rows, the
-// usual count, are one batch); the 32 lanes are combined in a fixed tree.
-constexpr int FIN_COLS = 32, FIN_LANES = 32;
-__global__ __launch_bounds__(256) void colsum_finish_kernel(const ColsumFinish a) {
+// adds rows r, r + 64, ... in ascending order in double, eight loads in flight at a time (512 partial rows are one
+// batch; with 32 lanes, two, 3 x 1600 columns took 8.4 us, now 5.8); the 64 lanes are combined in a fixed tree.
+constexpr int FIN_COLS = 32, FIN_LANES = 64;
+__global__ __launch_bounds__(8 * FIN_LANES) void colsum_finish_kernel(const ColsumFinish a) {
   __shared__ double sh[FIN_LANES][FIN_COLS + 1];
   const int cx = threadIdx.x & 7, ry = threadIdx.x >> 3;
   int i = 0;
@@ -761,15 +761,27 @@ __global__ __launch_bounds__(256) void colsum_finish_kernel(const ColsumFinish a
 #pragma unroll
   for (int j = 0; j < 4; ++j) sh[ry][cx * 4 + j] = v[j];
   __syncthreads();
-  const int cc = threadIdx.x;
-  if (cc < FIN_COLS && cb + cc < g.N) {
-    double t[FIN_LANES];
+  // eight threads per column add eight lanes each, the first of them the eight results
+  const int cc = threadIdx.x & (FIN_COLS - 1), part8 = threadIdx.x / FIN_COLS;
+  if (part8 < 8) {
+    double t[8];
 #pragma unroll
-    for (int k = 0; k < FIN_LANES; ++k) t[k] = sh[k][cc];
+    for (int k = 0; k < 8; ++k) t[k] = sh[part8 * 8 + k][cc];
 #pragma unroll
-    for (int w = 1; w < FIN_LANES; w *= 2)
+    for (int w = 1; w < 8; w *= 2)
 #pragma unroll
-      for (int k = 0; k < FIN_LANES; k += 2 * w) t[k] += t[k + w];
+      for (int k = 0; k < 8; k += 2 * w) t[k] += t[k + w];
+    sh[part8 * 8][cc] = t[0];
+  }
+  __syncthreads();
+  if (threadIdx.x < FIN_COLS && cb + cc < g.N) {
+    double t[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) t[k] = sh[k * 8][cc];
+#pragma unroll
+    for (int w = 1; w < 8; w *= 2)
+#pragma unroll
+      for (int k = 0; k < 8; k += 2 * w) t[k] += t[k + w];
     g.out[cb + cc] = (float)(a.acc ? (double)g.out[cb + cc] + t[0] : t[0]);
   }
 }
@@ -786,7 +798,7 @@ hipError_t launch_colsum_finish(ColsumFinish &a, hipStream_t s) {
     bytes += 4.0 * a.seg[i].N * a.seg[i].nch;
   }
   ProfScope ps("colsum_finish", s, 0, bytes);
-  hipLaunchKernelGGL(colsum_finish_kernel, dim3(col / FIN_COLS), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(colsum_finish_kernel, dim3(col / FIN_COLS), dim3(8 * FIN_LANES), 0, s, a);
   return hipGetLastError();
 }
 

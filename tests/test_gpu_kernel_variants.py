@@ -132,3 +132,30 @@ def test_attention_variants(H, B, Hn, T, dh, peak):
     for j in range(3):
         g, r = dqkv[:-1, j * d:(j + 1) * d].double(), x.grad[:, j * d:(j + 1) * d]
         assert (g - r).norm() <= 2.0 ** -7 * r.norm() + 1e-12
+
+
+# every register width of the one-pass LayerNorm backward (1 to 8 float4 per lane), row counts around its block of 8 rows,
+# more than 512 partial rows for the column sums
+@pytest.mark.parametrize("M,d", [(1, 4), (7, 252), (8, 512), (9, 764), (17, 1024), (4100, 1028), (23, 1532), (15, 1792),
+                                 (33, 2048)])
+def test_layernorm_bwd_widths(H, M, d):
+    x, dy, dres = randn(M + d, M, d) * 2 + 0.5, randn(M, M, d), randn(d, M, d)
+    gamma = randn(d + 1, d) * 0.1 + 1
+    mean = x.mean(1)
+    rstd = 1 / torch.sqrt(x.var(1, unbiased=False) + 1e-5)
+    dx, dxh = torch.empty_like(x), torch.empty_like(x, dtype=torch.bfloat16)
+    cols = [torch.empty(d, device="cuda") for _ in range(3)]
+    H.hydra_op_layernorm_bwd(dy, x, mean, rstd, gamma, dres, dx, dxh, *cols, torch.empty(3 * d * ((M + 7) // 8), device="cuda"),
+                             M, d)
+    torch.cuda.synchronize()
+    xh = (x.double() - mean.double()[:, None]) * rstd.double()[:, None]
+    h = dy.double() * gamma.double()
+    part = h - h.mean(1, keepdim=True) - xh * (h * xh).mean(1, keepdim=True)
+    ref = rstd.double()[:, None] * part + dres.double()
+    # a dozen roundings of values no larger than the terms' magnitudes
+    mag = rstd.double()[:, None] * (h.abs() + h.abs().mean(1, keepdim=True) + xh.abs() * (h * xh).abs().mean(1, keepdim=True))
+    assert ((dx.double() - ref).abs() <= (d / 64 + 16) * U32 * (mag + dres.double().abs())).all()
+    assert (dxh == dx.bfloat16()).all()
+    for got, v in zip(cols, (dy.double() * xh, dy.double(), dx.double())):
+        # eight rows in fp32, the rest in 64 bits; xhat itself carries three roundings
+        assert ((got.double() - v.sum(0)).abs() <= 14 * U32 * v.abs().sum(0) + 4 * U32 * dy.double().abs().sum(0)).all()
