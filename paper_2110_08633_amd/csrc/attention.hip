@@ -314,7 +314,7 @@ __device__ __forceinline__ bool merge_groups(f32x16_t (&acc)[NA], int grp, float
 // backward, part 1: dQ.  Same decomposition as the forward kernel.  Per tile:
 // p = exp(s - L), dP = dO V^T, dS = p (dP - D) / sqrt(dh) with
 // D_i = sum_c dO[i,c] O[i,c] (written out for part 2), dQ += dS K.  Both backward
-// kernels together at B 4, H 16, T 2048, dh 128: 830 -> 280 us; at B 4, H 12, T 512, dh 64: 41 -> 28 us.
+// kernels together at B 4, H 16, T 2048, dh 128: 830 -> 270 us; at B 4, H 12, T 512, dh 64: 41 -> 28 us.
 // ---------------------------------------------------------------------------
 template <int DH, int KW>
 __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
@@ -505,7 +505,9 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
     const bf16_t *const qs = smem + (it & 1) * STAGE + grp * 2 * TILE, *const os = qs + TILE;
     const float *const ls = Ls + ((it & 1) * KW + grp) * 128;
     if (i0 + AK - 1 >= kr0 && i0 < T) {  // else no query of the tile comes after a key of this wavefront
-#pragma unroll
+      // one half tile at a time: unrolled, the two halves' results do not fit the 256 registers two wavefronts per SIMD
+      // leave at head width 128 (the two backward kernels at B 4, H 16, T 2048, dh 128: 289 -> 270 us)
+#pragma unroll 1
       for (int nt = 0; nt < 2; ++nt) {
         f32x16_t s, dp;
 #pragma unroll
@@ -540,8 +542,10 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
         for (int k2 = 0; k2 < 2; ++k2) {
           const bf16x8_t pf = row_operand(p, k2), df = row_operand(ds, k2);
 #pragma unroll
-          for (int nd = 0; nd < ND; ++nd) {
+          for (int nd = 0; nd < ND; ++nd)
             acc[ND + nd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.tr(os, nd, nt * 2 + k2), pf, acc[ND + nd], 0, 0, 0);
+#pragma unroll
+          for (int nd = 0; nd < ND; ++nd) {
             acc[nd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.tr(qs, nd, nt * 2 + k2), df, acc[nd], 0, 0, 0);
           }
         }
@@ -606,7 +610,7 @@ static hipError_t attn_bwd(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o
 // wavefronts per CU make 512): us with one / two groups, forward, then backward -
 //   B 4, H 12, T 512, dh 64 (192 blocks) 10.8 / 10.1, 29.9 / 28.0;   B 2, H 12, T 2048, dh 64 (384) 33 / 27, 93 / 76;
 //   B 1, H 32, T 1024, dh 128 (256) 27 / 23, 91 / 76;   B 5, H 12, T 1024, dh 64 (480) 19.9 / 19.3, 55 / 59;
-//   B 3, H 25, T 1000, dh 64 (600) 23 / 25, 67 / 80;   B 4, H 16, T 2048, dh 128 (1024) 79 / 98, 280 / 325.
+//   B 3, H 25, T 1000, dh 64 (600) 23 / 25, 67 / 80;   B 4, H 16, T 2048, dh 128 (1024) 79 / 98, 279 / 318.
 // Sequences of one or two tiles have nothing to share out.
 static bool two_groups(int B, int H, int T, int limit) { return T > 4 * AK && (long)((T + AQ - 1) / AQ) * B * H <= limit; }
 
