@@ -13,6 +13,8 @@
 // r = 0..15.  Tiles of 64 rows go straight to LDS (one copy, read both along the
 // head dimension and, transposing, along the rows); probabilities stay in the
 // registers they are computed in.
+#include <cfloat>
+
 #include "gemm_common.h"
 
 namespace hydra {
@@ -179,7 +181,9 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__r
   RowFrag<DH> fr;
   fr.init(lane);
 
-  float m = -INFINITY, l = 0.f;
+  // the reference maximum starts at the lowest finite value: a row whose scores of a tile are all -inf then adds
+  // exp2(-inf) = 0, where -inf - -inf would be NaN
+  float m = -FLT_MAX, l = 0.f;
   f32x16_t acc[ND];
 #pragma unroll
   for (int nd = 0; nd < ND; ++nd)
@@ -221,8 +225,7 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__r
     tmax = max_halves(tmax);
     // The reference maximum m of a row (log2 domain) only has to keep the exponentials in range, so it is moved -
     // and the sum and the output rescaled - only when some row's maximum has outgrown it by more than 2^8; the
-    // result does not depend on which reference is used.  Finite from a
-    // wavefront's first tile on: a tile that it does not skip starts at or before its first row.
+    // result does not depend on which reference is used.
     const float tm = tmax * scale_log2e;
     if (__builtin_amdgcn_ballot_w64(tm > m + 8.f)) {
       const float mn = __builtin_fmaxf(m, tm);

@@ -134,6 +134,34 @@ def test_attention_variants(H, B, Hn, T, dh, peak):
         assert (g - r).norm() <= 2.0 ** -7 * r.norm() + 1e-12
 
 
+# a score of -inf (here by overflow: finite operands, a product beyond fp32) weighs nothing, in whichever group of
+# wavefronts and at whichever place of its tile it falls - also where it is all a row sees of a tile (keys 0..63, or the
+# diagonal key of row 64 + 128 i, which opens the second group's first tile)
+@pytest.mark.parametrize("B,Hn,T,dh", [(1, 2, 328, 64), (1, 1, 264, 128), (40, 16, 264, 64), (1, 1, 136, 128)])
+@pytest.mark.parametrize("keys", [(64, 65), (192, 193), (0, 64), (0, 128)])
+def test_attention_scores_of_minus_infinity(H, B, Hn, T, dh, keys):
+    d = Hn * dh
+    keys = slice(min(keys[0], T - 1), min(keys[1], T))
+    qkv = randn(T + dh, B * T, 3 * d).bfloat16().view(B, T, 3, Hn, dh)
+    qkv[:, :, 0, :, 0], qkv[:, :, 1, :, 0] = 2.0 ** 66, 0.0
+    qkv[:, keys, 1, :, 0] = -2.0 ** 66
+    o, lse = torch.empty(B * T, d, device="cuda").bfloat16(), torch.empty(B * Hn * T, device="cuda")
+    H.hydra_op_attention_fwd(qkv, o, lse, B, Hn, T, dh)
+    torch.cuda.synchronize()
+    q, k, v = (qkv[:, :, j].double().transpose(1, 2) for j in range(3))
+    s = (q @ k.transpose(2, 3).contiguous()) / dh ** 0.5
+    s[..., keys] = float("-inf")
+    s = s.masked_fill(torch.ones(T, T, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+    ref_lse = torch.logsumexp(s, -1, keepdim=True)
+    p = torch.exp(s - ref_lse)
+    seen = torch.isfinite(ref_lse[0, 0, :, 0])  # rows that see a key with a finite score
+    ref, mag = (p @ v)[:, :, seen], (p @ v.abs())[:, :, seen]
+    got = o.view(B, T, Hn, dh).transpose(1, 2)[:, :, seen].double()
+    # as in test_attention_variants
+    assert ((got - ref).abs() <= 2.0 ** -8 * ref.abs() + (2.0 ** -8 + 2.0 ** -12) * mag).all()
+    assert (lse.view(B, Hn, T)[..., seen].double() - ref_lse[:, :, seen, 0]).abs().max() < 1e-3
+
+
 # every register width of the one-pass LayerNorm backward (1 to 8 float4 per lane), row counts around its block of 8 rows,
 # more than 512 partial rows for the column sums
 @pytest.mark.parametrize("M,d", [(1, 4), (7, 252), (8, 512), (9, 764), (17, 1024), (4100, 1028), (23, 1532), (15, 1792),
