@@ -67,12 +67,24 @@ struct RowTile {
     row = tid >> 3;
     off = (int)((row * ld + ((tid & 7) ^ swz(row)) * 8) * 2);
   }
-  // base: element (first row of the tile, first column of the head), uniform; rows from `valid` on read as zero
+  // base: element (first row of the tile, first column of the head), uniform; rows from `valid` on read as zero.
+  // DIRECT: straight to LDS, which wants aligned addresses; else through registers, whose loads take any
+  template <bool DIRECT>
   __device__ __forceinline__ void load(const bf16_t *base, int valid, uint32_t lds, int wave) const {
     const int o0 = row < valid ? off : BUF_OUT, o1 = row + 32 < valid ? off : BUF_OUT;
 #pragma unroll
-    for (int i = 0; i < N; ++i)
-      load_to_lds(base + (i & 1) * 32 * ld + (i >> 1) * 64, i & 1 ? o1 : o0, lds + (i * 256 + wave * 64) * 16);
+    for (int i = 0; i < N; ++i) {
+      const bf16_t *const b = base + (i & 1) * 32 * ld + (i >> 1) * 64;
+      const int o = i & 1 ? o1 : o0;
+      const uint32_t dst = lds + (i * 256 + wave * 64) * 16;
+      if constexpr (DIRECT) {
+        load_to_lds(b, o, dst);
+      } else {
+        u32x4_t v = {0u, 0u, 0u, 0u};
+        if (o != BUF_OUT) v = *(gvec_ptr)((const char *)b + o);
+        *(__attribute__((address_space(3))) u32x4_t *)(uintptr_t)(dst + (threadIdx.x & 63) * 16) = v;
+      }
+    }
   }
 };
 template <int DH>
@@ -143,7 +155,7 @@ __device__ __forceinline__ void block_place(int pairs, int &z, int &rb) {
 // through LDS; 103 us without these; 79 us with the long blocks first.  Measured without gain: tiles two and three
 // ahead, raised wavefront priority around the MFMAs, MFMAs and exponentials interleaved by scheduling directives (spills).
 // ---------------------------------------------------------------------------
-template <int DH, int KW>
+template <int DH, int KW, bool DIRECT>
 __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__restrict__ qkv, bf16_t *__restrict__ o,
                                                                float *__restrict__ lse, int T, int H, int d, int nb, int pairs,
                                                                float scale_log2e) {
@@ -171,8 +183,8 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__r
   auto load = [&](int it) {
     const int j0 = (it * KW + grp) * AK;
     const uint32_t s = lds0 + (it & 1) * STAGE * 2;
-    tile.load(kp + (int64_t)j0 * ld, T - j0, s, wave);
-    tile.load(vp + (int64_t)j0 * ld, T - j0, s + TILE * 2, wave);
+    tile.template load<DIRECT>(kp + (int64_t)j0 * ld, T - j0, s, wave);
+    tile.template load<DIRECT>(vp + (int64_t)j0 * ld, T - j0, s + TILE * 2, wave);
   };
   load(0);
   bf16x8_t qf[DH / 16];
@@ -319,7 +331,7 @@ __device__ __forceinline__ bool merge_groups(f32x16_t (&acc)[NA], int grp, float
 // D_i = sum_c dO[i,c] O[i,c] (written out for part 2), dQ += dS K.  Both backward
 // kernels together at B 4, H 16, T 2048, dh 128: 830 -> 270 us; at B 4, H 12, T 512, dh 64: 41 -> 28 us.
 // ---------------------------------------------------------------------------
-template <int DH, int KW>
+template <int DH, int KW, bool DIRECT>
 __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
                                                                   const bf16_t *__restrict__ d_o, const float *__restrict__ lse,
                                                                   float *__restrict__ dsum, bf16_t *__restrict__ dqkv, int T,
@@ -348,8 +360,8 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *
   auto load = [&](int it) {
     const int j0 = (it * KW + grp) * AK;
     const uint32_t s = lds0 + (it & 1) * STAGE * 2;
-    tile.load(kp + (int64_t)j0 * ld, T - j0, s, wave);
-    tile.load(vp + (int64_t)j0 * ld, T - j0, s + TILE * 2, wave);
+    tile.template load<DIRECT>(kp + (int64_t)j0 * ld, T - j0, s, wave);
+    tile.template load<DIRECT>(vp + (int64_t)j0 * ld, T - j0, s + TILE * 2, wave);
   };
   load(0);
   bf16x8_t qf[DH / 16], dof[DH / 16];
@@ -438,7 +450,7 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *
 // s^T = K Q^T, p^T = exp(s^T - L), dP^T = V dO^T, dS^T = p^T (dP^T - D)/sqrt(dh),
 // dV += p^T dO, dK += dS^T Q.  No atomics: every key row has one owner.
 // ---------------------------------------------------------------------------
-template <int DH, int KW>
+template <int DH, int KW, bool DIRECT>
 __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
                                                                    const bf16_t *__restrict__ d_o,
                                                                    const float *__restrict__ lse,
@@ -469,8 +481,8 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
   auto load = [&](int it) {
     const int i0 = first(it);
     const uint32_t s = lds0 + (it & 1) * STAGE * 2;
-    tq.load(qp + (int64_t)i0 * ld, T - i0, s, wave);
-    to.load(dop + (int64_t)i0 * d, T - i0, s + TILE * 2, wave);
+    tq.template load<DIRECT>(qp + (int64_t)i0 * ld, T - i0, s, wave);
+    to.template load<DIRECT>(dop + (int64_t)i0 * d, T - i0, s + TILE * 2, wave);
   };
   auto load_stat = [&](int i0) -> float {
     const int qi = i0 + (tid & 63);
@@ -589,21 +601,21 @@ static constexpr size_t attn_lds(int dh, int kw, int nacc, int extra, size_t sta
     hipLaunchKernelGGL(kern, dim3(nb * B * H), dim3(256 * KW), LDS_, s, __VA_ARGS__);                            \
   } while (0)
 
-template <int DH, int KW>
+template <int DH, int KW, bool DIRECT>
 static hipError_t attn_fwd(const bf16_t *qkv, bf16_t *o, float *lse, int B, int H, int T, hipStream_t s) {
   const int nb = (T + AQ - 1) / AQ, d = H * DH;
-  HYDRA_ATTN((attn_fwd_kernel<DH, KW>), attn_lds(DH, KW, DH / 32, 2, 0), qkv, o, lse, T, H, d, nb, B * H,
+  HYDRA_ATTN((attn_fwd_kernel<DH, KW, DIRECT>), attn_lds(DH, KW, DH / 32, 2, 0), qkv, o, lse, T, H, d, nb, B * H,
              LOG2E / sqrtf((float)DH));
   return hipGetLastError();
 }
 
-template <int DH, int KW>
+template <int DH, int KW, bool DIRECT>
 static hipError_t attn_bwd(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o, const float *lse, float *dsum, bf16_t *dqkv,
                            int B, int H, int T, hipStream_t s) {
   const int nb = (T + AQ - 1) / AQ, d = H * DH;
   const float scale = 1.0f / sqrtf((float)DH);
-  HYDRA_ATTN((attn_bwd_dq_kernel<DH, KW>), attn_lds(DH, KW, DH / 32, 0, 0), qkv, o, d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale);
-  HYDRA_ATTN((attn_bwd_dkv_kernel<DH, KW>), attn_lds(DH, KW, DH / 16, 0, KW * 256 * 4), qkv, d_o, lse, dsum, dqkv, T, H, d, nb, B * H,
+  HYDRA_ATTN((attn_bwd_dq_kernel<DH, KW, DIRECT>), attn_lds(DH, KW, DH / 32, 0, 0), qkv, o, d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale);
+  HYDRA_ATTN((attn_bwd_dkv_kernel<DH, KW, DIRECT>), attn_lds(DH, KW, DH / 16, 0, KW * 256 * 4), qkv, d_o, lse, dsum, dqkv, T, H, d, nb, B * H,
              scale);
   return hipGetLastError();
 }
@@ -617,26 +629,29 @@ static hipError_t attn_bwd(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o
 // Sequences of one or two tiles have nothing to share out.
 static bool two_groups(int B, int H, int T, int limit) { return T > 4 * AK && (long)((T + AQ - 1) / AQ) * B * H <= limit; }
 
+// The kernel form of a call: {head width, groups, direct}.  Tensors off the 16-byte grid (qkv or d_o; heads and rows are
+// multiples of it) take one group and tiles through registers.
+#define HYDRA_ATTN_FORM(FN_, ...)                                                                      \
+  (dh == 64 ? !direct ? FN_<64, 1, false>(__VA_ARGS__) : two ? FN_<64, 2, true>(__VA_ARGS__) : FN_<64, 1, true>(__VA_ARGS__) \
+            : !direct ? FN_<128, 1, false>(__VA_ARGS__) : two ? FN_<128, 2, true>(__VA_ARGS__) : FN_<128, 1, true>(__VA_ARGS__))
+
 hipError_t launch_attention_fwd(const void *qkv, void *o, float *lse, int B, int H, int T, int dh, hipStream_t s) {
+  if (!attention_fused_supported(DT_BF16, dh)) return hipErrorInvalidValue;
   // causal half of both products
   ProfScope ps("attention_fwd", s, 2.0 * B * H * dh * ((double)T * (T + 1.0)), 0);
-  const bool two = two_groups(B, H, T, 512);
-  const bf16_t *in = (const bf16_t *)qkv;
-  if (dh == 64) return two ? attn_fwd<64, 2>(in, (bf16_t *)o, lse, B, H, T, s) : attn_fwd<64, 1>(in, (bf16_t *)o, lse, B, H, T, s);
-  if (dh == 128) return two ? attn_fwd<128, 2>(in, (bf16_t *)o, lse, B, H, T, s) : attn_fwd<128, 1>(in, (bf16_t *)o, lse, B, H, T, s);
-  return hipErrorInvalidValue;
+  const bool two = two_groups(B, H, T, 512), direct = ((uintptr_t)qkv & 15) == 0;
+  return HYDRA_ATTN_FORM(attn_fwd, (const bf16_t *)qkv, (bf16_t *)o, lse, B, H, T, s);
 }
 
 hipError_t launch_attention_bwd(const void *qkv, const void *o, const void *d_o, const float *lse, float *dsum,
                                 void *dqkv, int B, int H, int T, int dh, hipStream_t s) {
+  if (!attention_fused_supported(DT_BF16, dh)) return hipErrorInvalidValue;
   // five causal products of T x T x dh each (s and dP in both kernels count once: the recomputation is overhead)
   ProfScope ps("attention_bwd", s, 5.0 * B * H * dh * ((double)T * (T + 1.0)), 0);
-  const bool two = two_groups(B, H, T, 400);
-  const bf16_t *a = (const bf16_t *)qkv, *b = (const bf16_t *)o, *c = (const bf16_t *)d_o;
-  bf16_t *out = (bf16_t *)dqkv;
-  if (dh == 64) return two ? attn_bwd<64, 2>(a, b, c, lse, dsum, out, B, H, T, s) : attn_bwd<64, 1>(a, b, c, lse, dsum, out, B, H, T, s);
-  if (dh == 128) return two ? attn_bwd<128, 2>(a, b, c, lse, dsum, out, B, H, T, s) : attn_bwd<128, 1>(a, b, c, lse, dsum, out, B, H, T, s);
-  return hipErrorInvalidValue;
+  const bool two = two_groups(B, H, T, 400), direct = (((uintptr_t)qkv | (uintptr_t)d_o) & 15) == 0;
+  return HYDRA_ATTN_FORM(attn_bwd, (const bf16_t *)qkv, (const bf16_t *)o, (const bf16_t *)d_o, lse, dsum, (bf16_t *)dqkv, B, H,
+                         T, s);
 }
+#undef HYDRA_ATTN_FORM
 
 }  // namespace hydra

@@ -162,6 +162,31 @@ def test_attention_scores_of_minus_infinity(H, B, Hn, T, dh, keys):
     assert (lse.view(B, Hn, T)[..., seen].double() - ref_lse[:, :, seen, 0]).abs().max() < 1e-3
 
 
+# tensors that start off the 16-byte grid (by one element, by eight bytes): the same bits as from aligned ones
+@pytest.mark.parametrize("shift", [1, 4])
+@pytest.mark.parametrize("B,Hn,T,dh", [(1, 1, 8, 64), (2, 3, 72, 128), (1, 2, 200, 64), (9, 13, 584, 64), (5, 21, 584, 128)])
+def test_attention_unaligned_tensors(H, B, Hn, T, dh, shift):
+    d, n = Hn * dh, B * T
+    qkv, d_o = randn(T + dh, n, 3 * d).bfloat16(), randn(T + dh + 1, n, d).bfloat16()
+
+    def run(shift):
+        def at(x):
+            buf = torch.full((x.numel() + shift + 8,), 7.0, device="cuda").bfloat16()
+            buf[shift:shift + x.numel()] = x.reshape(-1)
+            return buf, buf[shift:shift + x.numel()]
+        bufs = [at(x) for x in (qkv, d_o, torch.zeros_like(d_o), torch.zeros_like(qkv))]
+        q, g, o, dq = (v for _, v in bufs)
+        lse, dsum = (torch.zeros(B * Hn * T, device="cuda") for _ in range(2))
+        H.hydra_op_attention_fwd(q, o, lse, B, Hn, T, dh)
+        H.hydra_op_attention_bwd(q, o, g, lse, dsum, dq, B, Hn, T, dh)
+        torch.cuda.synchronize()
+        assert all((b[:shift] == 7.0).all() and (b[-8:] == 7.0).all() for b, _ in bufs)
+        return o, dq, lse, dsum
+
+    for a, b in zip(run(0), run(shift)):
+        assert torch.equal(a, b)
+
+
 # every register width of the one-pass LayerNorm backward (1 to 8 float4 per lane), row counts around its block of 8 rows,
 # more than 512 partial rows for the column sums
 @pytest.mark.parametrize("M,d", [(1, 4), (7, 252), (8, 512), (9, 764), (17, 1024), (4100, 1028), (23, 1532), (15, 1792),
