@@ -592,13 +592,13 @@ static constexpr size_t attn_lds(int dh, int kw, int nacc, int extra, size_t sta
   return tiles > merge ? tiles : merge;
 }
 
-#define HYDRA_ATTN(KERN_, LDS_, ...)                                                                             \
-  do {                                                                                                           \
-    auto kern = KERN_;                                                                                           \
-    static hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                                 (int)(LDS_));                                                   \
-    if (attr != hipSuccess) return attr;                                                                         \
-    hipLaunchKernelGGL(kern, dim3(nb * B * H), dim3(256 * KW), LDS_, s, __VA_ARGS__);                            \
+#define HYDRA_ATTN(KERN_, LDS_, ...)                                               \
+  do {                                                                             \
+    auto kern = KERN_;                                                             \
+    static OncePerGpu once;                                                        \
+    const hipError_t attr = allow_lds(once, (const void *)kern, LDS_);             \
+    if (attr != hipSuccess) return attr;                                           \
+    hipLaunchKernelGGL(kern, dim3(nb * B * H), dim3(256 * KW), LDS_, s, __VA_ARGS__); \
   } while (0)
 
 template <int DH, int KW, bool DIRECT>

@@ -3,6 +3,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "once_per_gpu.h"
 #include "tile_ops.h"
 
 namespace hydra {
@@ -324,6 +325,14 @@ template <int n> __device__ __forceinline__ void wait_loads_le() {
   // reads have returned; expcnt is left alone
   static_assert(n >= 0 && n <= 63, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((n & 15) | ((n >> 4) << 14) | 0x0070);
+}
+
+// lets a kernel have `bytes` of dynamic LDS on the current GPU; once: one object per kernel
+inline hipError_t allow_lds(OncePerGpu &once, const void *kern, size_t bytes) {
+  int gpu = -1;
+  const hipError_t e = hipGetDevice(&gpu);
+  if (e != hipSuccess) return e;
+  return (hipError_t)once.run(gpu, [&] { return (int)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); });
 }
 
 constexpr int GEMM_GROUP_MAX = 4;

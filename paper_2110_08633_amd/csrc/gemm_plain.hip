@@ -330,8 +330,9 @@ static hipError_t launch_shape(const GemmDesc *d, int n, hipStream_t s) {
     gg.tile0[i] = tiles;
     tiles += a.tiles_m * a.tiles_n;
   }
-#define HYDRA_SET_LDS(KERN_)                                                                                           \
-  static hipError_t attr = hipFuncSetAttribute((const void *)KERN_, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
+#define HYDRA_SET_LDS(KERN_)                                        \
+  static OncePerGpu once;                                           \
+  const hipError_t attr = allow_lds(once, (const void *)KERN_, lds); \
   if (attr != hipSuccess) return attr
 #define HYDRA_PLAIN(TA_, TB_)                                                                  \
   do {                                                                                         \

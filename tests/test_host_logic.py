@@ -3,6 +3,7 @@ layout, scheduler decisions, and the shard-buffer state machine in dry-run mode
 (no HIP call is made)."""
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -377,3 +378,35 @@ def test_host_rounding_to_bf16_is_round_to_nearest_even():
         assert np.array_equal(got[:n], want[:n]) and (n > 0 or got[0] == 0xABCD)
     with pytest.raises(H.HydraError):
         H.hydra_host_round_bf16(None, x, 4)
+
+
+def test_kernel_attributes_are_set_once_on_every_gpu(tmp_path):
+    """The helper behind a kernel's LDS limit: a limit set on one GPU says nothing about another, and a failure is not
+    remembered."""
+    src = tmp_path / "t.cpp"
+    src.write_text(r'''
+#include "once_per_gpu.h"
+#include <cstdio>
+#include <vector>
+int main() {
+  hydra::OncePerGpu once;
+  std::vector<int> calls;
+  auto set = [&](int gpu, int result) { return once.run(gpu, [&] { calls.push_back(gpu); return result; }); };
+  const int ok[] = {set(0, 0), set(0, 0), set(1, 0), set(1, 0), set(63, 0), set(63, 0), set(0, 0)};
+  for (int e : ok) if (e) return 1;
+  if (calls != std::vector<int>{0, 1, 63}) return 2;
+  calls.clear();
+  if (set(2, 7) != 7 || set(2, 0) != 0 || set(2, 9) != 0) return 3;
+  if (calls != std::vector<int>{2, 2}) return 4;
+  calls.clear();
+  if (set(64, 0) || set(64, 0) || calls.size() != 2) return 5;
+  return 0;
+}
+''')
+    exe = tmp_path / "t"
+    csrc = os.path.join(ROOT, "paper_2110_08633_amd", "csrc")
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", csrc, str(src), "-o", str(exe)])
+    assert subprocess.run([str(exe)]).returncode == 0
+    # and no launcher keeps such a limit per process
+    for f in os.listdir(csrc):
+        assert not re.search(r"static\s+(const\s+)?hipError_t\s+\w+\s*=\s*hipFuncSetAttribute", open(os.path.join(csrc, f)).read()), f
