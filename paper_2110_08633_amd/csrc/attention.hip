@@ -629,11 +629,11 @@ static hipError_t attn_bwd(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o
 // Sequences of one or two tiles have nothing to share out.
 static bool two_groups(int B, int H, int T, int limit) { return T > 4 * AK && (long)((T + AQ - 1) / AQ) * B * H <= limit; }
 
-// The kernel form of a call: {head width, groups, direct}.  Tensors off the 16-byte grid (qkv or d_o; heads and rows are
-// multiples of it) take one group and tiles through registers.
-#define HYDRA_ATTN_FORM(FN_, ...)                                                                      \
-  (dh == 64 ? !direct ? FN_<64, 1, false>(__VA_ARGS__) : two ? FN_<64, 2, true>(__VA_ARGS__) : FN_<64, 1, true>(__VA_ARGS__) \
-            : !direct ? FN_<128, 1, false>(__VA_ARGS__) : two ? FN_<128, 2, true>(__VA_ARGS__) : FN_<128, 1, true>(__VA_ARGS__))
+// The kernel form of a call: head width, groups, direct loads.  Tensors off the 16-byte grid (qkv or d_o; heads and rows
+// are multiples of it) move their tiles through registers.
+#define HYDRA_ATTN_DIRECT(FN_, DH_, KW_, ...) (direct ? FN_<DH_, KW_, true>(__VA_ARGS__) : FN_<DH_, KW_, false>(__VA_ARGS__))
+#define HYDRA_ATTN_GROUPS(FN_, DH_, ...) (two ? HYDRA_ATTN_DIRECT(FN_, DH_, 2, __VA_ARGS__) : HYDRA_ATTN_DIRECT(FN_, DH_, 1, __VA_ARGS__))
+#define HYDRA_ATTN_FORM(FN_, ...) (dh == 64 ? HYDRA_ATTN_GROUPS(FN_, 64, __VA_ARGS__) : HYDRA_ATTN_GROUPS(FN_, 128, __VA_ARGS__))
 
 hipError_t launch_attention_fwd(const void *qkv, void *o, float *lse, int B, int H, int T, int dh, hipStream_t s) {
   if (!attention_fused_supported(DT_BF16, dh)) return hipErrorInvalidValue;
@@ -653,5 +653,7 @@ hipError_t launch_attention_bwd(const void *qkv, const void *o, const void *d_o,
                          T, s);
 }
 #undef HYDRA_ATTN_FORM
+#undef HYDRA_ATTN_GROUPS
+#undef HYDRA_ATTN_DIRECT
 
 }  // namespace hydra

@@ -164,7 +164,8 @@ def test_attention_scores_of_minus_infinity(H, B, Hn, T, dh, keys):
 
 # tensors that start off the 16-byte grid (by one element, by eight bytes): the same bits as from aligned ones
 @pytest.mark.parametrize("shift", [1, 4])
-@pytest.mark.parametrize("B,Hn,T,dh", [(1, 1, 8, 64), (2, 3, 72, 128), (1, 2, 200, 64), (9, 13, 584, 64), (5, 21, 584, 128)])
+@pytest.mark.parametrize("B,Hn,T,dh", [(1, 1, 8, 64), (2, 3, 72, 128), (1, 2, 200, 64), (9, 13, 584, 64), (5, 21, 584, 128),
+                                       (3, 5, 328, 128), (1, 7, 1000, 64)])
 def test_attention_unaligned_tensors(H, B, Hn, T, dh, shift):
     d, n = Hn * dh, B * T
     qkv, d_o = randn(T + dh, n, 3 * d).bfloat16(), randn(T + dh + 1, n, d).bfloat16()
