@@ -434,9 +434,10 @@ double gemm_flops(const GemmDesc &d) {
 }
 
 static const char *gemm_name(int bn, int ta, int tb) {
-  static const char *n128[4] = {"gemm_bf16_128x128_nt", "gemm_bf16_128x128_nn", "gemm_bf16_128x128_tt",
-                                "gemm_bf16_128x128_tn"};
-  static const char *n64[4] = {"gemm_bf16_x64_nt", "gemm_bf16_x64_nn", "gemm_bf16_x64_tt", "gemm_bf16_x64_tn"};
+  static const char *n128[4] = {"gemm_bf16_staged_128x128_nt", "gemm_bf16_staged_128x128_nn",
+                                "gemm_bf16_staged_128x128_tt", "gemm_bf16_staged_128x128_tn"};
+  static const char *n64[4] = {"gemm_bf16_staged_x64_nt", "gemm_bf16_staged_x64_nn", "gemm_bf16_staged_x64_tt",
+                               "gemm_bf16_staged_x64_tn"};
   return (bn == 128 ? n128 : n64)[ta * 2 + tb];
 }
 
@@ -470,10 +471,12 @@ hipError_t launch_gemm(const GemmDesc &d, hipStream_t s) {
   if (gemm_plain_ok(d)) return launch_gemm_plain(d, s);
   // batched and causal products (attention at head widths without a fused kernel), and leading dimensions beyond what
   // the single-product kernel addresses.  128x128 tiles for many rounds of them, 64x64 ones when 128x64 tiles would
-  // not occupy half the CUs (a third faster there)
+  // not occupy half the CUs (a third faster there); neither where both operands are contraction-contiguous (scores of
+  // 64 pairs of T 1024, head width 32, causal: 52 us with 128x64 tiles, 55 with 128x128)
+  const bool nt = !d.ta && !d.tb;
   const long t128 = (long)((d.M + 127) / 128) * ((d.N + 127) / 128) * nbatch;
-  int tile = (d.N > 64 && t128 >= 2048) ? 1 : 2;
-  if (tile == 2 && !(d.ta == 0 && d.tb == 0) && (long)((d.M + 127) / 128) * ((d.N + 63) / 64) * nbatch < 128 && d.M > 64) tile = 3;
+  int tile = (!nt && d.N > 64 && t128 >= 2048) ? 1 : 2;
+  if (tile == 2 && !nt && (long)((d.M + 127) / 128) * ((d.N + 63) / 64) * nbatch < 128 && d.M > 64) tile = 3;
   // slices in flight: a deeper pipeline pays once the contraction is long enough to amortise filling it
   const int D = (d.causal == CAUSAL_NONE && d.K >= 24 * BK) ? 4 : 2;
 #define HYDRA_LAUNCH(BM_, BN_, DD_)                                                                      \

@@ -92,6 +92,25 @@ def test_gemm_bf16_tile_shapes(H, ta, tb, M, N, K):
     assert ((out.double() - ref).abs() <= 2 * (K + 4) * U32 * mag).all()
 
 
+def test_scores_of_many_pairs_take_128x64_tiles(H):
+    """Attention at a head width without a fused kernel: the batched score products (both operands contraction-contiguous)
+    keep the faster 128x64 tiles also when there are thousands of them."""
+    from paper_2110_08633_amd import runtime as R
+    cfg = dict(L=1, d=512, H=16, F=512, V=64, T=512, B=8, k=1, dtype="bf16")
+    sess = R.Session(R.arena_bytes_for([cfg], 2), max_slots=2, flags=H.FLAG_TIMING)
+    n = H.hydra_model_layout(H.model_desc(cfg, 1e-4)).n_params
+    host = [np.zeros(n, np.float32) for _ in range(3)]
+    pinned = [torch.from_numpy(h).pin_memory().numpy() for h in host]
+    rec = sess.add_model(cfg, None, 1e-4, host=tuple(pinned))
+    tok = np.zeros((cfg["B"], cfg["T"]), np.int32)
+    sess.train_step_manual(rec, tok, tok)
+    H.hydra_sync(sess.ctx)
+    names = {k["name"]: k["launches"] for k in H.hydra_kernel_stats(sess.ctx)}
+    sess.close()
+    # forward, recomputation and dP
+    assert names.get("gemm_bf16_staged_x64_nt") == 3 and "gemm_bf16_staged_128x128_nt" not in names, names
+
+
 # one group of wavefronts per block (short sequences, or many row blocks) and two (few row blocks); last tiles and row
 # blocks partly empty; an odd number of tiles for two groups to share; peaked scores, for which the running maximum moves
 ATT_CASES = [(1, 1, 8, 64, 1.0), (2, 3, 72, 128, 1.0), (1, 3, 256, 64, 1.0), (1, 2, 264, 64, 6.0), (3, 5, 328, 128, 1.0),
