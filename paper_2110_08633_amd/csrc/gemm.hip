@@ -154,7 +154,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, const int bid,
       }
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the patch is written (LDS serves a wavefront in order)
     __builtin_amdgcn_wave_barrier();
-    store_patch<WTN>(g, coff, patch, m0 + wm * WTM + i * 32, n0 + wn * WTN, lane, vec);
+    store_patch<WTN, 32, false>(g, coff, patch, m0 + wm * WTM + i * 32, n0 + wn * WTN, lane, vec);
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
   }
@@ -458,6 +458,16 @@ static bool bf16_operands_ok(const GemmDesc &d) {
            (d.sB1 & 7) || (d.sB2 & 7));
 }
 
+// Single products whose contraction fits one slice of the register-staged kernel: there is nothing to pipeline, a launch
+// is its write-out, and that kernel's shorter way to the first MFMA wins with both operands contraction-contiguous and
+// otherwise once 128x64 tiles go round the CUs; not where rows are unaligned, which the other kernel stores better.
+// us at K 64, staged / direct to LDS: nt 1000x1000 6.4 / 6.8, 201x2304 4.1 / 4.3, 2048x4096 8.3 / 9.4; tn 1024x4096 6.4 /
+// 7.0, 1600x6400 11.0 / 12.3, 4096x4096 14.4 / 15.2, but 768x2304 4.6 / 4.3; nn 2048x4096 8.5 / 9.6, but 1000x1000 6.4 / 4.8;
+// rows of 1001: nn 1000x1001 11.1 / 5.1
+static bool one_slice(const GemmDesc &d) {
+  return d.K <= BK && !(d.ldc & 3) && ((!d.ta && !d.tb) || (long)((d.M + 127) / 128) * ((d.N + 63) / 64) > 256);
+}
+
 hipError_t launch_gemm(const GemmDesc &d, hipStream_t s) {
   if (d.M <= 0 || d.N <= 0 || d.nb1 * d.nb2 <= 0) return hipSuccess;
   GemmArgs a;
@@ -468,9 +478,9 @@ hipError_t launch_gemm(const GemmDesc &d, hipStream_t s) {
     return launch_gemm_f32(a, d, nbatch, s);
   }
   if (!bf16_operands_ok(d)) return hipErrorInvalidValue;
-  if (gemm_plain_ok(d)) return launch_gemm_plain(d, s);
-  // batched and causal products (attention at head widths without a fused kernel), and leading dimensions beyond what
-  // the single-product kernel addresses.  128x128 tiles for many rounds of them, 64x64 ones when 128x64 tiles would
+  if (gemm_plain_ok(d) && !one_slice(d)) return launch_gemm_plain(d, s);
+  // batched and causal products (attention at head widths without a fused kernel), one-slice products, and leading
+  // dimensions beyond what the single-product kernel addresses.  128x128 tiles for many rounds of them, 64x64 ones when 128x64 tiles would
   // not occupy half the CUs (a third faster there); neither where both operands are contraction-contiguous (scores of
   // 64 pairs of T 1024, head width 32, causal: 52 us with 128x64 tiles, 55 with 128x128)
   const bool nt = !d.ta && !d.tb;

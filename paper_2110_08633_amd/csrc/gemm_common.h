@@ -266,7 +266,7 @@ __device__ __forceinline__ void store_patch_rows(const GemmArgs &g, int64_t coff
   }
 }
 
-template <int WTN, int PR = 32>
+template <int WTN, int PR, bool COALESCE>
 __device__ __forceinline__ void store_patch(const GemmArgs &g, int64_t coff, const float *patch, int row0, int col0,
                                             int lane, bool vec) {
   if (vec && col0 + WTN <= g.N && row0 + PR <= g.M) {  // uniform over the wavefront
@@ -276,19 +276,20 @@ __device__ __forceinline__ void store_patch(const GemmArgs &g, int64_t coff, con
     return;
   }
   constexpr int SP = WTN + 4, LPR = WTN / 4;
-  if (!vec && g.epi == EPI_NONE) {
+  if (COALESCE && !vec && g.epi == EPI_NONE) {
     // rows that vector stores cannot address (an LM head's gradient has an odd number of columns): neighbouring lanes
     // store neighbouring columns, eight instructions' worth at a time (768x50257x2048 tn: 233 -> 208 us)
     constexpr int U = PR * WTN % 512 == 0 ? 8 : 4;
     static_assert(PR * WTN % (64 * U) == 0, "whole batches");
+    const int end = min(PR, g.M - row0) * WTN;
 #pragma unroll 1
-    for (int p0 = lane; p0 < PR * WTN; p0 += 64 * U) {
+    for (int p0 = 0; p0 < end; p0 += 64 * U) {
       float v[U];
       int64_t idx[U];
       bool in[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int r = (p0 + u * 64) / WTN, cc = (p0 + u * 64) % WTN;
+        const int r = (p0 + u * 64 + lane) / WTN, cc = (p0 + u * 64 + lane) % WTN;
         in[u] = row0 + r < g.M && col0 + cc < g.N;
         idx[u] = coff + (int64_t)(row0 + r) * g.ldc + col0 + cc;
         v[u] = patch[r * SP + cc] * g.alpha;
@@ -306,8 +307,8 @@ __device__ __forceinline__ void store_patch(const GemmArgs &g, int64_t coff, con
   }
   // ragged edge, or an unaligned GELU: one copy of the code
 #pragma unroll 1
-  for (int p = lane; p < PR * LPR; p += 64) {
-    const int r = p / LPR, c = (p % LPR) * 4;
+  for (int p = 0; p < PR * LPR / 64; ++p) {
+    const int r = (p * 64 + lane) / LPR, c = ((p * 64 + lane) % LPR) * 4;
     const f32x4_t v4 = *(const f32x4_t *)(patch + r * SP + c);
     const int row = row0 + r, col = col0 + c;
     if (row < g.M && col < g.N) epilogue_store4<bf16_t>(g, coff, row, col, v4, vec);

@@ -284,7 +284,7 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
         *(f32x4_t *)(patch + (h * 16 + (lane & 15)) * SP + j * 16 + (lane >> 4) * 4) = acc[i + h][j];
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
-    store_patch<WTN, PR>(g, 0, patch, m0 + wm * WTM + (kg * MG + i) * 16, n0 + wn * WTN, lane, vec);
+    store_patch<WTN, PR, true>(g, 0, patch, m0 + wm * WTM + (kg * MG + i) * 16, n0 + wn * WTN, lane, vec);
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
   }

@@ -1,5 +1,7 @@
 """The kernel variants a call may be routed to, each at the sizes where it can go wrong: edges of tiles, remainders, the
 smallest and largest of its range.  References in float64; tolerances are bounds derived from the operand types."""
+import contextlib
+
 import numpy as np
 import pytest
 
@@ -12,6 +14,20 @@ U32 = 2.0 ** -24  # half a unit in the last place of a 24-bit significand
 def H():
     from paper_2110_08633_amd import hydra
     return hydra
+
+
+@contextlib.contextmanager
+def launched(H):
+    """Yields a dict that holds, after the block, the launches per kernel name of what ran in it."""
+    from paper_2110_08633_amd import runtime as R
+    sess = R.Session(1 << 20, flags=H.FLAG_TIMING)
+    names = {}
+    try:
+        yield names
+        torch.cuda.synchronize()
+        names.update({k["name"]: k["launches"] for k in H.hydra_kernel_stats(sess.ctx)})
+    finally:
+        sess.close()
 
 
 def randn(seed, *shape):
@@ -90,6 +106,33 @@ def test_gemm_bf16_tile_shapes(H, ta, tb, M, N, K):
     # products of bf16 values are exact in fp32; each of the K + 4 additions and scalings errs by at most a unit in the
     # last place of the sum of magnitudes (the matrix instruction may truncate)
     assert ((out.double() - ref).abs() <= 2 * (K + 4) * U32 * mag).all()
+
+
+# a contraction of one slice or less: which of the two kernels takes it depends on layout, tiles and rows; M, N, K, layout,
+# extra leading dimension of the result, whether the register-staged kernel is expected
+ONE_SLICE = [(1000, 1000, 64, "nt", 0, True), (8, 768, 40, "nt", 0, True), (8, 768, 64, "nt", 1, False),
+             (1000, 1001, 64, "nt", 0, False), (2049, 4100, 8, "nn", 0, True), (1000, 1000, 64, "nn", 0, False),
+             (1024, 4096, 64, "tn", 0, True), (1601, 6400, 40, "tt", 0, True), (768, 2304, 64, "tn", 0, False),
+             (1024, 4096, 65, "tn", 0, False), (1000, 1000, 72, "nt", 0, False), (4099, 1003, 24, "tn", 0, False)]
+
+
+@pytest.mark.parametrize("M,N,K,layout,ext,staged", ONE_SLICE)
+def test_gemm_bf16_one_slice(H, M, N, K, layout, ext, staged):
+    ta, tb = layout[0] == "t", layout[1] == "n"
+    r8 = lambda n: (n + 7) // 8 * 8
+    A, B, resid = randn(M + K, M, K).bfloat16(), randn(N + K + 1, K, N).bfloat16(), randn(M + N + 2, M, N + ext)
+    As, Bs = A.t().contiguous() if ta else A, B if tb else B.t().contiguous()
+    dA, dB = stored(As, r8(As.shape[1]), 0), stored(Bs, r8(Bs.shape[1]), 0)
+    out, act = torch.full((M, N + ext), 7.0, device="cuda"), torch.full((M, N + ext), 7.0, device="cuda").bfloat16()
+    with launched(H) as names:
+        H.hydra_op_gemm(1, ta, tb, M, N, K, 1.0, dA, dA.shape[1], dB, dB.shape[1], None, resid, out, act, N + ext)
+    assert [n.startswith("gemm_bf16_staged") for n in names] == [staged], names
+    ref = A.double() @ B.double() + resid[:, :N].double()
+    mag = A.double().abs() @ B.double().abs() + resid[:, :N].double().abs()
+    # as in test_gemm_bf16_tile_shapes
+    assert ((out[:, :N].double() - ref).abs() <= 2 * (K + 4) * U32 * mag).all()
+    assert ((act[:, :N].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2 * (K + 4) * U32 * mag).all()
+    assert (out[:, N:] == 7.0).all() and (act[:, N:] == 7.0).all()
 
 
 def test_scores_of_many_pairs_take_128x64_tiles(H):
