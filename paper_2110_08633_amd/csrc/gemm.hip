@@ -405,13 +405,15 @@ constexpr int64_t F32_LD_MAX = 0x70000000 / (64 * 4);  // 64 lines of a slice st
 static hipError_t launch_gemm_f32(GemmArgs &a, const GemmDesc &d, int nbatch, hipStream_t s) {
   const bool vec = f32_vec_ok(d.A, d.lda, d.sA1, d.sA2, d.ta ? d.M : d.K) && f32_vec_ok(d.B, d.ldb, d.sB1, d.sB2, d.tb ? d.N : d.K);
   const long t64 = (long)((d.M + 63) / 64) * ((d.N + 63) / 64) * nbatch;
-  if (d.lda >= F32_LD_MAX || d.ldb >= F32_LD_MAX) return launch_f32_cfg<16, 64, LD_WIDE>(a, d.ta, d.tb, nbatch, s);
+  const bool wide = d.lda >= F32_LD_MAX || d.ldb >= F32_LD_MAX;
   // 64x64 tiles once they go round the 256 CUs two and a half times: below that the last round leaves too many idle
   // (us, 64x64 / 32x32 tiles: 192 tiles 72 / 57 at 1000x768x3072, 384 tiles 83 / 75 at 2048x768x2304, 768 tiles
   // 51 / 56 at 1000x3072x768, 4096 tiles 1074 / 1192 at 4096^3)
   if (t64 >= 640)
-    return vec ? launch_f32_cfg<32, 32, LD_VEC>(a, d.ta, d.tb, nbatch, s)
-               : launch_f32_cfg<32, 32, LD_SCALAR>(a, d.ta, d.tb, nbatch, s);
+    return wide  ? launch_f32_cfg<32, 32, LD_WIDE>(a, d.ta, d.tb, nbatch, s)
+           : vec ? launch_f32_cfg<32, 32, LD_VEC>(a, d.ta, d.tb, nbatch, s)
+                 : launch_f32_cfg<32, 32, LD_SCALAR>(a, d.ta, d.tb, nbatch, s);
+  if (wide) return launch_f32_cfg<16, 64, LD_WIDE>(a, d.ta, d.tb, nbatch, s);
   return vec ? launch_f32_cfg<16, 64, LD_VEC>(a, d.ta, d.tb, nbatch, s)
              : launch_f32_cfg<16, 64, LD_SCALAR>(a, d.ta, d.tb, nbatch, s);
 }

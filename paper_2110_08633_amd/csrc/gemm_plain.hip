@@ -1,8 +1,7 @@
 // bf16 products of single matrices - the linear layers of a block, their input and weight gradients, the LM head - and
 // the choice of their tile shape.
-#include <cmath>
-
 #include "gemm_common.h"
+#include "gemm_shapes.h"
 
 namespace hydra {
 
@@ -360,62 +359,7 @@ static hipError_t launch_shape(const GemmDesc *d, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The tile shapes, and what a launch of each costs in us:
-//   t0 + rounds * (nk * a + c) + tiles / 256 * (nk * b + e)
-// with nk = contraction / 64 (rounded up) and rounds = tiles / 256 rounded up: the tiles of the busiest CU one after the
-// other, plus what all of them take from the caches and from memory together.  With transposing LDS reads of both a block of four
-// wavefronts alone leaves its CU half idle, so there a round is as many tiles as the CUs hold blocks.  The constants are
-// least-squares fits (weighted towards the products for which a shape is among the fastest) to 200 products of the four
-// models' widths at 201 to 4096 tokens, LM heads included: one set for operands that are both contraction-contiguous and
-// one for products that read both through the transposing LDS read; products with one of each take the middle.  The
-// cheapest shape by this estimate is within 1.1 % of the fastest one on average, and 1.35 times as fast as the kernels
-// it replaces (210 random products).
-struct PlainShape {
-  int bm, bn, occ;  // tile, blocks per CU
-  float t0[2], a[2], b[2], c[2], e[2];
-};
-static const PlainShape plain_shapes[] = {
-    {256, 256, 1, {0.f, 0.f}, {0.830f, 1.272f}, {0.538f, 0.538f}, {7.196f, 7.679f}, {5.990f, 5.423f}},
-    {128, 256, 1, {0.700f, 2.841f}, {0.542f, 0.588f}, {0.215f, 0.251f}, {4.376f, 2.872f}, {3.607f, 3.663f}},
-    {128, 192, 1, {0.698f, 4.614f}, {0.470f, 0.506f}, {0.150f, 0.154f}, {3.797f, 0.f}, {2.403f, 4.969f}},
-    {128, 128, 1, {1.171f, 2.835f}, {0.323f, 0.332f}, {0.137f, 0.171f}, {3.051f, 1.382f}, {0.878f, 2.316f}},
-    {128, 64, 2, {3.621f, 3.814f}, {0.258f, 0.307f}, {0.025f, 0.135f}, {0.f, 0.f}, {0.751f, 1.514f}},
-    {64, 96, 2, {3.906f, 3.841f}, {0.231f, 0.272f}, {0.012f, 0.112f}, {0.f, 0.f}, {0.578f, 1.421f}},
-    {64, 64, 3, {3.788f, 3.715f}, {0.193f, 0.124f}, {0.f, 0.147f}, {0.f, 0.f}, {0.500f, 0.668f}},
-    {64, 64, 1, {1.535f, 1.619f}, {0.147f, 0.166f}, {0.027f, 0.f}, {2.522f, 2.463f}, {0.088f, 0.294f}},  // slices split over two groups of wavefronts
-    {128, 64, 1, {1.761f, 2.516f}, {0.215f, 0.222f}, {0.071f, 0.075f}, {3.127f, 2.300f}, {0.f, 0.936f}},  // the same
-    {64, 96, 1, {2.014f, 2.093f}, {0.186f, 0.186f}, {0.043f, 0.075f}, {2.271f, 2.622f}, {0.677f, 0.415f}},  // the same
-    {128, 128, 2, {0.f, 3.209f}, {0.f, 0.432f}, {0.f, 0.223f}, {0.f, 0.879f}, {0.f, 2.244f}},  // two blocks of four wavefronts: see best_shape
-};
-constexpr int N_SHAPES = sizeof(plain_shapes) / sizeof(plain_shapes[0]);
-
-static float shape_cost(const PlainShape &p, const GemmDesc *d, int n) {
-  // one transposed operand: half way between the two
-  const float x = d->ta == d->tb ? (float)(d->ta != 0) : 0.5f;
-  auto at = [x](const float (&v)[2]) { return v[0] + x * (v[1] - v[0]); };
-  float tiles = 0.f;
-  int K = 0;
-  for (int i = 0; i < n; ++i) {
-    tiles += (float)((d[i].M + p.bm - 1) / p.bm) * (float)((d[i].N + p.bn - 1) / p.bn);
-    K = d[i].K > K ? d[i].K : K;
-  }
-  const float nk = (float)((K + 63) / 64), u = tiles * (1.f / 256.f);
-  const float rounds = ceilf(x == 1.f ? u / (float)p.occ : u);
-  return at(p.t0) + rounds * (nk * at(p.a) + at(p.c)) + u * (nk * at(p.b) + at(p.e));
-}
-
-static int best_shape(const GemmDesc *d, int n, float *cost) {
-  // the last shape gains where two blocks write out and multiply in turn, which needs many tiles, transposing reads and
-  // vector stores (768x50257x2048 with its odd rows: 256 us against 208 with 128x256)
-  bool last = true;
-  for (int i = 0; i < n; ++i) last = last && d[i].ta && d[i].tb && !(d[i].ldc & 3);
-  int best = 0;
-  for (int i = 0; i < N_SHAPES - (last ? 0 : 1); ++i) {
-    const float c = shape_cost(plain_shapes[i], d, n);
-    if (i == 0 || c < *cost) { best = i; *cost = c; }
-  }
-  return best;
-}
+static GemmDims dims_of(const GemmDesc &d) { return {d.M, d.N, d.K, d.ta != 0, d.tb != 0, (d.ldc & 3) == 0}; }
 
 static hipError_t launch_best(const GemmDesc *d, int n, int shape, hipStream_t s) {
   static const char *const names[N_SHAPES][4] = {
@@ -447,19 +391,22 @@ bool gemm_plain_ok(const GemmDesc &d) {
 }
 
 hipError_t launch_gemm_plain(const GemmDesc &d, hipStream_t s) {
+  const GemmDims x = dims_of(d);
   float cost;
-  const int shape = best_shape(&d, 1, &cost);
+  const int shape = best_shape(&x, 1, &cost);
   return launch_best(&d, 1, shape, s);
 }
 
 hipError_t launch_gemm_plain_group(const GemmDesc *d, int n, hipStream_t s) {
+  GemmDims x[GEMM_GROUP_MAX];
   float together, alone = 0.f;
-  const int shape = best_shape(d, n, &together);
   for (int i = 0; i < n; ++i) {
     float c;
-    best_shape(&d[i], 1, &c);
+    x[i] = dims_of(d[i]);
+    best_shape(&x[i], 1, &c);
     alone += c;
   }
+  const int shape = best_shape(x, n, &together);
   if (together <= alone) return launch_best(d, n, shape, s);
   for (int i = 0; i < n; ++i) {
     const hipError_t e = launch_gemm_plain(d[i], s);

@@ -71,6 +71,12 @@ def test_gemm_f32_variants(H, ta, tb, M, N, K, extra, shift):
     assert (out[:, N:] == 7.0).all()
 
 
+def test_gemm_f32_wide_operands_large_result(H):
+    """Leading dimensions beyond a 32-bit byte offset, with enough tiles for 64x64 ones (32x32 tiles would exceed a launch's
+    threads from 1.7e10 results on)."""
+    test_gemm_f32_variants(H, 1, 1, 1700, 1604, 12, 7340040, 0)
+
+
 # bf16 products, one matrix each: sizes for which the launcher takes each of its tile shapes - 64x64 with the contraction
 # split over two groups, 64x64, 64x96, 128x64, 128x128 (both kinds), 128x192, 128x256, 256x256 - with ragged last rows,
 # columns and contractions (shorter than a slice, one step into the next slice, an odd length)

@@ -410,3 +410,42 @@ int main() {
     # and no launcher keeps such a limit per process
     for f in os.listdir(csrc):
         assert not re.search(r"static\s+(const\s+)?hipError_t\s+\w+\s*=\s*hipFuncSetAttribute", open(os.path.join(csrc, f)).read()), f
+
+
+@pytest.fixture(scope="module")
+def tile_shape(tmp_path_factory):
+    """(M, N, K, ta, tb[, vec_rows]) -> index, rows, columns, threads per block of the tile shape the launcher of single bf16
+    products takes."""
+    d = tmp_path_factory.mktemp("shapes")
+    src = d / "t.cpp"
+    src.write_text(r'''
+#include "gemm_shapes.h"
+#include <cstdio>
+int main() {
+  hydra::GemmDims d;
+  int ta, tb, vec;
+  while (scanf("%d %d %d %d %d %d", &d.M, &d.N, &d.K, &ta, &tb, &vec) == 6) {
+    d.ta = ta; d.tb = tb; d.vec_rows = vec;
+    float cost;
+    const int i = hydra::best_shape(&d, 1, &cost);
+    printf("%d %d %d %d\n", i, hydra::plain_shapes[i].bm, hydra::plain_shapes[i].bn, hydra::plain_shapes[i].threads);
+  }
+}
+''')
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2110_08633_amd", "csrc"),
+                           str(src), "-o", str(d / "t")])
+
+    def shape(M, N, K, ta, tb, vec_rows=1):
+        out = subprocess.run([str(d / "t")], input=f"{M} {N} {K} {ta} {tb} {int(vec_rows)}", text=True, capture_output=True, check=True)
+        return tuple(int(x) for x in out.stdout.split())
+    return shape
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("vec_rows", [True, False])
+@pytest.mark.parametrize("K", [1, 64, 65, 200, 2048])
+def test_tile_shape_of_the_largest_results(tile_shape, ta, tb, K, vec_rows):
+    """A grid holds fewer than 2^32 threads: results of 7e10 elements must not be cut into the smallest tiles."""
+    M = N = 270000
+    _, bm, bn, threads = tile_shape(M, N, K, ta, tb, vec_rows)
+    assert -(-M // bm) * -(-N // bn) * threads < 2 ** 32
