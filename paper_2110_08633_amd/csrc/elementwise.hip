@@ -450,7 +450,9 @@ __global__ __launch_bounds__(512, NR <= 7 ? 4 : 2) void layernorm_bwd_fused_kern
 #pragma clang fp contract(off)
   __shared__ float red[2][4][NR * 256];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int row = blockIdx.x * LNB_ROWS + wave;
+  const int blk = blockIdx.y * gridDim.x + blockIdx.x;
+  if (blk >= (M + LNB_ROWS - 1) / LNB_ROWS) return;
+  const int row = blk * LNB_ROWS + wave;
   const bool in = row < M;  // uniform over the wavefront
   float4 xh[NR], g[NR], o[NR];
   if (in) {
@@ -495,7 +497,7 @@ __global__ __launch_bounds__(512, NR <= 7 ? 4 : 2) void layernorm_bwd_fused_kern
       }
     }
   }
-  float *out = part + (int64_t)blockIdx.x * 3 * d;
+  float *out = part + (int64_t)blk * 3 * d;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {  // dy * xhat, dy, dx
     float(*const buf)[NR * 256] = red[q & 1];
@@ -542,8 +544,10 @@ hipError_t launch_layernorm_bwd_fused(const float *dy, const float *x, const flo
                                       int d, hipStream_t s) {
   if (!layernorm_bwd_fused_supported(d)) return hipErrorInvalidValue;
   const int nr = (d + 255) / 256;
-  dim3 grid(layernorm_bwd_fused_blocks(M)), block(512);
-  ProfScope ps("layernorm_bwd", s, 0, (double)M * d * ((dres ? 16.0 : 12.0) + (dx_bf16 ? 2.0 : 0.0)) + 12.0 * grid.x * d);
+  // (a row of blocks holds at most 2^32 threads, 2^23 blocks of 512)
+  const int blocks = layernorm_bwd_fused_blocks(M), gx = blocks < (1 << 22) ? blocks : 1 << 22;
+  dim3 grid(gx, (blocks + gx - 1) / gx), block(512);
+  ProfScope ps("layernorm_bwd", s, 0, (double)M * d * ((dres ? 16.0 : 12.0) + (dx_bf16 ? 2.0 : 0.0)) + 12.0 * blocks * d);
 #define HYDRA_LNB(NR_)                                                                                                  \
   hipLaunchKernelGGL(layernorm_bwd_fused_kernel<NR_>, grid, block, 0, s, dy, x, mean, rstd, gamma, dres, dx,             \
                      (bf16_t *)dx_bf16, part, M, d)

@@ -281,3 +281,25 @@ def test_layernorm_bwd_widths(H, M, d):
     for got, v in zip(cols, (dy.double() * xh, dy.double(), dx.double())):
         # eight rows in fp32, the rest in 64 bits; xhat itself carries three roundings
         assert ((got.double() - v.sum(0)).abs() <= 14 * U32 * v.abs().sum(0) + 4 * U32 * dy.double().abs().sum(0)).all()
+
+
+def test_layernorm_bwd_more_blocks_than_a_row_of_the_grid_holds(H):
+    M, d = 67200003, 4
+    x, dy = randn(1, M, d), randn(2, M, d)
+    gamma = randn(3, d) * 0.1 + 1
+    mean = x.mean(1)
+    rstd = 1 / torch.sqrt(((x - mean[:, None]) ** 2).mean(1) + 1e-5)
+    dx, cols = torch.full((M + 1, d), 7.0, device="cuda"), [torch.empty(d, device="cuda") for _ in range(3)]
+    H.hydra_op_layernorm_bwd(dy, x, mean, rstd, gamma, None, dx, None, *cols, torch.empty(3 * d * ((M + 7) // 8), device="cuda"),
+                             M, d)
+    torch.cuda.synchronize()
+    assert (dx[-1] == 7.0).all()
+    xh = (x - mean[:, None]) * rstd[:, None]
+    h = dy * gamma
+    part = h - h.mean(1, keepdim=True) - xh * (h * xh).mean(1, keepdim=True)
+    mag = h.abs() + h.abs().mean(1, keepdim=True) + xh.abs() * (h * xh).abs().mean(1, keepdim=True)
+    # a dozen roundings on either side
+    assert ((dx[:-1] - rstd[:, None] * part).abs() <= 32 * U32 * rstd[:, None] * mag).all()
+    for got, v in zip(cols, (dy * xh, dy, dx[:-1])):
+        # eight rows in fp32, the rest in 64 bits; xhat itself carries three roundings on either side
+        assert ((got.double() - v.sum(0, dtype=torch.float64)).abs() <= 20 * U32 * v.abs().sum(0, dtype=torch.float64)).all()
