@@ -135,9 +135,12 @@ __device__ __forceinline__ uint32_t lds_addr(const void *p) {
 // Block -> (sample and head, row block): all pairs' row blocks of one index before those of the next, the ones with the
 // most tiles first (the longest ones would otherwise be started last and run alone).  Consecutive block ids go
 // round-robin to the 8 XCDs, so with a multiple of 8 pairs a pair's keys and values stay in one XCD's L2.
-__device__ __forceinline__ void block_place(int pairs, int &z, int &rb) {
-  rb = blockIdx.x / pairs;
-  z = blockIdx.x - rb * pairs;
+// False for blocks that only fill up the last row of a two-dimensional grid (see HYDRA_ATTN).
+__device__ __forceinline__ bool block_place(int pairs, int nb, int &z, int &rb) {
+  const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
+  rb = id / (uint32_t)pairs;
+  z = id - rb * (uint32_t)pairs;
+  return rb < nb;
 }
 
 // ---------------------------------------------------------------------------
@@ -165,7 +168,7 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__r
   const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
   int z, qb;
-  block_place(pairs, z, qb);
+  if (!block_place(pairs, nb, z, qb)) return;
   qb = nb - 1 - qb;
   const int b = z / H, h = z % H;
   const int q0 = qb * AQ, r0 = q0 + wave * 32;
@@ -342,7 +345,7 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *
   const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
   int z, qb;
-  block_place(pairs, z, qb);
+  if (!block_place(pairs, nb, z, qb)) return;
   qb = nb - 1 - qb;
   const int b = z / H, h = z % H;
   const int q0 = qb * AQ, r0 = q0 + wave * 32;
@@ -463,7 +466,7 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
   const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
   int z, kb;
-  block_place(pairs, z, kb);
+  if (!block_place(pairs, nb, z, kb)) return;
   const int b = z / H, h = z % H;
   const int k0 = kb * AQ, kr0 = k0 + wave * 32;
   const int64_t ld = 3 * (int64_t)d;
@@ -592,13 +595,15 @@ static constexpr size_t attn_lds(int dh, int kw, int nacc, int extra, size_t sta
   return tiles > merge ? tiles : merge;
 }
 
+// (a row of the grid holds at most 2^32 threads)
 #define HYDRA_ATTN(KERN_, LDS_, ...)                                               \
   do {                                                                             \
     auto kern = KERN_;                                                             \
     static OncePerGpu once;                                                        \
     const hipError_t attr = allow_lds(once, (const void *)kern, LDS_);             \
     if (attr != hipSuccess) return attr;                                           \
-    hipLaunchKernelGGL(kern, dim3(nb * B * H), dim3(256 * KW), LDS_, s, __VA_ARGS__); \
+    const uint32_t blocks = (uint32_t)nb * B * H, gx = blocks < (1u << 22) ? blocks : 1u << 22; \
+    hipLaunchKernelGGL(kern, dim3(gx, (blocks + gx - 1) / gx), dim3(256 * KW), LDS_, s, __VA_ARGS__); \
   } while (0)
 
 template <int DH, int KW, bool DIRECT>

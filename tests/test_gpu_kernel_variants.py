@@ -202,6 +202,23 @@ def test_attention_variants(H, B, Hn, T, dh, peak):
         assert (g - r).norm() <= 2.0 ** -7 * r.norm() + 1e-12
 
 
+def test_attention_more_blocks_than_a_row_of_the_grid_holds(H):
+    B, T, dh = (1 << 24) + 3, 8, 64
+    one = randn(1, T, 3 * dh).bfloat16()
+    qkv = one.repeat(B, 1)
+    o, lse = torch.zeros(B, T * dh, device="cuda").bfloat16(), torch.zeros(B, T, device="cuda")
+    H.hydra_op_attention_fwd(qkv, o, lse, B, 1, T, dh)
+    torch.cuda.synchronize()
+    del qkv
+    o1, lse1 = torch.zeros(1, T * dh, device="cuda").bfloat16(), torch.zeros(1, T, device="cuda")
+    H.hydra_op_attention_fwd(one, o1, lse1, 1, 1, T, dh)
+    assert torch.equal(lse, lse1.expand(B, T))
+    for part in o.split(1 << 20):
+        assert torch.equal(part, o1.expand_as(part))
+    del o
+    torch.cuda.empty_cache()
+
+
 # a score of -inf (here by overflow: finite operands, a product beyond fp32) weighs nothing, in whichever group of
 # wavefronts and at whichever place of its tile it falls - also where it is all a row sees of a tile (keys 0..63, or the
 # diagonal key of row 64 + 128 i, which opens the second group's first tile)
