@@ -420,10 +420,17 @@ static hipError_t launch_gemm_f32(GemmArgs &a, const GemmDesc &d, int nbatch, hi
 
 template <int BM, int BN, int WM, int WN, int D>
 static hipError_t launch_bf16_cfg(const GemmArgs &a, int ta, int tb, dim3 grid, hipStream_t s) {
-  if (ta == 0 && tb == 0) hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, 0, 0, D>), grid, dim3(256), 0, s, a);
-  else if (ta == 0 && tb == 1) hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, 0, 1, D>), grid, dim3(256), 0, s, a);
-  else if (ta == 1 && tb == 1) hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, 1, 1, D>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, 1, 0, D>), grid, dim3(256), 0, s, a);
+  if (ta == 0 && tb == 0) {
+    // (both operands contraction-contiguous: only ever 128x64 tiles)
+    if constexpr (BM == 128 && BN == 64) hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, 0, 0, D>), grid, dim3(256), 0, s, a);
+    else return hipErrorInvalidValue;
+  } else if (ta == 0) {
+    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, 0, 1, D>), grid, dim3(256), 0, s, a);
+  } else if (tb == 1) {
+    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, 1, 1, D>), grid, dim3(256), 0, s, a);
+  } else {
+    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, 1, 0, D>), grid, dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 
@@ -489,7 +496,8 @@ hipError_t launch_gemm(const GemmDesc &d, hipStream_t s) {
   const long t128 = (long)((d.M + 127) / 128) * ((d.N + 127) / 128) * nbatch;
   int tile = (!nt && d.N > 64 && t128 >= 2048) ? 1 : 2;
   if (tile == 2 && !nt && (long)((d.M + 127) / 128) * ((d.N + 63) / 64) * nbatch < 128 && d.M > 64) tile = 3;
-  // slices in flight: a deeper pipeline pays once the contraction is long enough to amortise filling it
+  // slices in flight: a deeper pipeline pays once the contraction is long enough to amortise filling it (of the products
+  // that come here, those with leading dimensions beyond the single-product kernel's)
   const int D = (d.causal == CAUSAL_NONE && d.K >= 24 * BK) ? 4 : 2;
 #define HYDRA_LAUNCH(BM_, BN_, DD_)                                                                      \
   do {                                                                                                    \

@@ -52,8 +52,8 @@ template <int R, int RCL, int BK_, int NW>
 struct LdsMover {
   static constexpr int CPL = (RCL ? R : BK_) / 8;        // chunks per line
   static constexpr int NCH = R * BK_ / 8;                // chunks per slice
-  static constexpr int N = (NCH + 64 * NW - 1) / (64 * NW);
-  static_assert(NCH % 64 == 0, "whole wavefronts");
+  static constexpr int N = NCH / (64 * NW);              // loads per wavefront
+  static_assert(NCH == N * 64 * NW, "every wavefront loads alike");
   const bf16_t *base;
   int64_t kstep;   // elements per slice
   int off[N];      // byte offset within a slice, BUF_OUT for rows past the matrix
@@ -78,7 +78,6 @@ struct LdsMover {
   }
   // chunk i of slice t into the operand's tile at lds; krem: contraction steps left from the start of the slice
   __device__ __forceinline__ void issue(int i, int t, int krem, uint32_t lds, int wave) const {
-    if (NCH % (64 * NW) && i == N - 1 && wave >= NCH / 64 - i * NW) return;  // uniform over the wavefront
     load_to_lds(base + t * kstep, kloc[i] < krem ? off[i] : BUF_OUT, lds + (i * NW + wave) * 64 * 16);
   }
 };
@@ -118,7 +117,7 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
   constexpr int NG = WM * WN, NW = NG * KW, WTM = BM / WM, WTN = BN / WN, MI = WTM / 16, NJ = WTN / 16;
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && MI * 16 * WM == BM && NJ * 16 * WN == BN, "wavefront tiles");
   constexpr int STAGE = (BM + BN) * BK_, KS = BK_ / 32 / KW;  // steps of a slice per wavefront
-  static_assert(KS * KW * 32 == BK_, "the groups share the steps of a slice evenly");
+  static_assert(KS * KW * 32 == BK_ && KS % 2 == 0, "the groups share a slice evenly, an even number of steps each");
   typedef LdsMover<BM, TA, BK_, NW> MA;
   typedef LdsMover<BN, TB, BK_, NW> MB;
   constexpr int NL = MA::N + MB::N;
@@ -156,10 +155,8 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
   for (int p = 0; p < S; ++p)
 #pragma unroll
     for (int l = 0; l < NL; ++l) issue(l, p, p);
-  // a slice has landed when at most the loads of the S - 1 younger ones are in flight (a wavefront that issues fewer
-  // loads than the others waits for a little more than it has to)
-  constexpr int NLMIN = NL - (MA::NCH % (64 * NW) ? 1 : 0) - (MB::NCH % (64 * NW) ? 1 : 0);
-  wait_loads_le<(S - 1) * NLMIN>();
+  // a slice has landed when at most the loads of the S - 1 younger ones are in flight
+  wait_loads_le<(S - 1) * NL>();
   block_barrier();
   bf16x8_t af[2][MI], bfr[2][NJ];
 #pragma unroll
@@ -167,20 +164,18 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
 #pragma unroll
   for (int j = 0; j < NJ; ++j) bfr[0][j] = fb.get(lds + BM * BK_, j, 0);
 
-  // One slice from stage st.  cur: fragment set that holds its first step (changes from slice to slice when a slice
-  // has an odd number of steps).
-  auto slice = [&](int t, int st, auto curc) {
-    constexpr int CUR = decltype(curc)::value;
+  // one slice from stage st; its first step sits in fragment set 0
+  auto slice = [&](int t, int st) {
     const bf16_t *const as = lds + st * STAGE;
     const int st_next = st + 1 == S ? 0 : st + 1;
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
       constexpr int NR = MI + NJ, NS = MI * NJ;
-      const int c = (CUR + kk) & 1, nx = c ^ 1, nkk = kk + 1 < KS ? kk + 1 : 0;
+      const int c = kk & 1, nx = c ^ 1, nkk = kk + 1 < KS ? kk + 1 : 0;
       const bf16_t *na = as;
       if (kk + 1 == KS) {
         // slice t + 1 has landed, and this wavefront's reads of slice t are complete before anybody overwrites it
-        wait_loads_le<(S - 2) * NLMIN>();
+        wait_loads_le<(S - 2) * NL>();
         block_barrier();
         na = lds + st_next * STAGE;
       }
@@ -211,20 +206,9 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
         }
     }
   };
-  int t = 0, st = 0;
-  if constexpr (KS % 2 == 0) {
-    for (; t < nk; ++t) {
-      slice(t, st, std::integral_constant<int, 0>());
-      if (++st == S) st = 0;
-    }
-  } else {
-    for (; t + 1 < nk; t += 2) {
-      slice(t, st, std::integral_constant<int, 0>());
-      if (++st == S) st = 0;
-      slice(t + 1, st, std::integral_constant<int, 1>());
-      if (++st == S) st = 0;
-    }
-    if (t < nk) slice(t, st, std::integral_constant<int, 0>());
+  for (int t = 0, st = 0; t < nk; ++t) {
+    slice(t, st);
+    if (++st == S) st = 0;
   }
   wait_loads_le<0>();
   block_barrier();  // the write-out reuses the stages
@@ -312,8 +296,8 @@ __global__ __launch_bounds__(64 * WM * WN * KW, OCC * WM * WN * KW / 4) void gem
   gemm16_tile<BM, BN, WM, WN, KW, TA, TB, BK_, S>(gg.p[i], blockIdx.x - gg.tile0[i], gg.tile0[i + 1] - gg.tile0[i], lds_dyn);
 }
 
-// d[0..n): one product, or a group of contraction-strided ones
-template <int BM, int BN, int WM, int WN, int KW, int BK_, int S, int OCC>
+// d[0..n): one product, or a group of contraction-strided ones.  TN_ONLY: the shape is chosen for such products alone
+template <int BM, int BN, int WM, int WN, int KW, int BK_, int S, int OCC, bool TN_ONLY = false>
 static hipError_t launch_shape(const GemmDesc *d, int n, hipStream_t s) {
   constexpr size_t lds = (size_t)S * (BM + BN) * BK_ * 2;
   constexpr int threads = 64 * WM * WN * KW;
@@ -345,14 +329,16 @@ static hipError_t launch_shape(const GemmDesc *d, int n, hipStream_t s) {
     auto kern = gemm_plain_group_kernel<BM, BN, WM, WN, KW, 1, 1, BK_, S, OCC>;
     HYDRA_SET_LDS(kern);
     hipLaunchKernelGGL(kern, dim3(tiles), dim3(threads), lds, s, gg);
-  } else if (!d->ta && !d->tb) {
-    HYDRA_PLAIN(0, 0);
-  } else if (!d->ta) {
-    HYDRA_PLAIN(0, 1);
-  } else if (d->tb) {
+  } else if (d->ta && d->tb) {
     HYDRA_PLAIN(1, 1);
-  } else {
+  } else if constexpr (TN_ONLY) {
+    return hipErrorInvalidValue;
+  } else if (d->ta) {
     HYDRA_PLAIN(1, 0);
+  } else if (d->tb) {
+    HYDRA_PLAIN(0, 1);
+  } else {
+    HYDRA_PLAIN(0, 0);
   }
 #undef HYDRA_PLAIN
 #undef HYDRA_SET_LDS
@@ -381,7 +367,7 @@ static hipError_t launch_best(const GemmDesc *d, int n, int shape, hipStream_t s
     case 7: return launch_shape<64, 64, 2, 2, 2, 128, 4, 1>(d, n, s);
     case 8: return launch_shape<128, 64, 2, 2, 2, 128, 3, 1>(d, n, s);
     case 9: return launch_shape<64, 96, 2, 2, 2, 128, 3, 1>(d, n, s);
-    default: return launch_shape<128, 128, 2, 2, 1, 64, 2, 2>(d, n, s);
+    default: return launch_shape<128, 128, 2, 2, 1, 64, 2, 2, true>(d, n, s);
   }
 }
 
