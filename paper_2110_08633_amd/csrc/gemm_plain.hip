@@ -348,14 +348,14 @@ static hipError_t launch_shape(const GemmDesc *d, int n, hipStream_t s) {
 static GemmDims dims_of(const GemmDesc &d) { return {d.M, d.N, d.K, d.ta != 0, d.tb != 0, (d.ldc & 3) == 0}; }
 
 static hipError_t launch_best(const GemmDesc *d, int n, int shape, hipStream_t s) {
-  static const char *const names[N_SHAPES][4] = {
-#define HYDRA_N(X) {"gemm_bf16_" X "_nt", "gemm_bf16_" X "_nn", "gemm_bf16_" X "_tt", "gemm_bf16_" X "_tn"}
+  static const char *const names[N_SHAPES][5] = {
+#define HYDRA_N(X) {"gemm_bf16_" X "_nt", "gemm_bf16_" X "_nn", "gemm_bf16_" X "_tt", "gemm_bf16_" X "_tn", "gemm_bf16_" X "_tn_group"}
       HYDRA_N("256x256"), HYDRA_N("128x256"), HYDRA_N("128x192"), HYDRA_N("128x128"), HYDRA_N("128x64"),
       HYDRA_N("64x96"), HYDRA_N("64x64"), HYDRA_N("64x64k2"), HYDRA_N("128x64k2"), HYDRA_N("64x96k2"), HYDRA_N("128x128x2")};
 #undef HYDRA_N
   double flops = 0;
   for (int i = 0; i < n; ++i) flops += gemm_flops(d[i]);
-  ProfScope ps(n > 1 ? "gemm_bf16_tn_group" : names[shape][d->ta * 2 + d->tb], s, flops, 0);
+  ProfScope ps(names[shape][n > 1 ? 4 : d->ta * 2 + d->tb], s, flops, 0);
   switch (shape) {
     case 0: return launch_shape<256, 256, 2, 4, 1, 64, 2, 1>(d, n, s);
     case 1: return launch_shape<128, 256, 2, 4, 1, 64, 3, 1>(d, n, s);

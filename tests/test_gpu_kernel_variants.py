@@ -77,9 +77,8 @@ def test_gemm_f32_wide_operands_large_result(H):
     test_gemm_f32_variants(H, 1, 1, 1700, 1604, 12, 7340040, 0)
 
 
-# bf16 products, one matrix each: sizes for which the launcher takes each of its tile shapes - 64x64 with the contraction
-# split over two groups, 64x64, 64x96, 128x64, 128x128 (both kinds), 128x192, 128x256, 256x256 - with ragged last rows,
-# columns and contractions (shorter than a slice, one step into the next slice, an odd length)
+# bf16 products, one matrix each, with ragged last rows, columns and contractions (shorter than a slice, one step into the
+# next slice, an odd length); EVERY_SHAPE below takes every tile shape
 PLAIN_CASES = [(1, 1, 8), (33, 40, 72), (201, 2304, 768), (520, 264, 200), (513, 1024, 1001), (2050, 776, 2056),
                (1100, 1608, 600), (900, 3300, 776), (1030, 4104, 1000), (2000, 3000, 520), (1000, 6408, 1608),
                (4100, 4104, 72), (1000, 16392, 4096)]
@@ -114,9 +113,134 @@ def test_gemm_bf16_tile_shapes(H, ta, tb, M, N, K):
     assert ((out.double() - ref).abs() <= 2 * (K + 4) * U32 * mag).all()
 
 
+# the smallest products of several tiles, ragged on every side, for which the launcher takes a tile shape: per shape one for
+# both operands contraction-contiguous, one for one of each kind, one for both strided.  (The CPU suite holds this table
+# against the choice as well.)
+EVERY_SHAPE = {
+    "256x256": ((908, 14548, 200), (641, 13668, 136), (649, 18632, 131)),
+    "128x256": ((325, 16392, 264), (260, 16420, 136), (387, 16364, 1293)),
+    "128x192": ((194, 18568, 200), (194, 16388, 136), (8778, 516, 901)),
+    "128x128": ((130, 10916, 136), (130, 10916, 136), (193, 11748, 133)),
+    "128x64": ((2643, 68, 136), (5442, 132, 136), (6977, 388, 133)),
+    "64x96": ((131, 7748, 136), (129, 5444, 136), (8934, 264, 525)),
+    "64x64": ((66, 68, 136), (66, 68, 136), (66, 68, 131)),
+    "64x64k2": ((66, 68, 328), (66, 4452, 136), (66, 5076, 131)),
+    "128x64k2": ((8217, 100, 2904), (129, 8180, 392), (193, 8104, 325)),
+    "64x96k2": ((66, 8344, 1160), (131, 7596, 136), (5335, 264, 131)),
+    "128x128x2": (None, None, (195, 16484, 131)),
+}
+SHAPE_CASES = [(shape, layout, *dims[i]) for shape, dims in EVERY_SHAPE.items()
+               for layout, i in (("nt", 0), ("nn", 1), ("tt", 1), ("tn", 2)) if dims[i]]
+# a single, partly empty row or column of tiles
+SHAPE_CASES += [("256x256", "nt", 200, 58084, 216), ("256x256", "nt", 58084, 200, 216), ("256x256", "nn", 200, 45660, 72),
+                ("256x256", "tn", 200, 44395, 67), ("128x256", "nt", 100, 49156, 272), ("128x192", "nt", 100, 34580, 264),
+                ("128x128", "nt", 100, 16504, 72)]
+
+
+@pytest.mark.parametrize("shape,layout,M,N,K", SHAPE_CASES)
+def test_gemm_bf16_every_tile_shape(H, shape, layout, M, N, K):
+    ta, tb = layout[0] == "t", layout[1] == "n"
+    r8 = lambda n: (n + 7) // 8 * 8
+    A, B, bias, resid = randn(M + K, M, K).bfloat16(), randn(N + K + 1, K, N).bfloat16(), randn(N, N), randn(M + N + 2, M, N + 1)
+    As, Bs = A.t().contiguous() if ta else A, B if tb else B.t().contiguous()
+    dA, dB = stored(As, r8(As.shape[1]), 0), stored(Bs, r8(Bs.shape[1]) + 8, 0)
+    prod, mag = A.double() @ B.double(), A.double().abs() @ B.double().abs()
+    # aligned rows: two results, nothing added; then rows off the 16-byte grid with everything a caller can add
+    out, act = torch.empty(M, N, device="cuda"), torch.empty(M, N, device="cuda").bfloat16()
+    with launched(H) as names:
+        H.hydra_op_gemm(1, ta, tb, M, N, K, 1.0, dA, dA.shape[1], dB, dB.shape[1], None, None, out, act, N)
+    assert list(names) == [f"gemm_bf16_{shape}_{layout}"], names
+    # as in test_gemm_bf16_tile_shapes
+    assert ((out.double() - prod).abs() <= 2 * (K + 4) * U32 * mag).all()
+    assert ((act.double() - prod).abs() <= 2.0 ** -8 * prod.abs() + 2 * (K + 4) * U32 * mag).all()
+    out, act = torch.full((M, N + 1), 7.0, device="cuda"), torch.full((M, N + 1), 7.0, device="cuda").bfloat16()
+    H.hydra_op_gemm(1, ta, tb, M, N, K, 0.5, dA, dA.shape[1], dB, dB.shape[1], bias, resid, out, act, N + 1)
+    prod = 0.5 * prod + bias.double() + resid[:, :N].double()
+    mag = 0.5 * mag + bias.double().abs() + resid[:, :N].double().abs()
+    assert ((out[:, :N].double() - prod).abs() <= 2 * (K + 4) * U32 * mag).all()
+    assert ((act[:, :N].double() - prod).abs() <= 2.0 ** -8 * prod.abs() + 2 * (K + 4) * U32 * mag).all()
+    assert (out[:, N:] == 7.0).all() and (act[:, N:] == 7.0).all()
+
+
+# the shapes whose wavefront groups exchange partial sums through LDS, and others, while a second stream keeps the device busy
+@pytest.mark.parametrize("shape,layout,M,N,K", [("64x64k2", "nt", 201, 2304, 768), ("128x64k2", "nn", 1100, 1608, 600),
+                                                ("64x96k2", "nt", 2048, 768, 2304), ("64x96k2", "tn", 2048, 768, 2304),
+                                                ("128x64k2", "tn", 1100, 1608, 600), ("256x256", "nt", 1024, 12288, 1024),
+                                                ("128x128x2", "tn", 1000, 6408, 1608)])
+def test_gemm_bf16_repeats_bitwise_under_concurrency(H, shape, layout, M, N, K):
+    ta, tb = layout[0] == "t", layout[1] == "n"
+    A, B = randn(M + K, *((K, (M + 7) // 8 * 8) if ta else (M, K))).bfloat16(), randn(N + K + 1, *((K, N) if tb else (N, K))).bfloat16()
+    run = lambda o, s: H.hydra_op_gemm(1, ta, tb, M, N, K, 1.0, A, A.shape[1], B, B.shape[1], None, None, o, None, N, s)
+    big, bigC = randn(5, 4096, 4096).bfloat16(), torch.empty(4096, 4096, device="cuda")
+    outs = [torch.zeros(M, N, device="cuda") for _ in range(12)]
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with launched(H) as names:
+        run(outs[0], None)
+    assert list(names) == [f"gemm_bf16_{shape}_{layout}"], names
+    for o in outs:
+        H.hydra_op_gemm(1, 0, 0, 4096, 4096, 4096, 1.0, big, 4096, big, 4096, None, None, bigC, None, 4096, s2)
+        run(o, s1)
+    torch.cuda.synchronize()
+    a, b = (A[:, :M].t() if ta else A).double(), (B if tb else B.t()).double()
+    assert ((outs[0].double() - a @ b).abs() <= 2 * (K + 4) * U32 * (a.abs() @ b.abs())).all()
+    for o in outs[1:]:
+        assert torch.equal(o, outs[0])
+
+
+# leading dimensions beyond what the single-product kernel addresses: the register-staged kernel, with two and with four
+# slices in flight and each of its tiles
+@pytest.mark.parametrize("layout,M,N,K,wide", [("nt", 70, 90, 200, "ab"), ("nt", 130, 90, 1608, "a"), ("nn", 70, 90, 1608, "a"),
+                                               ("nn", 50, 90, 1608, "a"), ("tt", 70, 90, 72, "ab"), ("tn", 70, 90, 72, "ab"),
+                                               ("tn", 5800, 5801, 70, "a"), ("tn", 70, 90, 1544, "a")])
+def test_gemm_bf16_wide_leading_dimensions(H, layout, M, N, K, wide):
+    ta, tb, W = layout[0] == "t", layout[1] == "n", 4000008
+    r8 = lambda n: (n + 7) // 8 * 8
+    A, B = randn(M + K, M, K).bfloat16(), randn(N + K + 1, K, N).bfloat16()
+    As, Bs = A.t().contiguous() if ta else A, B if tb else B.t().contiguous()
+    dA, dB = stored(As, W if "a" in wide else r8(As.shape[1]), 0), stored(Bs, W if "b" in wide else r8(Bs.shape[1]), 0)
+    out = torch.full((M, N + 1), 7.0, device="cuda")
+    with launched(H) as names:
+        H.hydra_op_gemm(1, ta, tb, M, N, K, 1.0, dA, dA.shape[1], dB, dB.shape[1], None, None, out, None, N + 1)
+    assert [n.startswith("gemm_bf16_staged") for n in names] == [True], names
+    # as in test_gemm_bf16_tile_shapes
+    assert ((out[:, :N].double() - A.double() @ B.double()).abs()
+            <= 2 * (K + 4) * U32 * (A.double().abs() @ B.double().abs())).all()
+    assert (out[:, N:] == 7.0).all()
+
+
+# the weight gradients of a block in one launch: block widths and token counts for which it takes each tile shape
+GROUP_CASES = {"256x256": (672, 7312, 8), "128x256": (160, 15760, 1368), "128x192": (160, 10896, 776), "128x128": (96, 12080, 72),
+               "128x64": (288, 4808, 200), "64x96": (96, 8712, 920), "64x64": (32, 64, 8), "64x64k2": (32, 6280, 8),
+               "128x64k2": (96, 7904, 328), "64x96k2": (96, 6352, 136), "128x128x2": (96, 12040, 8)}
+
+
+@pytest.mark.parametrize("shape", GROUP_CASES)
+def test_grouped_weight_gradients_of_every_tile_shape(H, shape):
+    """One bf16 training step of a one-block model, every gradient against the oracle."""
+    import synth_inputs as SI
+    from oracle import decoder as D
+    from paper_2110_08633_amd import runtime as R
+    from tests.parity_utils import assert_close
+    d, F, M = GROUP_CASES[shape]
+    cfg = SI.small_cfg(L=1, d=d, H=d // 32, F=F, V=64, T=8, B=M // 8, dtype="bf16")
+    W = SI.make_weights(cfg, 3)
+    tok, tgt = SI.make_batch(cfg, 5)
+    P = D.cast_params(W, np.float64)
+    ref = D.train_step(P, D.zeros_like_params(P), D.zeros_like_params(P), tok, tgt, cfg, 1e-3, 1)
+    sess = R.Session(R.arena_bytes_for([cfg], 3), max_slots=2, flags=H.FLAG_TIMING)
+    got = sess.train_step_manual(sess.add_model(cfg, W, 1e-3), tok, tgt)
+    H.hydra_sync(sess.ctx)
+    names = {k["name"]: k["launches"] for k in H.hydra_kernel_stats(sess.ctx)}
+    sess.close()
+    assert names.get(f"gemm_bf16_{shape}_tn_group") == 1, names
+    for n, g in ref["grads"].items():
+        assert_close(got["grads"][n], g, 2e-2, n)  # the suite's tolerance of the bf16 path
+
+
 # a contraction of one slice or less: which of the two kernels takes it depends on layout, tiles and rows; M, N, K, layout,
 # extra leading dimension of the result, whether the register-staged kernel is expected
-ONE_SLICE = [(1000, 1000, 64, "nt", 0, True), (8, 768, 40, "nt", 0, True), (8, 768, 64, "nt", 1, False),
+ONE_SLICE = [(512, 512, 64, "nt", 0, True), (1000, 1000, 64, "nt", 0, True), (8, 768, 40, "nt", 0, True), (8, 768, 64, "nt", 1, False),
              (1000, 1001, 64, "nt", 0, False), (2049, 4100, 8, "nn", 0, True), (1000, 1000, 64, "nn", 0, False),
              (1024, 4096, 64, "tn", 0, True), (1601, 6400, 40, "tt", 0, True), (768, 2304, 64, "tn", 0, False),
              (1024, 4096, 65, "tn", 0, False), (1000, 1000, 72, "nt", 0, False), (4099, 1003, 24, "tn", 0, False)]
@@ -200,6 +324,22 @@ def test_attention_variants(H, B, Hn, T, dh, peak):
     for j in range(3):
         g, r = dqkv[:-1, j * d:(j + 1) * d].double(), x.grad[:, j * d:(j + 1) * d]
         assert (g - r).norm() <= 2.0 ** -7 * r.norm() + 1e-12
+    # and element by element on the scale of what was added (a late key's gradient is a thousandth of the tensor's norm):
+    # p and dS are rounded to 8 bits, dS = p (dP - D) / sqrt(dh) carries the error of D's input o, the result is rounded
+    # once more; 2^-11 for fp32 sums and exponentials on either side
+    heads = lambda t: t.reshape(B, T, Hn, dh).transpose(1, 2)
+    q, k, v, p, g_o = q.detach(), k.detach(), v.detach(), p.detach(), heads(d_o.double())
+    dP, D = g_o @ v.transpose(2, 3).contiguous(), (g_o * heads(ref)).sum(-1, keepdim=True)
+    d_err = (g_o.abs() * heads(2.0 ** -8 * ref.abs() + (2.0 ** -8 + 2.0 ** -12) * mag)).sum(-1, keepdim=True)
+    fp32 = 2.0 ** -11 * (g_o.abs() @ v.abs().transpose(2, 3).contiguous() + (g_o * heads(ref)).abs().sum(-1, keepdim=True))
+    ds_err = p * (2.0 ** -8 * (dP - D).abs() + d_err + fp32) / dh ** 0.5
+    bounds = (ds_err @ k.abs(), ds_err.transpose(2, 3).contiguous() @ q.abs(),
+              (2.0 ** -8 + 2.0 ** -11) * (p.transpose(2, 3).contiguous() @ g_o.abs()))
+    for j, b in enumerate(bounds):
+        g, r = heads(dqkv[:-1, j * d:(j + 1) * d].double()), heads(x.grad[:, j * d:(j + 1) * d])
+        assert ((g - r).abs() <= 2.0 ** -8 * r.abs() + b).all(), "qkv"[j]
+        last = slice((T - 1) // 32 * 32, T)  # what a wavefront owns of the end of the sequence would fail as zeros
+        assert (r.abs() > 2.0 ** -8 * r.abs() + b)[:, :, last].any(), "qkv"[j]
 
 
 def test_attention_more_blocks_than_a_row_of_the_grid_holds(H):

@@ -219,13 +219,13 @@ def test_single_slice_gemm_under_concurrency(H):
         assert_close(o.cpu().numpy(), ref, 1e-5, "single-slice gemm")
 
 
-# products large enough for each tile shape the launcher picks for contraction-contiguous operands (256x256,
-# 256x128 with eight wavefronts, 128x128, 128x64 in both pipeline depths), with and without ragged edges
+# full-size products of contraction-contiguous operands, with and without ragged edges (every tile shape by name:
+# test_gemm_bf16_every_tile_shape)
 LARGE_NT = [(1024, 12288, 1024), (1000, 12200, 512), (2048, 4096, 1024), (2000, 4100, 1024), (1024, 4096, 4096),
             (1000, 4000, 2048), (2048, 2304, 768), (2048, 768, 2304), (1100, 3000, 192),
-            # a single, partly empty row of tiles: 256x128 (40 rows), 128x128 (100 rows), 256x256 (200 rows)
+            # a few partly empty rows of tiles
             (40, 26000, 128), (100, 30000, 2048), (200, 50000, 256),
-            # and a single, partly empty column of tiles
+            # and columns of tiles
             (52000, 120, 128), (30000, 100, 2048), (50000, 200, 256)]
 
 
@@ -287,8 +287,9 @@ def test_weight_gradient_products_every_element(H, M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(2048, 4096, 1024), (1024, 4096, 4096), (2048, 2304, 768)])
 def test_large_tile_gemms_repeat_bitwise_under_concurrency(H, M, N, K):
-    """The tiles whose wavefront groups exchange partial sums through LDS (and the other direct-to-LDS tiles) while a
-    second stream keeps the device busy: every repetition must give the same bits, and sampled rows the oracle's."""
+    """Large tiles, operands straight to LDS, while a second stream keeps the device busy: every repetition must give the
+    same bits, and sampled rows the oracle's.  (Tiles whose wavefront groups exchange partial sums through LDS:
+    test_gemm_bf16_repeats_bitwise_under_concurrency.)"""
     rng = np.random.default_rng(M + N + K)
     A = bf16_round(rng.standard_normal((M, K)).astype(np.float32))
     Bt = bf16_round(rng.standard_normal((N, K)).astype(np.float32))

@@ -449,3 +449,14 @@ def test_tile_shape_of_the_largest_results(tile_shape, ta, tb, K, vec_rows):
     M = N = 270000
     _, bm, bn, threads = tile_shape(M, N, K, ta, tb, vec_rows)
     assert -(-M // bm) * -(-N // bn) * threads < 2 ** 32
+
+
+def test_gemm_cases_take_the_tile_shapes_they_name(tile_shape):
+    """The products that the GPU suite runs for each tile shape still select it (a refit of the cost constants can change
+    that)."""
+    from tests import test_gpu_kernel_variants as V
+    order = list(V.EVERY_SHAPE)
+    for shape, layout, M, N, K in V.SHAPE_CASES:
+        assert order[tile_shape(M, N, K, int(layout[0] == "t"), int(layout[1] == "n"), N % 4 == 0)[0]] == shape, (shape, layout, M, N, K)
+    assert {(c[0], c[1]) for c in V.SHAPE_CASES} == {(s, l) for s in order for l in ("nt", "nn", "tt", "tn")} - {
+        ("128x128x2", l) for l in ("nt", "nn", "tt")}
