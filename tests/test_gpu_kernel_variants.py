@@ -215,15 +215,13 @@ GROUP_CASES = {"256x256": (672, 7312, 8), "128x256": (160, 15760, 1368), "128x19
                "128x64k2": (96, 7904, 328), "64x96k2": (96, 6352, 136), "128x128x2": (96, 12040, 8)}
 
 
-@pytest.mark.parametrize("shape", GROUP_CASES)
-def test_grouped_weight_gradients_of_every_tile_shape(H, shape):
-    """One bf16 training step of a one-block model, every gradient against the oracle."""
+def one_block_step(H, d, F, M):
+    """One bf16 training step of a one-block model: every gradient against the oracle; returns the launches per kernel name."""
     import synth_inputs as SI
     from oracle import decoder as D
     from paper_2110_08633_amd import runtime as R
     from tests.parity_utils import assert_close
-    d, F, M = GROUP_CASES[shape]
-    cfg = SI.small_cfg(L=1, d=d, H=d // 32, F=F, V=64, T=8, B=M // 8, dtype="bf16")
+    cfg = SI.small_cfg(L=1, d=d, H=d // 8, F=F, V=64, T=8, B=M // 8, dtype="bf16")
     W = SI.make_weights(cfg, 3)
     tok, tgt = SI.make_batch(cfg, 5)
     P = D.cast_params(W, np.float64)
@@ -233,9 +231,23 @@ def test_grouped_weight_gradients_of_every_tile_shape(H, shape):
     H.hydra_sync(sess.ctx)
     names = {k["name"]: k["launches"] for k in H.hydra_kernel_stats(sess.ctx)}
     sess.close()
-    assert names.get(f"gemm_bf16_{shape}_tn_group") == 1, names
     for n, g in ref["grads"].items():
         assert_close(got["grads"][n], g, 2e-2, n)  # the suite's tolerance of the bf16 path
+    return names
+
+
+@pytest.mark.parametrize("shape", GROUP_CASES)
+def test_grouped_weight_gradients_of_every_tile_shape(H, shape):
+    assert one_block_step(H, *GROUP_CASES[shape]).get(f"gemm_bf16_{shape}_tn_group") == 1
+
+
+# the MLP's products with GELU and its derivative in their write-out: width, hidden width and tokens for which both take a
+# tile shape
+@pytest.mark.parametrize("shape,d,F,M", [("256x256", 200, 4744, 2960), ("128x256", 264, 3512, 1736), ("128x192", 264, 3600, 1048),
+                                         ("128x128", 72, 1224, 1552), ("128x64", 72, 72, 136), ("64x96", 72, 10896, 136),
+                                         ("64x64", 136, 72, 72), ("64x64k2", 72, 456, 1544), ("64x96k2", 1160, 2736, 328)])
+def test_gelu_epilogues_of_the_tile_shapes(H, shape, d, F, M):
+    assert one_block_step(H, d, F, M).get(f"gemm_bf16_{shape}_nt", 0) >= 2  # forward and backward
 
 
 # a contraction of one slice or less: which of the two kernels takes it depends on layout, tiles and rows; M, N, K, layout,
