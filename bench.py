@@ -17,7 +17,8 @@ pass over the same work in the SAME mode (spilled, two lanes) with every launch 
 stream - where every byte of state crosses the host link twice per step that is the write-back copy kernel, bound
 by the link; `roofline_mfma` is the matrix kernel with the largest share of the same pass.  The other BASELINE
 workloads (configs 2-4) follow as objects of their own, and `cpu_baseline` times the CPU oracle on a bounded
-sample of the headline workload.
+sample of the headline workload.  The line carries the figures (a few kilobytes, so that a log's tail holds all of
+it); the full report - every kernel, transfer and overlap figure of every workload - goes to stderr before it.
 """
 import argparse
 import json
@@ -344,6 +345,43 @@ def workload_text(name, cfg, n_models, wl, host):
             + "; weights: a seeded N(0,0.02) block tiled, LayerNorm gains 1, biases 0; uniform tokens")
 
 
+def stdout_line(out):
+    """The report without its tables: what main() prints on stdout."""
+    pick = lambda d, *keys: {k: d[k] for k in keys if d and k in d}
+    overlap = ("transfer_busy_ms_per_step", "kernel_busy_ms_per_step", "transfer_hidden_frac", "tasks_in_flight_frac_of_transfer")
+    link = ("both_directions_GBps_over_wall", "frac_of_link_cap")
+    roof = ("bound", "achieved", "peak", "unit", "frac", "traffic", "kernel", "launches", "avg_us")
+
+    def workload(w):
+        b = pick(w, "value", "unit", "steps", "warmup", "ms_per_step", "tokens_per_step", "shard_buffers")
+        b.update(link=pick(w.get("link"), *link), overlap=pick(w.get("overlap"), *overlap))
+        if "kernel_pass" in w:
+            kp = w["kernel_pass"]
+            b["kernel_pass"] = dict(pick(kp, "ms_per_step", "gemm_aggregate"), overlap=pick(kp.get("overlap"), *overlap))
+        if "kernels_alone" in w:
+            b["kernels_alone"] = pick(w["kernels_alone"], "ms_per_step", "gemm_aggregate")
+        for k in ("resident", "spill_micro4", "spill_micro8"):
+            if k in w:
+                b[k] = pick(w[k], "value", "unit", "ms_per_step")
+        return b
+
+    line = {}
+    for k, v in out.items():
+        if k in ("roofline", "roofline_mfma"):
+            line[k] = pick(v, *roof)
+        elif k in ("kernels_alone", "kernel_pass"):
+            line[k] = workload(out)[k]
+        elif k in WORKLOADS:
+            line[k] = workload(v)
+        elif k == "link":
+            line[k] = pick(v, "h2d_GB_per_step", "d2h_GB_per_step", *link)
+        elif k == "overlap":
+            line[k] = pick(v, *overlap)
+        elif k != "kernels":
+            line[k] = v
+    return line
+
+
 def bench_workload(name, steps, warmup, timing_steps, R, H, torch, n_models=0, layers=0, lanes=2, extra_flags=0,
                    micro=1):
     """One BASELINE workload as stated: spilled run (value), then the same mode with every kernel bracketed."""
@@ -588,7 +626,8 @@ def main():
         out["block_gemm_large_shapes"] = block_gemm_large_shapes(H, torch)
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(cpu_cfg)
-    print(json.dumps(out))
+    log("full report: " + json.dumps(out))
+    print(json.dumps(stdout_line(out)), flush=True)
 
 
 if __name__ == "__main__":

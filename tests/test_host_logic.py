@@ -460,3 +460,40 @@ def test_gemm_cases_take_the_tile_shapes_they_name(tile_shape):
         assert order[tile_shape(M, N, K, int(layout[0] == "t"), int(layout[1] == "n"), N % 4 == 0)[0]] == shape, (shape, layout, M, N, K)
     assert {(c[0], c[1]) for c in V.SHAPE_CASES} == {(s, l) for s in order for l in ("nt", "nn", "tt", "tn")} - {
         ("128x128x2", l) for l in ("nt", "nn", "tt")}
+
+
+def test_bench_line_fits_a_log_tail():
+    """bench.py's stdout line: the contract's keys and every workload's headline figures in a few kilobytes, however long
+    the kernel tables of the full report are."""
+    import json
+
+    import bench as B
+    run = dict(seconds=2.0, steps=3, h2d=10 ** 12, d2h=10 ** 12, host=dict.fromkeys(
+        ("host_promote_ms", "host_writeback_ms", "host_task_ms", "host_batch_ms"), 1234.567),
+        overlap=dict(n_intervals=9, transfer_ms=5000.1, h2d_ms=4000.2, d2h_ms=4000.3, compute_ms=3000.4, hidden_ms=2000.5,
+                     bytes_h2d=10 ** 12, bytes_d2h=10 ** 12, kernel_ms=1000.6, hidden_kernel_ms=900.7),
+        kernels=[dict(name=f"gemm_bf16_kernel_with_a_long_name_{i}", launches=12345, ms=100.0 + i, flops=1e13, bytes=0.0) for i in range(40)])
+    report = B.kernel_report(run)
+    parts = dict(link=B.link_report(run), overlap=B.overlap_report(run))
+    kernel_pass = dict(report, steps=2, ms_per_step=1234.567, overlap=parts["overlap"])
+    alone = dict(report, what="x" * 80, ms_per_step=1234.567)
+    head = dict(value=12345.6, unit="tokens/s", steps=20, warmup=5, ms_per_step=1234.567)
+    w = dict(head, workload="w" * 600, tokens_per_step=4096, shard_buffers=8, kernel_pass=kernel_pass, kernels_alone=alone, **parts)
+    extra = dict(resident=head, spill_micro4=dict(head, **parts), spill_micro8=dict(head, **parts),
+                 pilot_costs_us=dict(forward=[1234.5] * 30, backward_with_adam=[1234.5] * 30))
+    out = dict(head, metric="m" * 60, n_gpus=1, higher_is_better=True, scaling="weak", vs_baseline=None, dtype="bf16",
+               data="synthetic", config=dict(workload="w" * 600, mode="spill"), final_losses=[10.0] * 2,
+               roofline=report["roofline"], roofline_mfma=report["roofline_mfma"], gemm_aggregate=report["gemm_aggregate"],
+               kernels_alone=alone, kernel_pass=kernel_pass, kernels=report["kernels"], gpt2s=dict(w, **extra), gpt2m=w, gpt2xl=w,
+               block_gemm_large_shapes={n: dict(MxNxK="1024x16384x4096", us=123.4, TFLOPs=1234.5, frac_of_mfma_peak=0.1234)
+                                        for n in ("qkv", "mlp_up", "mlp_down")},
+               cpu_baseline=dict(value=1.0, unit="tokens/s", cores=16, kind="oracle", sample="s" * 300), **parts)
+    line = json.dumps(B.stdout_line(out))
+    assert len(json.dumps(out)) > 30000 and len(line) < 6500, len(line)
+    got = json.loads(line)
+    for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+              "vs_baseline", "dtype", "data", "config", "cpu_baseline", "gemm_aggregate"):
+        assert got[k] == out[k], k
+    assert got["roofline"]["frac"] == report["roofline"]["frac"] and got["roofline_mfma"]["kernel"] == report["roofline_mfma"]["kernel"]
+    assert all(got[n]["value"] == 12345.6 for n in ("gpt2s", "gpt2m", "gpt2xl"))
+    assert got["overlap"]["transfer_hidden_frac"] == parts["overlap"]["transfer_hidden_frac"]
