@@ -377,7 +377,10 @@ hydra_status hydra_pilot_costs(hydra_ctx *ctx, int32_t model, const int32_t *tok
 /* C[M,N] = alpha * op(A) * op(B) (+ bias[N]) (+ resid[M,N]); ta = 0: A is [M,K]
  * row-major, 1: A is [K,M]; tb = 0: B is [N,K] row-major, 1: B is [K,N].
  * out_f32 / out_act (operand dtype) may each be NULL. Leading dimensions in
- * elements. */
+ * elements.  bf16: A and B 16-byte aligned with leading dimensions that are
+ * multiples of 8 (HYDRA_E_HIP otherwise); where K is no multiple of 8, the
+ * elements between K and the next multiple in the rows of an operand stored
+ * with contiguous k are read and must be zero. */
 hydra_status hydra_op_gemm(int32_t dtype, int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K,
                            float alpha, const void *A, int64_t lda, const void *B, int64_t ldb,
                            const float *bias, const float *resid, float *out_f32, void *out_act,

@@ -153,8 +153,8 @@ __device__ __forceinline__ bool block_place(int pairs, int nb, int &z, int &rb) 
 // tiles g, g + KW, ... and the partial results are merged through LDS at the end
 // (launches that would leave CUs without work).
 // Bound: per tile and wavefront 1024 clocks of MFMAs at head width 128 (512 at 64) and 960 of vector ALU, which overlap
-// only between the two or more wavefronts of a SIMD; counters at B 4, H 16, T 2048, dh 128: matrix pipes 0.40 busy,
-// vector ALU 0.43, LDS 0.20.  That launch: 255 us with one wavefront per SIMD, register-staged tiles and probabilities
+// only between the two or more wavefronts of a SIMD; counters at B 4, H 16, T 2048, dh 128: matrix pipes 0.43 busy,
+// vector ALU 0.41, LDS 0.22.  That launch: 255 us with one wavefront per SIMD, register-staged tiles and probabilities
 // through LDS; 103 us without these; 79 us with the long blocks first.  Measured without gain: tiles two and three
 // ahead, raised wavefront priority around the MFMAs, MFMAs and exponentials interleaved by scheduling directives (spills).
 // ---------------------------------------------------------------------------
@@ -524,7 +524,8 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
     const float *const ls = Ls + ((it & 1) * KW + grp) * 128;
     if (i0 + AK - 1 >= kr0 && i0 < T) {  // else no query of the tile comes after a key of this wavefront
       // one half tile at a time: unrolled, the two halves' results do not fit the 256 registers two wavefronts per SIMD
-      // leave at head width 128 (the two backward kernels at B 4, H 16, T 2048, dh 128: 289 -> 270 us)
+      // leave at head width 128 (the two backward kernels at B 4, H 16, T 2048, dh 128: 289 -> 270 us).  Even so one to
+      // three registers are spilled there (8 to 16 bytes of scratch per lane); at head width 64 none
 #pragma unroll 1
       for (int nt = 0; nt < 2; ++nt) {
         f32x16_t s, dp;

@@ -1,6 +1,6 @@
-// GEMM kernels for gfx950: bf16 MFMA (LDS-tiled, fp32 accumulate) and an fp32 MFMA
-// kernel, both with the same fused epilogues (bias, residual, GELU,
-// GELU', scale) and the same causal short-cuts for attention operands.
+// GEMM kernels for gfx950: register-staged bf16 MFMA (batched and causal products, and the single ones that
+// gemm_plain.hip leaves) and fp32 MFMA, both with the same fused epilogues (bias, residual, GELU, GELU', scale) and the
+// same causal short-cuts for attention operands.
 //
 // The linear layers of a block (y = x*W + b), their input gradients
 // (dx = dy*W^T) and weight gradients (dW = x^T*dy) and the batched attention
@@ -9,6 +9,21 @@
 
 namespace hydra {
 
+// ---------------------------------------------------------------------------
+// Register-staged bf16 MFMA kernel.  256 threads = 4 wavefronts arranged WM x WN
+// over a BM x BN tile of C.  K is consumed in slices of BK = 64:
+//   global -> registers : 16-byte loads, issued D slices ahead
+//   registers -> LDS    : one slice ahead, two LDS buffers, one barrier per slice
+//   LDS -> MFMA operands: ds_read_b128 for operands whose contraction index is
+//                         contiguous in memory, ds_read_tr16_b64 (transposing
+//                         read) for operands stored with it strided, so both
+//                         kinds sit in LDS exactly as they sit in memory
+// LDS tiles carry no padding; their 16-byte chunks are XOR-swizzled so that the
+// operand reads of 16 neighbouring lanes fall into distinct banks.
+// The MFMA is issued with the B fragment as first operand, which leaves every
+// lane with runs of 4 consecutive columns of one row of C: the epilogue then
+// stores 16-byte (fp32) or 8-byte (bf16) vectors.
+// ---------------------------------------------------------------------------
 // One tile of one product: g describes the product, bid is the workgroup's index among the nt workgroups that
 // work on it, z its batch index.
 template <int BM, int BN, int WM, int WN, int TA, int TB, int D>
@@ -170,7 +185,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const GemmArgs g) {
 // no reduced-precision split; each is a chain of fused multiply-adds over its
 // contraction steps in ascending order).  The instruction needs 64 clocks for 4096 flop, so
 // LDS and the load path are far from binding (a 32x32 result per wavefront
-// reads 16 bytes of LDS per clock and CU); what costs is everything that keeps
+// reads 8 bytes of LDS per clock, 32 on a CU's four SIMDs); what costs is everything that keeps
 // the matrix pipes waiting: too few tiles for 256 CUs and trips to memory.
 // Hence small tiles, operands requested two slices ahead (16-byte loads into
 // registers where alignment allows), two LDS buffers and one barrier per slice.

@@ -81,21 +81,6 @@ __device__ __forceinline__ void epilogue_store(const GemmArgs &g, int64_t coff, 
   if (g.out_act) st_act<ActT>(g.out_act, idx, v);
 }
 
-// ---------------------------------------------------------------------------
-// bf16 MFMA kernel.  256 threads = 4 wavefronts arranged WM x WN over a
-// BM x BN tile of C.  K is consumed in slices of BK = 64:
-//   global -> registers : 16-byte loads, issued three slices ahead
-//   registers -> LDS    : one slice ahead, two LDS buffers, one barrier per slice
-//   LDS -> MFMA operands: ds_read_b128 for operands whose contraction index is
-//                         contiguous in memory, ds_read_tr16_b64 (transposing
-//                         read) for operands stored with it strided, so both
-//                         kinds sit in LDS exactly as they sit in memory
-// LDS tiles carry no padding; their 16-byte chunks are XOR-swizzled so that the
-// operand reads of 16 neighbouring lanes fall into distinct banks.
-// The MFMA is issued with the B fragment as first operand, which leaves every
-// lane with runs of 4 consecutive columns of one row of C: the epilogue then
-// stores 16-byte (fp32) or 8-byte (bf16) vectors.
-// ---------------------------------------------------------------------------
 // 4 consecutive columns of one row of C
 template <typename ActT>
 __device__ __forceinline__ void epilogue_store4(const GemmArgs &g, int64_t coff, int row, int col, const f32x4_t acc,

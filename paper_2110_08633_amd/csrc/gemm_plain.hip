@@ -14,32 +14,41 @@ namespace hydra {
 // bytes) and, at a few thousand rows, the 256 CUs themselves - a launch lasts as
 // long as the CU with the most tiles.  So the kernel is written for many tile
 // shapes (multiples of 16 either way) and the launcher picks the shape by those
-// three terms (tile_cost).  Per tile:
+// three terms (shape_cost).  Per tile:
 //   - WM x WN wavefronts, each (BM/WM) x (BN/WN) results; at least two
 //     wavefronts per SIMD are resident (one block of eight or several blocks of
 //     four), so that one computes while another waits;
 //   - buffer loads with the LDS flag (16 bytes per lane, lane l fills LDS base +
-//     16*l), S stages of BK contraction steps.  Rows past the matrix and steps
-//     past K are fetched from an out-of-range offset, which writes zeros: no
-//     branches, and the ragged end of K needs no code of its own;
+//     16*l), S stages of BK contraction steps.  Chunks that start past the matrix
+//     or past K are fetched from an out-of-range offset, which writes zeros: no
+//     branches, and the ragged end of K needs no code of its own.  A chunk of a
+//     contraction-contiguous operand holds eight steps: where K is no multiple of
+//     eight, its elements past K are read as they are, and the caller keeps them
+//     zero;
 //   - the only barrier of a slice sits before its last contraction step: every
 //     wavefront has read the slice by then, its stage is handed to the loads of
 //     slice t + S, and the first fragments of slice t + 1 are read while the last
 //     MFMAs of slice t run;
 //   - operands sit in LDS as in memory.  Contraction-contiguous ones are read
-//     with ds_read_b128, the others with the transposing ds_read_b64_tr_b16; the
-//     XOR swizzles below keep both free of bank conflicts (they are applied on
-//     the global side: which 16 bytes a lane fetches).
+//     with ds_read_b128, the others with the transposing ds_read_b64_tr_b16; XOR
+//     swizzles spread both over the banks (applied on the global side: which 16
+//     bytes a lane fetches).  Counted conflict cycles: 2 to 8 % of the LDS cycles
+//     with slices of 64, but half of them where contraction-contiguous operands
+//     sit in slices of 128 (16 rows there fall into 8 slots, see swz_kc).
 // Measured, us, the kernels this one replaced / now (MxNxK; n: operand contraction-contiguous, t: not):
 //   nt 201x768x2304 13.4 / 9.4, 2048x2304x768 14.7 / 12.7, 1000x3072x768 11.1 / 9.9, 1024x16384x4096 115 / 100,
 //   4096^3 116 / 104; tn 768x2304x2048 20.1 / 17.1, 3072x768x2048 28.8 / 19.0, 1600x6400x1000 41 / 34,
 //   4096x4096x1024 53 / 40, 4096^3 204 / 124; nn 2048x768x50257 437 / 272, 4096^3 188 / 111;
 //   tn 768x50257x2048 270 / 208.
+// 720 random products: 1.40 times as fast on average (nt 1.56, tn 1.22, nn 1.25), 7 of them more than 5 % slower, 0.83 at
+// worst.
+// The 256x256 shape with a contraction-strided first operand spills 5 or 6 registers (24 and 28 bytes of scratch per lane).
+// Reloads inside the loop wait for the direct-to-LDS loads in flight, which is part of why its constants are the higher ones.
 // What bounds the large ones now: with loads, LDS reads and MFMAs switched off in turn, 1024x16384x4096 takes 71 us of
 // loads alone (25 bytes per clock and CU), 73 us of MFMAs alone at the clock the chip holds for them, 100 us together.
 // ---------------------------------------------------------------------------
-// 16-byte chunk position within a line of LDS.  [row][BK]: 16 rows at one chunk index must fall into distinct slots
-// of the 256-byte bank period.  [k][R]: a read takes two neighbouring chunks of lines k..k+3 and k+8..k+11.
+// 16-byte chunk position within a line of LDS.  [row][BK]: 16 rows at one chunk index should fall into distinct slots
+// of the 256-byte bank period (at BK 128, lines of 256 bytes, they fall into 8).  [k][R]: a read takes two neighbouring chunks of lines k..k+3 and k+8..k+11.
 template <int BK_> __device__ __forceinline__ int swz_kc(int row) { return (BK_ >= 128 ? row : row >> 1) & (BK_ >= 64 ? 7 : 3); }
 template <int R> __device__ __forceinline__ int swz_rc(int k) {
   const int hi = ((k >> 3) & 1) << 1;

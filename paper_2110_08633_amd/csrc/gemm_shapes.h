@@ -19,9 +19,7 @@ struct GemmDims {
 // wavefronts alone leaves its CU half idle, so there a round is as many tiles as the CUs hold blocks.  The constants are
 // least-squares fits (weighted towards the products for which a shape is among the fastest) to 200 products of the four
 // models' widths at 201 to 4096 tokens, LM heads included: one set for operands that are both contraction-contiguous and
-// one for products that read both through the transposing LDS read; products with one of each take the middle.  The
-// cheapest shape by this estimate is within 1.1 % of the fastest one on average, and 1.35 times as fast as the kernels
-// it replaces (210 random products).
+// one for products that read both through the transposing LDS read; products with one of each take the middle.
 struct PlainShape {
   int bm, bn, occ, threads;  // tile, blocks per CU, threads per block
   float t0[2], a[2], b[2], c[2], e[2];

@@ -59,7 +59,7 @@ struct GemmDesc {
 
 hipError_t launch_gemm(const GemmDesc &g, hipStream_t s);
 // n products in one launch where they allow it (bf16, both operands stored with the contraction index strided, no
-// batching, contraction of at least 1536): the weight-gradient products of a block; otherwise one launch each
+// batching) and that is estimated to be faster: the weight-gradient products of a block; otherwise one launch each
 hipError_t launch_gemm_group(const GemmDesc *g, int n, hipStream_t s);
 
 // x0[m,:] = wte[tok[m],:] + wpe[m % T,:]
