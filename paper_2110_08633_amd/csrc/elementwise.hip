@@ -917,14 +917,34 @@ __global__ __launch_bounds__(256) void cross_entropy_kernel(const float *__restr
   }
 }
 
-// The same with the row held in registers between the passes (one block of 1024 threads per row, NV float4 per
-// thread): the logits are read once instead of twice.  Needs ld % 4 == 0, ld <= 4096 * NV and aligned pointers.
-template <typename OutT, int NV>
-__global__ __launch_bounds__(1024) void cross_entropy_row_kernel(const float *__restrict__ logits,
+// exp(x) for x <= 0 (or NaN) from the exponential instruction: x = t ln 2 + r with r exact to a few units of 2^-48, exp(x)
+// = 2^t (1 + r).  Six vector instructions where expf has twelve; largest relative error over [-80, 0] 1.4e-7, expf 0.8e-7
+// (both far below what a bf16 gradient keeps, and a sum over thousands of terms averages them); results below 2^-126 are
+// zero.  -inf gives a NaN remainder, which the minimum drops; NaN stays NaN.
+__device__ __forceinline__ float exp_nonpos(float x) {
+  const float t = x * 1.44269504088896341f;
+  float r = __builtin_fmaf(-t, 0.693147182464599609375f, x);
+  r = __builtin_fminf(__builtin_fmaf(-t, -1.904654299957768e-9f, r), 1.f);
+  const float p = __builtin_amdgcn_exp2f(t);
+  return __builtin_fmaf(p, r, p);
+}
+
+// The same with the row held in registers between the passes (one block of TB threads per row, NV float4 per thread):
+// the logits are read once instead of twice.  Needs ld % 4 == 0, ld <= 4 * TB * NV and aligned pointers.
+// Bound: HBM, and the vector ALU between the two barriers of a row (a block waits there, so what overlaps is other rows: the
+// smaller the row, the fewer threads hold it and the more rows a CU has in flight).  NT: logits that do not stay in the
+// 256 MB cache anyway are read past it, which leaves it to the gradients that the next product reads.
+// us, bf16, 2048 rows of 50257 / 30000 / 8192 / 2000 columns: 1024 threads a row, expf 152 / 95 / 21 / 13.8; now 125 / 62 /
+// 17 / 7.4 (4.9 TB/s at the first).
+// The fp32 form keeps expf: gradients that are zero but for rounding keep their bits.
+template <typename OutT, int NV, int TB, bool NT>
+__global__ __launch_bounds__(TB) void cross_entropy_row_kernel(const float *__restrict__ logits,
                                                                  const int32_t *__restrict__ targets,
                                                                  float *__restrict__ row_loss, OutT *__restrict__ dlogits,
                                                                  int V, int64_t ld, float inv_n) {
-  __shared__ float sh[16];
+  typedef __attribute__((ext_vector_type(4))) float f4;
+  constexpr int NW = TB / 64;
+  __shared__ float sh[2 * NW];
   const int row = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float *lr = logits + (int64_t)row * ld;
@@ -934,56 +954,56 @@ __global__ __launch_bounds__(1024) void cross_entropy_row_kernel(const float *__
   if (tgt < 0 || tgt >= V) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      const int q = i * 1024 + tid;
+      const int q = i * TB + tid;
       if (q < n4) st4(dr + 4 * q, 0.f, 0.f, 0.f, 0.f);
     }
     if (tid == 0) row_loss[row] = 0.f;
     return;
   }
-  float4 v[NV];
+  f4 v[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int q = i * TB + tid;
+    v[i] = f4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    if (q < n4) v[i] = NT ? __builtin_nontemporal_load((const f4 *)lr + q) : ((const f4 *)lr)[q];
+  }
   float mx = -INFINITY;
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const int q = i * 1024 + tid, c = 4 * q;
-    float4 w = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-    if (q < n4) {
-      w = *(const float4 *)(lr + c);
-      if (c + 3 >= V) {  // the pad columns V..ld-1 take no part
-        if (c + 0 >= V) w.x = -INFINITY;
-        if (c + 1 >= V) w.y = -INFINITY;
-        if (c + 2 >= V) w.z = -INFINITY;
-        w.w = -INFINITY;
-      }
+    const int c = 4 * (i * TB + tid);
+    if (c + 3 >= V) {  // the pad columns V..ld-1 take no part
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (c + e >= V) v[i][e] = -INFINITY;
     }
-    v[i] = w;
-    mx = fmaxf(fmaxf(mx, fmaxf(w.x, w.y)), fmaxf(w.z, w.w));
+    mx = fmaxf(fmaxf(mx, fmaxf(v[i][0], v[i][1])), fmaxf(v[i][2], v[i][3]));
   }
   mx = wave_max(mx);
   if (lane == 0) sh[wave] = mx;
   __syncthreads();
   float bmx = sh[0];
 #pragma unroll
-  for (int w = 1; w < 16; ++w) bmx = fmaxf(bmx, sh[w]);
-  __syncthreads();
+  for (int w = 1; w < NW; ++w) bmx = fmaxf(bmx, sh[w]);
   float sum = 0.f;
 #pragma unroll
   for (int i = 0; i < NV; ++i) {  // exp(-inf) = 0 for pad columns and unused slots
-    v[i] = make_float4(expf(v[i].x - bmx), expf(v[i].y - bmx), expf(v[i].z - bmx), expf(v[i].w - bmx));
-    sum += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[i][e] = sizeof(OutT) == 2 ? exp_nonpos(v[i][e] - bmx) : expf(v[i][e] - bmx);
+    sum += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
   }
   sum = wave_sum(sum);
-  if (lane == 0) sh[wave] = sum;
+  if (lane == 0) sh[NW + wave] = sum;
   __syncthreads();
   float bsum = 0.f;
 #pragma unroll
-  for (int w = 0; w < 16; ++w) bsum += sh[w];  // fixed order
+  for (int w = 0; w < NW; ++w) bsum += sh[NW + w];  // fixed order
   const float inv = 1.0f / bsum;
   if (tid == 0) row_loss[row] = (logf(bsum) + bmx) - lr[tgt];
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const int q = i * 1024 + tid, c = 4 * q;
+    const int q = i * TB + tid, c = 4 * q;
     if (q < n4) {
-      float4 g = make_float4(v[i].x * inv, v[i].y * inv, v[i].z * inv, v[i].w * inv);
+      float4 g = make_float4(v[i][0] * inv, v[i][1] * inv, v[i][2] * inv, v[i][3] * inv);
       if (tgt >= c && tgt < c + 4) {
         if (tgt == c) g.x -= 1.f;
         else if (tgt == c + 1) g.y -= 1.f;
@@ -999,16 +1019,37 @@ template <typename OutT>
 static bool launch_ce_row(const float *logits, const int32_t *targets, float *row_loss, OutT *dlogits, int M, int V,
                           int64_t ld, float inv_n, hipStream_t s) {
   if ((ld & 3) || ld > 4096 * 16 || (((uintptr_t)logits) & 15) || (((uintptr_t)dlogits) & 15)) return false;
-  const int nv = (int)((ld / 4 + 1023) / 1024);
-#define HYDRA_CE(NV_)                                                                                          \
-  hipLaunchKernelGGL((cross_entropy_row_kernel<OutT, NV_>), dim3(M), dim3(1024), 0, s, logits, targets, row_loss, \
+#define HYDRA_CE(NV_, TB_, NT_)                                                                                       \
+  hipLaunchKernelGGL((cross_entropy_row_kernel<OutT, NV_, TB_, NT_>), dim3(M), dim3(TB_), 0, s, logits, targets, row_loss, \
                      dlogits, V, ld, inv_n)
-  if (nv <= 1) HYDRA_CE(1);
-  else if (nv <= 2) HYDRA_CE(2);
-  else if (nv <= 4) HYDRA_CE(4);
-  else if (nv <= 8) HYDRA_CE(8);
-  else if (nv <= 13) HYDRA_CE(13);
-  else HYDRA_CE(16);
+#define HYDRA_CE_NT(NV_, TB_)            \
+  do {                                   \
+    if (nt) HYDRA_CE(NV_, TB_, true);    \
+    else HYDRA_CE(NV_, TB_, false);      \
+  } while (0)
+  if constexpr (sizeof(OutT) == 2) {
+    // us, 2048 rows, read through / past the cache: 8192 columns (67 MB of logits) 17.2 / 18.8, 16384 (134 MB) 33.7 / 34.6,
+    // 30000 (246 MB) 70 / 62, 50257 (412 MB) 134 / 125.  Threads: 30000 columns 102 with 1024, 70 with 512; 16384 the same
+    // with 512 and 256; 50257 with 512 (25 vectors per thread, 144 registers) 131
+    const bool nt = (double)M * (double)ld * 4.0 >= 192e6;
+    if (ld <= 1024) HYDRA_CE(1, 256, false);
+    else if (ld <= 2048) HYDRA_CE(2, 256, false);
+    else if (ld <= 4096) HYDRA_CE_NT(4, 256);
+    else if (ld <= 8192) HYDRA_CE_NT(8, 256);
+    else if (ld <= 16384) HYDRA_CE_NT(8, 512);
+    else if (ld <= 32768) HYDRA_CE_NT(16, 512);
+    else if (ld <= 13 * 4096) HYDRA_CE_NT(13, 1024);
+    else HYDRA_CE_NT(16, 1024);
+  } else {
+    const int nv = (int)((ld / 4 + 1023) / 1024);
+    if (nv <= 1) HYDRA_CE(1, 1024, false);
+    else if (nv <= 2) HYDRA_CE(2, 1024, false);
+    else if (nv <= 4) HYDRA_CE(4, 1024, false);
+    else if (nv <= 8) HYDRA_CE(8, 1024, false);
+    else if (nv <= 13) HYDRA_CE(13, 1024, false);
+    else HYDRA_CE(16, 1024, false);
+  }
+#undef HYDRA_CE_NT
 #undef HYDRA_CE
   return true;
 }

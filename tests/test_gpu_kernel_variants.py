@@ -472,3 +472,42 @@ def test_layernorm_bwd_more_blocks_than_a_row_of_the_grid_holds(H):
     for got, v in zip(cols, (dy * xh, dy, dx[:-1])):
         # eight rows in fp32, the rest in 64 bits; xhat itself carries three roundings on either side
         assert ((got.double() - v.sum(0, dtype=torch.float64)).abs() <= 20 * U32 * v.abs().sum(0, dtype=torch.float64)).all()
+
+
+# bf16 cross-entropy: rows, columns, leading dimension.  256 threads hold a row of up to 8192 columns, 512 up to 32768, 1024
+# up to 65536; from 192 MB of logits on they are read past the cache
+@pytest.mark.parametrize("M,V,ld", [(3, 1, 4), (5, 1021, 1024), (5, 1025, 1028), (5, 2049, 2052), (5, 4097, 4100), (5, 8193, 8196),
+                                    (5, 16385, 16388), (5, 32769, 32772), (5, 53249, 53252), (5, 65536, 65536),
+                                    (12100, 3999, 4096), (5900, 8190, 8192), (2940, 16384, 16384), (1470, 32760, 32768),
+                                    (910, 53240, 53248), (740, 65000, 65024)])
+def test_cross_entropy_rows(H, M, V, ld):
+    z = stored(randn(V, M, V) * 2, ld, 0)
+    tgt = torch.randint(0, V, (M,), device="cuda", dtype=torch.int32)
+    tgt[-1] = -1
+    if V > 4:
+        tgt[0], tgt[1] = 3, V - 1
+        z[0, 4] = z[0, V - 1] = -float("inf")
+        z[2, V // 2] = float("nan")
+    row, dl = torch.full((M,), 7.0, device="cuda"), torch.full((M, ld), 7.0, device="cuda").bfloat16()
+    H.hydra_op_cross_entropy(1, z, tgt, row, dl, M, V, ld, 0.25)
+    if V > 4:
+        assert torch.isnan(row[2]) and torch.isnan(dl[2, :V]).all()
+        z[2] = 0.0
+        row[2] = float(np.log(V))
+    keep = (tgt >= 0).nonzero()[:, 0]
+    for r in range(0, len(keep), 256):  # some rows at a time: 64-bit copies of all would be large
+        i = keep[r:r + 256]
+        x, t = z[i, :V].double(), tgt[i].long()[:, None]
+        lse = torch.logsumexp(x, 1, keepdim=True)
+        p = torch.exp(x - lse)
+        one = torch.zeros_like(p).scatter_(1, t, 1.0)
+        ref, got = 0.25 * (p - one), dl[i, :V].double()
+        # half a unit of 8 bits of the result; 2^-20 of what is subtracted: exponential (two units of 24 bits), the sum (a few,
+        # its terms are added in a tree), reciprocal and two products, with a factor of two in reserve
+        ok = (got - ref).abs() <= 2.0 ** -8 * ref.abs() + 0.25 * 2.0 ** -20 * (p + one)
+        assert (ok | (i == 2)[:, None]).all() if V > 4 else ok.all()
+        loss = (lse - x.gather(1, t))[:, 0]
+        assert ((row[i].double() - loss).abs() <= 2.0 ** -20 * (1 + lse[:, 0].abs() + x.abs().nan_to_num(posinf=0).amax(1))).all()
+    if V > 4:
+        dl[2] = 0.0  # (the pad of a row with a NaN is NaN too)
+    assert (dl[keep][:, V:] == 0).all() and (dl[-1] == 0).all() and row[-1] == 0
