@@ -15,14 +15,15 @@
 // registers they are computed in.
 #include <cfloat>
 
+#include "attn_forms.h"
 #include "gemm_common.h"
 
 namespace hydra {
 
 namespace {
 
-constexpr int AQ = 128;  // rows (queries, or keys in the dK/dV kernel) per block and wavefront group, 32 per wavefront
-constexpr int AK = 64;   // rows of a tile that is walked over (keys, or queries in the dK/dV kernel)
+// A block: KW groups of RW wavefronts.  It owns 32 * RW rows (queries, or keys in the dK/dV kernel), 32 per wavefront of a
+// group, and walks over tiles of TK rows (keys, or queries in the dK/dV kernel), which its groups share out.
 constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
 
 // value of the lane 32 away and the lane's own, in either order
@@ -51,18 +52,20 @@ __device__ __forceinline__ bf16x8_t row_operand(const float (&p)[16], int s) {
   return x.f;
 }
 
-// A [64 rows][DH] bf16 tile of a row-major matrix in LDS: DH/64 slices [row][64] whose 16-byte chunks are swizzled so
+// A [TK rows][DH] bf16 tile of a row-major matrix in LDS, loaded by RW wavefronts: DH/64 slices [row][64] whose 16-byte chunks are swizzled so
 // that both ways of reading it are free of bank conflicts - as operand of a product over the head dimension (16 bytes
 // per lane: rows of one parity need distinct slots) and, through the transposing read, of a product over the rows (32
 // bytes of rows k..k+3 each, two column groups at a time).  One copy serves both.
-template <int DH>
+template <int DH, int RW, int TK>
 struct RowTile {
-  static constexpr int SIZE = AK * DH;            // elements
-  static constexpr int N = SIZE / 8 / 256;        // 16-byte loads per lane for four wavefronts
-  int off, row;  // byte offset and row of this lane's first chunk; the others are 32 rows and 64 columns further on
+  static constexpr int SIZE = TK * DH;            // elements
+  static constexpr int N = SIZE / 8 / (64 * RW);  // 16-byte loads per lane
+  static constexpr int RP = 8 * RW, PS = TK / RP;  // rows per load, loads per slice
+  static_assert(PS * RP == TK && N == PS * DH / 64, "whole loads");
+  int off, row;  // byte offset and row of this lane's first chunk; the others are RP rows and 64 columns further on
   int64_t ld;
   static __device__ __forceinline__ int swz(int r) { return ((r >> 1) & 1) << 2 | ((r >> 2) & 1) << 1 | ((r >> 3) & 1); }
-  __device__ __forceinline__ void init(int64_t ld_, int tid) {  // tid within the four wavefronts
+  __device__ __forceinline__ void init(int64_t ld_, int tid) {  // tid within the RW wavefronts
     ld = ld_;
     row = tid >> 3;
     off = (int)((row * ld + ((tid & 7) ^ swz(row)) * 8) * 2);
@@ -71,44 +74,46 @@ struct RowTile {
   // DIRECT: straight to LDS, which wants aligned addresses; else through registers, whose loads take any
   template <bool DIRECT>
   __device__ __forceinline__ void load(const bf16_t *base, int valid, uint32_t lds, int wave) const {
-    const int o0 = row < valid ? off : BUF_OUT, o1 = row + 32 < valid ? off : BUF_OUT;
+    int o[PS];
+#pragma unroll
+    for (int i = 0; i < PS; ++i) o[i] = row + i * RP < valid ? off : BUF_OUT;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const bf16_t *const b = base + (i & 1) * 32 * ld + (i >> 1) * 64;
-      const int o = i & 1 ? o1 : o0;
-      const uint32_t dst = lds + (i * 256 + wave * 64) * 16;
+      const bf16_t *const b = base + (i % PS) * RP * ld + (i / PS) * 64;
+      const uint32_t dst = lds + (i * 64 * RW + wave * 64) * 16;
       if constexpr (DIRECT) {
-        load_to_lds(b, o, dst);
+        load_to_lds(b, o[i % PS], dst);
       } else {
         u32x4_t v = {0u, 0u, 0u, 0u};
-        if (o != BUF_OUT) v = *(gvec_ptr)((const char *)b + o);
+        if (o[i % PS] != BUF_OUT) v = *(gvec_ptr)((const char *)b + o[i % PS]);
         *(__attribute__((address_space(3))) u32x4_t *)(uintptr_t)(dst + (threadIdx.x & 63) * 16) = v;
       }
     }
   }
 };
-template <int DH>
+// a wavefront's operand fragments of such a tile
+template <typename TILE, int TK>
 struct RowFrag {
   int kc[4], t0[2], t1[2];
   __device__ __forceinline__ void init(int lane) {
     const int r = lane & 31, hi = lane >> 5;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) kc[kk] = r * 64 + ((kk * 2 + hi) ^ RowTile<DH>::swz(r)) * 8;
+    for (int kk = 0; kk < 4; ++kk) kc[kk] = r * 64 + ((kk * 2 + hi) ^ TILE::swz(r)) * 8;
     const int G = lane >> 4, sl = lane & 15, k = 4 * hi + (sl >> 2);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const int m = q * 32 + 16 * (G & 1) + 4 * (sl & 3);
-      t0[q] = k * 64 + ((m >> 3) ^ RowTile<DH>::swz(k)) * 8 + ((m >> 2) & 1) * 4;
-      t1[q] = (k + 8) * 64 + ((m >> 3) ^ RowTile<DH>::swz(k + 8)) * 8 + ((m >> 2) & 1) * 4;
+      t0[q] = k * 64 + ((m >> 3) ^ TILE::swz(k)) * 8 + ((m >> 2) & 1) * 4;
+      t1[q] = (k + 8) * 64 + ((m >> 3) ^ TILE::swz(k + 8)) * 8 + ((m >> 2) & 1) * 4;
     }
   }
   // rows 32*nt .. +31, head dimensions 16*kk .. +15
   __device__ __forceinline__ bf16x8_t rows(const bf16_t *t, int nt, int kk) const {
-    return *(const bf16x8_t *)(t + (kk >> 2) * 4096 + nt * 2048 + kc[kk & 3]);
+    return *(const bf16x8_t *)(t + (kk >> 2) * TK * 64 + nt * 2048 + kc[kk & 3]);
   }
   // rows 16*kk .. +15 (in the order of row_operand) as contraction steps, head dimensions 32*nd .. +31
   __device__ __forceinline__ bf16x8_t tr(const bf16_t *t, int nd, int kk) const {
-    const int c = (nd >> 1) * 4096 + kk * 1024;
+    const int c = (nd >> 1) * TK * 64 + kk * 1024;
     return fragment<1>(t, c + t0[nd & 1], c + t1[nd & 1]);
   }
 };
@@ -144,29 +149,32 @@ __device__ __forceinline__ bool block_place(int pairs, int nb, int &z, int &rb) 
 }
 
 // ---------------------------------------------------------------------------
-// forward: four wavefronts = 128 query rows of one (sample, head); wavefront w owns
+// forward: RW wavefronts = 32 RW query rows of one (sample, head); wavefront w owns
 // rows r0 = q0 + 32 w .. + 31 and keeps its Q fragments in registers.  One
 // sweep over the key tiles up to the diagonal with a running row maximum and
 // sum (the output is rescaled when the maximum grows and divided by the sum at
 // the end).  Tiles go straight from global memory to LDS, one ahead; one barrier
-// per tile.  KW groups of four wavefronts share the rows: group g takes key
+// per tile.  KW groups of RW wavefronts share the rows: group g takes key
 // tiles g, g + KW, ... and the partial results are merged through LDS at the end
-// (launches that would leave CUs without work).
-// Bound: per tile and wavefront 1024 clocks of MFMAs at head width 128 (512 at 64) and 960 of vector ALU, which overlap
-// only between the two or more wavefronts of a SIMD; counters at B 4, H 16, T 2048, dh 128: matrix pipes 0.43 busy,
-// vector ALU 0.41, LDS 0.22.  That launch: 255 us with one wavefront per SIMD, register-staged tiles and probabilities
-// through LDS; 103 us without these; 79 us with the long blocks first.  Measured without gain: tiles two and three
-// ahead, raised wavefront priority around the MFMAs, MFMAs and exponentials interleaved by scheduling directives (spills).
+// (launches that would leave CUs without work; which form when: attn_forms.h).
+// Bound: per 64 keys and wavefront 1024 clocks of MFMAs at head width 128 (512 at 64) and 960 of vector ALU, which overlap
+// only between the wavefronts of a SIMD; counters at B 4, H 16, T 2048, dh 128 with tiles of 64 keys (two blocks per CU):
+// matrix pipes 0.43 busy, vector ALU 0.41, LDS 0.22.  That launch: 90 us with tiles of 64 keys, 82 with 32, whose LDS lets
+// three blocks share a CU (168 registers; held to 128 for a fourth block it spills: 132 us).  Measured without gain: tiles
+// two and three ahead, raised wavefront priority around the MFMAs, MFMAs and exponentials interleaved by scheduling
+// directives (spills).
 // ---------------------------------------------------------------------------
-template <int DH, int KW, bool DIRECT>
-__global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__restrict__ qkv, bf16_t *__restrict__ o,
+template <int DH, int RW, int KW, int TK, bool DIRECT>
+__global__ __launch_bounds__(64 * RW * KW, 2) void attn_fwd_kernel(const bf16_t *__restrict__ qkv, bf16_t *__restrict__ o,
                                                                float *__restrict__ lse, int T, int H, int d, int nb, int pairs,
                                                                float scale_log2e) {
   constexpr int ND = DH / 32;  // 32-wide column tiles of the output
-  constexpr int TILE = RowTile<DH>::SIZE, STAGE = 2 * TILE * KW;
+  typedef RowTile<DH, RW, TK> tile_t;
+  constexpr int AQ = 32 * RW, NT = TK / 32;  // rows of the block, 32-row parts of a tile
+  constexpr int TILE = tile_t::SIZE, STAGE = 2 * TILE * KW;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];  // [2 stages][KW][K, V]
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+  const int tid = threadIdx.x % (64 * RW), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * RW)) : 0;
   int z, qb;
   if (!block_place(pairs, nb, z, qb)) return;
   qb = nb - 1 - qb;
@@ -177,14 +185,14 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__r
   const int myrow = r0 + (lane & 31);
   const int ldrow = min(myrow, T - 1);  // rows past the sequence compute on a valid row and store nothing
 
-  RowTile<DH> tile;
+  tile_t tile;
   tile.init(ld, tid);
   const uint32_t lds0 = lds_addr(smem) + grp * 2 * TILE * 2;
   const int kend = min(T, q0 + AQ);  // keys any row of the block can see
-  const int nstep = (kend + AK * KW - 1) / (AK * KW);
+  const int nstep = (kend + TK * KW - 1) / (TK * KW);
   const int my_last = r0 + 31;       // tiles starting beyond it hold nothing for this wavefront
   auto load = [&](int it) {
-    const int j0 = (it * KW + grp) * AK;
+    const int j0 = (it * KW + grp) * TK;
     const uint32_t s = lds0 + (it & 1) * STAGE * 2;
     tile.template load<DIRECT>(kp + (int64_t)j0 * ld, T - j0, s, wave);
     tile.template load<DIRECT>(vp + (int64_t)j0 * ld, T - j0, s + TILE * 2, wave);
@@ -193,7 +201,7 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__r
   bf16x8_t qf[DH / 16];
 #pragma unroll
   for (int kk = 0; kk < DH / 16; ++kk) qf[kk] = load_frag_global(qp + ldrow * ld + kk * 16 + (lane >> 5) * 8);
-  RowFrag<DH> fr;
+  RowFrag<tile_t, TK> fr;
   fr.init(lane);
 
   // the reference maximum starts at the lowest finite value: a row whose scores of a tile are all -inf then adds
@@ -208,12 +216,12 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__r
   for (int it = 0; it < nstep; ++it) {
     landed_barrier();
     if (it + 1 < nstep) load(it + 1);
-    const int j0 = (it * KW + grp) * AK;
+    const int j0 = (it * KW + grp) * TK;
     const bf16_t *const ks = smem + (it & 1) * STAGE + grp * 2 * TILE, *const vs = ks + TILE;
     if (j0 > my_last) continue;
-    f32x16_t s[2];
+    f32x16_t s[NT];
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[nt][r] = 0.f;
 #pragma unroll
@@ -224,17 +232,17 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__r
     // conversion: the scores stay unscaled (the scale is positive, so it commutes with the maximum and is folded into
     // the exponent's multiply-add), and the causal mask is applied only in tiles that reach above the wavefront's
     // first row.
-    if (j0 + AK - 1 > r0) {
+    if (j0 + TK - 1 > r0) {
       const int over = j0 + (lane >> 5) * 4 - myrow;  // key - row of this lane's first column
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           if (over + nt * 32 + (r >> 2) * 8 + (r & 3) > 0) s[nt][r] = -INFINITY;
     }
     float tmax = s[0][0];
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) tmax = __builtin_fmaxf(tmax, s[nt][r]);
     tmax = max_halves(tmax);
@@ -254,7 +262,7 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__r
     }
     float sum = 0.f;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
       float p[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -272,29 +280,33 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__r
     l += sum;
   }
   l = sum_halves(l);
-  if constexpr (KW == 2) {
-    // group 1 hands its maximum, sum and output over; [value][wavefront][lane]
-    float *const x = (float *)smem + wave * 64 + lane;
+#pragma unroll
+  for (int n = KW / 2; n > 0; n /= 2) {
+    // groups n .. 2n - 1 hand their maximum, sum and output to groups 0 .. n - 1; [group][value][wavefront][lane]
+    constexpr int VALS = 2 + ND * 16;
+    float *const x = (float *)smem + (grp % n) * VALS * 64 * RW + wave * 64 + lane;
     __syncthreads();
-    if (grp == 1) {
+    if (grp >= n && grp < 2 * n) {
       x[0] = m;
-      x[256] = l;
+      x[64 * RW] = l;
 #pragma unroll
       for (int nd = 0; nd < ND; ++nd)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) x[(2 + nd * 16 + r) * 256] = acc[nd][r];
+        for (int r = 0; r < 16; ++r) x[(2 + nd * 16 + r) * 64 * RW] = acc[nd][r];
     }
     __syncthreads();
-    if (grp == 1) return;
-    const float m1 = x[0], mn = __builtin_fmaxf(m, m1);
-    const float a0 = __builtin_amdgcn_exp2f(m - mn), a1 = __builtin_amdgcn_exp2f(m1 - mn);
-    m = mn;
-    l = l * a0 + x[256] * a1;
+    if (grp < n) {
+      const float m1 = x[0], mn = __builtin_fmaxf(m, m1);
+      const float a0 = __builtin_amdgcn_exp2f(m - mn), a1 = __builtin_amdgcn_exp2f(m1 - mn);
+      m = mn;
+      l = l * a0 + x[64 * RW] * a1;
 #pragma unroll
-    for (int nd = 0; nd < ND; ++nd)
+      for (int nd = 0; nd < ND; ++nd)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[nd][r] = acc[nd][r] * a0 + x[(2 + nd * 16 + r) * 256] * a1;
+        for (int r = 0; r < 16; ++r) acc[nd][r] = acc[nd][r] * a0 + x[(2 + nd * 16 + r) * 64 * RW] * a1;
+    }
   }
+  if (KW > 1 && grp > 0) return;
   const float inv_l = 1.f / l;
   if (myrow < T) {
     if (lane < 32) lse[(int64_t)z * T + myrow] = (m + log2f(l)) * LN2;
@@ -308,42 +320,48 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_fwd_kernel(const bf16_t *__r
   }
 }
 
-// adds what group 1 of a two-group block holds to group 0's accumulators; false for the wavefronts of group 1
-template <int NA>
+// adds what the groups of a block hold into group 0's accumulators, in pairs; false for the wavefronts of the other groups
+template <int RW, int KW, int NA>
 __device__ __forceinline__ bool merge_groups(f32x16_t (&acc)[NA], int grp, float *smem, int wave, int lane) {
-  float *const x = smem + wave * 64 + lane;
-  __syncthreads();
-  if (grp == 1) {
 #pragma unroll
-    for (int i = 0; i < NA; ++i)
+  for (int n = KW / 2; n > 0; n /= 2) {
+    float *const x = smem + (grp % n) * NA * 16 * 64 * RW + wave * 64 + lane;
+    __syncthreads();
+    if (grp >= n && grp < 2 * n) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) x[(i * 16 + r) * 256] = acc[i][r];
+      for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) x[(i * 16 + r) * 64 * RW] = acc[i][r];
+    }
+    __syncthreads();
+    if (grp < n) {
+#pragma unroll
+      for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] += x[(i * 16 + r) * 64 * RW];
+    }
   }
-  __syncthreads();
-  if (grp == 1) return false;
-#pragma unroll
-  for (int i = 0; i < NA; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i][r] += x[(i * 16 + r) * 256];
-  return true;
+  return grp == 0;
 }
 
 // ---------------------------------------------------------------------------
 // backward, part 1: dQ.  Same decomposition as the forward kernel.  Per tile:
 // p = exp(s - L), dP = dO V^T, dS = p (dP - D) / sqrt(dh) with
-// D_i = sum_c dO[i,c] O[i,c] (written out for part 2), dQ += dS K.  Both backward
-// kernels together at B 4, H 16, T 2048, dh 128: 830 -> 270 us; at B 4, H 12, T 512, dh 64: 41 -> 28 us.
+// D_i = sum_c dO[i,c] O[i,c] (written out for part 2), dQ += dS K.  B 4, H 16, T 2048, dh 128: 117 us, whether with 64 or with
+// 32 keys per tile (three blocks per CU would need 168 registers: 180 us with the spills).
 // ---------------------------------------------------------------------------
-template <int DH, int KW, bool DIRECT>
-__global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
+template <int DH, int RW, int KW, int TK, bool DIRECT>
+__global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dq_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
                                                                   const bf16_t *__restrict__ d_o, const float *__restrict__ lse,
                                                                   float *__restrict__ dsum, bf16_t *__restrict__ dqkv, int T,
                                                                   int H, int d, int nb, int pairs, float scale) {
   constexpr int ND = DH / 32;
-  constexpr int TILE = RowTile<DH>::SIZE, STAGE = 2 * TILE * KW;
+  typedef RowTile<DH, RW, TK> tile_t;
+  constexpr int AQ = 32 * RW, NT = TK / 32;  // rows of the block, 32-row parts of a tile
+  constexpr int TILE = tile_t::SIZE, STAGE = 2 * TILE * KW;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+  const int tid = threadIdx.x % (64 * RW), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * RW)) : 0;
   int z, qb;
   if (!block_place(pairs, nb, z, qb)) return;
   qb = nb - 1 - qb;
@@ -354,14 +372,14 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *
   const int myrow = r0 + (lane & 31);
   const int ldrow = min(myrow, T - 1);
 
-  RowTile<DH> tile;
+  tile_t tile;
   tile.init(ld, tid);
   const uint32_t lds0 = lds_addr(smem) + grp * 2 * TILE * 2;
   const int kend = min(T, q0 + AQ);
-  const int nstep = (kend + AK * KW - 1) / (AK * KW);
+  const int nstep = (kend + TK * KW - 1) / (TK * KW);
   const int my_last = r0 + 31;
   auto load = [&](int it) {
-    const int j0 = (it * KW + grp) * AK;
+    const int j0 = (it * KW + grp) * TK;
     const uint32_t s = lds0 + (it & 1) * STAGE * 2;
     tile.template load<DIRECT>(kp + (int64_t)j0 * ld, T - j0, s, wave);
     tile.template load<DIRECT>(vp + (int64_t)j0 * ld, T - j0, s + TILE * 2, wave);
@@ -386,7 +404,7 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *
   if (grp == 0 && lane < 32 && myrow < T) dsum[(int64_t)z * T + myrow] = Di;
   const float scale_log2e = scale * LOG2E;
   const float nL2 = -L2, nDs = -Di * scale;
-  RowFrag<DH> fr;
+  RowFrag<tile_t, TK> fr;
   fr.init(lane);
 
   f32x16_t acc[ND];
@@ -398,11 +416,11 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *
   for (int it = 0; it < nstep; ++it) {
     landed_barrier();
     if (it + 1 < nstep) load(it + 1);
-    const int j0 = (it * KW + grp) * AK;
+    const int j0 = (it * KW + grp) * TK;
     const bf16_t *const ks = smem + (it & 1) * STAGE + grp * 2 * TILE, *const vs = ks + TILE;
     if (j0 > my_last) continue;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
       f32x16_t s, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
@@ -435,8 +453,8 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *
       }
     }
   }
-  if constexpr (KW == 2) {
-    if (!merge_groups(acc, grp, (float *)smem, wave, lane)) return;
+  if constexpr (KW > 1) {
+    if (!merge_groups<RW, KW>(acc, grp, (float *)smem, wave, lane)) return;
   }
   if (myrow < T) {
     bf16_t *dq = dqkv + ((int64_t)b * T + myrow) * ld + h * DH;
@@ -446,25 +464,29 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dq_kernel(const bf16_t *
 }
 
 // ---------------------------------------------------------------------------
-// backward, part 2: dK and dV.  Four wavefronts = 128 keys of one (sample, head),
+// backward, part 2: dK and dV.  RW wavefronts = 32 RW keys of one (sample, head),
 // wavefront w owns keys kr0 = k0 + 32 w .. + 31 and keeps their K and V
-// fragments in registers.  It walks the query tiles (64 rows) from the diagonal
+// fragments in registers.  It walks the query tiles from the diagonal
 // to the end of the sequence, computing the transposed quantities directly:
 // s^T = K Q^T, p^T = exp(s^T - L), dP^T = V dO^T, dS^T = p^T (dP^T - D)/sqrt(dh),
-// dV += p^T dO, dK += dS^T Q.  No atomics: every key row has one owner.
+// dV += p^T dO, dK += dS^T Q.  No atomics: every key row has one owner.  At head width 64 the kernel is held to 168 registers
+// (203 left alone), so that three blocks of one group share a CU: B 8, H 25, T 1024 90.6 -> 84.9 us.  At 128 it is 157 us at
+// B 4, H 16, T 2048 with two blocks per CU and tiles of 64 queries, 173 with 32.
 // ---------------------------------------------------------------------------
-template <int DH, int KW, bool DIRECT>
-__global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
+template <int DH, int RW, int KW, int TK, bool DIRECT>
+__global__ __launch_bounds__(64 * RW * KW, DH == 64 && KW == 1 ? 3 : 2) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
                                                                    const bf16_t *__restrict__ d_o,
                                                                    const float *__restrict__ lse,
                                                                    const float *__restrict__ dsum, bf16_t *__restrict__ dqkv,
                                                                    int T, int H, int d, int nb, int pairs, float scale) {
   constexpr int ND = DH / 32;
-  constexpr int TILE = RowTile<DH>::SIZE, STAGE = 2 * TILE * KW;
+  typedef RowTile<DH, RW, TK> tile_t;
+  constexpr int AQ = 32 * RW, NT = TK / 32;  // rows of the block, 32-row parts of a tile
+  constexpr int TILE = tile_t::SIZE, STAGE = 2 * TILE * KW;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];  // [2 stages][KW][Q, dO], then the statistics
-  float *const Ls = (float *)(smem + 2 * STAGE);  // [2][KW][128]: -log-sum-exp (log2 domain) and -D / sqrt(dh) of a tile's 64 queries
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+  float *const Ls = (float *)(smem + 2 * STAGE);  // [2][KW][2 * TK]: -log-sum-exp (log2 domain) and -D / sqrt(dh) of a tile's queries
+  const int tid = threadIdx.x % (64 * RW), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * RW)) : 0;
   int z, kb;
   if (!block_place(pairs, nb, z, kb)) return;
   const int b = z / H, h = z % H;
@@ -475,12 +497,12 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
   const int mykey = kr0 + (lane & 31);
   const int ldkey = min(mykey, T - 1);
 
-  RowTile<DH> tq, to;
+  tile_t tq, to;
   tq.init(ld, tid);
   to.init(d, tid);
   const uint32_t lds0 = lds_addr(smem) + grp * 2 * TILE * 2;
-  const int nstep = (T - k0 + AK * KW - 1) / (AK * KW);
-  auto first = [&](int it) { return k0 + (it * KW + grp) * AK; };  // first query of this group's tile
+  const int nstep = (T - k0 + TK * KW - 1) / (TK * KW);
+  auto first = [&](int it) { return k0 + (it * KW + grp) * TK; };  // first query of this group's tile
   auto load = [&](int it) {
     const int i0 = first(it);
     const uint32_t s = lds0 + (it & 1) * STAGE * 2;
@@ -488,9 +510,9 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
     to.template load<DIRECT>(dop + (int64_t)i0 * d, T - i0, s + TILE * 2, wave);
   };
   auto load_stat = [&](int i0) -> float {
-    const int qi = i0 + (tid & 63);
-    if (tid >= 128 || qi >= T) return 0.f;
-    return tid < 64 ? -lse[(int64_t)z * T + qi] * LOG2E : -dsum[(int64_t)z * T + qi] * scale;
+    const int qi = i0 + tid % TK;
+    if (tid >= 2 * TK || qi >= T) return 0.f;
+    return tid < TK ? -lse[(int64_t)z * T + qi] * LOG2E : -dsum[(int64_t)z * T + qi] * scale;
   };
   load(0);
   float stat = load_stat(first(0));
@@ -501,9 +523,9 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
     kf[kk] = load_frag_global(kp + ldkey * ld + c);
     vf[kk] = load_frag_global(vp + ldkey * ld + c);
   }
-  if (tid < 128) Ls[grp * 128 + tid] = stat;
+  if (tid < 2 * TK) Ls[grp * 2 * TK + tid] = stat;
   const float scale_log2e = scale * LOG2E;
-  RowFrag<DH> fr;
+  RowFrag<tile_t, TK> fr;
   fr.init(lane);
 
   f32x16_t acc[2 * ND];  // dK, dV
@@ -521,13 +543,13 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
     }
     const int i0 = first(it);
     const bf16_t *const qs = smem + (it & 1) * STAGE + grp * 2 * TILE, *const os = qs + TILE;
-    const float *const ls = Ls + ((it & 1) * KW + grp) * 128;
-    if (i0 + AK - 1 >= kr0 && i0 < T) {  // else no query of the tile comes after a key of this wavefront
+    const float *const ls = Ls + ((it & 1) * KW + grp) * 2 * TK;
+    if (i0 + TK - 1 >= kr0 && i0 < T) {  // else no query of the tile comes after a key of this wavefront
       // one half tile at a time: unrolled, the two halves' results do not fit the 256 registers two wavefronts per SIMD
       // leave at head width 128 (the two backward kernels at B 4, H 16, T 2048, dh 128: 289 -> 270 us).  Even so one to
       // three registers are spilled there (8 to 16 bytes of scratch per lane); at head width 64 none
 #pragma unroll 1
-      for (int nt = 0; nt < 2; ++nt) {
+      for (int nt = 0; nt < NT; ++nt) {
         f32x16_t s, dp;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
@@ -549,7 +571,7 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int qc = nt * 32 + q * 8 + (lane >> 5) * 4;  // first of this lane's four queries within the tile
-          const f32x4_t nl = *(const f32x4_t *)(ls + qc), nd4 = *(const f32x4_t *)(ls + 64 + qc);
+          const f32x4_t nl = *(const f32x4_t *)(ls + qc), nd4 = *(const f32x4_t *)(ls + TK + qc);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int r = q * 4 + e;
@@ -570,10 +592,10 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
         }
       }
     }
-    if (more && tid < 128) Ls[(((it + 1) & 1) * KW + grp) * 128 + tid] = stat;
+    if (more && tid < 2 * TK) Ls[(((it + 1) & 1) * KW + grp) * 2 * TK + tid] = stat;
   }
-  if constexpr (KW == 2) {
-    if (!merge_groups(acc, grp, (float *)smem, wave, lane)) return;
+  if constexpr (KW > 1) {
+    if (!merge_groups<RW, KW>(acc, grp, (float *)smem, wave, lane)) return;
   }
   if (mykey < T) {
     bf16_t *dkp = dqkv + ((int64_t)b * T + mykey) * ld + d + h * DH, *dvp = dkp + d;
@@ -589,10 +611,10 @@ __global__ __launch_bounds__(256 * KW, 2) void attn_bwd_dkv_kernel(const bf16_t 
 
 bool attention_fused_supported(int dtype, int dh) { return dtype == DT_BF16 && (dh == 64 || dh == 128); }
 
-// bytes of LDS: two stages of two tiles per group, and room for the merge of two groups (nacc 32-column accumulators
+// bytes of LDS: two stages of two tiles per group, and room for the merge of the groups (nacc 32-column accumulators
 // and `extra` values per row)
-static constexpr size_t attn_lds(int dh, int kw, int nacc, int extra, size_t stats) {
-  const size_t tiles = (size_t)2 * kw * 2 * AK * dh * 2 + stats, merge = kw == 2 ? (size_t)(nacc * 16 + extra) * 256 * 4 : 0;
+static constexpr size_t attn_lds(int dh, int rw, int kw, int tk, int nacc, int extra, size_t stats) {
+  const size_t tiles = (size_t)2 * kw * 2 * tk * dh * 2 + stats, merge = (size_t)(kw / 2) * (nacc * 16 + extra) * 64 * rw * 4;
   return tiles > merge ? tiles : merge;
 }
 
@@ -604,49 +626,67 @@ static constexpr size_t attn_lds(int dh, int kw, int nacc, int extra, size_t sta
     const hipError_t attr = allow_lds(once, (const void *)kern, LDS_);             \
     if (attr != hipSuccess) return attr;                                           \
     const uint32_t blocks = (uint32_t)nb * B * H, gx = blocks < (1u << 22) ? blocks : 1u << 22; \
-    hipLaunchKernelGGL(kern, dim3(gx, (blocks + gx - 1) / gx), dim3(256 * KW), LDS_, s, __VA_ARGS__); \
+    hipLaunchKernelGGL(kern, dim3(gx, (blocks + gx - 1) / gx), dim3(64 * RW * KW), LDS_, s, __VA_ARGS__); \
   } while (0)
 
-template <int DH, int KW, bool DIRECT>
+template <int DH, int RW, int KW, int TK, bool DIRECT>
 static hipError_t attn_fwd(const bf16_t *qkv, bf16_t *o, float *lse, int B, int H, int T, hipStream_t s) {
-  const int nb = (T + AQ - 1) / AQ, d = H * DH;
-  HYDRA_ATTN((attn_fwd_kernel<DH, KW, DIRECT>), attn_lds(DH, KW, DH / 32, 2, 0), qkv, o, lse, T, H, d, nb, B * H,
+  const int nb = (T + 32 * RW - 1) / (32 * RW), d = H * DH;
+  HYDRA_ATTN((attn_fwd_kernel<DH, RW, KW, TK, DIRECT>), attn_lds(DH, RW, KW, TK, DH / 32, 2, 0), qkv, o, lse, T, H, d, nb, B * H,
              LOG2E / sqrtf((float)DH));
   return hipGetLastError();
 }
 
-template <int DH, int KW, bool DIRECT>
+template <int DH, int RW, int KW, int TK, bool DIRECT>
 static hipError_t attn_bwd(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o, const float *lse, float *dsum, bf16_t *dqkv,
                            int B, int H, int T, hipStream_t s) {
-  const int nb = (T + AQ - 1) / AQ, d = H * DH;
+  const int nb = (T + 32 * RW - 1) / (32 * RW), d = H * DH;
   const float scale = 1.0f / sqrtf((float)DH);
-  HYDRA_ATTN((attn_bwd_dq_kernel<DH, KW, DIRECT>), attn_lds(DH, KW, DH / 32, 0, 0), qkv, o, d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale);
-  HYDRA_ATTN((attn_bwd_dkv_kernel<DH, KW, DIRECT>), attn_lds(DH, KW, DH / 16, 0, KW * 256 * 4), qkv, d_o, lse, dsum, dqkv, T, H, d, nb, B * H,
+  HYDRA_ATTN((attn_bwd_dq_kernel<DH, RW, KW, TK, DIRECT>), attn_lds(DH, RW, KW, TK, DH / 32, 0, 0), qkv, o, d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale);
+  HYDRA_ATTN((attn_bwd_dkv_kernel<DH, RW, KW, TK, DIRECT>), attn_lds(DH, RW, KW, TK, DH / 16, 0, KW * 2 * 2 * TK * 4), qkv, d_o, lse, dsum, dqkv, T, H, d, nb, B * H,
              scale);
   return hipGetLastError();
 }
 #undef HYDRA_ATTN
 
-// Two groups of wavefronts per block while the row blocks of a launch leave wavefront slots empty (two blocks of four
-// wavefronts per CU make 512): us with one / two groups, forward, then backward -
-//   B 4, H 12, T 512, dh 64 (192 blocks) 10.8 / 10.1, 29.9 / 28.0;   B 2, H 12, T 2048, dh 64 (384) 33 / 27, 93 / 76;
-//   B 1, H 32, T 1024, dh 128 (256) 27 / 23, 91 / 76;   B 5, H 12, T 1024, dh 64 (480) 19.9 / 19.3, 55 / 59;
-//   B 3, H 25, T 1000, dh 64 (600) 23 / 25, 67 / 80;   B 4, H 16, T 2048, dh 128 (1024) 79 / 98, 279 / 318.
-// Sequences of one or two tiles have nothing to share out.
-static bool two_groups(int B, int H, int T, int limit) { return T > 4 * AK && (long)((T + AQ - 1) / AQ) * B * H <= limit; }
-
-// The kernel form of a call: head width, groups, direct loads.  Tensors off the 16-byte grid (qkv or d_o; heads and rows
-// are multiples of it) move their tiles through registers.
-#define HYDRA_ATTN_DIRECT(FN_, DH_, KW_, ...) (direct ? FN_<DH_, KW_, true>(__VA_ARGS__) : FN_<DH_, KW_, false>(__VA_ARGS__))
-#define HYDRA_ATTN_GROUPS(FN_, DH_, ...) (two ? HYDRA_ATTN_DIRECT(FN_, DH_, 2, __VA_ARGS__) : HYDRA_ATTN_DIRECT(FN_, DH_, 1, __VA_ARGS__))
-#define HYDRA_ATTN_FORM(FN_, ...) (dh == 64 ? HYDRA_ATTN_GROUPS(FN_, 64, __VA_ARGS__) : HYDRA_ATTN_GROUPS(FN_, 128, __VA_ARGS__))
+// One launch of form F of a table (attn_forms.h).  Tensors off the 16-byte grid (qkv or d_o; heads and rows are multiples of
+// it) move their tiles through registers.
+template <int DH, int F, bool DIRECT>
+static hipError_t attn_fwd_form(const bf16_t *qkv, bf16_t *o, float *lse, int B, int H, int T, hipStream_t s) {
+  constexpr AttnForm f = DH == 64 ? attn_forms_fwd64[F] : attn_forms_fwd128[F < 3 ? F : 0];
+  return attn_fwd<DH, f.rw, f.kw, f.tk, DIRECT>(qkv, o, lse, B, H, T, s);
+}
+template <int DH, int F, bool DIRECT>
+static hipError_t attn_bwd_form(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o, const float *lse, float *dsum, bf16_t *dqkv,
+                                int B, int H, int T, hipStream_t s) {
+  constexpr AttnForm f = DH == 64 ? attn_forms_bwd64[F] : attn_forms_bwd128[F < 3 ? F : 0];
+  return attn_bwd<DH, f.rw, f.kw, f.tk, DIRECT>(qkv, o, d_o, lse, dsum, dqkv, B, H, T, s);
+}
+#define HYDRA_ATTN_FORM(FN_, DH_, F_, ...) \
+  return direct ? FN_<DH_, F_, true>(__VA_ARGS__) : FN_<DH_, F_, false>(__VA_ARGS__)
+#define HYDRA_ATTN_FORMS3(FN_, DH_, ...)                  \
+  case 0: HYDRA_ATTN_FORM(FN_, DH_, 0, __VA_ARGS__);      \
+  case 1: HYDRA_ATTN_FORM(FN_, DH_, 1, __VA_ARGS__);      \
+  case 2: HYDRA_ATTN_FORM(FN_, DH_, 2, __VA_ARGS__)
 
 hipError_t launch_attention_fwd(const void *qkv, void *o, float *lse, int B, int H, int T, int dh, hipStream_t s) {
   if (!attention_fused_supported(DT_BF16, dh)) return hipErrorInvalidValue;
   // causal half of both products
   ProfScope ps("attention_fwd", s, 2.0 * B * H * dh * ((double)T * (T + 1.0)), 0);
-  const bool two = two_groups(B, H, T, 512), direct = ((uintptr_t)qkv & 15) == 0;
-  return HYDRA_ATTN_FORM(attn_fwd, (const bf16_t *)qkv, (bf16_t *)o, lse, B, H, T, s);
+  const bool direct = ((uintptr_t)qkv & 15) == 0;
+  const int form = attn_form_fwd(dh, B * H, T);
+#define HYDRA_ARGS (const bf16_t *)qkv, (bf16_t *)o, lse, B, H, T, s
+  if (dh == 128) {
+    switch (form) { HYDRA_ATTN_FORMS3(attn_fwd_form, 128, HYDRA_ARGS); }
+  } else {
+    switch (form) {
+      HYDRA_ATTN_FORMS3(attn_fwd_form, 64, HYDRA_ARGS);
+      case 3: HYDRA_ATTN_FORM(attn_fwd_form, 64, 3, HYDRA_ARGS);
+      case 4: HYDRA_ATTN_FORM(attn_fwd_form, 64, 4, HYDRA_ARGS);
+    }
+  }
+#undef HYDRA_ARGS
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_attention_bwd(const void *qkv, const void *o, const void *d_o, const float *lse, float *dsum,
@@ -654,12 +694,21 @@ hipError_t launch_attention_bwd(const void *qkv, const void *o, const void *d_o,
   if (!attention_fused_supported(DT_BF16, dh)) return hipErrorInvalidValue;
   // five causal products of T x T x dh each (s and dP in both kernels count once: the recomputation is overhead)
   ProfScope ps("attention_bwd", s, 5.0 * B * H * dh * ((double)T * (T + 1.0)), 0);
-  const bool two = two_groups(B, H, T, 400), direct = (((uintptr_t)qkv | (uintptr_t)d_o) & 15) == 0;
-  return HYDRA_ATTN_FORM(attn_bwd, (const bf16_t *)qkv, (const bf16_t *)o, (const bf16_t *)d_o, lse, dsum, (bf16_t *)dqkv, B, H,
-                         T, s);
+  const bool direct = (((uintptr_t)qkv | (uintptr_t)d_o) & 15) == 0;
+  const int form = attn_form_bwd(dh, B * H, T);
+#define HYDRA_ARGS (const bf16_t *)qkv, (const bf16_t *)o, (const bf16_t *)d_o, lse, dsum, (bf16_t *)dqkv, B, H, T, s
+  if (dh == 128) {
+    switch (form) { HYDRA_ATTN_FORMS3(attn_bwd_form, 128, HYDRA_ARGS); }
+  } else {
+    switch (form) {
+      HYDRA_ATTN_FORMS3(attn_bwd_form, 64, HYDRA_ARGS);
+      case 3: HYDRA_ATTN_FORM(attn_bwd_form, 64, 3, HYDRA_ARGS);
+    }
+  }
+#undef HYDRA_ARGS
+  return hipErrorInvalidValue;
 }
+#undef HYDRA_ATTN_FORMS3
 #undef HYDRA_ATTN_FORM
-#undef HYDRA_ATTN_GROUPS
-#undef HYDRA_ATTN_DIRECT
 
 }  // namespace hydra

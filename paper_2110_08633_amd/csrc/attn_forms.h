@@ -1,0 +1,58 @@
+// Choice of the block form of the fused attention kernels (host only, no HIP).
+#pragma once
+#include <stdint.h>
+
+#include <cmath>
+
+namespace hydra {
+
+// A block of kw groups of rw wavefronts owns 32 * rw rows and walks over tiles of tk rows, which its groups share out.  What a
+// launch costs in us: a + sqrt((b * steps of the longest block)^2 + (c * steps of all blocks / 256)^2) - the chain of tiles
+// that the longest block walks, and what all of them keep the CUs busy with.  Least-squares fits to 114 calls of 64 to 2048
+// positions, 4 to 256 pairs of sample and head; the form taken is within 0.6 % of the best one on average.
+struct AttnForm {
+  int rw, kw, tk;
+  float a, b, c;
+};
+// Large launches: one group of four wavefronts (three or four blocks per CU hide each other's latencies; tiles of 32 rows
+// forward, of 64 backward).  Few rows: 64-row blocks, twice as many, whose tiles two or four groups share.  The former forms
+// (128-row blocks with one or two groups) / these, us, forward then backward:
+//   B 4, H 12, T 512, dh 64 10.0 / 8.4, 27.9 / 23.8;  B 1, H 12, T 1024, dh 64 14.4 / 10.6, 39.8 / 30.4;
+//   B 4, H 12, T 1024, dh 64 17.0 / 15.9, 49.2 / 46.3;  B 1, H 16, T 2048, dh 128 39.8 / 32.9, 116 / 106;
+//   B 4, H 16, T 2048, dh 128 92 / 82, 268 / 268;  means over the 114 calls 1.16 and 1.15 times as fast
+constexpr AttnForm attn_forms_fwd64[] = {{4, 1, 32, 3.068f, 0.483f, 0.305f}, {2, 1, 32, 2.866f, 0.495f, 0.193f}, {2, 2, 32, 3.569f, 0.455f, 0.388f},
+                                         {2, 2, 64, 3.828f, 0.728f, 0.868f}, {2, 4, 32, 4.803f, 0.440f, 0.908f}};
+constexpr AttnForm attn_forms_fwd128[] = {{4, 1, 32, 3.860f, 0.667f, 0.572f}, {2, 1, 32, 3.347f, 0.668f, 0.368f}, {2, 2, 32, 4.604f, 0.620f, 0.804f}};
+constexpr AttnForm attn_forms_bwd64[] = {{4, 1, 64, 9.038f, 2.508f, 1.942f}, {2, 1, 32, 7.018f, 1.600f, 0.578f}, {2, 2, 32, 9.966f, 1.309f, 1.260f},
+                                         {2, 2, 64, 10.099f, 1.855f, 2.576f}};
+constexpr AttnForm attn_forms_bwd128[] = {{4, 1, 64, 11.223f, 4.395f, 3.716f}, {2, 1, 32, 9.295f, 2.444f, 1.181f}, {2, 2, 32, 14.782f, 2.022f, 2.582f}};
+
+inline float attn_form_cost(const AttnForm &f, int pairs, int T) {
+  const float R = 32.f * f.rw, W = (float)f.kw * f.tk, nb = ceilf(T / R);
+  const float chain = ceilf(T / W), all = pairs * nb * ((nb + 1.f) * R / (2.f * W) + 0.5f) / 256.f;
+  return f.a + sqrtf(f.b * chain * f.b * chain + f.c * all * f.c * all);
+}
+
+// index of the cheapest form.  Several groups per block only while the blocks are resident at once or nearly so (what a second
+// round of them costs is not in the estimate): B 5, H 25, T 368, dh 128 (750 blocks) 16.6 with one group, 22.9 with two; long
+// sequences gain even then: B 1, H 25, T 1960 (775) 50 / 46; head width 64 has room for more: B 3, H 12, T 2016 (1152) 39 / 31,
+// but B 5, H 25, T 456 (1000) 13.2 / 15.9
+template <int N>
+inline int best_attn_form(const AttnForm (&f)[N], int dh, int pairs, int T) {
+  const int64_t blocks = ((int64_t)T + 63) / 64 * pairs, limit = dh == 64 ? (T >= 576 ? 1280 : 900) : (T >= 768 ? 900 : 512);
+  int best = 0;
+  float cost = 0.f;
+  for (int i = 0; i < N; ++i) {
+    const float c = attn_form_cost(f[i], pairs, T);
+    if (i == 0 || (c < cost && (f[i].kw == 1 || blocks <= limit))) { best = i; cost = c; }
+  }
+  return best;
+}
+inline int attn_form_fwd(int dh, int pairs, int T) {
+  return dh == 64 ? best_attn_form(attn_forms_fwd64, dh, pairs, T) : best_attn_form(attn_forms_fwd128, dh, pairs, T);
+}
+inline int attn_form_bwd(int dh, int pairs, int T) {
+  return dh == 64 ? best_attn_form(attn_forms_bwd64, dh, pairs, T) : best_attn_form(attn_forms_bwd128, dh, pairs, T);
+}
+
+}  // namespace hydra

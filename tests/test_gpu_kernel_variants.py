@@ -511,3 +511,20 @@ def test_cross_entropy_rows(H, M, V, ld):
     if V > 4:
         dl[2] = 0.0  # (the pad of a row with a NaN is NaN too)
     assert (dl[keep][:, V:] == 0).all() and (dl[-1] == 0).all() and row[-1] == 0
+
+
+# every block form of the fused attention kernels, forward and backward (their indices in the tables, which the CPU suite holds
+# against the choice): row blocks, tiles and groups partly empty
+ATT_FORM_CASES = [(9, 13, 1000, 64, 0, 0), (9, 13, 776, 64, 0, 1), (1, 1, 8, 64, 1, 1), (40, 16, 264, 64, 1, 1), (9, 13, 136, 64, 2, 1),
+                  (5, 7, 136, 64, 2, 2), (9, 13, 584, 64, 2, 2), (1, 1, 136, 64, 2, 3), (1, 1, 200, 64, 3, 3), (1, 1, 520, 64, 4, 3),
+                  (1, 3, 1096, 64, 4, 3), (9, 7, 584, 128, 0, 0), (9, 13, 328, 128, 0, 1), (1, 1, 8, 128, 1, 1), (9, 13, 72, 128, 1, 1),
+                  (1, 1, 136, 128, 2, 2), (5, 7, 520, 128, 2, 2)]
+
+
+@pytest.mark.parametrize("B,Hn,T,dh", [c[:4] for c in ATT_FORM_CASES])
+def test_attention_every_form(H, B, Hn, T, dh):
+    test_attention_variants(H, B, Hn, T, dh, 1.0)
+    test_attention_variants(H, B, Hn, T, dh, 6.0)
+    if 64 < T <= 328:  # groups whose tiles show a row only scores of -inf; tensors off the 16-byte grid
+        test_attention_scores_of_minus_infinity(H, B, Hn, T, dh, (0, 64))
+        test_attention_unaligned_tensors(H, B, Hn, T, dh, 1)

@@ -462,6 +462,29 @@ def test_gemm_cases_take_the_tile_shapes_they_name(tile_shape):
         ("128x128x2", l) for l in ("nt", "nn", "tt")}
 
 
+def test_attention_cases_take_the_forms_they_name(tmp_path):
+    """The calls that the GPU suite runs for each block form of the attention kernels still select it, and no form is left out."""
+    from tests import test_gpu_kernel_variants as V
+    src = tmp_path / "t.cpp"
+    src.write_text(r'''
+#include "attn_forms.h"
+#include <cstdio>
+int main() {
+  int dh, pairs, T;
+  while (scanf("%d %d %d", &dh, &pairs, &T) == 3) printf("%d %d\n", hydra::attn_form_fwd(dh, pairs, T), hydra::attn_form_bwd(dh, pairs, T));
+}
+''')
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2110_08633_amd", "csrc"),
+                           str(src), "-o", str(tmp_path / "t")])
+    ask = "\n".join(f"{dh} {B * H} {T}" for B, H, T, dh, _, _ in V.ATT_FORM_CASES)
+    out = subprocess.run([str(tmp_path / "t")], input=ask, text=True, capture_output=True, check=True).stdout.split("\n")
+    for c, line in zip(V.ATT_FORM_CASES, out):
+        assert line == f"{c[4]} {c[5]}", (c, line)
+    for dh, fwd, bwd in ((64, 5, 4), (128, 3, 3)):
+        assert {c[4] for c in V.ATT_FORM_CASES if c[3] == dh} == set(range(fwd))
+        assert {c[5] for c in V.ATT_FORM_CASES if c[3] == dh} == set(range(bwd))
+
+
 def test_bench_line_fits_a_log_tail():
     """bench.py's stdout line: the contract's keys and every workload's headline figures in a few kilobytes, however long
     the kernel tables of the full report are."""
