@@ -327,6 +327,8 @@ bool gemm_plain_ok(const GemmDesc &d);
 hipError_t launch_gemm_plain(const GemmDesc &d, hipStream_t s);
 // n products with both operands stored contraction-strided in one launch where that is estimated to be faster
 hipError_t launch_gemm_plain_group(const GemmDesc *d, int n, hipStream_t s);
+// the kernel for products with few tiles (gemm_split.hip); shape: index into split_shapes
+hipError_t launch_gemm_split(const GemmDesc &d, int shape, hipStream_t s);
 void gemm_fill_args(GemmArgs &a, const GemmDesc &d);
 double gemm_flops(const GemmDesc &d);
 

@@ -76,4 +76,48 @@ inline int best_shape(const GemmDims *d, int n, float *cost) {
   return best;
 }
 
+// Products that 64x64 tiles would leave half of the CUs idle for, or a quarter with a long contraction: smaller tiles whose
+// contraction eight wavefronts share out (gemm_split.hip).  Cost as above, with
+// rounds = tiles / 256 rounded up also where two blocks share a CU; fits to 443 products of random layers (64 to 8192 tokens,
+// widths 128 to 16384) with operands that are not in the L2s; the shape taken costs 0.2 % more than the best one on average.
+// The first entry is the 64x64 shape of plain_shapes with its slices split over two groups of wavefronts.  Before / now: both
+// operands contraction-contiguous 1.59 times as fast (181 products), one of each 1.44, both strided 1.29; 152x168x6120 nt
+// 23.9 -> 7.9 us, 201x768x2304 nt 9.4 -> 6.0, 417x896x7784 nt 29.6 -> 23.5, 360x448x2719 tn 14.7 -> 10.4.
+struct SplitShape {
+  int bm, bn;
+  float t0[2], a[2], b[2], c[2], e[2];
+};
+constexpr SplitShape split_shapes[] = {
+    {64, 64, {3.612f, 3.172f}, {0.178f, 0.232f}, {0.050f, 0.013f}, {0.f, 0.f}, {0.149f, 1.512f}},
+    {64, 32, {1.455f, 1.642f}, {0.149f, 0.199f}, {0.010f, 0.019f}, {1.284f, 0.584f}, {0.865f, 1.780f}},
+    {48, 32, {2.752f, 2.218f}, {0.118f, 0.188f}, {0.021f, 0.020f}, {0.f, 0.f}, {0.483f, 1.353f}},
+    {32, 32, {2.709f, 2.307f}, {0.087f, 0.147f}, {0.026f, 0.041f}, {0.f, 0.f}, {0.287f, 0.575f}},
+    {16, 32, {2.545f, 2.402f}, {0.047f, 0.129f}, {0.041f, 0.044f}, {0.144f, 0.f}, {0.000f, 0.120f}},
+    {16, 16, {2.676f, 2.586f}, {0.040f, 0.084f}, {0.007f, 0.068f}, {0.037f, 0.f}, {0.407f, 0.273f}},
+};
+constexpr int N_SPLIT = sizeof(split_shapes) / sizeof(split_shapes[0]), SHAPE_64X64K2 = 7;
+static_assert(plain_shapes[SHAPE_64X64K2].bm == 64 && plain_shapes[SHAPE_64X64K2].bn == 64 && plain_shapes[SHAPE_64X64K2].threads == 512, "");
+
+// below 384 contraction steps a launch is its latency, whatever the tile
+inline bool few_tiles(const GemmDims &d) {
+  const int64_t t = ((int64_t)d.M + 63) / 64 * (((int64_t)d.N + 63) / 64);
+  return (t <= 128 && d.K >= 384) || (t <= 192 && d.K >= 1024);
+}
+
+// index into split_shapes, -1 for its first entry
+inline int best_split_shape(const GemmDims &d) {
+  const float x = d.ta == d.tb ? (float)d.ta : 0.5f;  // one transposed operand: half way between the two
+  auto at = [x](const float (&v)[2]) { return v[0] + x * (v[1] - v[0]); };
+  const float nk = (float)((d.K + 63) / 64);
+  int best = 0;
+  float cost = 0.f;
+  for (int i = 0; i < N_SPLIT; ++i) {
+    const SplitShape &p = split_shapes[i];
+    const float u = (float)((d.M + p.bm - 1) / p.bm) * (float)((d.N + p.bn - 1) / p.bn) * (1.f / 256.f);
+    const float c = at(p.t0) + ceilf(u) * (nk * at(p.a) + at(p.c)) + u * (nk * at(p.b) + at(p.e));
+    if (i == 0 || c < cost) { best = i; cost = c; }
+  }
+  return best > 0 ? best : -1;
+}
+
 }  // namespace hydra

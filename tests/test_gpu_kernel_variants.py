@@ -528,3 +528,35 @@ def test_attention_every_form(H, B, Hn, T, dh):
     if 64 < T <= 328:  # groups whose tiles show a row only scores of -inf; tensors off the 16-byte grid
         test_attention_scores_of_minus_infinity(H, B, Hn, T, dh, (0, 64))
         test_attention_unaligned_tensors(H, B, Hn, T, dh, 1)
+
+
+# products with few tiles: every tile shape in every layout, ragged on every side, with contractions that leave most of the
+# eight wavefronts a slice, end within a slice, or are long (the CPU suite holds this table against the choice)
+SPLIT_CASES = [("64x32w8", "nt", 387, 900, 392), ("64x32w8", "nn", 387, 900, 712), ("64x32w8", "tt", 387, 900, 456),
+               ("64x32w8", "tn", 100, 2052, 391), ("64x32w8", "tn", 900, 516, 5121), ("48x32w8", "nt", 259, 900, 392),
+               ("48x32w8", "nn", 100, 2052, 392), ("48x32w8", "tt", 259, 900, 392), ("48x32w8", "tn", 259, 900, 385),
+               ("48x32w8", "nt", 900, 388, 5128), ("32x32w8", "nt", 49, 2052, 392), ("32x32w8", "nn", 49, 2052, 392),
+               ("32x32w8", "tt", 49, 2052, 456), ("32x32w8", "tn", 49, 2052, 391), ("32x32w8", "nn", 520, 388, 5128),
+               ("16x32w8", "nt", 17, 196, 392), ("16x32w8", "nn", 17, 388, 392), ("16x32w8", "tt", 387, 20, 392),
+               ("16x32w8", "tn", 17, 516, 385), ("16x32w8", "tt", 2000, 52, 5128), ("16x16w8", "nt", 9, 20, 392),
+               ("16x16w8", "nn", 9, 20, 456), ("16x16w8", "tt", 9, 20, 520), ("16x16w8", "tn", 9, 20, 385),
+               ("16x16w8", "nt", 520, 100, 5128), ("16x16w8", "tn", 520, 100, 5121), ("64x64k2", "nt", 387, 1300, 1160),
+               ("64x64k2", "tn", 195, 2052, 1293)]
+
+
+@pytest.mark.parametrize("shape,layout,M,N,K", SPLIT_CASES)
+def test_gemm_bf16_few_tiles(H, shape, layout, M, N, K):
+    test_gemm_bf16_every_tile_shape(H, shape, layout, M, N, K)
+
+
+@pytest.mark.parametrize("shape,layout,M,N,K", [("64x32w8", "nt", 387, 900, 392), ("48x32w8", "tn", 259, 904, 385),
+                                                ("32x32w8", "nt", 49, 2052, 392), ("16x32w8", "tn", 17, 520, 385),
+                                                ("16x16w8", "tn", 9, 24, 385)])
+def test_gemm_bf16_few_tiles_repeats_bitwise_under_concurrency(H, shape, layout, M, N, K):
+    test_gemm_bf16_repeats_bitwise_under_concurrency(H, shape, layout, M, N, K)
+
+
+@pytest.mark.parametrize("shape,d,F,M", [("48x32w8", 392, 520, 520), ("32x32w8", 392, 264, 520), ("16x32w8", 392, 72, 72),
+                                         ("16x16w8", 392, 72, 24)])
+def test_gelu_epilogues_of_few_tiles(H, shape, d, F, M):
+    assert one_block_step(H, d, F, M).get(f"gemm_bf16_{shape}_nt", 0) >= 2  # forward and backward

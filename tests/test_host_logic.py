@@ -462,6 +462,34 @@ def test_gemm_cases_take_the_tile_shapes_they_name(tile_shape):
         ("128x128x2", l) for l in ("nt", "nn", "tt")}
 
 
+def test_few_tile_cases_take_the_shapes_they_name(tmp_path):
+    """The products that the GPU suite runs for each shape of the few-tiles kernel still select it, and none is left out; the
+    products that name a shape of the other kernel do not come here."""
+    from tests import test_gpu_kernel_variants as V
+    src = tmp_path / "t.cpp"
+    src.write_text(r'''
+#include "gemm_shapes.h"
+#include <cstdio>
+int main() {
+  hydra::GemmDims d;
+  int ta, tb;
+  while (scanf("%d %d %d %d %d", &d.M, &d.N, &d.K, &ta, &tb) == 5) {
+    d.ta = ta; d.tb = tb; d.vec_rows = d.N % 4 == 0;
+    printf("%d\n", hydra::few_tiles(d) ? hydra::best_split_shape(d) : -2);
+  }
+}
+''')
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2110_08633_amd", "csrc"),
+                           str(src), "-o", str(tmp_path / "t")])
+    cases = V.SPLIT_CASES + V.SHAPE_CASES
+    ask = "\n".join(f"{M} {N} {K} {int(l[0] == 't')} {int(l[1] == 'n')}" for _, l, M, N, K in cases)
+    out = subprocess.run([str(tmp_path / "t")], input=ask, text=True, capture_output=True, check=True).stdout.split()
+    names = {-1: "64x64k2", 1: "64x32w8", 2: "48x32w8", 3: "32x32w8", 4: "16x32w8", 5: "16x16w8"}
+    for c, i in zip(cases, out):
+        assert (names[int(i)] == c[0]) if c in V.SPLIT_CASES else int(i) == -2, (c, i)
+    assert {(c[0], c[1]) for c in V.SPLIT_CASES} >= {(s, l) for i, s in names.items() if i > 0 for l in ("nt", "nn", "tt", "tn")}
+
+
 def test_attention_cases_take_the_forms_they_name(tmp_path):
     """The calls that the GPU suite runs for each block form of the attention kernels still select it, and no form is left out."""
     from tests import test_gpu_kernel_variants as V
