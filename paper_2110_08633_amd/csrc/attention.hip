@@ -469,12 +469,12 @@ __global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dq_kernel(const bf16
 // fragments in registers.  It walks the query tiles from the diagonal
 // to the end of the sequence, computing the transposed quantities directly:
 // s^T = K Q^T, p^T = exp(s^T - L), dP^T = V dO^T, dS^T = p^T (dP^T - D)/sqrt(dh),
-// dV += p^T dO, dK += dS^T Q.  No atomics: every key row has one owner.  At head width 64 the kernel is held to 168 registers
-// (203 left alone), so that three blocks of one group share a CU: B 8, H 25, T 1024 90.6 -> 84.9 us.  At 128 it is 157 us at
+// dV += p^T dO, dK += dS^T Q.  No atomics: every key row has one owner.  At head width 64 large launches hold the kernel to
+// 168 registers (203 left alone), so that three blocks share a CU: B 8, H 25, T 1024 90.6 -> 84.9 us.  At 128 it is 157 us at
 // B 4, H 16, T 2048 with two blocks per CU and tiles of 64 queries, 173 with 32.
 // ---------------------------------------------------------------------------
-template <int DH, int RW, int KW, int TK, bool DIRECT>
-__global__ __launch_bounds__(64 * RW * KW, DH == 64 && KW == 1 ? 3 : 2) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
+template <int DH, int RW, int KW, int TK, bool DIRECT, int OCC>
+__global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
                                                                    const bf16_t *__restrict__ d_o,
                                                                    const float *__restrict__ lse,
                                                                    const float *__restrict__ dsum, bf16_t *__restrict__ dqkv,
@@ -643,8 +643,17 @@ static hipError_t attn_bwd(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o
   const int nb = (T + 32 * RW - 1) / (32 * RW), d = H * DH;
   const float scale = 1.0f / sqrtf((float)DH);
   HYDRA_ATTN((attn_bwd_dq_kernel<DH, RW, KW, TK, DIRECT>), attn_lds(DH, RW, KW, TK, DH / 32, 0, 0), qkv, o, d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale);
-  HYDRA_ATTN((attn_bwd_dkv_kernel<DH, RW, KW, TK, DIRECT>), attn_lds(DH, RW, KW, TK, DH / 16, 0, KW * 2 * 2 * TK * 4), qkv, d_o, lse, dsum, dqkv, T, H, d, nb, B * H,
-             scale);
+  // a third block per CU once there are enough of them (B 5, H 16, T 976, 640 blocks: both passes 80 us with two, 84 with three)
+#define HYDRA_DKV(OCC_)                                                                                                  \
+  HYDRA_ATTN((attn_bwd_dkv_kernel<DH, RW, KW, TK, DIRECT, OCC_>), attn_lds(DH, RW, KW, TK, DH / 16, 0, KW * 2 * 2 * TK * 4), qkv, \
+             d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale)
+  if constexpr (DH == 64 && RW == 4) {
+    if ((int64_t)nb * B * H > 3 * 256) HYDRA_DKV(3);
+    else HYDRA_DKV(2);
+  } else {
+    HYDRA_DKV(2);
+  }
+#undef HYDRA_DKV
   return hipGetLastError();
 }
 #undef HYDRA_ATTN

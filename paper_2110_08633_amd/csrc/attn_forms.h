@@ -9,18 +9,18 @@ namespace hydra {
 // A block of kw groups of rw wavefronts owns 32 * rw rows and walks over tiles of tk rows, which its groups share out.  What a
 // launch costs in us: a + sqrt((b * steps of the longest block)^2 + (c * steps of all blocks / 256)^2) - the chain of tiles
 // that the longest block walks, and what all of them keep the CUs busy with.  Least-squares fits to 114 calls of 64 to 2048
-// positions, 4 to 256 pairs of sample and head; the form taken is within 0.6 % of the best one on average.
+// positions, 4 to 256 pairs of sample and head; the form taken is within 1 % of the best one on average.
 struct AttnForm {
   int rw, kw, tk;
   float a, b, c;
 };
-// Large launches: one group of four wavefronts (three or four blocks per CU hide each other's latencies; tiles of 32 rows
-// forward, of 64 backward).  Few rows: 64-row blocks, twice as many, whose tiles two or four groups share.  The former forms
+// Large launches: one group of four wavefronts, two to four blocks per CU; tiles of 64 rows, forward at head width 128 of 32
+// (three blocks per CU; at 64 the two are within 1 %: B 8, H 25, T 1024 forward and backward 176 us with 64, 178 with 32).  Few rows: 64-row blocks, twice as many, whose tiles two or four groups share.  The former forms
 // (128-row blocks with one or two groups) / these, us, forward then backward:
 //   B 4, H 12, T 512, dh 64 10.0 / 8.4, 27.9 / 23.8;  B 1, H 12, T 1024, dh 64 14.4 / 10.6, 39.8 / 30.4;
 //   B 4, H 12, T 1024, dh 64 17.0 / 15.9, 49.2 / 46.3;  B 1, H 16, T 2048, dh 128 39.8 / 32.9, 116 / 106;
 //   B 4, H 16, T 2048, dh 128 92 / 82, 268 / 268;  means over the 114 calls 1.16 and 1.15 times as fast
-constexpr AttnForm attn_forms_fwd64[] = {{4, 1, 32, 3.068f, 0.483f, 0.305f}, {2, 1, 32, 2.866f, 0.495f, 0.193f}, {2, 2, 32, 3.569f, 0.455f, 0.388f},
+constexpr AttnForm attn_forms_fwd64[] = {{4, 1, 64, 3.147f, 0.762f, 0.666f}, {2, 1, 32, 2.866f, 0.495f, 0.193f}, {2, 2, 32, 3.569f, 0.455f, 0.388f},
                                          {2, 2, 64, 3.828f, 0.728f, 0.868f}, {2, 4, 32, 4.803f, 0.440f, 0.908f}};
 constexpr AttnForm attn_forms_fwd128[] = {{4, 1, 32, 3.860f, 0.667f, 0.572f}, {2, 1, 32, 3.347f, 0.668f, 0.368f}, {2, 2, 32, 4.604f, 0.620f, 0.804f}};
 constexpr AttnForm attn_forms_bwd64[] = {{4, 1, 64, 9.038f, 2.508f, 1.942f}, {2, 1, 32, 7.018f, 1.600f, 0.578f}, {2, 2, 32, 9.966f, 1.309f, 1.260f},
