@@ -42,8 +42,8 @@ namespace hydra {
 //   tn 768x50257x2048 270 / 208.
 // 720 random products: 1.40 times as fast on average (nt 1.56, tn 1.22, nn 1.25), 7 of them more than 5 % slower, 0.83 at
 // worst.
-// The 256x256 shape with a contraction-strided first operand spills 5 or 6 registers (24 and 28 bytes of scratch per lane).
-// Reloads inside the loop wait for the direct-to-LDS loads in flight, which is part of why its constants are the higher ones.
+// With both operands contraction-strided the 256x256 shape takes slices of 32 steps (large_tn); "tt" products, which no caller
+// of the library has, take 64 and spill 6 registers (28 bytes of scratch per lane), reloaded inside the loop.
 // What bounds the large ones now: with loads, LDS reads and MFMAs switched off in turn, 1024x16384x4096 takes 71 us of
 // loads alone (25 bytes per clock and CU), 73 us of MFMAs alone at the clock the chip holds for them, 100 us together.
 // ---------------------------------------------------------------------------
@@ -52,7 +52,7 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
   constexpr int NG = WM * WN, NW = NG * KW, WTM = BM / WM, WTN = BN / WN, MI = WTM / 16, NJ = WTN / 16;
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && MI * 16 * WM == BM && NJ * 16 * WN == BN, "wavefront tiles");
   constexpr int STAGE = (BM + BN) * BK_, KS = BK_ / 32 / KW;  // steps of a slice per wavefront
-  static_assert(KS * KW * 32 == BK_ && KS % 2 == 0, "the groups share a slice evenly, an even number of steps each");
+  static_assert(KS * KW * 32 == BK_ && (KS % 2 == 0 || KS == 1), "the groups share a slice evenly, one step or an even number each");
   typedef LdsMover<BM, TA, BK_, NW> MA;
   typedef LdsMover<BN, TB, BK_, NW> MB;
   constexpr int NL = MA::N + MB::N;
@@ -95,14 +95,15 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
 #pragma unroll
   for (int j = 0; j < NJ; ++j) bfr[0][j] = fb.get(lds + BM * BK_, j, 0);
 
-  // one slice from stage st; its first step sits in fragment set 0
-  auto slice = [&](int t, int st) {
+  // one slice from stage st; its first step sits in fragment set P0
+  auto slice = [&](int t, int st, auto parity) {
+    constexpr int P0 = decltype(parity)::value;
     const bf16_t *const as = lds + st * STAGE;
     const int st_next = st + 1 == S ? 0 : st + 1;
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
       constexpr int NR = MI + NJ, NS = MI * NJ;
-      const int c = kk & 1, nx = c ^ 1, nkk = kk + 1 < KS ? kk + 1 : 0;
+      const int c = (kk + P0) & 1, nx = c ^ 1, nkk = kk + 1 < KS ? kk + 1 : 0;
       const bf16_t *na = as;
       if (kk + 1 == KS) {
         // slice t + 1 has landed, and this wavefront's reads of slice t are complete before anybody overwrites it
@@ -137,9 +138,15 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
         }
     }
   };
-  for (int t = 0, st = 0; t < nk; ++t) {
-    slice(t, st);
+  typedef std::integral_constant<int, 0> even;
+  typedef std::integral_constant<int, KS & 1> odd;  // slices of one step: the fragment sets change places from slice to slice
+  for (int t = 0, st = 0; t < nk;) {
+    slice(t, st, even());
     if (++st == S) st = 0;
+    if (++t >= nk || KS > 1) continue;
+    slice(t, st, odd());
+    if (++st == S) st = 0;
+    ++t;
   }
   wait_loads_le<0>();
   block_barrier();  // the write-out reuses the stages
@@ -227,8 +234,9 @@ __global__ __launch_bounds__(64 * WM * WN * KW, OCC * WM * WN * KW / 4) void gem
   gemm16_tile<BM, BN, WM, WN, KW, TA, TB, BK_, S>(gg.p[i], blockIdx.x - gg.tile0[i], gg.tile0[i + 1] - gg.tile0[i], lds_dyn);
 }
 
-// d[0..n): one product, or a group of contraction-strided ones.  TN_ONLY: the shape is chosen for such products alone
-template <int BM, int BN, int WM, int WN, int KW, int BK_, int S, int OCC, bool TN_ONLY = false>
+// d[0..n): one product, or a group of contraction-strided ones.  LAYOUTS: the kernels for these alone are built
+enum { ALL_LAYOUTS, TN_ONLY, ALL_BUT_TN };
+template <int BM, int BN, int WM, int WN, int KW, int BK_, int S, int OCC, int LAYOUTS = ALL_LAYOUTS>
 static hipError_t launch_shape(const GemmDesc *d, int n, hipStream_t s) {
   constexpr size_t lds = (size_t)S * (BM + BN) * BK_ * 2;
   constexpr int threads = 64 * WM * WN * KW;
@@ -254,15 +262,19 @@ static hipError_t launch_shape(const GemmDesc *d, int n, hipStream_t s) {
     HYDRA_SET_LDS(kern);                                                                       \
     hipLaunchKernelGGL(kern, dim3(tiles), dim3(threads), lds, s, gg.p[0]);                      \
   } while (0)
-  if (n > 1) {
-    for (int i = n; i <= GEMM_GROUP_MAX; ++i) gg.tile0[i] = tiles;
-    gg.n = n;
-    auto kern = gemm_plain_group_kernel<BM, BN, WM, WN, KW, 1, 1, BK_, S, OCC>;
-    HYDRA_SET_LDS(kern);
-    hipLaunchKernelGGL(kern, dim3(tiles), dim3(threads), lds, s, gg);
-  } else if (d->ta && d->tb) {
-    HYDRA_PLAIN(1, 1);
-  } else if constexpr (TN_ONLY) {
+  if (d->ta && d->tb) {
+    if constexpr (LAYOUTS == ALL_BUT_TN) {
+      return hipErrorInvalidValue;
+    } else if (n > 1) {
+      for (int i = n; i <= GEMM_GROUP_MAX; ++i) gg.tile0[i] = tiles;
+      gg.n = n;
+      auto kern = gemm_plain_group_kernel<BM, BN, WM, WN, KW, 1, 1, BK_, S, OCC>;
+      HYDRA_SET_LDS(kern);
+      hipLaunchKernelGGL(kern, dim3(tiles), dim3(threads), lds, s, gg);
+    } else {
+      HYDRA_PLAIN(1, 1);
+    }
+  } else if constexpr (LAYOUTS == TN_ONLY) {
     return hipErrorInvalidValue;
   } else if (d->ta) {
     HYDRA_PLAIN(1, 0);
@@ -282,13 +294,15 @@ static hipError_t launch_best(const GemmDesc *d, int n, int shape, hipStream_t s
   static const char *const names[N_SHAPES][5] = {
 #define HYDRA_N(X) {"gemm_bf16_" X "_nt", "gemm_bf16_" X "_nn", "gemm_bf16_" X "_tt", "gemm_bf16_" X "_tn", "gemm_bf16_" X "_tn_group"}
       HYDRA_N("256x256"), HYDRA_N("128x256"), HYDRA_N("128x192"), HYDRA_N("128x128"), HYDRA_N("128x64"),
-      HYDRA_N("64x96"), HYDRA_N("64x64"), HYDRA_N("64x64k2"), HYDRA_N("128x64k2"), HYDRA_N("64x96k2"), HYDRA_N("128x128x2")};
+      HYDRA_N("64x96"), HYDRA_N("64x64"), HYDRA_N("64x64k2"), HYDRA_N("128x64k2"), HYDRA_N("64x96k2"), HYDRA_N("128x128x2"), HYDRA_N("128x256x2")};
 #undef HYDRA_N
   double flops = 0;
   for (int i = 0; i < n; ++i) flops += gemm_flops(d[i]);
   ProfScope ps(names[shape][n > 1 ? 4 : d->ta * 2 + d->tb], s, flops, 0);
   switch (shape) {
-    case 0: return launch_shape<256, 256, 2, 4, 1, 64, 2, 1>(d, n, s);
+    case SHAPE_256X256:
+      if (d->ta && d->tb) return launch_shape<256, 256, 2, 4, 1, 32, 4, 1, TN_ONLY>(d, n, s);  // see large_tn
+      return launch_shape<256, 256, 2, 4, 1, 64, 2, 1, ALL_BUT_TN>(d, n, s);
     case 1: return launch_shape<128, 256, 2, 4, 1, 64, 3, 1>(d, n, s);
     case 2: return launch_shape<128, 192, 2, 4, 1, 64, 3, 1>(d, n, s);
     case 3: return launch_shape<128, 128, 2, 4, 1, 64, 4, 1>(d, n, s);
@@ -298,7 +312,9 @@ static hipError_t launch_best(const GemmDesc *d, int n, int shape, hipStream_t s
     case 7: return launch_shape<64, 64, 2, 2, 2, 128, 4, 1>(d, n, s);
     case 8: return launch_shape<128, 64, 2, 2, 2, 128, 3, 1>(d, n, s);
     case 9: return launch_shape<64, 96, 2, 2, 2, 128, 3, 1>(d, n, s);
-    default: return launch_shape<128, 128, 2, 2, 1, 64, 2, 2, true>(d, n, s);
+    case 10: return launch_shape<128, 128, 2, 2, 1, 64, 2, 2, TN_ONLY>(d, n, s);
+    case SHAPE_128X256X2: return launch_shape<128, 256, 2, 2, 1, 32, 3, 2, TN_ONLY>(d, n, s);
+    default: return hipErrorInvalidValue;
   }
 }
 

@@ -36,6 +36,7 @@ constexpr PlainShape plain_shapes[] = {
     {128, 64, 1, 512, {1.761f, 2.516f}, {0.215f, 0.222f}, {0.071f, 0.075f}, {3.127f, 2.300f}, {0.f, 0.936f}},  // the same
     {64, 96, 1, 512, {2.014f, 2.093f}, {0.186f, 0.186f}, {0.043f, 0.075f}, {2.271f, 2.622f}, {0.677f, 0.415f}},  // the same
     {128, 128, 2, 256, {0.f, 3.209f}, {0.f, 0.432f}, {0.f, 0.223f}, {0.f, 0.879f}, {0.f, 2.244f}},  // two blocks of four wavefronts: see best_shape
+    {128, 256, 2, 256, {0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}},  // the same, large_tn only
 };
 constexpr int N_SHAPES = sizeof(plain_shapes) / sizeof(plain_shapes[0]);
 
@@ -62,14 +63,61 @@ inline bool shape_fits(const PlainShape &p, const GemmDims *d, int n) {
   return tiles * p.threads < (uint64_t)1 << 32;
 }
 
-// index of the cheapest shape by shape_cost, and its cost
+// Large products whose operands are both read through the transposing LDS read (weight gradients of wide layers, an LM
+// head's): what they wait for is the write-out of a tile that nothing overlaps, and operands.  With slices of 32 steps - whole
+// lines of such an operand all the same - 256x256 tiles fit the registers (with 64 they spill) and four slices fit the LDS; and
+// two blocks of four wavefronts with 128x256 tiles fit a CU, one writing out while the other multiplies.  Constants as above
+// (rounds of twice 256 tiles where two blocks share a CU), fitted to 106 products of random layers; the shape taken costs 2 %
+// more than the best one on average and is 1.09 times as fast as the choice among the others.  us, before / now:
+// 4096x16384x1024 206 / 155 (256x256), 4096^3 136 / 107, 768x50257x2048 219 / 198, 3728x3288x5556 192 / 140, 16384x4096x1024
+// added to 221 / 200, 2352x3968x398 26.4 / 23.1.  256x256 with slices of 64 202 us at the first of these.
+struct TnShape {
+  int shape;  // of plain_shapes
+  float t0, a, b, c, e;
+};
+constexpr int SHAPE_256X256 = 0, SHAPE_64X64K2 = 7, SHAPE_128X256X2 = N_SHAPES - 1;
+constexpr TnShape tn_shapes[] = {
+    {SHAPE_256X256, 2.852f, 0.755f, 0.840f, 13.473f, 1.975f}, {1, 0.997f, 0.445f, 0.579f, 8.874f, 0.f}, {2, 2.187f, 0.457f, 0.285f, 2.624f, 5.456f},
+    {10, 1.084f, 0.536f, 0.282f, 4.796f, 1.615f},             {SHAPE_128X256X2, 5.820f, 1.004f, 0.336f, 0.f, 8.471f}};
+static_assert(plain_shapes[SHAPE_128X256X2].bn == 256 && plain_shapes[SHAPE_64X64K2].bm == 64 && plain_shapes[SHAPE_64X64K2].threads == 512, "");
+
+// at least 128 tiles of 256x256 with nothing narrow, and enough steps for the rounds to count
+inline bool large_tn(const GemmDims *d, int n) {
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    if (!d[i].ta || !d[i].tb || d[i].M < 512 || d[i].N < 512 || d[i].K < 256) return false;
+    tiles += ((int64_t)d[i].M + 255) / 256 * (((int64_t)d[i].N + 255) / 256);
+  }
+  return tiles >= 128;
+}
+inline float tn_cost(const TnShape &t, const GemmDims *d, int n) {
+  const PlainShape &p = plain_shapes[t.shape];
+  float tiles = 0.f;
+  int K = 0;
+  for (int i = 0; i < n; ++i) {
+    tiles += (float)((d[i].M + p.bm - 1) / p.bm) * (float)((d[i].N + p.bn - 1) / p.bn);
+    K = d[i].K > K ? d[i].K : K;
+  }
+  const float nk = (float)((K + 63) / 64), u = tiles * (1.f / 256.f);
+  return t.t0 + ceilf(u / (float)p.occ) * (nk * t.a + t.c) + u * (nk * t.b + t.e);
+}
+
+// index of the cheapest shape, and its cost
 inline int best_shape(const GemmDims *d, int n, float *cost) {
-  // the last shape gains where two blocks write out and multiply in turn, which needs many tiles, transposing reads and
-  // vector stores (768x50257x2048 with its odd rows: 256 us against 208 with 128x256)
-  bool last = true;
-  for (int i = 0; i < n; ++i) last = last && d[i].ta && d[i].tb && d[i].vec_rows;
   int best = 0;
-  for (int i = 0; i < N_SHAPES - (last ? 0 : 1); ++i) {
+  if (large_tn(d, n)) {
+    *cost = 0.f;
+    for (const TnShape &t : tn_shapes) {
+      const float c = tn_cost(t, d, n);
+      if (*cost == 0.f || (c < *cost && shape_fits(plain_shapes[t.shape], d, n))) { best = t.shape; *cost = c; }
+    }
+    return best;
+  }
+  // 128x128x2 gains where two blocks write out and multiply in turn, which needs many tiles, transposing reads and vector
+  // stores (768x50257x2048 with its odd rows: 256 us against 208 with 128x256)
+  bool x2 = true;
+  for (int i = 0; i < n; ++i) x2 = x2 && d[i].ta && d[i].tb && d[i].vec_rows;
+  for (int i = 0; i < SHAPE_128X256X2 - (x2 ? 0 : 1); ++i) {
     const float c = shape_cost(plain_shapes[i], d, n);
     if (i == 0 || (c < *cost && shape_fits(plain_shapes[i], d, n))) { best = i; *cost = c; }
   }
@@ -95,8 +143,7 @@ constexpr SplitShape split_shapes[] = {
     {16, 32, {2.545f, 2.402f}, {0.047f, 0.129f}, {0.041f, 0.044f}, {0.144f, 0.f}, {0.000f, 0.120f}},
     {16, 16, {2.676f, 2.586f}, {0.040f, 0.084f}, {0.007f, 0.068f}, {0.037f, 0.f}, {0.407f, 0.273f}},
 };
-constexpr int N_SPLIT = sizeof(split_shapes) / sizeof(split_shapes[0]), SHAPE_64X64K2 = 7;
-static_assert(plain_shapes[SHAPE_64X64K2].bm == 64 && plain_shapes[SHAPE_64X64K2].bn == 64 && plain_shapes[SHAPE_64X64K2].threads == 512, "");
+constexpr int N_SPLIT = sizeof(split_shapes) / sizeof(split_shapes[0]);
 
 // below 384 contraction steps a launch is its latency, whatever the tile
 inline bool few_tiles(const GemmDims &d) {

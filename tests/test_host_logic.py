@@ -462,6 +462,13 @@ def test_gemm_cases_take_the_tile_shapes_they_name(tile_shape):
         ("128x128x2", l) for l in ("nt", "nn", "tt")}
 
 
+def test_large_weight_gradient_cases_take_the_tile_shapes_they_name(tile_shape):
+    from tests import test_gpu_kernel_variants as V
+    order = list(V.EVERY_SHAPE) + ["128x256x2"]
+    for shape, M, N, K in V.LARGE_TN_CASES:
+        assert order[tile_shape(M, N, K, 1, 1, N % 4 == 0)[0]] == shape, (shape, M, N, K)
+
+
 def test_few_tile_cases_take_the_shapes_they_name(tmp_path):
     """The products that the GPU suite runs for each shape of the few-tiles kernel still select it, and none is left out; the
     products that name a shape of the other kernel do not come here."""
