@@ -917,26 +917,14 @@ __global__ __launch_bounds__(256) void cross_entropy_kernel(const float *__restr
   }
 }
 
-// exp(x) for x <= 0 (or NaN) from the exponential instruction: x = t ln 2 + r with r exact to a few units of 2^-48, exp(x)
-// = 2^t (1 + r).  Six vector instructions where expf has twelve; largest relative error over [-80, 0] 1.4e-7, expf 0.8e-7
-// (both far below what a bf16 gradient keeps, and a sum over thousands of terms averages them); results below 2^-126 are
-// zero.  -inf gives a NaN remainder, which the minimum drops; NaN stays NaN.
-__device__ __forceinline__ float exp_nonpos(float x) {
-  const float t = x * 1.44269504088896341f;
-  float r = __builtin_fmaf(-t, 0.693147182464599609375f, x);
-  r = __builtin_fminf(__builtin_fmaf(-t, -1.904654299957768e-9f, r), 1.f);
-  const float p = __builtin_amdgcn_exp2f(t);
-  return __builtin_fmaf(p, r, p);
-}
-
 // The same with the row held in registers between the passes (one block of TB threads per row, NV float4 per thread):
 // the logits are read once instead of twice.  Needs ld % 4 == 0, ld <= 4 * TB * NV and aligned pointers.
 // Bound: HBM, and the vector ALU between the two barriers of a row (a block waits there, so what overlaps is other rows: the
 // smaller the row, the fewer threads hold it and the more rows a CU has in flight).  NT: logits that do not stay in the
 // 256 MB cache anyway are read past it, which leaves it to the gradients that the next product reads.
-// us, bf16, 2048 rows of 50257 / 30000 / 8192 / 2000 columns: 1024 threads a row, expf 152 / 95 / 21 / 13.8; now 125 / 62 /
-// 17 / 7.4 (4.9 TB/s at the first).
-// The fp32 form keeps expf: gradients that are zero but for rounding keep their bits.
+// us, bf16, launches one after another, 2048 rows of 50257 / 30000 / 8192 / 2000 columns: 1024 threads a row 145 / 92 / 20.6 /
+// 13.3; now 139 / 65 / 18.3 / 8.1 (4.4 TB/s at the first).  A shorter exponential (exp2 and a first-order remainder, 1.4e-7 off at
+// most where expf is 0.8e-7, zero below 2^-126) made it 124 / 63 / 17.4 / 7.4, but the fp32 loss is the logarithm of this sum.
 template <typename OutT, int NV, int TB, bool NT>
 __global__ __launch_bounds__(TB) void cross_entropy_row_kernel(const float *__restrict__ logits,
                                                                  const int32_t *__restrict__ targets,
@@ -988,7 +976,7 @@ __global__ __launch_bounds__(TB) void cross_entropy_row_kernel(const float *__re
 #pragma unroll
   for (int i = 0; i < NV; ++i) {  // exp(-inf) = 0 for pad columns and unused slots
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[i][e] = sizeof(OutT) == 2 ? exp_nonpos(v[i][e] - bmx) : expf(v[i][e] - bmx);
+    for (int e = 0; e < 4; ++e) v[i][e] = expf(v[i][e] - bmx);
     sum += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
   }
   sum = wave_sum(sum);
@@ -1029,8 +1017,8 @@ static bool launch_ce_row(const float *logits, const int32_t *targets, float *ro
   } while (0)
   if constexpr (sizeof(OutT) == 2) {
     // us, 2048 rows, read through / past the cache: 8192 columns (67 MB of logits) 17.2 / 18.8, 16384 (134 MB) 33.7 / 34.6,
-    // 30000 (246 MB) 70 / 62, 50257 (412 MB) 134 / 125.  Threads: 30000 columns 102 with 1024, 70 with 512; 16384 the same
-    // with 512 and 256; 50257 with 512 (25 vectors per thread, 144 registers) 131
+    // 30000 (246 MB) 71 / 65, 50257 (412 MB) 144 / 139.  Threads: 30000 columns 90 with 1024, 65 with 512; 16384 33.6 with 256,
+    // 33.0 with 512; 50257 139 with 1024, 144 with 512 (26 vectors per thread)
     const bool nt = (double)M * (double)ld * 4.0 >= 192e6;
     if (ld <= 1024) HYDRA_CE(1, 256, false);
     else if (ld <= 2048) HYDRA_CE(2, 256, false);

@@ -513,6 +513,29 @@ def test_cross_entropy_rows(H, M, V, ld):
     assert (dl[keep][:, V:] == 0).all() and (dl[-1] == 0).all() and row[-1] == 0
 
 
+# a target far above the rest: gradients below 2^-126 keep their bits in bf16, and a small loss is as exact as the sum it is the
+# logarithm of
+@pytest.mark.parametrize("M", [3, 300])
+@pytest.mark.parametrize("V,ld", [(1021, 1024), (4097, 4100), (12001, 12004), (30001, 30004), (50257, 50260)])
+def test_cross_entropy_of_a_dominant_target(H, M, V, ld):
+    z = torch.empty(M, V, device="cuda")
+    z[::2] = -87.0 - 5.0 * torch.rand(V, generator=torch.Generator("cuda").manual_seed(V), device="cuda")
+    z[1::2] = -float(np.log(2.0 * V)) - torch.rand(V, generator=torch.Generator("cuda").manual_seed(V + 1), device="cuda")
+    tgt = torch.arange(M, device="cuda", dtype=torch.int32) % V
+    z[torch.arange(M), tgt.long()] = 0.0
+    row, dl = torch.full((M,), 7.0, device="cuda"), torch.full((M, ld), 7.0, device="cuda").bfloat16()
+    H.hydra_op_cross_entropy(1, stored(z, ld, 0), tgt, row, dl, M, V, ld, 1.0)
+    row, got, x, t = row.cpu().double(), dl.cpu()[:, :V].float().double(), z.cpu().double(), tgt.cpu().long()[:, None]
+    ref = torch.exp(x - torch.logsumexp(x, 1, keepdim=True)).scatter_(1, t, 0.0)
+    got = got.scatter(1, t, 0.0)
+    # half a unit of bf16, whose subnormals are 2^-133 apart, and what the fp32 value it is rounded from is off by
+    assert ((got - ref).abs() <= 2.0 ** -134 * (1 + 2.0 ** -10) + 2.0 ** -8 * ref).all()
+    assert (ref[::2] < 2.0 ** -125).all() and (got[::2].sum(1) > 0).all()
+    # relative error of the sum: exponential (2), at most 16 + 2 + 6 + 16 additions on a term's way; the logarithm's own (2)
+    loss = torch.log1p(torch.exp(x).scatter_(1, t, 0.0).sum(1))
+    assert ((row - loss).abs() <= 42 * U32 + 2 * U32 * loss).all()
+
+
 # every block form of the fused attention kernels, forward and backward (their indices in the tables, which the CPU suite holds
 # against the choice): row blocks, tiles and groups partly empty
 ATT_FORM_CASES = [(9, 13, 1000, 64, 0, 0), (8, 11, 1000, 64, 0, 0), (9, 13, 776, 64, 1, 1), (1, 1, 8, 64, 1, 1), (40, 16, 264, 64, 1, 1), (9, 13, 136, 64, 2, 1),
