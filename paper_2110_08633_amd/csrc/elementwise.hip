@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdlib>
 
+#include "ce_threads.h"
 #include "kernels.h"
 
 namespace hydra {
@@ -919,8 +920,8 @@ __global__ __launch_bounds__(256) void cross_entropy_kernel(const float *__restr
 
 // The same with the row held in registers between the passes (one block of TB threads per row, NV float4 per thread):
 // the logits are read once instead of twice.  Needs ld % 4 == 0, ld <= 4 * TB * NV and aligned pointers.
-// Bound: HBM, and the vector ALU between the two barriers of a row (a block waits there, so what overlaps is other rows: the
-// smaller the row, the fewer threads hold it and the more rows a CU has in flight).  NT: logits that do not stay in the
+// Bound: HBM, and the vector ALU between the two barriers of a row (a block waits there, so what overlaps is other rows:
+// see ce_threads.h).  NT: logits that do not stay in the
 // 256 MB cache anyway are read past it, which leaves it to the gradients that the next product reads.
 // us, bf16, launches one after another, 2048 rows of 50257 / 30000 / 8192 / 2000 columns: 1024 threads a row 145 / 92 / 20.6 /
 // 13.3; now 139 / 65 / 18.3 / 8.1 (4.4 TB/s at the first).  A shorter exponential (exp2 and a first-order remainder, 1.4e-7 off at
@@ -1010,33 +1011,38 @@ static bool launch_ce_row(const float *logits, const int32_t *targets, float *ro
 #define HYDRA_CE(NV_, TB_, NT_)                                                                                       \
   hipLaunchKernelGGL((cross_entropy_row_kernel<OutT, NV_, TB_, NT_>), dim3(M), dim3(TB_), 0, s, logits, targets, row_loss, \
                      dlogits, V, ld, inv_n)
-#define HYDRA_CE_NT(NV_, TB_)            \
-  do {                                   \
-    if (nt) HYDRA_CE(NV_, TB_, true);    \
-    else HYDRA_CE(NV_, TB_, false);      \
+#define HYDRA_CE_NT(NV_, TB_)                             \
+  do {                                                    \
+    if (sizeof(OutT) == 2 && nt) HYDRA_CE(NV_, TB_, true); \
+    else HYDRA_CE(NV_, TB_, false);                       \
   } while (0)
+  bool nt = false;
   if constexpr (sizeof(OutT) == 2) {
     // us, 2048 rows, read through / past the cache: 8192 columns (67 MB of logits) 17.2 / 18.8, 16384 (134 MB) 33.7 / 34.6,
     // 30000 (246 MB) 71 / 65, 50257 (412 MB) 144 / 139.  Threads: 30000 columns 90 with 1024, 65 with 512; 16384 33.6 with 256,
     // 33.0 with 512; 50257 139 with 1024, 144 with 512 (26 vectors per thread)
-    const bool nt = (double)M * (double)ld * 4.0 >= 192e6;
-    if (ld <= 1024) HYDRA_CE(1, 256, false);
-    else if (ld <= 2048) HYDRA_CE(2, 256, false);
-    else if (ld <= 4096) HYDRA_CE_NT(4, 256);
-    else if (ld <= 8192) HYDRA_CE_NT(8, 256);
-    else if (ld <= 16384) HYDRA_CE_NT(8, 512);
-    else if (ld <= 32768) HYDRA_CE_NT(16, 512);
-    else if (ld <= 13 * 4096) HYDRA_CE_NT(13, 1024);
-    else HYDRA_CE_NT(16, 1024);
-  } else {
-    const int nv = (int)((ld / 4 + 1023) / 1024);
-    if (nv <= 1) HYDRA_CE(1, 1024, false);
-    else if (nv <= 2) HYDRA_CE(2, 1024, false);
-    else if (nv <= 4) HYDRA_CE(4, 1024, false);
-    else if (nv <= 8) HYDRA_CE(8, 1024, false);
-    else if (nv <= 13) HYDRA_CE(13, 1024, false);
-    else HYDRA_CE(16, 1024, false);
+    nt = (double)M * (double)ld * 4.0 >= 192e6;
+    const int tb = ce_row_threads(M, ld);
+    if (tb == 256) {
+      if (ld <= 1024) HYDRA_CE(1, 256, false);
+      else if (ld <= 2048) HYDRA_CE(2, 256, false);
+      else if (ld <= 4096) HYDRA_CE_NT(4, 256);
+      else HYDRA_CE_NT(8, 256);
+      return true;
+    }
+    if (tb == 512) {
+      if (ld <= 16384) HYDRA_CE_NT(8, 512);
+      else HYDRA_CE_NT(16, 512);
+      return true;
+    }
   }
+  const int nv = (int)((ld / 4 + 1023) / 1024);
+  if (nv <= 1) HYDRA_CE(1, 1024, false);
+  else if (nv <= 2) HYDRA_CE(2, 1024, false);
+  else if (nv <= 4) HYDRA_CE(4, 1024, false);
+  else if (nv <= 8) HYDRA_CE(8, 1024, false);
+  else if (nv <= 13) HYDRA_CE_NT(13, 1024);
+  else HYDRA_CE_NT(16, 1024);
 #undef HYDRA_CE_NT
 #undef HYDRA_CE
   return true;

@@ -475,11 +475,12 @@ def test_layernorm_bwd_more_blocks_than_a_row_of_the_grid_holds(H):
 
 
 # bf16 cross-entropy: rows, columns, leading dimension.  256 threads hold a row of up to 8192 columns, 512 up to 32768, 1024
-# up to 65536; from 192 MB of logits on they are read past the cache
+# up to 65536, and from 2049 on where there are no more than 256 rows; from 192 MB of logits on they are read past the cache
 @pytest.mark.parametrize("M,V,ld", [(3, 1, 4), (5, 1021, 1024), (5, 1025, 1028), (5, 2049, 2052), (5, 4097, 4100), (5, 8193, 8196),
                                     (5, 16385, 16388), (5, 32769, 32772), (5, 53249, 53252), (5, 65536, 65536),
                                     (12100, 3999, 4096), (5900, 8190, 8192), (2940, 16384, 16384), (1470, 32760, 32768),
-                                    (910, 53240, 53248), (740, 65000, 65024)])
+                                    (910, 53240, 53248), (740, 65000, 65024), (257, 2049, 2052), (257, 4097, 4100), (257, 8193, 8196),
+                                    (257, 16385, 16388)])
 def test_cross_entropy_rows(H, M, V, ld):
     z = stored(randn(V, M, V) * 2, ld, 0)
     tgt = torch.randint(0, V, (M,), device="cuda", dtype=torch.int32)

@@ -520,6 +520,27 @@ int main() {
         assert {c[5] for c in V.ATT_FORM_CASES if c[3] == dh} == set(range(bwd))
 
 
+def test_cross_entropy_threads_per_row(tmp_path):
+    """Few rows: a CU holds one at most, and 1024 threads are the fastest way through it (also from 2049 columns on, where 256
+    threads take 5 to 16 % longer); many rows: the fewer threads the more of them are in flight, as long as the row fits."""
+    src = tmp_path / "t.cpp"
+    src.write_text(r'''
+#include "ce_threads.h"
+#include <cstdio>
+int main() {
+  int M, ld;
+  while (scanf("%d %d", &M, &ld) == 2) printf("%d\n", hydra::ce_row_threads(M, ld));
+}
+''')
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2110_08633_amd", "csrc"),
+                           str(src), "-o", str(tmp_path / "t")])
+    cases = [(M, ld) for M in (1, 64, 256, 257, 2048, 100000) for ld in (4, 2048, 2052, 4100, 8192, 8196, 32768, 32772, 65536)]
+    out = subprocess.run([str(tmp_path / "t")], input="\n".join(f"{M} {ld}" for M, ld in cases), text=True, capture_output=True, check=True)
+    for (M, ld), tb in zip(cases, map(int, out.stdout.split())):
+        few = M <= 256
+        assert tb == (256 if ld <= 2048 else 1024 if few else 256 if ld <= 8192 else 512 if ld <= 32768 else 1024), (M, ld, tb)
+
+
 def test_bench_line_fits_a_log_tail():
     """bench.py's stdout line: the contract's keys and every workload's headline figures in a few kilobytes, however long
     the kernel tables of the full report are."""
