@@ -554,6 +554,34 @@ def test_attention_every_form(H, B, Hn, T, dh):
         test_attention_unaligned_tensors(H, B, Hn, T, dh, 1)
 
 
+# a row whose weight sits almost wholly on one of its first 128 keys: that weight is exact in every form, so the result is off
+# by its own rounding only
+@pytest.mark.parametrize("B,Hn,T,dh", [c[:4] for c in ATT_FORM_CASES if c[2] >= 136])
+def test_attention_heaviest_weight_is_exact(H, B, Hn, T, dh):
+    n = B * T
+    qkv = torch.zeros(B, T, 3, Hn, dh, device="cuda")
+    qkv[:, :, 2] = randn(T, B, T, Hn, dh)
+    g = torch.Generator("cuda").manual_seed(T + dh)
+    # score of a row's key 0: 0, of one key: 4.6 to 5.4 (e^5.4 = 221 stays below the 2^8 that would move any reference), others -8
+    qkv[:, :, 0, :, 0] = (4.6 + 0.8 * torch.rand(B, T, Hn, generator=g, device="cuda")) * dh ** 0.5
+    qkv[:, :, 0, :, 1] = dh ** 0.5
+    qkv[:, 1:, 1, :, 1] = -8.0
+    for heavy in (17, 33, 64, 70, 95, 96, 127):
+        x = qkv.clone()
+        x[:, heavy, 1, :, 0], x[:, heavy, 1, :, 1] = 1.0, 0.0
+        x = x.bfloat16()
+        o, lse = torch.empty(n, Hn * dh, device="cuda").bfloat16(), torch.empty(B * Hn * T, device="cuda")
+        H.hydra_op_attention_fwd(x, o, lse, B, Hn, T, dh)
+        q, k, v = (x[:, :, j].double().transpose(1, 2) for j in range(3))
+        s = (q[:, :, heavy:] @ k.transpose(2, 3).contiguous()) / dh ** 0.5
+        s = s.masked_fill(torch.ones(T, T, dtype=torch.bool, device="cuda").triu(1)[heavy:], float("-inf"))
+        ref = torch.softmax(s, -1) @ v
+        got = o.view(B, T, Hn, dh).transpose(1, 2)[:, :, heavy:].double()
+        # the other weights are 1.5 % at most and rounded to 8 bits themselves (2^-9 of them); were the heavy one rounded, its
+        # 0.29 units of 1 / 100 to 1 / 221 would come on top of the result's rounding: 1.2 to 1.4 times as much
+        assert (got - ref).norm() <= 1.02 * (ref.bfloat16().double() - ref).norm(), heavy
+
+
 # products with few tiles: every tile shape in every layout, ragged on every side, with contractions that leave most of the
 # eight wavefronts a slice, end within a slice, or are long (the CPU suite holds this table against the choice)
 SPLIT_CASES = [("64x32w8", "nt", 387, 900, 392), ("64x32w8", "nn", 387, 900, 712), ("64x32w8", "tt", 387, 900, 456),
