@@ -36,23 +36,32 @@ inline float attn_form_cost(const AttnForm &f, int pairs, int T) {
 // index of the cheapest form.  Several groups per block only while the blocks are resident at once or nearly so (what a second
 // round of them costs is not in the estimate): B 5, H 25, T 368, dh 128 (750 blocks) 16.6 with one group, 22.9 with two; long
 // sequences gain even then: B 1, H 25, T 1960 (775) 50 / 46; head width 64 has room for more: B 3, H 12, T 2016 (1152) 39 / 31,
-// but B 5, H 25, T 456 (1000) 13.2 / 15.9
+// but B 5, H 25, T 456 (1000) 13.2 / 15.9.
+// For the same reason, from one block of 128 rows per CU on, another form has to be estimated below `whole` times the first one:
+// us, forward B 3, H 25, T 1024, dh 64 22.0 with the first form, 26.2 with two groups (estimates 22.3, 21.5), backward B 7, H 25,
+// T 328, dh 64 34.5 / 40.0 with 64-row blocks (32.4, 32.0), B 7, H 12, T 672, dh 128 74.5 / 83.0 (84.4, 83.3).  Of 2400 random
+// calls, forward and backward, 174 were more than 3 % (73 more than 5 %) slower than with the two forms before this table, now
+// 48 (23); the form taken is 0.2 to 0.3 % off the best one on average.
 template <int N>
-inline int best_attn_form(const AttnForm (&f)[N], int dh, int pairs, int T) {
+inline int best_attn_form(const AttnForm (&f)[N], int dh, int pairs, int T, float whole) {
   const int64_t blocks = ((int64_t)T + 63) / 64 * pairs, limit = dh == 64 ? (T >= 576 ? 1280 : 900) : (T >= 768 ? 900 : 512);
+  const bool filled = ((int64_t)T + 127) / 128 * pairs >= 256;
   int best = 0;
   float cost = 0.f;
   for (int i = 0; i < N; ++i) {
-    const float c = attn_form_cost(f[i], pairs, T);
+    const float c = attn_form_cost(f[i], pairs, T) * (i == 0 && filled ? whole : 1.f);
     if (i == 0 || (c < cost && (f[i].kw == 1 || blocks <= limit))) { best = i; cost = c; }
   }
   return best;
 }
 inline int attn_form_fwd(int dh, int pairs, int T) {
-  return dh == 64 ? best_attn_form(attn_forms_fwd64, dh, pairs, T) : best_attn_form(attn_forms_fwd128, dh, pairs, T);
+  return dh == 64 ? best_attn_form(attn_forms_fwd64, dh, pairs, T, 0.92f) : best_attn_form(attn_forms_fwd128, dh, pairs, T, 1.f);
 }
+// head width 64, backward: a sequence of one 64-row tile is one step of the first form and two of the others (B 4, H 12, T 56
+// 9.4 / 9.9), up to 32 rows it is one of each and the smaller block is done sooner (7.9 / 6.8)
 inline int attn_form_bwd(int dh, int pairs, int T) {
-  return dh == 64 ? best_attn_form(attn_forms_bwd64, dh, pairs, T) : best_attn_form(attn_forms_bwd128, dh, pairs, T);
+  if (dh == 64 && T > 32 && T <= 64) return 0;
+  return dh == 64 ? best_attn_form(attn_forms_bwd64, dh, pairs, T, 0.92f) : best_attn_form(attn_forms_bwd128, dh, pairs, T, 0.95f);
 }
 
 }  // namespace hydra

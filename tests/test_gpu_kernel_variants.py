@@ -539,9 +539,9 @@ def test_cross_entropy_of_a_dominant_target(H, M, V, ld):
 
 # every block form of the fused attention kernels, forward and backward (their indices in the tables, which the CPU suite holds
 # against the choice): row blocks, tiles and groups partly empty
-ATT_FORM_CASES = [(9, 13, 1000, 64, 0, 0), (8, 11, 1000, 64, 0, 0), (9, 13, 776, 64, 1, 1), (1, 1, 8, 64, 1, 1), (40, 16, 264, 64, 1, 1), (9, 13, 136, 64, 2, 1),
-                  (5, 7, 136, 64, 2, 2), (9, 13, 584, 64, 2, 2), (1, 1, 136, 64, 2, 3), (1, 1, 200, 64, 3, 3), (1, 1, 520, 64, 4, 3),
-                  (1, 3, 1096, 64, 4, 3), (9, 7, 584, 128, 0, 0), (9, 13, 328, 128, 0, 1), (1, 1, 8, 128, 1, 1), (9, 13, 72, 128, 1, 1),
+ATT_FORM_CASES = [(9, 13, 1000, 64, 0, 0), (8, 11, 1000, 64, 0, 0), (9, 13, 776, 64, 0, 0), (25, 8, 520, 64, 1, 1), (1, 1, 8, 64, 1, 1), (40, 16, 264, 64, 1, 1), (9, 13, 136, 64, 2, 1),
+                  (5, 7, 136, 64, 2, 2), (9, 13, 584, 64, 0, 0), (7, 11, 456, 64, 2, 2), (3, 8, 56, 64, 1, 0), (1, 1, 136, 64, 2, 3), (1, 1, 200, 64, 3, 3), (1, 1, 520, 64, 4, 3),
+                  (1, 3, 1096, 64, 4, 3), (9, 7, 584, 128, 0, 0), (9, 13, 328, 128, 0, 0), (1, 1, 8, 128, 1, 1), (9, 13, 72, 128, 1, 1),
                   (1, 1, 136, 128, 2, 2), (5, 7, 520, 128, 2, 2)]
 
 

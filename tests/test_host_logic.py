@@ -497,6 +497,11 @@ int main() {
     assert {(c[0], c[1]) for c in V.SPLIT_CASES} >= {(s, l) for i, s in names.items() if i > 0 for l in ("nt", "nn", "tt", "tn")}
 
 
+# calls whose 128-row blocks fill the chip, and one-tile backward calls: measured 8 to 18 % (4 %) slower with the other forms
+WHOLE_BLOCKS = [(3, 25, 1024, 64, 0, 0), (5, 25, 832, 64, 0, 0), (7, 25, 560, 64, 0, 0), (7, 25, 328, 64, None, 0), (6, 25, 576, 64, None, 0),
+                (7, 32, 240, 64, 0, 0), (7, 12, 672, 128, None, 0), (7, 12, 648, 128, None, 0), (4, 12, 56, 64, 1, 0), (4, 12, 40, 64, 1, 0)]
+
+
 def test_attention_cases_take_the_forms_they_name(tmp_path):
     """The calls that the GPU suite runs for each block form of the attention kernels still select it, and no form is left out."""
     from tests import test_gpu_kernel_variants as V
@@ -511,10 +516,11 @@ int main() {
 ''')
     subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2110_08633_amd", "csrc"),
                            str(src), "-o", str(tmp_path / "t")])
-    ask = "\n".join(f"{dh} {B * H} {T}" for B, H, T, dh, _, _ in V.ATT_FORM_CASES)
+    cases = V.ATT_FORM_CASES + WHOLE_BLOCKS
+    ask = "\n".join(f"{dh} {B * H} {T}" for B, H, T, dh, _, _ in cases)
     out = subprocess.run([str(tmp_path / "t")], input=ask, text=True, capture_output=True, check=True).stdout.split("\n")
-    for c, line in zip(V.ATT_FORM_CASES, out):
-        assert line == f"{c[4]} {c[5]}", (c, line)
+    for c, line in zip(cases, out):
+        assert c[4] in (None, int(line[0])) and c[5] in (None, int(line[2])), (c, line)
     for dh, fwd, bwd in ((64, 5, 4), (128, 3, 3)):
         assert {c[4] for c in V.ATT_FORM_CASES if c[3] == dh} == set(range(fwd))
         assert {c[5] for c in V.ATT_FORM_CASES if c[3] == dh} == set(range(bwd))
