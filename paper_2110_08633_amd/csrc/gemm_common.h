@@ -325,7 +325,7 @@ constexpr int GEMM_GROUP_MAX = 4;
 // the single-product kernel (gemm_plain.hip): any layout, any K, no batching and no causal short-cut
 bool gemm_plain_ok(const GemmDesc &d);
 hipError_t launch_gemm_plain(const GemmDesc &d, hipStream_t s);
-// n products with both operands stored contraction-strided in one launch where that is estimated to be faster
+// n products with both operands stored contraction-strided, in one launch
 hipError_t launch_gemm_plain_group(const GemmDesc *d, int n, hipStream_t s);
 // the kernel for products with few tiles (gemm_split.hip); shape: index into split_shapes
 hipError_t launch_gemm_split(const GemmDesc &d, int shape, hipStream_t s);

@@ -632,6 +632,12 @@ def test_gemm_bf16_large_weight_gradients_repeat_bitwise_under_concurrency(H, sh
     test_gemm_bf16_repeats_bitwise_under_concurrency(H, shape, "tn", M, N, K)
 
 
+# a group that four launches were once estimated to be faster for (they take 1.2 times as long)
+def test_weight_gradients_of_a_block_stay_together(H):
+    names = one_block_step(H, 1160, 4640, 776)
+    assert sum(n for name, n in names.items() if name.endswith("_tn_group")) == 1, names
+
+
 @pytest.mark.parametrize("shape,d,F,M", [("256x256", 1024, 3592, 264), ("128x256x2", 1024, 2056, 264)])
 def test_grouped_large_weight_gradients(H, shape, d, F, M):
     assert one_block_step(H, d, F, M).get(f"gemm_bf16_{shape}_tn_group") == 1
