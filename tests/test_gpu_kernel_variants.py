@@ -617,9 +617,9 @@ def test_gelu_epilogues_of_few_tiles(H, shape, d, F, M):
 # large products of contraction-strided operands (at least 128 tiles of 256x256): the shapes with slices of 32 steps, an odd and
 # an even number of them, the last one partly empty, and the others that large_tn may choose (the CPU suite holds this table
 # against the choice); then the weight gradients of a block in one launch
-LARGE_TN_CASES = [("256x256", 3001, 4100, 257), ("256x256", 3001, 4100, 289), ("128x256x2", 3001, 3004, 257),
-                  ("128x256x2", 3001, 3004, 289), ("128x192", 2051, 4100, 257), ("128x128x2", 515, 13000, 257),
-                  ("128x256", 515, 13000, 701)]
+LARGE_TN_CASES = [("256x256", 641, 17132, 257), ("256x256", 641, 17132, 289), ("128x256x2", 1300, 17864, 257),
+                  ("128x256x2", 1300, 17864, 289), ("128x192", 515, 18352, 257), ("128x128x2", 515, 10788, 257),
+                  ("128x256", 515, 12496, 257)]
 
 
 @pytest.mark.parametrize("shape,M,N,K", LARGE_TN_CASES)
@@ -627,7 +627,7 @@ def test_gemm_bf16_large_weight_gradients(H, shape, M, N, K):
     test_gemm_bf16_every_tile_shape(H, shape, "tn", M, N, K)
 
 
-@pytest.mark.parametrize("shape,M,N,K", [("256x256", 3001, 4104, 257), ("128x256x2", 3001, 3008, 257)])
+@pytest.mark.parametrize("shape,M,N,K", [("256x256", 641, 17136, 257), ("128x256x2", 1300, 17864, 257)])
 def test_gemm_bf16_large_weight_gradients_repeat_bitwise_under_concurrency(H, shape, M, N, K):
     test_gemm_bf16_repeats_bitwise_under_concurrency(H, shape, "tn", M, N, K)
 
@@ -638,6 +638,6 @@ def test_weight_gradients_of_a_block_stay_together(H):
     assert sum(n for name, n in names.items() if name.endswith("_tn_group")) == 1, names
 
 
-@pytest.mark.parametrize("shape,d,F,M", [("256x256", 1024, 3592, 264), ("128x256x2", 1024, 2056, 264)])
+@pytest.mark.parametrize("shape,d,F,M", [("256x256", 1160, 2744, 264), ("128x256x2", 1544, 4480, 264)])
 def test_grouped_large_weight_gradients(H, shape, d, F, M):
     assert one_block_step(H, d, F, M).get(f"gemm_bf16_{shape}_tn_group") == 1

@@ -469,6 +469,17 @@ def test_large_weight_gradient_cases_take_the_tile_shapes_they_name(tile_shape):
         assert order[tile_shape(M, N, K, 1, 1, N % 4 == 0)[0]] == shape, (shape, M, N, K)
 
 
+@pytest.mark.parametrize("M,N,K,shape", [(1936, 9792, 2578, "128x128x2"), (11576, 1568, 3495, "128x128x2"), (13752, 1472, 2625, "128x128x2"),
+                                         (8512, 2599, 2425, "128x256"), (3001, 3004, 289, "128x128x2"), (14024, 568, 292, "128x64"),
+                                         (4096, 16384, 1024, "256x256"), (3728, 3288, 5556, "256x256")])
+def test_large_weight_gradients_keep_the_shape_that_is_faster(tile_shape, M, N, K, shape):
+    """Measured: the first six take 9 to 15 % longer with 256x256 (two with 128x192 or 128x256x2) tiles, the last two 11 and 26 %
+    longer without."""
+    from tests import test_gpu_kernel_variants as V
+    order = list(V.EVERY_SHAPE) + ["128x256x2"]
+    assert order[tile_shape(M, N, K, 1, 1, N % 4 == 0)[0]] == shape
+
+
 def test_few_tile_cases_take_the_shapes_they_name(tmp_path):
     """The products that the GPU suite runs for each shape of the few-tiles kernel still select it, and none is left out; the
     products that name a shape of the other kernel do not come here."""
