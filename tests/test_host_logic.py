@@ -506,6 +506,13 @@ int main() {
     for c, i in zip(cases, out):
         assert (names[int(i)] == c[0]) if c in V.SPLIT_CASES else int(i) == -2, (c, i)
     assert {(c[0], c[1]) for c in V.SPLIT_CASES} >= {(s, l) for i, s in names.items() if i > 0 for l in ("nt", "nn", "tt", "tn")}
+    # products of a block and of a head of 64 words: the MLP's first (forward and, with the derivative, backward) and no other
+    for shape, d, F, M in V.GELU_SPLIT_CASES:
+        others = [(M, 3 * d, d), (M, d, d), (M, d, F), (M, d, 3 * d), (M, 64, d), (M, d, 64)]
+        ask = "\n".join(f"{m} {n} {k} 0 0" for m, n, k in [(M, F, d)] + others)
+        got = [int(i) for i in subprocess.run([str(tmp_path / "t")], input=ask, text=True, capture_output=True, check=True).stdout.split()]
+        assert names[got[0]] == shape and all(names.get(i) != shape for i in got[1:]), (shape, got)
+    assert {c[0] for c in V.GELU_SPLIT_CASES} == {s for i, s in names.items() if i > 0}
 
 
 # calls whose 128-row blocks fill the chip, and one-tile backward calls: measured 8 to 18 % (4 %) slower with the other forms
