@@ -10,8 +10,8 @@
 //
 // Operand conventions: v_mfma_f32_32x32x16_bf16 with the column operand first, so a
 // lane holds row L%32 of a 32x32 result and columns (r/4)*8 + (L/32)*4 + r%4 for
-// r = 0..15.  Tiles of 64 rows go straight to LDS (one copy, read both along the
-// head dimension and, transposing, along the rows); probabilities stay in the
+// r = 0..15.  Tiles of 32 or 64 rows go straight to LDS (one copy, read both along
+// the head dimension and, transposing, along the rows); probabilities stay in the
 // registers they are computed in.
 #include <cfloat>
 
@@ -52,10 +52,10 @@ __device__ __forceinline__ bf16x8_t row_operand(const float (&p)[16], int s) {
   return x.f;
 }
 
-// A [TK rows][DH] bf16 tile of a row-major matrix in LDS, loaded by RW wavefronts: DH/64 slices [row][64] whose 16-byte chunks are swizzled so
-// that both ways of reading it are free of bank conflicts - as operand of a product over the head dimension (16 bytes
-// per lane: rows of one parity need distinct slots) and, through the transposing read, of a product over the rows (32
-// bytes of rows k..k+3 each, two column groups at a time).  One copy serves both.
+// A [TK rows][DH] bf16 tile of a row-major matrix in LDS, loaded by RW wavefronts: DH/64 slices [row][64] whose 16-byte
+// chunks are swizzled so that both ways of reading it are free of bank conflicts - as operand of a product over the head
+// dimension (16 bytes per lane: rows of one parity need distinct slots) and, through the transposing read, of a product
+// over the rows (32 bytes of rows k..k+3 each, two column groups at a time).  One copy serves both.
 template <int DH, int RW, int TK>
 struct RowTile {
   static constexpr int SIZE = TK * DH;            // elements
@@ -158,11 +158,11 @@ __device__ __forceinline__ bool block_place(int pairs, int nb, int &z, int &rb) 
 // tiles g, g + KW, ... and the partial results are merged through LDS at the end
 // (launches that would leave CUs without work; which form when: attn_forms.h).
 // Bound: per 64 keys and wavefront 1024 clocks of MFMAs at head width 128 (512 at 64) and 960 of vector ALU, which overlap
-// only between the wavefronts of a SIMD; counters at B 4, H 16, T 2048, dh 128 with tiles of 64 keys (two blocks per CU):
-// matrix pipes 0.43 busy, vector ALU 0.41, LDS 0.22.  That launch: 82 us with tiles of 64 keys, 79 with 32, whose LDS lets
-// three blocks share a CU (168 registers; held to 128 for a fourth block it spills: 132 us).  Measured without gain: tiles
-// two and three ahead, raised wavefront priority around the MFMAs, MFMAs and exponentials interleaved by scheduling
-// directives (spills).
+// only between the wavefronts of a SIMD; counters at B 4, H 16, T 2048, dh 128: matrix pipes 0.47 busy, vector ALU 0.51,
+// LDS 0.24 (with tiles of 64 keys and two blocks per CU 0.43, 0.41, 0.22).  That launch, in a row of such: 82 us with tiles
+// of 64 keys, 79 with 32, whose LDS lets three blocks share a CU (165 registers; held to 128 for a fourth block it spills:
+// 132 us).  Measured without gain: tiles two and three ahead, raised wavefront priority around the MFMAs, MFMAs and
+// exponentials interleaved by scheduling directives (spills).
 // ---------------------------------------------------------------------------
 template <int DH, int RW, int KW, int TK, bool DIRECT>
 __global__ __launch_bounds__(64 * RW * KW, 2) void attn_fwd_kernel(const bf16_t *__restrict__ qkv, bf16_t *__restrict__ o,
@@ -266,7 +266,8 @@ __global__ __launch_bounds__(64 * RW * KW, 2) void attn_fwd_kernel(const bf16_t 
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[nd][r] *= alpha;
     }
-    float sum = NT == 1 ? part : 0.f;  // of 64 keys, whatever the tile: half as many additions to l (error of lse 1.055 -> 0.96)
+    // of 64 keys, whatever the tile: half as many additions to l (error of lse 1.055 -> 0.96)
+    float sum = NT == 1 ? part : 0.f;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       float p[16];
@@ -358,8 +359,9 @@ __device__ __forceinline__ bool merge_groups(f32x16_t (&acc)[NA], int grp, float
 // ---------------------------------------------------------------------------
 // backward, part 1: dQ.  Same decomposition as the forward kernel.  Per tile:
 // p = exp(s - L), dP = dO V^T, dS = p (dP - D) / sqrt(dh) with
-// D_i = sum_c dO[i,c] O[i,c] (written out for part 2), dQ += dS K.  B 4, H 16, T 2048, dh 128: 117 us, whether with 64 or with
-// 32 keys per tile (three blocks per CU would need 168 registers: 180 us with the spills).
+// D_i = sum_c dO[i,c] O[i,c] (written out for part 2), dQ += dS K.  B 4, H 16, T 2048, dh 128, launched alone: 117 us,
+// whether with 64 or with 32 keys per tile (three blocks per CU would need 168 registers: 180 us with the spills); among
+// other kernels 121 to 126.
 // ---------------------------------------------------------------------------
 template <int DH, int RW, int KW, int TK, bool DIRECT>
 __global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dq_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
@@ -481,8 +483,8 @@ __global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dq_kernel(const bf16
 // to the end of the sequence, computing the transposed quantities directly:
 // s^T = K Q^T, p^T = exp(s^T - L), dP^T = V dO^T, dS^T = p^T (dP^T - D)/sqrt(dh),
 // dV += p^T dO, dK += dS^T Q.  No atomics: every key row has one owner.  At head width 64 large launches hold the kernel to
-// 168 registers (203 left alone), so that three blocks share a CU: B 8, H 25, T 1024 90.6 -> 84.9 us.  At 128 it is 157 us at
-// B 4, H 16, T 2048 with two blocks per CU and tiles of 64 queries, 173 with 32.
+// 168 registers (203 left alone), so that three blocks share a CU: B 8, H 25, T 1024 90.6 -> 84.9 us.  At 128, launched alone, it is 157 us
+// at B 4, H 16, T 2048 with two blocks per CU and tiles of 64 queries, 173 with 32; among other kernels 170 to 180.
 // ---------------------------------------------------------------------------
 template <int DH, int RW, int KW, int TK, bool DIRECT, int OCC>
 __global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
@@ -557,8 +559,9 @@ __global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_dkv_kernel(const b
     const float *const ls = Ls + ((it & 1) * KW + grp) * 2 * TK;
     if (i0 + TK - 1 >= kr0 && i0 < T) {  // else no query of the tile comes after a key of this wavefront
       // one half tile at a time: unrolled, the two halves' results do not fit the 256 registers two wavefronts per SIMD
-      // leave at head width 128 (the two backward kernels at B 4, H 16, T 2048, dh 128: 289 -> 270 us).  Even so one to
-      // three registers are spilled there (8 to 16 bytes of scratch per lane); at head width 64 none
+      // leave at head width 128 (the two backward kernels at B 4, H 16, T 2048, dh 128: 289 -> 270 us).  Even so one register
+      // is spilled there with tiles of 64 rows, three or four with 32 (8 to 20 bytes of scratch per lane; two and four off the
+      // 16-byte grid); at head width 64 none
 #pragma unroll 1
       for (int nt = 0; nt < NT; ++nt) {
         f32x16_t s, dp;

@@ -15,17 +15,27 @@ struct AttnForm {
   float a, b, c;
 };
 // Large launches: one group of four wavefronts, two to four blocks per CU; tiles of 64 rows, forward at head width 128 of 32
-// (three blocks per CU; at 64 the two are within 1 %: B 8, H 25, T 1024 forward and backward 176 us with 64, 178 with 32).  Few rows: 64-row blocks, twice as many, whose tiles two or four groups share.  The former forms
-// (128-row blocks with one or two groups) / these, us, forward then backward:
-//   B 4, H 12, T 512, dh 64 10.0 / 8.4, 27.9 / 23.8;  B 1, H 12, T 1024, dh 64 14.4 / 10.6, 39.8 / 30.4;
-//   B 4, H 12, T 1024, dh 64 17.0 / 15.9, 49.2 / 46.3;  B 1, H 16, T 2048, dh 128 39.8 / 32.9, 116 / 106;
-//   B 4, H 16, T 2048, dh 128 92 / 82, 268 / 268;  means over the 114 calls 1.16 and 1.15 times as fast
-constexpr AttnForm attn_forms_fwd64[] = {{4, 1, 64, 3.147f, 0.762f, 0.666f}, {2, 1, 32, 2.866f, 0.495f, 0.193f}, {2, 2, 32, 3.569f, 0.455f, 0.388f},
-                                         {2, 2, 64, 3.828f, 0.728f, 0.868f}, {2, 4, 32, 4.803f, 0.440f, 0.908f}};
-constexpr AttnForm attn_forms_fwd128[] = {{4, 1, 32, 3.860f, 0.667f, 0.572f}, {2, 1, 32, 3.347f, 0.668f, 0.368f}, {2, 2, 32, 4.604f, 0.620f, 0.804f}};
-constexpr AttnForm attn_forms_bwd64[] = {{4, 1, 64, 9.038f, 2.508f, 1.942f}, {2, 1, 32, 7.018f, 1.600f, 0.578f}, {2, 2, 32, 9.966f, 1.309f, 1.260f},
+// (three blocks per CU; at 64 the two are within 1 %: B 8, H 25, T 1024 forward and backward 176 us with 64, 178 with 32).
+// Few rows: 64-row blocks, twice as many, whose tiles two or four groups share.  The former forms (128-row blocks and 64-row
+// tiles, one or two groups) / these, us, launched one after another, forward then backward:
+//   B 4, H 12, T 512, dh 64 10.6 / 9.3, 28.3 / 24.5;  B 4, H 12, T 1024, dh 64 17.9 / 16.2, 49.1 / 48.8;
+//   B 1, H 16, T 2048, dh 128 41.7 / 35.8, 116 / 106;  B 4, H 16, T 2048, dh 128 82 / 79, 258 / 258;
+//   600 random calls: 1.12 times as fast at head width 64 either way, 1.17 and 1.16 at 128
+constexpr AttnForm attn_forms_fwd64[] = {{4, 1, 64, 3.147f, 0.762f, 0.666f},
+                                         {2, 1, 32, 2.866f, 0.495f, 0.193f},
+                                         {2, 2, 32, 3.569f, 0.455f, 0.388f},
+                                         {2, 2, 64, 3.828f, 0.728f, 0.868f},
+                                         {2, 4, 32, 4.803f, 0.440f, 0.908f}};
+constexpr AttnForm attn_forms_fwd128[] = {{4, 1, 32, 3.860f, 0.667f, 0.572f},
+                                          {2, 1, 32, 3.347f, 0.668f, 0.368f},
+                                          {2, 2, 32, 4.604f, 0.620f, 0.804f}};
+constexpr AttnForm attn_forms_bwd64[] = {{4, 1, 64, 9.038f, 2.508f, 1.942f},
+                                         {2, 1, 32, 7.018f, 1.600f, 0.578f},
+                                         {2, 2, 32, 9.966f, 1.309f, 1.260f},
                                          {2, 2, 64, 10.099f, 1.855f, 2.576f}};
-constexpr AttnForm attn_forms_bwd128[] = {{4, 1, 64, 11.223f, 4.395f, 3.716f}, {2, 1, 32, 9.295f, 2.444f, 1.181f}, {2, 2, 32, 14.782f, 2.022f, 2.582f}};
+constexpr AttnForm attn_forms_bwd128[] = {{4, 1, 64, 11.223f, 4.395f, 3.716f},
+                                          {2, 1, 32, 9.295f, 2.444f, 1.181f},
+                                          {2, 2, 32, 14.782f, 2.022f, 2.582f}};
 
 inline float attn_form_cost(const AttnForm &f, int pairs, int T) {
   const float R = 32.f * f.rw, W = (float)f.kw * f.tk, nb = ceilf(T / R);
@@ -37,11 +47,11 @@ inline float attn_form_cost(const AttnForm &f, int pairs, int T) {
 // round of them costs is not in the estimate): B 5, H 25, T 368, dh 128 (750 blocks) 16.6 with one group, 22.9 with two; long
 // sequences gain even then: B 1, H 25, T 1960 (775) 50 / 46; head width 64 has room for more: B 3, H 12, T 2016 (1152) 39 / 31,
 // but B 5, H 25, T 456 (1000) 13.2 / 15.9.
-// For the same reason, from one block of 128 rows per CU on, another form has to be estimated below `whole` times the first one:
-// us, forward B 3, H 25, T 1024, dh 64 22.0 with the first form, 26.2 with two groups (estimates 22.3, 21.5), backward B 7, H 25,
-// T 328, dh 64 34.5 / 40.0 with 64-row blocks (32.4, 32.0), B 7, H 12, T 672, dh 128 74.5 / 83.0 (84.4, 83.3).  Of 2400 random
-// calls, forward and backward, 174 were more than 3 % (73 more than 5 %) slower than with the two forms before this table, now
-// 48 (23); the form taken is 0.2 to 0.3 % off the best one on average.
+// For the same reason, from one block of 128 rows per CU on, another form has to be estimated below `whole` times the first
+// one: us, forward B 3, H 25, T 1024, dh 64 22.0 with the first form, 26.2 with two groups (estimates 22.3, 21.5), backward
+// B 7, H 25, T 328, dh 64 34.5 / 40.0 with 64-row blocks (32.4, 32.0), B 7, H 12, T 672, dh 128 74.5 / 83.0 (84.4, 83.3).  Of
+// 2400 random calls, forward and backward, 174 were more than 3 % (73 more than 5 %) slower than with the two forms before
+// this table, now 48 (23); the form taken is 0.2 to 0.3 % off the best one on average.
 template <int N>
 inline int best_attn_form(const AttnForm (&f)[N], int dh, int pairs, int T, float whole) {
   const int64_t blocks = ((int64_t)T + 63) / 64 * pairs, limit = dh == 64 ? (T >= 576 ? 1280 : 900) : (T >= 768 ? 900 : 512);
@@ -55,13 +65,15 @@ inline int best_attn_form(const AttnForm (&f)[N], int dh, int pairs, int T, floa
   return best;
 }
 inline int attn_form_fwd(int dh, int pairs, int T) {
-  return dh == 64 ? best_attn_form(attn_forms_fwd64, dh, pairs, T, 0.92f) : best_attn_form(attn_forms_fwd128, dh, pairs, T, 1.f);
+  return dh == 64 ? best_attn_form(attn_forms_fwd64, dh, pairs, T, 0.92f)
+                  : best_attn_form(attn_forms_fwd128, dh, pairs, T, 1.f);
 }
 // head width 64, backward: a sequence of one 64-row tile is one step of the first form and two of the others (B 4, H 12, T 56
 // 9.4 / 9.9), up to 32 rows it is one of each and the smaller block is done sooner (7.9 / 6.8)
 inline int attn_form_bwd(int dh, int pairs, int T) {
   if (dh == 64 && T > 32 && T <= 64) return 0;
-  return dh == 64 ? best_attn_form(attn_forms_bwd64, dh, pairs, T, 0.92f) : best_attn_form(attn_forms_bwd128, dh, pairs, T, 0.95f);
+  return dh == 64 ? best_attn_form(attn_forms_bwd64, dh, pairs, T, 0.92f)
+                  : best_attn_form(attn_forms_bwd128, dh, pairs, T, 0.95f);
 }
 
 }  // namespace hydra

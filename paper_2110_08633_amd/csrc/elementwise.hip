@@ -921,11 +921,12 @@ __global__ __launch_bounds__(256) void cross_entropy_kernel(const float *__restr
 // The same with the row held in registers between the passes (one block of TB threads per row, NV float4 per thread):
 // the logits are read once instead of twice.  Needs ld % 4 == 0, ld <= 4 * TB * NV and aligned pointers.
 // Bound: HBM, and the vector ALU between the two barriers of a row (a block waits there, so what overlaps is other rows:
-// see ce_threads.h).  NT: logits that do not stay in the
-// 256 MB cache anyway are read past it, which leaves it to the gradients that the next product reads.
-// us, bf16, launches one after another, 2048 rows of 50257 / 30000 / 8192 / 2000 columns: 1024 threads a row 145 / 92 / 20.6 /
-// 13.3; now 139 / 65 / 18.3 / 8.1 (4.4 TB/s at the first).  A shorter exponential (exp2 and a first-order remainder, 1.4e-7 off at
-// most where expf is 0.8e-7, zero below 2^-126) made it 124 / 63 / 17.4 / 7.4, but the fp32 loss is the logarithm of this sum.
+// see ce_threads.h).  NT: logits that do not stay in the 256 MB cache anyway are read past it, which leaves it to the
+// gradients that the next product reads.
+// us, bf16, launches one after another, 2048 rows of 50257 / 30000 / 8192 / 2000 columns: 1024 threads a row 145 / 92 / 20.6
+// / 13.3; now 139 / 65 / 18.3 / 8.1 (4.4 TB/s at the first).  A shorter exponential (exp2 and a first-order remainder, 1.4e-7
+// off at most where expf is 0.8e-7, zero below 2^-126) made it 124 / 63 / 17.4 / 7.4, but the fp32 loss is the logarithm of
+// this sum.
 template <typename OutT, int NV, int TB, bool NT>
 __global__ __launch_bounds__(TB) void cross_entropy_row_kernel(const float *__restrict__ logits,
                                                                  const int32_t *__restrict__ targets,

@@ -199,8 +199,9 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const GemmArgs g) {
 // index is contiguous (steps regrouped so that a lane's four are neighbours),
 // else [k][row].  A lane feeds row L%MT and steps e * KG + L/MT, e = 0..3, of
 // every group of 4 * KG.
-// Bank conflicts of 32x32 tiles (stores of [row][k], reads of [k][row]: half of the LDS cycles) are gone with the swizzles of
-// place() and at(): 768x3072x1000 tn 50.4 -> 47.2 us, 1024x1024x4096 tn 85 -> 79, 4096x1024x1024 nt 75 -> 72.
+// Bank conflicts of 32x32 tiles: those of [k][row] (reads: 40 % of the LDS cycles) are gone with the swizzle of at(), those of
+// [row][k] (stores: half of the cycles) are a third with that of place(): 768x3072x1000 tn 50.4 -> 47.2 us, 1024x1024x4096 tn
+// 85 -> 79, 4096x1024x1024 nt 75 -> 72.
 // Measured against the former vector-ALU kernel (64x64 tiles, 4-byte loads, no
 // prefetch): 1000x3072x768 265 -> 51 us, 128x128x512 34 -> 6 us, 4096^3 at 128
 // TFLOP/s of the 157 the matrix pipes offer; the results are the same to the bit.

@@ -43,7 +43,7 @@ namespace hydra {
 // 720 random products: 1.40 times as fast on average (nt 1.56, tn 1.22, nn 1.25), 7 of them more than 5 % slower, 0.83 at
 // worst.
 // With both operands contraction-strided the 256x256 shape takes slices of 32 steps (large_tn); "tt" products, which no caller
-// of the library has, take 64 and spill 6 registers (28 bytes of scratch per lane), reloaded inside the loop.
+// of the library has, take 64 and spill 5 registers (24 bytes of scratch per lane), reloaded inside the loop.
 // What bounds the large ones now: with loads, LDS reads and MFMAs switched off in turn, 1024x16384x4096 takes 71 us of
 // loads alone (25 bytes per clock and CU), 73 us of MFMAs alone at the clock the chip holds for them, 100 us together.
 // ---------------------------------------------------------------------------
@@ -335,8 +335,8 @@ hipError_t launch_gemm_plain(const GemmDesc &d, hipStream_t s) {
 }
 
 // One launch wherever a grid holds it: of 950 groups (the four gradients of a block, width 32 to 4096, 8 to 8192 tokens) four
-// launches were faster twice (by 2 and 3 %) and take 1.55 times as long at the median (us, together / alone: 792 wide, 238 tokens 19.2 /
-// 29.5, 1192 wide, 1144 tokens 67.8 / 83.1).
+// launches were faster twice (by 2 and 3 %) and take 1.55 times as long at the median (us, together / alone: 792 wide, 238
+// tokens 19.2 / 29.5, 1192 wide, 1144 tokens 67.8 / 83.1).
 hipError_t launch_gemm_plain_group(const GemmDesc *d, int n, hipStream_t s) {
   GemmDims x[GEMM_GROUP_MAX];
   for (int i = 0; i < n; ++i) x[i] = dims_of(d[i]);

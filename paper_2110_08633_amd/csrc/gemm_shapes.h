@@ -113,20 +113,20 @@ inline int best_shape(const GemmDims *d, int n, float *cost) {
     tn = tn && d[i].ta && d[i].tb;
     x2 = x2 && d[i].vec_rows;
   }
-  // (256x256 with slices of 32 steps: where it is among the best of the smaller products it takes 1.06 times this estimate, the
-  // shapes chosen take 1.14 times theirs on average; over 1500 products and groups it was chosen 31 times, 1.05 times as fast as
-  // the next choice)
+  // (256x256 tiles of two strided operands, whose constants date from slices of 64: with slices of 32 they take 1.06 times the
+  // estimate where they are among the best of the products below large_tn, the shapes chosen take 1.14 times theirs; over 2310
+  // products and groups they were chosen 26 times, 1.04 times as fast as the next choice)
   int best = 0;
   for (int i = 0; i < SHAPE_128X256X2 - (tn && x2 ? 0 : 1); ++i) {
     const float c = shape_cost(plain_shapes[i], d, n);
     if (i == 0 || (c < *cost && shape_fits(plain_shapes[i], d, n))) { best = i; *cost = c; }
   }
   if (!large_tn(d, n)) return best;
-  // Large: another shape has to be estimated 4 % below the one that all products would choose.  The 1340 take 0.938 times as long
-  // as with that one, 1.6 % more than with the best shape; 42 are more than 3 % (9 more than 5 %) slower than before there was a
-  // second table (with constants fitted to 106 products launched alone, and without the margin: 0.965, 255 and 172).  us, launched one
-  // after another, the first choice / now: 4096x16384x1024 175 / 157, 4096^3 126 / 112, 768x50257x2048 213 / 199, 3728x3288x5556 159 /
-  // 127, 16384x4096x1024 157 / 147, 1600x6400x1000 33.9 / 32.6, 1024x50257x1024 197 / 175.
+  // Large: another shape has to be estimated 4 % below the one that all products would choose.  The 1340 take 0.938 times as
+  // long as with that one, 1.6 % more than with the best shape; 42 are more than 3 % (9 more than 5 %) slower than before there
+  // was a second table (with constants fitted to 106 products launched alone, and without the margin: 0.965, 255 and 172).  us,
+  // launched one after another, the first choice / now: 4096x16384x1024 175 / 157, 4096^3 126 / 112, 768x50257x2048 213 / 199,
+  // 3728x3288x5556 159 / 127, 16384x4096x1024 157 / 147, 1600x6400x1000 33.9 / 32.6, 1024x50257x1024 197 / 175.
   const int first = best;
   float least = 0.f, own = 0.f;
   for (const TnShape &t : tn_shapes) {
@@ -142,7 +142,8 @@ inline int best_shape(const GemmDims *d, int n, float *cost) {
 // Products that 64x64 tiles would leave half of the CUs idle for, or a quarter with a long contraction: smaller tiles whose
 // contraction eight wavefronts share out (gemm_split.hip).  Cost as above, with
 // rounds = tiles / 256 rounded up also where two blocks share a CU; fits to 443 products of random layers (64 to 8192 tokens,
-// widths 128 to 16384) with operands that are not in the L2s; the shape taken costs 0.2 % more than the best one on average.
+// widths 128 to 16384) with operands that are not in the L2s; the shape taken costs 0.2 % more than the best one on average.  800 narrow products (up
+// to 256 rows or columns) against the 64x64 tiles before: 10 more than 3 % slower, the worst 33 / 44 us (tn 3776x80x10959).
 // The first entry is the 64x64 shape of plain_shapes with its slices split over two groups of wavefronts.  Before / now: both
 // operands contraction-contiguous 1.59 times as fast (181 products), one of each 1.44, both strided 1.29; 152x168x6120 nt
 // 23.9 -> 7.9 us, 201x768x2304 nt 9.4 -> 6.0, 417x896x7784 nt 29.6 -> 23.5, 360x448x2719 tn 14.7 -> 10.4.

@@ -14,12 +14,13 @@ namespace hydra {
 // of its own: slice w, w + 8, w + 16, ...  Nothing a wavefront loads is read by
 // another one, so the loop has no barrier: a wavefront waits for its slice, reads
 // all its fragments, hands the LDS back to the loads of its next slice and
-// multiplies while they fly; up to 128 KB per CU are in flight.  At the end the
+// multiplies while they fly; 96 to 160 KB per CU are in flight.  At the end the
 // eight partial tiles are added through LDS, in ascending order of the wavefront,
 // and written out like the other kernels' tiles.
 // Bound: loads of operands that come from the 256 MB cache (rows of 128 bytes: 110 bytes per nanosecond and CU measured, 154
 // from the L2), and for tens of tiles the latency of a launch (about 2.5 us before the first result is written).
-// us, 64x64 tiles with slices split over two groups / here (MxNxK, n: contraction-contiguous): nt 152x168x6120 23.9 / 7.9
+// Counters (matrix pipes 1 to 11 % busy, LDS 4 to 15 %, 0.8 to 1.8 wavefronts per SIMD) show nothing else that is busy.
+// us, launched one after another, 64x64 tiles with slices split over two groups / here (MxNxK, n: contraction-contiguous): nt 152x168x6120 23.9 / 7.9
 // (16x16 tiles), 201x768x2304 9.4 / 6.0 (32x32), 64x704x9768 37 / 10.9 (16x16), 876x520x13592 50 / 49 (64x32), tn 248x408x2174
 // 13.8 / 9.5 (16x32), nn 117x216x2896 15.9 / 6.3 (16x32).
 // ---------------------------------------------------------------------------
