@@ -172,7 +172,7 @@ __global__ __launch_bounds__(64 * RW * KW, 2) void attn_fwd_kernel(const bf16_t 
   typedef RowTile<DH, RW, TK> tile_t;
   constexpr int AQ = 32 * RW, NT = TK / 32;  // rows of the block, 32-row parts of a tile
   constexpr int TILE = tile_t::SIZE, STAGE = 2 * TILE * KW;
-  constexpr int FOLLOW = 4 / KW;  // tiles of a group in which the reference maximum follows the maximum, see below
+  constexpr int FOLLOW = 4;  // tiles of a group in which the reference maximum follows the maximum, see below
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];  // [2 stages][KW][K, V]
   const int tid = threadIdx.x % (64 * RW), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * RW)) : 0;
@@ -250,11 +250,11 @@ __global__ __launch_bounds__(64 * RW * KW, 2) void attn_fwd_kernel(const bf16_t 
     // The reference maximum m of a row (log2 domain) only has to keep the exponentials in range, so it is moved -
     // and the sum and the output rescaled - only when some row's maximum has outgrown it by more than 2^8.  Except in
     // the first FOLLOW tiles: a weight equal to the reference is exactly 1, every other one carries a bf16 rounding, and
-    // the heaviest weight of a row is the one whose rounding counts.  At least 128 keys are seen that way whatever the
-    // form.  Error of o against 64 bits, B 4, H 16, T 2048, dh 128: 1.009 times that of 64-key tiles with the first tile's
-    // maximum as reference, now 0.986 times; B 3, H 32, T 392 1.029 times that of two groups with such tiles, now 0.999.
-    // 77.5 -> 79 us and 16.1 -> 16.8.
-    const float tm = tmax * scale_log2e, room = FOLLOW > 1 && it < FOLLOW ? 0.f : 8.f;
+    // the heaviest weight of a row is the one whose rounding counts.  Error of o against 64 bits, B 4, H 16, T 2048, dh 128:
+    // 1.009 times that of 64-key tiles with the first tile's maximum as reference, now 0.985 times; B 3, H 32, T 392 1.029
+    // times that of two groups with such tiles, now 0.999; B 1, H 16, T 2048 (two groups) 1.006, now 0.982.  77.5 -> 79 us,
+    // 16.1 -> 16.8 and no change.
+    const float tm = tmax * scale_log2e, room = it < FOLLOW ? 0.f : 8.f;
     if (__builtin_amdgcn_ballot_w64(tm > m + room)) {
       const float mn = __builtin_fmaxf(m, tm);
       const float alpha = __builtin_amdgcn_exp2f(m - mn);
