@@ -41,6 +41,16 @@ __device__ __forceinline__ bf16x8_t load_frag_global(const bf16_t *p) {
   return x.f;
 }
 
+// s + the products of eight bf16 elements
+__device__ __forceinline__ float dot8(const u32x4_t a, const u32x4_t b, float s) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    s = __builtin_fmaf(__uint_as_float(a[e] << 16), __uint_as_float(b[e] << 16), s);
+    s = __builtin_fmaf(__uint_as_float(a[e] & 0xffff0000u), __uint_as_float(b[e] & 0xffff0000u), s);
+  }
+  return s;
+}
+
 // Results r = 8*s .. 8*s + 7 of a lane (row L%32, columns (r/4)*8 + (L/32)*4 + r%4) as the row operand of a product
 // that contracts over those columns: rounded to bf16, they already sit in the right lane - lane half h holds steps
 // 4h .. 4h+3 and 8+4h .. 11+4h of the sixteen, and RowTile::tr feeds the other operand's steps in the same order.  So
@@ -359,15 +369,14 @@ __device__ __forceinline__ bool merge_groups(f32x16_t (&acc)[NA], int grp, float
 // ---------------------------------------------------------------------------
 // backward, part 1: dQ.  Same decomposition as the forward kernel.  Per tile:
 // p = exp(s - L), dP = dO V^T, dS = p (dP - D) / sqrt(dh) with
-// D_i = sum_c dO[i,c] O[i,c] (written out for part 2), dQ += dS K.  B 4, H 16, T 2048, dh 128, launched alone: 117 us,
+// D_i = sum_c dO[i,c] O[i,c] (OWN_D: summed here and written out), dQ += dS K.  B 4, H 16, T 2048, dh 128, launched alone: 117 us,
 // whether with 64 or with 32 keys per tile (three blocks per CU would need 168 registers: 180 us with the spills); among
 // other kernels 121 to 126.
 // ---------------------------------------------------------------------------
-template <int DH, int RW, int KW, int TK, bool DIRECT>
-__global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dq_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
-                                                                  const bf16_t *__restrict__ d_o, const float *__restrict__ lse,
-                                                                  float *__restrict__ dsum, bf16_t *__restrict__ dqkv, int T,
-                                                                  int H, int d, int nb, int pairs, float scale) {
+template <int DH, int RW, int KW, int TK, bool DIRECT, bool OWN_D>
+__device__ __forceinline__ void attn_bwd_dq(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o, const bf16_t *__restrict__ d_o,
+                                            const float *__restrict__ lse, float *__restrict__ dsum, bf16_t *__restrict__ dqkv, int T,
+                                            int H, int d, const int z, const int qb, float scale) {
   constexpr int ND = DH / 32;
   typedef RowTile<DH, RW, TK> tile_t;
   constexpr int AQ = 32 * RW, NT = TK / 32;  // rows of the block, 32-row parts of a tile
@@ -375,9 +384,6 @@ __global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dq_kernel(const bf16
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
   const int tid = threadIdx.x % (64 * RW), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * RW)) : 0;
-  int z, qb;
-  if (!block_place(pairs, nb, z, qb)) return;
-  qb = nb - 1 - qb;
   const int b = z / H, h = z % H;
   const int q0 = qb * AQ, r0 = q0 + wave * 32;
   const int64_t ld = 3 * (int64_t)d;
@@ -407,14 +413,16 @@ __global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dq_kernel(const bf16
       const int c = kk * 16 + (lane >> 5) * 8;
       qf[kk] = load_frag_global(qp + ldrow * ld + c);
       dof[kk] = load_frag_global(dop + c);
-      const bf16x8_t of = load_frag_global(op + c);
+      if constexpr (OWN_D) {
+        const bf16x8_t of = load_frag_global(op + c);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) dsum_part += (float)dof[kk][e] * (float)of[e];
+        for (int e = 0; e < 8; ++e) dsum_part += (float)dof[kk][e] * (float)of[e];
+      }
     }
   }
-  const float Di = sum_halves(dsum_part);
+  const float Di = OWN_D ? sum_halves(dsum_part) : dsum[(int64_t)z * T + ldrow];
   const float L2 = lse[(int64_t)z * T + ldrow] * LOG2E;
-  if (grp == 0 && lane < 32 && myrow < T) dsum[(int64_t)z * T + myrow] = Di;
+  if (OWN_D && grp == 0 && lane < 32 && myrow < T) dsum[(int64_t)z * T + myrow] = Di;
   const float scale_log2e = scale * LOG2E;
   const float nL2 = -L2, nDs = -Di * scale;
   RowFrag<tile_t, TK> fr;
@@ -476,22 +484,30 @@ __global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dq_kernel(const bf16
   }
 }
 
+template <int DH, int RW, int KW, int TK, bool DIRECT>
+__global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dq_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
+                                                                  const bf16_t *__restrict__ d_o, const float *__restrict__ lse,
+                                                                  float *__restrict__ dsum, bf16_t *__restrict__ dqkv, int T,
+                                                                  int H, int d, int nb, int pairs, float scale) {
+  int z, qb;
+  if (!block_place(pairs, nb, z, qb)) return;
+  attn_bwd_dq<DH, RW, KW, TK, DIRECT, true>(qkv, o, d_o, lse, dsum, dqkv, T, H, d, z, nb - 1 - qb, scale);
+}
+
 // ---------------------------------------------------------------------------
 // backward, part 2: dK and dV.  RW wavefronts = 32 RW keys of one (sample, head),
 // wavefront w owns keys kr0 = k0 + 32 w .. + 31 and keeps their K and V
 // fragments in registers.  It walks the query tiles from the diagonal
 // to the end of the sequence, computing the transposed quantities directly:
 // s^T = K Q^T, p^T = exp(s^T - L), dP^T = V dO^T, dS^T = p^T (dP^T - D)/sqrt(dh),
-// dV += p^T dO, dK += dS^T Q.  No atomics: every key row has one owner.  At head width 64 large launches hold the kernel to
-// 168 registers (203 left alone), so that three blocks share a CU: B 8, H 25, T 1024 90.6 -> 84.9 us.  At 128, launched alone, it is 157 us
+// dV += p^T dO, dK += dS^T Q.  No atomics: every key row has one owner.  At head width 128, launched alone, it is 157 us
 // at B 4, H 16, T 2048 with two blocks per CU and tiles of 64 queries, 173 with 32; among other kernels 170 to 180.
 // ---------------------------------------------------------------------------
-template <int DH, int RW, int KW, int TK, bool DIRECT, int OCC>
-__global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
-                                                                   const bf16_t *__restrict__ d_o,
-                                                                   const float *__restrict__ lse,
-                                                                   const float *__restrict__ dsum, bf16_t *__restrict__ dqkv,
-                                                                   int T, int H, int d, int nb, int pairs, float scale) {
+template <int DH, int RW, int KW, int TK, bool DIRECT, bool OWN_D>
+__device__ __forceinline__ void attn_bwd_dkv(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
+                                             const bf16_t *__restrict__ d_o, const float *__restrict__ lse,
+                                             const float *__restrict__ dsum, bf16_t *__restrict__ dqkv, int T, int H, int d,
+                                             const int z, const int kb, float scale) {
   constexpr int ND = DH / 32;
   typedef RowTile<DH, RW, TK> tile_t;
   constexpr int AQ = 32 * RW, NT = TK / 32;  // rows of the block, 32-row parts of a tile
@@ -500,13 +516,11 @@ __global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_dkv_kernel(const b
   float *const Ls = (float *)(smem + 2 * STAGE);  // [2][KW][2 * TK]: -log-sum-exp (log2 domain) and -D / sqrt(dh) of a tile's queries
   const int tid = threadIdx.x % (64 * RW), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * RW)) : 0;
-  int z, kb;
-  if (!block_place(pairs, nb, z, kb)) return;
   const int b = z / H, h = z % H;
   const int k0 = kb * AQ, kr0 = k0 + wave * 32;
   const int64_t ld = 3 * (int64_t)d;
   const bf16_t *qp = qkv + (int64_t)b * T * ld + h * DH, *kp = qp + d, *vp = qp + 2 * d;
-  const bf16_t *dop = d_o + (int64_t)b * T * d + h * DH;
+  const bf16_t *dop = d_o + (int64_t)b * T * d + h * DH, *op = o + (int64_t)b * T * d + h * DH;
   const int mykey = kr0 + (lane & 31);
   const int ldkey = min(mykey, T - 1);
 
@@ -522,13 +536,46 @@ __global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_dkv_kernel(const b
     tq.template load<DIRECT>(qp + (int64_t)i0 * ld, T - i0, s, wave);
     to.template load<DIRECT>(dop + (int64_t)i0 * d, T - i0, s + TILE * 2, wave);
   };
-  auto load_stat = [&](int i0) -> float {
-    const int qi = i0 + tid % TK;
-    if (tid >= 2 * TK || qi >= T) return 0.f;
-    return tid < TK ? -lse[(int64_t)z * T + qi] * LOG2E : -dsum[(int64_t)z * T + qi] * scale;
+  // The statistics of a tile's queries.  OWN_D: D is summed here, by PR threads per query, from loads that fly while the tile
+  // before is worked on; else the first 2 TK threads fetch what part 1 left.
+  constexpr int PR = 64 * RW / TK, NV = DH / 8 / PR;  // threads per query, 16-byte loads of O and dO per thread
+  static_assert(!OWN_D || (PR >= 2 && PR * TK == 64 * RW && NV * PR * 8 == DH), "every thread has a part of a query");
+  struct Stat { float x; u32x4_t a[OWN_D ? NV : 1], b[OWN_D ? NV : 1]; };
+  auto load_stat = [&](int i0, Stat &st) {
+    if constexpr (OWN_D) {
+      const int qi = i0 + tid / PR, part = tid % PR;
+      const bool in = qi < T;
+      const int64_t at = (int64_t)min(qi, T - 1) * d + part * 8;
+      st.x = in && part == 0 ? -lse[(int64_t)z * T + qi] * LOG2E : 0.f;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        st.a[v] = *(gvec_ptr)(dop + at + v * PR * 8);
+        st.b[v] = *(gvec_ptr)(op + at + v * PR * 8);
+      }
+    } else {
+      const int qi = i0 + tid % TK;
+      st.x = 0.f;
+      if (tid >= 2 * TK || qi >= T) return;
+      st.x = tid < TK ? -lse[(int64_t)z * T + qi] * LOG2E : -dsum[(int64_t)z * T + qi] * scale;
+    }
+  };
+  // of the tile from query i0 on, to ls
+  auto store_stat = [&](const Stat &st, int i0, float *ls) {
+    if constexpr (OWN_D) {
+      float s = 0.f;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) s = dot8(st.a[v], st.b[v], s);
+#pragma unroll
+      for (int x = 1; x < PR; x *= 2) s += __shfl_xor(s, x);
+      const int r = tid / PR, part = tid % PR;
+      if (part < 2) ls[part * TK + r] = part ? (i0 + r < T ? -s * scale : 0.f) : st.x;
+    } else {
+      if (tid < 2 * TK) ls[tid] = st.x;
+    }
   };
   load(0);
-  float stat = load_stat(first(0));
+  Stat stat;
+  load_stat(first(0), stat);
   bf16x8_t kf[DH / 16], vf[DH / 16];
 #pragma unroll
   for (int kk = 0; kk < DH / 16; ++kk) {
@@ -536,7 +583,7 @@ __global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_dkv_kernel(const b
     kf[kk] = load_frag_global(kp + ldkey * ld + c);
     vf[kk] = load_frag_global(vp + ldkey * ld + c);
   }
-  if (tid < 2 * TK) Ls[grp * 2 * TK + tid] = stat;
+  store_stat(stat, first(0), Ls + grp * 2 * TK);
   const float scale_log2e = scale * LOG2E;
   RowFrag<tile_t, TK> fr;
   fr.init(lane);
@@ -551,7 +598,7 @@ __global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_dkv_kernel(const b
     landed_barrier();
     const bool more = it + 1 < nstep;
     if (more) {
-      stat = load_stat(first(it + 1));
+      load_stat(first(it + 1), stat);
       load(it + 1);
     }
     const int i0 = first(it);
@@ -606,7 +653,7 @@ __global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_dkv_kernel(const b
         }
       }
     }
-    if (more && tid < 2 * TK) Ls[(((it + 1) & 1) * KW + grp) * 2 * TK + tid] = stat;
+    if (more) store_stat(stat, first(it + 1), Ls + (((it + 1) & 1) * KW + grp) * 2 * TK);
   }
   if constexpr (KW > 1) {
     if (!merge_groups<RW, KW>(acc, grp, (float *)smem, wave, lane)) return;
@@ -621,6 +668,53 @@ __global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_dkv_kernel(const b
   }
 }
 
+template <int DH, int RW, int KW, int TK, bool DIRECT>
+__global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
+                                                                   const bf16_t *__restrict__ d_o,
+                                                                   const float *__restrict__ lse,
+                                                                   const float *__restrict__ dsum, bf16_t *__restrict__ dqkv,
+                                                                   int T, int H, int d, int nb, int pairs, float scale) {
+  int z, kb;
+  if (!block_place(pairs, nb, z, kb)) return;
+  attn_bwd_dkv<DH, RW, KW, TK, DIRECT, false>(qkv, nullptr, d_o, lse, dsum, dqkv, T, H, d, z, kb, scale);
+}
+
+// D alone, where part 2 does not sum it: 16 bytes of dO and O per lane, samples blockIdx.y, + gridDim.y, ...  Bound: HBM, and a
+// launch (2.5 us; 33 MB of B 4, H 16, T 2048, dh 128 about 9).
+template <int DH>
+__global__ __launch_bounds__(256) void attn_dsum_kernel(const bf16_t *__restrict__ o, const bf16_t *__restrict__ d_o,
+                                                        float *__restrict__ dsum, int B, int T, int H) {
+  constexpr uint32_t L = DH / 8;  // lanes per row
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x, row = i / L, t = row / (uint32_t)H, h = row - t * H;
+  if (t >= (uint32_t)T) return;  // whole rows of lanes
+  for (int b = blockIdx.y; b < B; b += gridDim.y) {
+    const int64_t at = ((int64_t)b * T * H * L + i) * 8;
+    float s = dot8(*(gvec_ptr)(d_o + at), *(gvec_ptr)(o + at), 0.f);
+#pragma unroll
+    for (int n = 1; n < (int)L; n *= 2) s += __shfl_xor(s, n);
+    if (i % L == 0) dsum[((int64_t)b * H + h) * T + t] = s;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// backward, both parts in one launch: 2 * pairs blocks per row block, those of part 2, which take longer, first.  Bound: at a few
+// hundred row blocks the chain of tiles of a block, 0.6 to 0.9 us per 64 rows, which the other part's blocks now share the CUs
+// with; at thousands the matrix pipes, as for the parts alone, less the tails of two launches.  us, two launches / one: B 4,
+// H 12, T 512, dh 64 23.9 / 19.9, B 1, H 12, T 512 19.7 / 13.2, B 8, H 25, T 1024 143 / 133, dh 128 B 1, H 16, T 512 35 / 24.
+// At head width 64 three blocks share a CU (168 registers) unless they sum D (213 to 243: two); at 128 two, with 5 to 41
+// registers spilled.
+// ---------------------------------------------------------------------------
+template <int DH, int RW, int KW, int TK, bool DIRECT, bool OWN_D, int OCC>
+__global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
+                                                               const bf16_t *__restrict__ d_o, const float *__restrict__ lse,
+                                                               float *__restrict__ dsum, bf16_t *__restrict__ dqkv, int T, int H,
+                                                               int d, int nb, int pairs, float scale) {
+  int z, rb;
+  if (!block_place(2 * pairs, nb, z, rb)) return;
+  if (z < pairs) attn_bwd_dkv<DH, RW, KW, TK, DIRECT, OWN_D>(qkv, o, d_o, lse, dsum, dqkv, T, H, d, z, rb, scale);
+  else attn_bwd_dq<DH, RW, KW, TK, DIRECT, OWN_D>(qkv, o, d_o, lse, dsum, dqkv, T, H, d, z - pairs, nb - 1 - rb, scale);
+}
+
 }  // namespace
 
 bool attention_fused_supported(int dtype, int dh) { return dtype == DT_BF16 && (dh == 64 || dh == 128); }
@@ -633,41 +727,42 @@ static constexpr size_t attn_lds(int dh, int rw, int kw, int tk, int nacc, int e
 }
 
 // (a row of the grid holds at most 2^32 threads)
-#define HYDRA_ATTN(KERN_, LDS_, ...)                                               \
+#define HYDRA_ATTN(KERN_, PARTS_, LDS_, ...)                                       \
   do {                                                                             \
     auto kern = KERN_;                                                             \
     static OncePerGpu once;                                                        \
     const hipError_t attr = allow_lds(once, (const void *)kern, LDS_);             \
     if (attr != hipSuccess) return attr;                                           \
-    const uint32_t blocks = (uint32_t)nb * B * H, gx = blocks < (1u << 22) ? blocks : 1u << 22; \
+    const uint32_t blocks = (uint32_t)nb * B * H * PARTS_, gx = blocks < (1u << 22) ? blocks : 1u << 22; \
     hipLaunchKernelGGL(kern, dim3(gx, (blocks + gx - 1) / gx), dim3(64 * RW * KW), LDS_, s, __VA_ARGS__); \
   } while (0)
 
 template <int DH, int RW, int KW, int TK, bool DIRECT>
 static hipError_t attn_fwd(const bf16_t *qkv, bf16_t *o, float *lse, int B, int H, int T, hipStream_t s) {
   const int nb = (T + 32 * RW - 1) / (32 * RW), d = H * DH;
-  HYDRA_ATTN((attn_fwd_kernel<DH, RW, KW, TK, DIRECT>), attn_lds(DH, RW, KW, TK, DH / 32, 2, 0), qkv, o, lse, T, H, d, nb, B * H,
+  HYDRA_ATTN((attn_fwd_kernel<DH, RW, KW, TK, DIRECT>), 1, attn_lds(DH, RW, KW, TK, DH / 32, 2, 0), qkv, o, lse, T, H, d, nb, B * H,
              LOG2E / sqrtf((float)DH));
   return hipGetLastError();
 }
 
-template <int DH, int RW, int KW, int TK, bool DIRECT>
+template <int DH, int RW, int KW, int TK, int MODE, bool DIRECT>
 static hipError_t attn_bwd(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o, const float *lse, float *dsum, bf16_t *dqkv,
                            int B, int H, int T, hipStream_t s) {
   const int nb = (T + 32 * RW - 1) / (32 * RW), d = H * DH;
   const float scale = 1.0f / sqrtf((float)DH);
-  HYDRA_ATTN((attn_bwd_dq_kernel<DH, RW, KW, TK, DIRECT>), attn_lds(DH, RW, KW, TK, DH / 32, 0, 0), qkv, o, d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale);
-  // a third block per CU once there are enough of them (B 5, H 16, T 976, 640 blocks: both passes 80 us with two, 84 with three)
-#define HYDRA_DKV(OCC_)                                                                                                  \
-  HYDRA_ATTN((attn_bwd_dkv_kernel<DH, RW, KW, TK, DIRECT, OCC_>), attn_lds(DH, RW, KW, TK, DH / 16, 0, KW * 2 * 2 * TK * 4), qkv, \
-             d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale)
-  if constexpr (DH == 64 && RW == 4) {
-    if ((int64_t)nb * B * H > 3 * 256) HYDRA_DKV(3);
-    else HYDRA_DKV(2);
+  constexpr size_t lds_dkv = attn_lds(DH, RW, KW, TK, DH / 16, 0, KW * 2 * 2 * TK * 4);
+  if constexpr (MODE != BWD_TWO) {  // see attn_bwd_mode
+    if constexpr (MODE == BWD_ONE_AFTER_D) {
+      const uint32_t lanes = (uint32_t)T * H * (DH / 8);  // of a sample
+      hipLaunchKernelGGL((attn_dsum_kernel<DH>), dim3((lanes + 255) / 256, B < 32768 ? B : 32768), dim3(256), 0, s, o, d_o, dsum, B, T, H);
+    }
+    HYDRA_ATTN((attn_bwd_kernel<DH, RW, KW, TK, DIRECT, MODE == BWD_ONE, MODE == BWD_ONE || DH == 128 ? 2 : 3>), 2, lds_dkv, qkv, o, d_o,
+               lse, dsum, dqkv, T, H, d, nb, B * H, scale);
   } else {
-    HYDRA_DKV(2);
+    HYDRA_ATTN((attn_bwd_dq_kernel<DH, RW, KW, TK, DIRECT>), 1, attn_lds(DH, RW, KW, TK, DH / 32, 0, 0), qkv, o, d_o, lse, dsum,
+               dqkv, T, H, d, nb, B * H, scale);
+    HYDRA_ATTN((attn_bwd_dkv_kernel<DH, RW, KW, TK, DIRECT>), 1, lds_dkv, qkv, d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale);
   }
-#undef HYDRA_DKV
   return hipGetLastError();
 }
 #undef HYDRA_ATTN
@@ -683,7 +778,14 @@ template <int DH, int F, bool DIRECT>
 static hipError_t attn_bwd_form(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o, const float *lse, float *dsum, bf16_t *dqkv,
                                 int B, int H, int T, hipStream_t s) {
   constexpr AttnForm f = DH == 64 ? attn_forms_bwd64[F] : attn_forms_bwd128[F < 3 ? F : 0];
-  return attn_bwd<DH, f.rw, f.kw, f.tk, DIRECT>(qkv, o, d_o, lse, dsum, dqkv, B, H, T, s);
+  const AttnBwdMode mode = attn_bwd_mode(DH, F, B * H, T);
+#define HYDRA_MODE(M_) \
+  if (mode == M_) return attn_bwd<DH, f.rw, f.kw, f.tk, M_, DIRECT>(qkv, o, d_o, lse, dsum, dqkv, B, H, T, s)
+  if constexpr (DH == 64 || F == 1) HYDRA_MODE(BWD_ONE);
+  if constexpr (DH == 128 || F != 1) HYDRA_MODE(BWD_ONE_AFTER_D);
+  if constexpr (DH == 128 && F == 0) HYDRA_MODE(BWD_TWO);
+#undef HYDRA_MODE
+  return hipErrorInvalidValue;
 }
 #define HYDRA_ATTN_FORM(FN_, DH_, F_, ...) \
   return direct ? FN_<DH_, F_, true>(__VA_ARGS__) : FN_<DH_, F_, false>(__VA_ARGS__)

@@ -76,4 +76,30 @@ inline int attn_form_bwd(int dh, int pairs, int T) {
                   : best_attn_form(attn_forms_bwd128, dh, pairs, T, 0.95f);
 }
 
+// The launches of the backward pass, whose two parts are dQ and dK/dV: two (part 2 reads the D = rowsum(dO * O) that part 1
+// wrote); one, in which the blocks of part 2 sum D themselves; or one after a small launch that sums D.  The figures and the
+// constants above are those of two launches.  Most calls wait for chains of tiles, those of one part as long as the other's, and
+// have room for both at once: two / one, us: B 4, H 12, T 512, dh 64 23.9 / 19.9; B 1, H 12, T 1024 30.3 / 23.7; B 2, H 4, T 64
+// 9.0 / 5.4; B 8, H 25, T 1024 143 / 133; B 1, H 16, T 1024, dh 128 57 / 44.  Over 910 random calls of 16 to 2048 positions the
+// mode taken here gives 0.75 (head width 64) and 0.87 (128) of the time of two launches, within 4 and 2 % of the best block form
+// and mode.
+enum AttnBwdMode { BWD_TWO, BWD_ONE, BWD_ONE_AFTER_D };
+constexpr AttnBwdMode attn_bwd_mode(int dh, int form, int pairs, int T) {
+  const int rows = 32 * (dh == 64 ? attn_forms_bwd64[form] : attn_forms_bwd128[form]).rw;
+  const int64_t blocks = ((int64_t)T + rows - 1) / rows * pairs;  // of each part
+  if (dh == 64) {
+    // Summing D takes registers: two such blocks fit a CU, of the others three.  With more blocks than the chip holds that is
+    // worth the 2.5 us of the launch before (us, one / after D, 64-row blocks: 448 blocks 27.0 / 27.4, 640 29.9 / 28.5, 896 76 /
+    // 69; 128-row: 525 32.7 / 33.9, 672 54 / 50.5); blocks of one group with 32-row tiles come at short sequences only, where it
+    // is not (B 8, H 25, T 256 23.5 / 26.7).
+    return blocks > 512 && form != 1 ? BWD_ONE_AFTER_D : BWD_ONE;
+  }
+  // Head width 128: with D to sum 40 registers are spilled, which only sequences of a tile or two do not feel (T 24 7.2 / 8.3 us,
+  // T 64 11.1 / 11.1, T 128 16.6 / 15.1).  Two launches remain where 128-row blocks abound: D is summed beside part 1's other
+  // work, and nobody waits for a chain (B 4, H 16, T 2048 271 us, after D 282; B 4, H 32, T 944 160 / 164; with fewer blocks B 3,
+  // H 25, T 1584, 975 blocks, 224 / 218, B 8, H 25, T 512, 800 blocks 106 / 98).
+  if (form == 0 && blocks >= 1000) return BWD_TWO;
+  return form == 1 && T <= 48 ? BWD_ONE : BWD_ONE_AFTER_D;
+}
+
 }  // namespace hydra

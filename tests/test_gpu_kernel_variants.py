@@ -554,6 +554,48 @@ def test_attention_every_form(H, B, Hn, T, dh):
         test_attention_unaligned_tensors(H, B, Hn, T, dh, 1)
 
 
+# every block form of the backward pass in every way its parts are launched (two launches, one, one after a launch that sums D;
+# the CPU suite holds the table against the choice): partly empty row blocks, tiles and groups
+ATT_BWD_CASES = [(1, 1, 40, 64, 0, 1), (11, 13, 200, 64, 0, 1), (40, 7, 208, 64, 0, 2), (40, 13, 40, 64, 0, 2), (1, 1, 8, 64, 1, 1),
+                 (1, 2, 88, 64, 1, 1), (5, 7, 136, 64, 2, 1), (25, 7, 168, 64, 2, 2), (1, 2, 104, 64, 3, 1), (1, 1, 1000, 64, 3, 1),
+                 (11, 5, 584, 64, 3, 2), (40, 13, 200, 128, 0, 0), (11, 13, 232, 128, 0, 2), (1, 2, 8, 128, 1, 1), (3, 5, 40, 128, 1, 1),
+                 (1, 3, 72, 128, 1, 2), (2, 1, 104, 128, 2, 2), (1, 3, 1000, 128, 2, 2)]
+
+
+@pytest.mark.parametrize("B,Hn,T,dh", [c[:4] for c in ATT_BWD_CASES])
+def test_attention_backward_launches(H, B, Hn, T, dh):
+    test_attention_variants(H, B, Hn, T, dh, 1.0)
+    test_attention_unaligned_tensors(H, B, Hn, T, dh, 1)
+    d = Hn * dh
+    qkv, o, d_o = randn(T, B * T, 3 * d).bfloat16(), randn(dh, B * T, d).bfloat16(), randn(B, B * T, d).bfloat16()
+    lse, dsum = torch.ones(B * Hn * T, device="cuda"), torch.full((B * Hn * T + 8,), 7.0, device="cuda")
+    H.hydra_op_attention_bwd(qkv, o, d_o, lse, dsum, torch.empty_like(qkv), B, Hn, T, dh)
+    x = (o.double() * d_o.double()).view(B, T, Hn, dh).transpose(1, 2)
+    # at most dh additions on a product's way to the sum
+    assert ((dsum[:-8].double() - x.sum(-1).reshape(-1)).abs() <= dh * U32 * x.abs().sum(-1).reshape(-1)).all()
+    assert (dsum[-8:] == 7.0).all()
+
+
+def test_attention_backward_more_samples_than_a_grid_column(H):
+    B, T, dh = 32768 + 5, 56, 128
+    one = [randn(T + n, T, n * dh).bfloat16() for n in (3, 1)]
+    qkv, d_o = (x.repeat(B, 1) for x in one)
+
+    def run(qkv, d_o, B):
+        o, dqkv = torch.zeros_like(d_o), torch.zeros_like(qkv)
+        lse, dsum = (torch.zeros(B * T, device="cuda") for _ in range(2))
+        H.hydra_op_attention_fwd(qkv, o, lse, B, 1, T, dh)
+        H.hydra_op_attention_bwd(qkv, o, d_o, lse, dsum, dqkv, B, 1, T, dh)
+        torch.cuda.synchronize()
+        return dqkv.view(B, -1), dsum.view(B, -1)
+
+    got = run(qkv, d_o, B)
+    for g in got:  # the first sample's as the others', and right
+        assert torch.equal(g, g[:1].expand_as(g))
+    for g, r in zip(got, run(*one, 1)):
+        assert (g[0].double() - r[0].double()).norm() <= 2.0 ** -8 * r[0].double().norm()
+
+
 # a row whose weight sits almost wholly on one of its first 128 keys: that weight is exact in every form, so the result is off
 # by its own rounding only
 @pytest.mark.parametrize("B,Hn,T,dh", [c[:4] for c in ATT_FORM_CASES if c[2] >= 136])

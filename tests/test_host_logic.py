@@ -544,6 +544,31 @@ int main() {
         assert {c[5] for c in V.ATT_FORM_CASES if c[3] == dh} == set(range(bwd))
 
 
+def test_attention_backward_cases_take_the_launches_they_name(tmp_path):
+    from tests import test_gpu_kernel_variants as V
+    src = tmp_path / "t.cpp"
+    src.write_text(r'''
+#include "attn_forms.h"
+#include <cstdio>
+int main() {
+  int dh, pairs, T;
+  while (scanf("%d %d %d", &dh, &pairs, &T) == 3) {
+    const int form = hydra::attn_form_bwd(dh, pairs, T);
+    printf("%d %d\n", form, (int)hydra::attn_bwd_mode(dh, form, pairs, T));
+  }
+}
+''')
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2110_08633_amd", "csrc"),
+                           str(src), "-o", str(tmp_path / "t")])
+    ask = "\n".join(f"{dh} {B * H} {T}" for B, H, T, dh, _, _ in V.ATT_BWD_CASES + [(32768 + 5, 1, 56, 128, 1, 2)])
+    out = subprocess.run([str(tmp_path / "t")], input=ask, text=True, capture_output=True, check=True).stdout.split("\n")
+    for c, line in zip(V.ATT_BWD_CASES + [(32768 + 5, 1, 56, 128, 1, 2)], out):
+        assert c[4:] == tuple(map(int, line.split())), (c, line)
+    # every kernel that attention.hip builds
+    assert {c[3:] for c in V.ATT_BWD_CASES} == {(64, f, 1) for f in range(4)} | {(64, f, 2) for f in (0, 2, 3)} | {
+        (128, 0, 0), (128, 0, 2), (128, 1, 1), (128, 1, 2), (128, 2, 2)}
+
+
 def test_cross_entropy_threads_per_row(tmp_path):
     """Few rows: a CU holds one at most, and 1024 threads are the fastest way through it (also from 2049 columns on, where 256
     threads take 5 to 16 % longer); many rows: the fewer threads the more of them are in flight, as long as the row fits."""
