@@ -5,16 +5,23 @@
 
 namespace hydra {
 
-// first row and column of the tile of workgroup bid of nt: contiguous runs of tiles per XCD, see xcd_group_rows
-template <int BM, int BN>
-__device__ __forceinline__ void tile_origin(const GemmArgs &g, int bid, int nt, int &m0, int &n0) {
+// first row and column of the tile of workgroup bid of nt: contiguous runs of tiles per XCD, see xcd_group_rows.  HALVES: every
+// tile has two workgroups, one per half of the contraction, numbered so that an XCD works on one half; the half is returned
+template <int BM, int BN, bool HALVES = false>
+__device__ __forceinline__ int tile_origin(const GemmArgs &g, int bid, int nt, int &m0, int &n0) {
   const int xcd = bid & 7, per = nt >> 3, rem = nt & 7;
-  const int tile = xcd * per + min(xcd, rem) + (bid >> 3);
+  int tile = xcd * per + min(xcd, rem) + (bid >> 3);
+  int half = 0;
+  if (HALVES && tile >= nt / 2) {
+    half = 1;
+    tile -= nt / 2;
+  }
   const int gsz = g.grp * g.tiles_n;
   const int grp = tile / gsz, in_grp = tile - grp * gsz;
   const int rows_in_grp = min(g.grp, g.tiles_m - grp * g.grp);
   m0 = (grp * g.grp + in_grp % rows_in_grp) * BM;
   n0 = (in_grp / rows_in_grp) * BN;
+  return half;
 }
 
 // 16-byte chunk position within a line of LDS.  [row][BK]: 16 rows at one chunk index should fall into distinct slots

@@ -301,6 +301,19 @@ __device__ __forceinline__ void store_patch(const GemmArgs &g, int64_t coff, con
 }
 
 
+// Adds a wavefront's staged patch to the results in memory, neighbouring lanes to neighbouring columns.
+template <int WTN, int PR>
+__device__ __forceinline__ void add_patch(const GemmArgs &g, const float *patch, int row0, int col0, int lane) {
+  constexpr int SP = WTN + 4;
+  static_assert(PR * WTN % 64 == 0, "whole instructions");
+#pragma unroll 4
+  for (int p0 = 0; p0 < PR * WTN; p0 += 64) {
+    const int r = (p0 + lane) / WTN, c = (p0 + lane) % WTN;
+    if (row0 + r < g.M && col0 + c < g.N)
+      unsafeAtomicAdd(g.out_f32 + (int64_t)(row0 + r) * g.ldc + col0 + c, patch[r * SP + c] * g.alpha);
+  }
+}
+
 // descriptor of 2 GB from p on (offsets are 32 bits wide: the base moves with the slice)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void *p) {
   return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 0x7ffffff0, 0x00020000);

@@ -46,8 +46,9 @@ namespace hydra {
 // of the library has, take 64 and spill 5 registers (24 bytes of scratch per lane), reloaded inside the loop.
 // What bounds the large ones now: with loads, LDS reads and MFMAs switched off in turn, 1024x16384x4096 takes 71 us of
 // loads alone (25 bytes per clock and CU), 73 us of MFMAs alone at the clock the chip holds for them, 100 us together.
+// HALVES: this workgroup multiplies one half of the contraction and adds its results to a cleared C (see best_half_shape).
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WM, int WN, int KW, int TA, int TB, int BK_, int S>
+template <int BM, int BN, int WM, int WN, int KW, int TA, int TB, int BK_, int S, bool HALVES = false>
 __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, const int nt, bf16_t *const lds) {
   constexpr int NG = WM * WN, NW = NG * KW, WTM = BM / WM, WTN = BN / WN, MI = WTM / 16, NJ = WTN / 16;
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && MI * 16 * WM == BM && NJ * 16 * WN == BN, "wavefront tiles");
@@ -59,23 +60,38 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = wave / NG, wm = (wave / WN) % WM, wn = wave % WN;
   int m0, n0;
-  tile_origin<BM, BN>(g, bid, nt, m0, n0);
-  const int nk = (g.K + BK_ - 1) / BK_;
+  int K = g.K;
+  const bf16_t *A = (const bf16_t *)g.A, *B = (const bf16_t *)g.B;
+  if constexpr (HALVES) {
+    const int K0 = ((K + BK_ - 1) / BK_ + 1) / 2 * BK_;  // steps of the first half
+    if (tile_origin<BM, BN, true>(g, bid, nt, m0, n0)) {
+      K -= K0;
+      A += (int64_t)K0 * (TA ? g.lda : 1);
+      B += (int64_t)K0 * (TB ? g.ldb : 1);
+    } else {
+      K = K0;
+    }
+  } else {
+    tile_origin<BM, BN>(g, bid, nt, m0, n0);
+  }
+  const int nk = (K + BK_ - 1) / BK_;
 
   MA ma;
   MB mb;
-  ma.init((const bf16_t *)g.A, g.lda, m0, g.M, tid);
-  mb.init((const bf16_t *)g.B, g.ldb, n0, g.N, tid);
+  ma.init(A, g.lda, m0, g.M, tid);
+  mb.init(B, g.ldb, n0, g.N, tid);
   Frag16<BM, TA, MI, BK_, KS> fa;
   Frag16<BN, TB, NJ, BK_, KS> fb;
   fa.init(wm * WTM, lane, kg * KS);
   fb.init(wn * WTN, lane, kg * KS);
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t *)lds);
-  // load l (first A's, then B's) of slice t into stage st
+  // load l (first A's, then B's) of slice t into stage st  (a whole contraction's length is read from the arguments: kept in a
+  // variable it costs the largest shapes registers they do not have)
   auto issue = [&](int l, int t, int st) {
     const uint32_t b = lds0 + st * STAGE * 2;
-    if (l < MA::N) ma.issue(l, t, g.K - t * BK_, b, wave);
-    else mb.issue(l - MA::N, t, g.K - t * BK_, b + BM * BK_ * 2, wave);
+    const int left = (HALVES ? K : g.K) - t * BK_;
+    if (l < MA::N) ma.issue(l, t, left, b, wave);
+    else mb.issue(l - MA::N, t, left, b + BM * BK_ * 2, wave);
   };
   f32x4_t acc[MI][NJ];
 #pragma unroll
@@ -205,7 +221,8 @@ __device__ __forceinline__ void gemm16_tile(const GemmArgs &g, const int bid, co
         *(f32x4_t *)(patch + (h * 16 + (lane & 15)) * SP + j * 16 + (lane >> 4) * 4) = acc[i + h][j];
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
-    store_patch<WTN, PR, true>(g, 0, patch, m0 + wm * WTM + (kg * MG + i) * 16, n0 + wn * WTN, lane, vec);
+    if constexpr (HALVES) add_patch<WTN, PR>(g, patch, m0 + wm * WTM + (kg * MG + i) * 16, n0 + wn * WTN, lane);
+    else store_patch<WTN, PR, true>(g, 0, patch, m0 + wm * WTM + (kg * MG + i) * 16, n0 + wn * WTN, lane, vec);
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
   }
@@ -215,6 +232,49 @@ template <int BM, int BN, int WM, int WN, int KW, int TA, int TB, int BK_, int S
 __global__ __launch_bounds__(64 * WM * WN * KW, OCC * WM * WN * KW / 4) void gemm_plain_kernel(const GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) bf16_t lds_dyn[];
   gemm16_tile<BM, BN, WM, WN, KW, TA, TB, BK_, S>(g, blockIdx.x, gridDim.x, lds_dyn);
+}
+
+template <int BM, int BN, int WM, int WN, int BK_, int S>
+__global__ __launch_bounds__(64 * WM * WN, WM * WN / 4) void gemm_halves_kernel(const GemmArgs g) {
+  extern __shared__ __attribute__((aligned(16))) bf16_t lds_dyn[];
+  gemm16_tile<BM, BN, WM, WN, 1, 0, 1, BK_, S, true>(g, blockIdx.x, gridDim.x, lds_dyn);
+}
+
+// the M x N results are cleared before the halves add to them
+__global__ __launch_bounds__(256) void clear_result_kernel(float *__restrict__ c, int64_t ldc, int M, int N) {
+  const int col = blockIdx.x * 256 + threadIdx.x;
+  if (col >= N) return;
+  for (int row = blockIdx.y; row < M; row += gridDim.y) c[row * ldc + col] = 0.f;
+}
+
+template <int SHAPE, int WM, int WN, int BK_, int S>
+static hipError_t launch_halves(const GemmDesc &d, hipStream_t s) {
+  constexpr int BM = half_shapes[SHAPE].bm, BN = half_shapes[SHAPE].bn;
+  constexpr size_t lds = (size_t)S * (BM + BN) * BK_ * 2;
+  GemmArgs a;
+  gemm_fill_args(a, d);
+  a.tiles_m = (a.M + BM - 1) / BM;
+  a.tiles_n = (a.N + BN - 1) / BN;
+  a.grp = xcd_group_rows(a.tiles_m, a.tiles_n, BM, BN, 32);
+  auto kern = gemm_halves_kernel<BM, BN, WM, WN, BK_, S>;
+  static OncePerGpu once;
+  const hipError_t attr = allow_lds(once, (const void *)kern, lds);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(clear_result_kernel, dim3((d.N + 255) / 256, d.M < 4096 ? d.M : 4096), dim3(256), 0, s, d.out_f32, d.ldc, d.M, d.N);
+  hipLaunchKernelGGL(kern, dim3(2 * a.tiles_m * a.tiles_n), dim3(64 * WM * WN), lds, s, a);
+  return hipGetLastError();
+}
+
+// A product that may be computed in two halves: fp32 results alone, nothing added to them, in memory of the GPU (atomic
+// additions to host memory are not carried out)
+static bool halves_ok(const GemmDesc &d) {
+  if (!d.out_f32 || d.out_act || d.resid || d.bias || d.epi != EPI_NONE) return false;
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, d.out_f32) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice;
 }
 
 // Several products of one layout in one launch (the weight-gradient products of a block: each alone may leave most of
@@ -330,7 +390,16 @@ hipError_t launch_gemm_plain(const GemmDesc &d, hipStream_t s) {
     const int split = best_split_shape(x);
     return split >= 0 ? launch_gemm_split(d, split, s) : launch_best(&d, 1, SHAPE_64X64K2, s);
   }
-  const int shape = best_shape(&x, 1, &cost);
+  const int shape = best_shape(&x, 1, &cost), half = best_half_shape(x, cost);
+  if (half >= 0 && halves_ok(d)) {
+    static const char *const names[] = {"gemm_bf16_128x128_halves_nn", "gemm_bf16_128x192_halves_nn", "gemm_bf16_128x256_halves_nn"};
+    ProfScope ps(names[half], s, gemm_flops(d), 0);
+    switch (half) {
+      case 0: return launch_halves<0, 2, 4, 64, 4>(d, s);
+      case 1: return launch_halves<1, 2, 4, 64, 3>(d, s);
+      case 2: return launch_halves<2, 2, 4, 64, 3>(d, s);
+    }
+  }
   return launch_best(&d, 1, shape, s);
 }
 

@@ -661,6 +661,46 @@ def test_gelu_epilogues_of_few_tiles(H, shape, d, F, M):
     assert one_block_step(H, d, F, M).get(f"gemm_bf16_{shape}_nt", 0) == 3  # forward, its recomputation and backward
 
 
+# long contractions whose halves are multiplied by a workgroup each: tiles and columns partly empty, halves of unequal length, the
+# last slice partly empty (the CPU suite holds this table against the choice)
+HALVES_CASES = [("128x128", 2349, 397, 11619), ("128x128", 1500, 1100, 10241), ("128x192", 1556, 1156, 12898),
+                ("128x192", 2045, 1511, 12445), ("128x256", 3285, 788, 10616), ("128x256", 2668, 1503, 10984)]
+
+
+@pytest.mark.parametrize("shape,M,N,K", HALVES_CASES)
+def test_gemm_bf16_in_halves(H, shape, M, N, K):
+    r8 = lambda n: (n + 7) // 8 * 8
+    A, B = torch.zeros(M, r8(K) + 8, device="cuda").bfloat16(), torch.full((K, r8(N) + 8), float("nan"), device="cuda").bfloat16()
+    A[:, :K], B[:, :N] = randn(M, M, K).bfloat16(), randn(N, K, N).bfloat16()
+    A[:, r8(K):] = float("nan")
+    a, b = A[:, :K].double(), B[:, :N].double()
+    prod, mag = 0.5 * (a @ b), 0.5 * (a.abs() @ b.abs())
+    outs = [torch.full((M, N + 3), 7.0, device="cuda") for _ in range(4)]
+    with launched(H) as names:
+        for o in outs:
+            H.hydra_op_gemm(1, 0, 1, M, N, K, 0.5, A, A.shape[1], B, B.shape[1], None, None, o, None, N + 3)
+    assert names == {f"gemm_bf16_{shape}_halves_nn": 4}, names
+    for o in outs:
+        assert torch.equal(o, outs[0]) and (o[:, N:] == 7.0).all()
+    # as in test_gemm_bf16_tile_shapes
+    assert ((outs[0][:, :N].double() - prod).abs() <= 2 * (K + 4) * U32 * mag).all()
+    # what a caller adds, a bf16 result, results in host memory: whole
+    resid, bias = randn(3, M, N), randn(4, N)
+    act, host = torch.empty(M, N, device="cuda").bfloat16(), torch.empty(M, N, pin_memory=True)
+    for args, want in (((bias, None, outs[0], None), prod + bias.double()), ((None, resid, outs[0], None), prod + resid.double()),
+                       ((None, None, None, act), prod), ((None, None, host, None), prod)):
+        o = args[2] if args[2] is not None else args[3]
+        o = o if o is not outs[0] else torch.empty(M, N, device="cuda")
+        with launched(H) as names:
+            H.hydra_op_gemm(1, 0, 1, M, N, K, 0.5, A, A.shape[1], B, B.shape[1], *args[:2], *((None, o) if args[2] is None else (o, None)), N)
+        assert not any("halves" in n for n in names), names
+        assert (o.cuda().double() - want).norm() <= 2.0 ** -8 * want.norm()
+
+
+def test_gemm_bf16_in_halves_under_concurrency(H):
+    test_gemm_bf16_repeats_bitwise_under_concurrency(H, "128x128_halves", "nn", 1500, 1096, 10248)
+
+
 # large products of contraction-strided operands (at least 128 tiles of 256x256): the shapes with slices of 32 steps, an odd and
 # an even number of them, the last one partly empty, and the others that large_tn may choose (the CPU suite holds this table
 # against the choice); then the weight gradients of a block in one launch

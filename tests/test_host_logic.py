@@ -515,6 +515,39 @@ int main() {
     assert {c[0] for c in V.GELU_SPLIT_CASES} == {s for i, s in names.items() if i > 0}
 
 
+def test_products_in_halves(tmp_path):
+    """The GPU suite's table of products computed in two halves; none of another layout, with few or many tiles or a short
+    contraction."""
+    from tests import test_gpu_kernel_variants as V
+    src = tmp_path / "t.cpp"
+    src.write_text(r'''
+#include "gemm_shapes.h"
+#include <cstdio>
+using namespace hydra;
+int main() {
+  int M, N, K, ta, tb;
+  while (scanf("%d %d %d %d %d", &M, &N, &K, &ta, &tb) == 5) {
+    GemmDims x{M, N, K, ta != 0, tb != 0, (N & 3) == 0};
+    float c = 0.f;
+    if (!few_tiles(x)) best_shape(&x, 1, &c);
+    printf("%d\n", few_tiles(x) ? -1 : best_half_shape(x, c));
+  }
+}
+''')
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2110_08633_amd", "csrc"),
+                           str(src), "-o", str(tmp_path / "t")])
+    names = ["128x128", "128x192", "128x256"]
+    cases = [(M, N, K, 0, 1, names.index(s)) for s, M, N, K in V.HALVES_CASES] + [(1500, 1096, 10248, 0, 1, 0)]
+    cases += [(M, N, K, ta, tb, -1) for _, M, N, K, in V.HALVES_CASES for ta, tb in ((0, 0), (1, 0), (1, 1))]
+    cases += [(M, N, K // 2, 0, 1, -1) for _, M, N, K, in V.HALVES_CASES]
+    cases += [(201, 768, 50257, 0, 1, -1), (8192, 1600, 50257, 0, 1, -1), (100000, 20000, 10240, 0, 1, -1)]
+    ask = "\n".join(" ".join(map(str, c[:5])) for c in cases)
+    out = subprocess.run([str(tmp_path / "t")], input=ask, text=True, capture_output=True, check=True).stdout.split()
+    for c, i in zip(cases, out):
+        assert int(i) == c[5], (c, i)
+    assert {s for s, *_ in V.HALVES_CASES} == set(names)
+
+
 # calls whose 128-row blocks fill the chip, and one-tile backward calls: measured 8 to 18 % (4 %) slower with the other forms
 WHOLE_BLOCKS = [(3, 25, 1024, 64, 0, 0), (5, 25, 832, 64, 0, 0), (7, 25, 560, 64, 0, 0), (7, 25, 328, 64, None, 0), (6, 25, 576, 64, None, 0),
                 (7, 32, 240, 64, 0, 0), (7, 12, 672, 128, None, 0), (7, 12, 648, 128, None, 0), (4, 12, 56, 64, 1, 0), (4, 12, 40, 64, 1, 0)]
