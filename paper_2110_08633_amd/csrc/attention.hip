@@ -700,7 +700,7 @@ __global__ __launch_bounds__(256) void attn_dsum_kernel(const bf16_t *__restrict
 // backward, both parts in one launch: 2 * pairs blocks per row block, those of part 2, which take longer, first.  Bound: at a few
 // hundred row blocks the chain of tiles of a block, 0.6 to 0.9 us per 64 rows, which the other part's blocks now share the CUs
 // with; at thousands the matrix pipes, as for the parts alone, less the tails of two launches.  us, two launches / one: B 4,
-// H 12, T 512, dh 64 23.9 / 19.9, B 1, H 12, T 512 19.7 / 13.2, B 8, H 25, T 1024 143 / 133, dh 128 B 1, H 16, T 512 35 / 24.
+// H 12, T 512, dh 64 23.9 / 18.7, B 1, H 12, T 512 19.7 / 13.2, B 8, H 25, T 1024 143 / 133, dh 128 B 1, H 16, T 512 35 / 24.
 // At head width 64 three blocks share a CU (168 registers) unless they sum D (213 to 243: two); at 128 two, with 5 to 41
 // registers spilled.
 // ---------------------------------------------------------------------------
@@ -782,7 +782,7 @@ static hipError_t attn_bwd_form(const bf16_t *qkv, const bf16_t *o, const bf16_t
 #define HYDRA_MODE(M_) \
   if (mode == M_) return attn_bwd<DH, f.rw, f.kw, f.tk, M_, DIRECT>(qkv, o, d_o, lse, dsum, dqkv, B, H, T, s)
   if constexpr (DH == 64 || F == 1) HYDRA_MODE(BWD_ONE);
-  if constexpr (DH == 128 || F != 1) HYDRA_MODE(BWD_ONE_AFTER_D);
+  if constexpr (DH == 128 || F == 0 || F == 2) HYDRA_MODE(BWD_ONE_AFTER_D);
   if constexpr (DH == 128 && F == 0) HYDRA_MODE(BWD_TWO);
 #undef HYDRA_MODE
   return hipErrorInvalidValue;

@@ -29,10 +29,11 @@ constexpr AttnForm attn_forms_fwd64[] = {{4, 1, 64, 3.147f, 0.762f, 0.666f},
 constexpr AttnForm attn_forms_fwd128[] = {{4, 1, 32, 3.860f, 0.667f, 0.572f},
                                           {2, 1, 32, 3.347f, 0.668f, 0.368f},
                                           {2, 2, 32, 4.604f, 0.620f, 0.804f}};
-constexpr AttnForm attn_forms_bwd64[] = {{4, 1, 64, 9.038f, 2.508f, 1.942f},
-                                         {2, 1, 32, 7.018f, 1.600f, 0.578f},
-                                         {2, 2, 32, 9.966f, 1.309f, 1.260f},
-                                         {2, 2, 64, 10.099f, 1.855f, 2.576f}};
+// (backward at head width 64: fitted to 340 calls with the launches of attn_bwd_mode, to the choice rather than the times)
+constexpr AttnForm attn_forms_bwd64[] = {{4, 1, 64, 3.557f, 3.333f, 1.875f},
+                                         {2, 1, 32, 2.999f, 1.706f, 0.618f},
+                                         {2, 2, 32, 7.170f, 0.823f, 1.938f},
+                                         {2, 2, 64, 7.611f, 0.983f, 4.965f}};
 constexpr AttnForm attn_forms_bwd128[] = {{4, 1, 64, 11.223f, 4.395f, 3.716f},
                                           {2, 1, 32, 9.295f, 2.444f, 1.181f},
                                           {2, 2, 32, 14.782f, 2.022f, 2.582f}};
@@ -72,27 +73,26 @@ inline int attn_form_fwd(int dh, int pairs, int T) {
 // 9.4 / 9.9), up to 32 rows it is one of each and the smaller block is done sooner (7.9 / 6.8)
 inline int attn_form_bwd(int dh, int pairs, int T) {
   if (dh == 64 && T > 32 && T <= 64) return 0;
-  return dh == 64 ? best_attn_form(attn_forms_bwd64, dh, pairs, T, 0.92f)
+  return dh == 64 ? best_attn_form(attn_forms_bwd64, dh, pairs, T, 0.954f)
                   : best_attn_form(attn_forms_bwd128, dh, pairs, T, 0.95f);
 }
 
 // The launches of the backward pass, whose two parts are dQ and dK/dV: two (part 2 reads the D = rowsum(dO * O) that part 1
-// wrote); one, in which the blocks of part 2 sum D themselves; or one after a small launch that sums D.  The figures and the
-// constants above are those of two launches.  Most calls wait for chains of tiles, those of one part as long as the other's, and
-// have room for both at once: two / one, us: B 4, H 12, T 512, dh 64 23.9 / 19.9; B 1, H 12, T 1024 30.3 / 23.7; B 2, H 4, T 64
-// 9.0 / 5.4; B 8, H 25, T 1024 143 / 133; B 1, H 16, T 1024, dh 128 57 / 44.  Over 910 random calls of 16 to 2048 positions the
-// mode taken here gives 0.75 (head width 64) and 0.87 (128) of the time of two launches, within 4 and 2 % of the best block form
-// and mode.
+// wrote); one, in which the blocks of part 2 sum D themselves; or one after a small launch that sums D.  (The figures above are
+// those of two launches, and so are the constants of head width 128.)  Most calls wait for chains of tiles, those of one part as
+// long as the other's, and have room for both at once: two / one, us: B 4, H 12, T 512, dh 64 23.9 / 18.7; B 1, H 12, T 1024
+// 30.3 / 24.6; B 2, H 4, T 64 9.0 / 5.4; B 8, H 25, T 1024 143 / 133; B 1, H 16, T 1024, dh 128 57 / 44.  Over 340 random calls
+// of 16 to 2048 positions form and mode are within 2 % of the best at head width 64, over 310 within 2 % at 128.
 enum AttnBwdMode { BWD_TWO, BWD_ONE, BWD_ONE_AFTER_D };
 constexpr AttnBwdMode attn_bwd_mode(int dh, int form, int pairs, int T) {
   const int rows = 32 * (dh == 64 ? attn_forms_bwd64[form] : attn_forms_bwd128[form]).rw;
   const int64_t blocks = ((int64_t)T + rows - 1) / rows * pairs;  // of each part
   if (dh == 64) {
     // Summing D takes registers: two such blocks fit a CU, of the others three.  With more blocks than the chip holds that is
-    // worth the 2.5 us of the launch before (us, one / after D, 64-row blocks: 448 blocks 27.0 / 27.4, 640 29.9 / 28.5, 896 76 /
-    // 69; 128-row: 525 32.7 / 33.9, 672 54 / 50.5); blocks of one group with 32-row tiles come at short sequences only, where it
-    // is not (B 8, H 25, T 256 23.5 / 26.7).
-    return blocks > 512 && form != 1 ? BWD_ONE_AFTER_D : BWD_ONE;
+    // worth the 2.5 us of the launch before (us, one / after D, 64-row blocks of two groups: 512 blocks 18.2 / 18.9, 640 29.9 /
+    // 28.5, 1056 50.5 / 44.6; 128-row: 525 32.7 / 33.9, 672 54 / 50.5); not for blocks of one group with 32-row tiles (B 8, H 25,
+    // T 256 23.5 / 26.7), and 64-row tiles shared by two groups are for few blocks anyway.
+    return blocks > 512 && (form == 0 || form == 2) ? BWD_ONE_AFTER_D : BWD_ONE;
   }
   // Head width 128: with D to sum 40 registers are spilled, which only sequences of a tile or two do not feel (T 24 7.2 / 8.3 us,
   // T 64 11.1 / 11.1, T 128 16.6 / 15.1).  Two launches remain where 128-row blocks abound: D is summed beside part 1's other

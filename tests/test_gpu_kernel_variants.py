@@ -556,9 +556,9 @@ def test_attention_every_form(H, B, Hn, T, dh):
 
 # every block form of the backward pass in every way its parts are launched (two launches, one, one after a launch that sums D;
 # the CPU suite holds the table against the choice): partly empty row blocks, tiles and groups
-ATT_BWD_CASES = [(1, 1, 40, 64, 0, 1), (11, 13, 200, 64, 0, 1), (40, 7, 208, 64, 0, 2), (40, 13, 40, 64, 0, 2), (1, 1, 8, 64, 1, 1),
-                 (1, 2, 88, 64, 1, 1), (5, 7, 136, 64, 2, 1), (25, 7, 168, 64, 2, 2), (1, 2, 104, 64, 3, 1), (1, 1, 1000, 64, 3, 1),
-                 (11, 5, 584, 64, 3, 2), (40, 13, 200, 128, 0, 0), (11, 13, 232, 128, 0, 2), (1, 2, 8, 128, 1, 1), (3, 5, 40, 128, 1, 1),
+ATT_BWD_CASES = [(1, 1, 40, 64, 0, 1), (11, 5, 888, 64, 0, 1), (40, 8, 232, 64, 0, 2), (40, 13, 40, 64, 0, 2), (1, 1, 8, 64, 1, 1),
+                 (1, 2, 88, 64, 1, 1), (11, 13, 200, 64, 1, 1), (5, 7, 136, 64, 2, 1), (11, 5, 584, 64, 2, 2), (1, 2, 104, 64, 3, 1),
+                 (1, 1, 1000, 64, 3, 1), (40, 13, 200, 128, 0, 0), (11, 13, 232, 128, 0, 2), (1, 2, 8, 128, 1, 1), (3, 5, 40, 128, 1, 1),
                  (1, 3, 72, 128, 1, 2), (2, 1, 104, 128, 2, 2), (1, 3, 1000, 128, 2, 2)]
 
 
