@@ -69,13 +69,13 @@ inline bool shape_fits(const PlainShape &p, const GemmDims *d, int n) {
 // two blocks of four wavefronts with 128x256 tiles fit a CU, one writing out while the other multiplies.  Constants as above
 // (rounds of twice 256 tiles where two blocks share a CU), fitted to 1340 products and groups of random layers launched one
 // after another with operands that are not in the L2s.
-struct TnShape {
+struct LargeShape {
   int shape;  // of plain_shapes
   float t0, a, b, c, e;
   float f;  // us per MB of fp32 results beyond the 220 that stay in the 256 MB cache
 };
 constexpr int SHAPE_256X256 = 0, SHAPE_64X64K2 = 7, SHAPE_128X256X2 = N_SHAPES - 1;
-constexpr TnShape tn_shapes[] = {{SHAPE_256X256, 4.386f, 0.934f, 0.622f, 9.367f, 0.776f, 0.063f},
+constexpr LargeShape tn_shapes[] = {{SHAPE_256X256, 4.386f, 0.934f, 0.622f, 9.367f, 0.776f, 0.063f},
                                  {1, 3.069f, 0.546f, 0.341f, 5.485f, 1.107f, 0.051f},
                                  {2, 3.256f, 0.308f, 0.429f, 5.147f, 0.f, 0.031f},
                                  {10, 4.982f, 0.484f, 0.239f, 2.171f, 1.423f, 0.114f},
@@ -91,7 +91,27 @@ inline bool large_tn(const GemmDims *d, int n) {
   }
   return tiles >= 128;
 }
-inline float tn_cost(const TnShape &t, const GemmDims *d, int n) {
+// Large products whose operands are both contraction-contiguous (forward, input gradients).  At short contractions the estimate
+// for all products misses what thousands of small tiles read again and write, and takes 128x64 where 256x256 are up to 1.8 times
+// as fast.  Constants as above, f = 0: fits to 539 products with more than 256 tiles of 256x256 (contractions of 128 to 6000
+// steps, results of up to 200 million, fp32 and bf16), operands not in the L2s.
+constexpr LargeShape nt_shapes[] = {{SHAPE_256X256, 8.001f, 1.171f, 0.524f, 2.448f, 9.053f, 0.f},
+                                    {1, 7.700f, 0.458f, 0.617f, 1.009f, 4.738f, 0.f},
+                                    {2, 5.271f, 0.297f, 0.586f, 1.018f, 3.906f, 0.f},
+                                    {3, 2.967f, 0.492f, 0.149f, 0.f, 3.591f, 0.f},
+                                    {4, 5.219f, 0.298f, 0.204f, 0.f, 1.374f, 0.f}};
+
+// more than one round of 256x256 tiles (with 192 to 256 of them the choice gave 1 % and 21 of 248 were more than 3 % slower), a
+// contraction no shorter than the fitted ones and results stored by vectors as theirs
+inline bool large_nt(const GemmDims *d, int n) {
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    if (d[i].ta || d[i].tb || d[i].K < 128 || !d[i].vec_rows) return false;
+    tiles += ((int64_t)d[i].M + 255) / 256 * (((int64_t)d[i].N + 255) / 256);
+  }
+  return tiles > 256;
+}
+inline float large_cost(const LargeShape &t, const GemmDims *d, int n) {
   const PlainShape &p = plain_shapes[t.shape];
   float tiles = 0.f, mb = 0.f;
   int K = 0;
@@ -121,19 +141,24 @@ inline int best_shape(const GemmDims *d, int n, float *cost) {
     const float c = shape_cost(plain_shapes[i], d, n);
     if (i == 0 || (c < *cost && shape_fits(plain_shapes[i], d, n))) { best = i; *cost = c; }
   }
-  if (!large_tn(d, n)) return best;
-  // Large: another shape has to be estimated 4 % below the one that all products would choose.  The 1340 take 0.938 times as
-  // long as with that one, 1.6 % more than with the best shape; 42 are more than 3 % (9 more than 5 %) slower than before there
-  // was a second table (with constants fitted to 106 products launched alone, and without the margin: 0.965, 255 and 172).  us,
-  // launched one after another, the first choice / now: 4096x16384x1024 175 / 157, 4096^3 126 / 112, 768x50257x2048 213 / 199,
-  // 3728x3288x5556 159 / 127, 16384x4096x1024 157 / 147, 1600x6400x1000 33.9 / 32.6, 1024x50257x1024 197 / 175.
+  // Large: another shape has to be estimated 4 % below the one that all products would choose.  The 1340 of two strided operands
+  // take 0.938 times as long as with that one, 1.6 % more than with the best shape; 42 are more than 3 % (9 more than 5 %) slower
+  // than before there was a second table (with constants fitted to 106 products launched alone, and without the margin: 0.965, 255
+  // and 172).  us, launched one after another, the first choice / now: 4096x16384x1024 175 / 157, 4096^3 126 / 112, 768x50257x2048
+  // 213 / 199, 3728x3288x5556 159 / 127, 16384x4096x1024 157 / 147, 1600x6400x1000 33.9 / 32.6, 1024x50257x1024 197 / 175.
+  // Contraction-contiguous: 0.936 times over 300 products that the constants were not fitted to, two more than 3 % slower
+  // (13226x1888x368 43 / 52, the worst); 1547x45480x512 198 / 129, 1087x38984x392 119 / 78, 2215x35944x360 162 / 140.
+  const bool nt = large_nt(d, n);
+  if (!nt && !large_tn(d, n)) return best;
   const int first = best;
   float least = 0.f, own = 0.f;
-  for (const TnShape &t : tn_shapes) {
-    const float c = tn_cost(t, d, n);
+  auto among = [&](const LargeShape &t) {
+    const float c = large_cost(t, d, n);
     if (t.shape == first) own = c;
     if (least == 0.f || (c < least && shape_fits(plain_shapes[t.shape], d, n))) { best = t.shape; least = c; }
-  }
+  };
+  if (nt) for (const LargeShape &t : nt_shapes) among(t);
+  else for (const LargeShape &t : tn_shapes) among(t);
   if (own == 0.f || least >= 0.96f * own) return first;
   *cost = least;
   return best;

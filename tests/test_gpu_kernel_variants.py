@@ -719,6 +719,16 @@ def test_gemm_bf16_large_weight_gradients_repeat_bitwise_under_concurrency(H, sh
     test_gemm_bf16_repeats_bitwise_under_concurrency(H, shape, "tn", M, N, K)
 
 
+# large products of contraction-contiguous operands (more than one round of 256x256 tiles, a short contraction): the shapes that
+# large_nt takes instead of the one that all products would (the CPU suite holds this table against both)
+LARGE_NT_CASES = [("256x256", 658, 39020, 136), ("256x256", 648, 33892, 328), ("128x256", 328, 33332, 520), ("128x192", 394, 35764, 328)]
+
+
+@pytest.mark.parametrize("shape,M,N,K", LARGE_NT_CASES)
+def test_gemm_bf16_large_products_of_short_contractions(H, shape, M, N, K):
+    test_gemm_bf16_every_tile_shape(H, shape, "nt", M, N, K)
+
+
 # a group that four launches were once estimated to be faster for (they take 1.2 times as long)
 def test_weight_gradients_of_a_block_stay_together(H):
     names = one_block_step(H, 1160, 4640, 776)

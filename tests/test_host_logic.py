@@ -469,6 +469,18 @@ def test_large_weight_gradient_cases_take_the_tile_shapes_they_name(tile_shape):
         assert order[tile_shape(M, N, K, 1, 1, N % 4 == 0)[0]] == shape, (shape, M, N, K)
 
 
+def test_large_products_of_short_contractions_take_the_tile_shapes_they_name(tile_shape):
+    """The others: results that are not stored by vectors, one round of tiles, a contraction shorter than the
+    fitted ones."""
+    from tests import test_gpu_kernel_variants as V
+    order = list(V.EVERY_SHAPE)
+    for shape, M, N, K in V.LARGE_NT_CASES:
+        assert order[tile_shape(M, N, K, 0, 0)[0]] == shape, (shape, M, N, K)
+        assert order[tile_shape(M, N, K, 0, 0, False)[0]] != shape, (shape, M, N, K)
+    assert {c[0] for c in V.LARGE_NT_CASES} == {"256x256", "128x256", "128x192"}
+    assert order[tile_shape(4096, 4096, 136, 0, 0)[0]] != "256x256" and order[tile_shape(658, 39020, 120, 0, 0)[0]] != "256x256"
+
+
 @pytest.mark.parametrize("M,N,K,shape", [(1936, 9792, 2578, "128x128x2"), (11576, 1568, 3495, "128x128x2"), (13752, 1472, 2625, "128x128x2"),
                                          (8512, 2599, 2425, "128x256"), (3001, 3004, 289, "128x128x2"), (14024, 568, 292, "128x64"),
                                          (4096, 16384, 1024, "256x256"), (3728, 3288, 5556, "256x256")])
