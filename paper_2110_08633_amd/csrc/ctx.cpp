@@ -208,6 +208,14 @@ static bool page_locked(const void *host) {
   return yes;
 }
 
+// memory that the runtime did not allocate
+static bool ordinary_memory(const void *p) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) == hipSuccess) return at.type == hipMemoryTypeUnregistered;
+  (void)hipGetLastError();
+  return true;
+}
+
 static hydra_status make_event(hydra_ctx *ctx, hipEvent_t *ev) {
   if (ctx->dry) return HYDRA_OK;
   HYDRA_HIP(ctx, hipEventCreateWithFlags(ev, hipEventDisableTiming));
@@ -935,11 +943,13 @@ hydra_status hydra_read_device(hydra_ctx *ctx, int32_t model, int32_t shard, int
       if (ctx->dry) return HYDRA_OK;
       const float *const logits = ctx->lanes[m->lane].logits;
       const size_t padded = (size_t)s.M * s.Vpad * 4;
-      // The runtime's two-dimensional copy into ordinary memory takes 6 to 8 us per row, whatever its length (us, 2-D / whole:
-      // 128 x 512 968 / 131, 64 x 300 470 / 14, 512 x 5000 4077 / 783, 2048 x 20000, 160 MB, 23 / 22 ms).  Rows without padding are
-      // one range; logits of moderate size are read with their padding, which is dropped on the host.
+      // The runtime's two-dimensional copy into ordinary memory takes about 7 us per short row; long rows are bound by the copy
+      // itself (us, 2-D / whole: 128 x 500 974 / 120, 64 x 300 437 / 15, 512 x 5000 4198 / 829, 2048 x 20000, 160 MB, 23 / 22 ms).
+      // Rows without padding are one range; up to 64 MB are read with their padding, which is dropped on the host.  Not into
+      // page-locked or device memory, where the 2-D copy does without the second pass and the host need not reach the
+      // destination (128 x 500 14 / 28 and 13 / -, 2048 x 8190 1185 / 6264 and 51 / -).
       std::unique_ptr<float[]> rows;
-      if (s.V != s.Vpad && padded <= LOGITS_WHOLE_BYTES) rows.reset(new (std::nothrow) float[padded / 4]);
+      if (s.V != s.Vpad && padded <= LOGITS_WHOLE_BYTES && ordinary_memory(host_dst)) rows.reset(new (std::nothrow) float[padded / 4]);
       if (s.V == s.Vpad || rows) {
         HYDRA_HIP(ctx, hipMemcpy(rows ? rows.get() : (float *)host_dst, logits, padded, hipMemcpyDeviceToHost));
         for (int64_t r = 0; rows && r < s.M; ++r) memcpy((float *)host_dst + r * s.V, rows.get() + r * s.Vpad, (size_t)s.V * 4);

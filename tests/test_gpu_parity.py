@@ -345,6 +345,30 @@ def test_sharding_does_not_change_gpu_results(rt):
             assert (o[2][name] == outs[0][2][name]).all(), name
 
 
+@pytest.mark.parametrize("V,B,T", [(512, 2, 64), (211, 2, 64), (50200, 4, 96)])  # no padding, some, more than is read whole
+def test_logits_are_read_into_every_kind_of_memory(rt, V, B, T):
+    """Ordinary memory, page-locked memory and a tensor of the GPU, which the host cannot write to."""
+    H, R = rt
+    cfg = SI.small_cfg(L=2, d=64, H=2, F=128, V=V, T=T, B=B, k=1, dtype="bf16")
+    sess = R.Session(R.arena_bytes_for([cfg], 2), max_slots=2)
+    rec = sess.add_model(cfg, SI.make_weights(cfg, 5), 1e-3)
+    H.hydra_set_batch(sess.ctx, rec["id"], *(np.ascontiguousarray(a, np.int32) for a in SI.make_batch(cfg, 6)))
+    for s in range(rec["S"] + 2):
+        H.hydra_shard_load_async(sess.ctx, rec["id"], s, H.LOAD_PARAMS)
+        H.hydra_shard_forward(sess.ctx, rec["id"], s)
+        if s != rec["S"] + 1:
+            H.hydra_shard_spill(sess.ctx, rec["id"], s, H.SPILL_EVICT)
+    plain = sess.read_logits(rec)
+    assert plain.shape == (B * T, V) and np.isfinite(plain).all() and plain.std(0).min() > 0
+    for kind in ("page-locked", "device"):
+        dst = torch.full((B * T * V + 64,), 7.0, device="cuda" if kind == "device" else "cpu", pin_memory=kind != "device")
+        torch.cuda.synchronize()
+        assert H.lib.hydra_read_device(sess.ctx, rec["id"], 0, H.RD_LOGITS, dst.data_ptr(), 4 * B * T * V) == 0, kind
+        got = dst.cpu().numpy()
+        assert (got[:-64].reshape(B * T, V) == plain).all() and (got[-64:] == 7.0).all(), kind
+    sess.close()
+
+
 @pytest.mark.parametrize("nm,flags", [(2, 0), (3, 6), (4, 0)])   # 6 = checkpoint spilling + poisoned buffers
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_micro_batches_equal_one_large_minibatch(rt, nm, flags, dtype):
