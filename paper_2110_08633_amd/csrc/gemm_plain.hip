@@ -2,6 +2,7 @@
 // the choice of their tile shape.
 #include "gemm16_ops.h"
 #include "gemm_shapes.h"
+#include "result_memory.h"
 
 namespace hydra {
 
@@ -265,16 +266,16 @@ static hipError_t launch_halves(const GemmDesc &d, hipStream_t s) {
   return hipGetLastError();
 }
 
-// A product that may be computed in two halves: fp32 results alone, nothing added to them, in memory of the GPU (atomic
-// additions to host memory are not carried out)
+// A product that may be computed in two halves: fp32 results alone, nothing added to them, in memory that takes the additions
 static bool halves_ok(const GemmDesc &d) {
   if (!d.out_f32 || d.out_act || d.resid || d.bias || d.epi != EPI_NONE) return false;
   hipPointerAttribute_t at;
-  if (hipPointerGetAttributes(&at, d.out_f32) != hipSuccess) {
+  int gpu;
+  if (hipPointerGetAttributes(&at, d.out_f32) != hipSuccess || hipGetDevice(&gpu) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  return at.type == hipMemoryTypeDevice;
+  return atomic_adds_ok(at, gpu);
 }
 
 // Several products of one layout in one launch (the weight-gradient products of a block: each alone may leave most of

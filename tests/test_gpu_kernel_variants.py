@@ -1,6 +1,7 @@
 """The kernel variants a call may be routed to, each at the sizes where it can go wrong: edges of tiles, remainders, the
 smallest and largest of its range.  References in float64; tolerances are bounds derived from the operand types."""
 import contextlib
+import ctypes as C
 
 import numpy as np
 import pytest
@@ -695,6 +696,27 @@ def test_gemm_bf16_in_halves(H, shape, M, N, K):
             H.hydra_op_gemm(1, 0, 1, M, N, K, 0.5, A, A.shape[1], B, B.shape[1], *args[:2], *((None, o) if args[2] is None else (o, None)), N)
         assert not any("halves" in n for n in names), names
         assert (o.cuda().double() - want).norm() <= 2.0 ** -8 * want.norm()
+
+
+def test_gemm_bf16_halves_are_not_added_to_fine_grained_memory(H):
+    hip, (_, M, N, K) = H.lib, HALVES_CASES[1]  # (the runtime that the library is linked to)
+    mem = C.c_void_p()
+    assert hip.hipExtMallocWithFlags(C.byref(mem), C.c_size_t(4 * M * N), C.c_uint(1)) == 0  # hipDeviceMallocFinegrained
+
+    class Result:
+        def data_ptr(self):
+            return mem.value
+
+    A, B = randn(1, M, (K + 7) // 8 * 8).bfloat16(), randn(2, K, (N + 7) // 8 * 8).bfloat16()
+    got, whole = torch.empty(M, N, device="cuda"), torch.empty(M, N, device="cuda")
+    with launched(H) as names:
+        H.hydra_op_gemm(1, 0, 1, M, N, K, 1.0, A, A.shape[1], B, B.shape[1], None, None, Result(), None, N)
+    assert names and not any("halves" in n for n in names), names
+    torch.cuda.synchronize()
+    assert hip.hipMemcpy(C.c_void_p(got.data_ptr()), mem, C.c_size_t(4 * M * N), C.c_int(3)) == 0
+    torch.cuda.synchronize()
+    H.hydra_op_gemm(1, 0, 1, M, N, K, 1.0, A, A.shape[1], B, B.shape[1], None, torch.zeros(M, N, device="cuda"), whole, None, N)
+    assert torch.equal(got, whole)
 
 
 def test_gemm_bf16_in_halves_under_concurrency(H):

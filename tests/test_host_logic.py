@@ -560,6 +560,31 @@ int main() {
     assert {s for s, *_ in V.HALVES_CASES} == set(names)
 
 
+def test_memory_that_halves_are_added_to(tmp_path):
+    """Plain memory of the GPU that computes; not another GPU's, nor memory of another kind."""
+    src = tmp_path / "t.cpp"
+    src.write_text(r'''
+#include "result_memory.h"
+int main() {
+  auto ok = [](hipMemoryType type, int device, unsigned flags) {
+    hipPointerAttribute_t at{};
+    at.type = type; at.device = device; at.allocationFlags = flags;
+    return hydra::atomic_adds_ok(at, 1);
+  };
+  if (!ok(hipMemoryTypeDevice, 1, hipDeviceMallocDefault) || !ok(hipMemoryTypeDevice, 1, hipDeviceMallocContiguous)) return 1;
+  for (int other : {-2, 0, 2}) if (ok(hipMemoryTypeDevice, other, hipDeviceMallocDefault)) return 2;
+  for (unsigned f : {hipDeviceMallocFinegrained, hipDeviceMallocUncached, hipMallocSignalMemory})
+    if (ok(hipMemoryTypeDevice, 1, f)) return 3;
+  for (hipMemoryType t : {hipMemoryTypeUnregistered, hipMemoryTypeHost, hipMemoryTypeArray, hipMemoryTypeManaged, hipMemoryTypeUnified})
+    if (ok(t, 1, hipDeviceMallocDefault)) return 4;
+  return 0;
+}
+''')
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I",
+                           os.path.join(ROOT, "paper_2110_08633_amd", "csrc"), str(src), "-o", str(tmp_path / "t")])
+    assert subprocess.run([str(tmp_path / "t")]).returncode == 0
+
+
 # calls whose 128-row blocks fill the chip, and one-tile backward calls: measured 8 to 18 % (4 %) slower with the other forms
 WHOLE_BLOCKS = [(3, 25, 1024, 64, 0, 0), (5, 25, 832, 64, 0, 0), (7, 25, 560, 64, 0, 0), (7, 25, 328, 64, None, 0), (6, 25, 576, 64, None, 0),
                 (7, 32, 240, 64, 0, 0), (7, 12, 672, 128, None, 0), (7, 12, 648, 128, None, 0), (4, 12, 56, 64, 1, 0), (4, 12, 40, 64, 1, 0)]
