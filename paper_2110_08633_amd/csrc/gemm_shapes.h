@@ -101,12 +101,14 @@ constexpr LargeShape nt_shapes[] = {{SHAPE_256X256, 8.001f, 1.171f, 0.524f, 2.44
                                     {3, 2.967f, 0.492f, 0.149f, 0.f, 3.591f, 0.f},
                                     {4, 5.219f, 0.298f, 0.204f, 0.f, 1.374f, 0.f}};
 
-// more than one round of 256x256 tiles (with 192 to 256 of them the choice gave 1 % and 21 of 248 were more than 3 % slower), a
-// contraction no shorter than the fitted ones and results stored by vectors as theirs
+// more than one round of 256x256 tiles (with 192 to 256 of them the choice gave 1 % and 21 of 248 were more than 3 % slower),
+// contractions and results of the fitted sizes stored by vectors as theirs, and a second operand of more than 6 MB: a smaller one
+// stays in an XCD's L2, and small tiles may read it again (16280x7280x256, 3.7 MB, 128x64 153 us, 256x256 177)
 inline bool large_nt(const GemmDims *d, int n) {
   int64_t tiles = 0;
   for (int i = 0; i < n; ++i) {
-    if (d[i].ta || d[i].tb || d[i].K < 128 || !d[i].vec_rows) return false;
+    if (d[i].ta || d[i].tb || d[i].K < 128 || d[i].K > 6000 || !d[i].vec_rows || d[i].M < 256 ||
+        (int64_t)d[i].M * d[i].N > 200000000 || (int64_t)d[i].N * d[i].K <= 3 << 20) return false;
     tiles += ((int64_t)d[i].M + 255) / 256 * (((int64_t)d[i].N + 255) / 256);
   }
   return tiles > 256;
@@ -146,8 +148,9 @@ inline int best_shape(const GemmDims *d, int n, float *cost) {
   // than before there was a second table (with constants fitted to 106 products launched alone, and without the margin: 0.965, 255
   // and 172).  us, launched one after another, the first choice / now: 4096x16384x1024 175 / 157, 4096^3 126 / 112, 768x50257x2048
   // 213 / 199, 3728x3288x5556 159 / 127, 16384x4096x1024 157 / 147, 1600x6400x1000 33.9 / 32.6, 1024x50257x1024 197 / 175.
-  // Contraction-contiguous: 0.936 times over 300 products that the constants were not fitted to, two more than 3 % slower
-  // (13226x1888x368 43 / 52, the worst); 1547x45480x512 198 / 129, 1087x38984x392 119 / 78, 2215x35944x360 162 / 140.
+  // Contraction-contiguous: of 75 products that the constants were not fitted to and that take another shape here, 0.81 times as
+  // long, two more than 3 % slower (6992x24656x224 220 / 233, 8395x19080x384 260 / 272); 1547x45480x512 199 / 132, 1087x38984x392
+  // 101 / 75, 2215x35944x360 160 / 143.  (A first choice that is not in the table, 64x96, stays: 306x49616x768.)
   const bool nt = large_nt(d, n);
   if (!nt && !large_tn(d, n)) return best;
   const int first = best;

@@ -479,6 +479,13 @@ def test_large_products_of_short_contractions_take_the_tile_shapes_they_name(til
         assert order[tile_shape(M, N, K, 0, 0, False)[0]] != shape, (shape, M, N, K)
     assert {c[0] for c in V.LARGE_NT_CASES} == {"256x256", "128x256", "128x192"}
     assert order[tile_shape(4096, 4096, 136, 0, 0)[0]] != "256x256" and order[tile_shape(658, 39020, 120, 0, 0)[0]] != "256x256"
+    # a second operand that an XCD's L2 holds (up to 20 % slower with the table's shapes), longer contractions, fewer rows and larger
+    # results than the fitted ones, a first choice that is not in the table: as all products
+    for M, N, K in [(16280, 7280, 256), (8672, 5152, 256), (9965, 4008, 224), (16175, 1344, 792), (13226, 1888, 368),
+                    (7691, 4464, 10304), (100, 70000, 768), (8192, 25200, 320), (306, 49616, 768)]:
+        assert tile_shape(M, N, K, 0, 0)[0] == tile_shape(M, N, K, 0, 0, False)[0], (M, N, K)
+    for M, N, K in [(1547, 45480, 512), (1087, 38984, 392), (2215, 35944, 360)]:
+        assert tile_shape(M, N, K, 0, 0)[0] != tile_shape(M, N, K, 0, 0, False)[0], (M, N, K)
 
 
 @pytest.mark.parametrize("M,N,K,shape", [(1936, 9792, 2578, "128x128x2"), (11576, 1568, 3495, "128x128x2"), (13752, 1472, 2625, "128x128x2"),
