@@ -170,30 +170,33 @@ inline int best_shape(const GemmDims *d, int n, float *cost) {
 // Input gradients of an LM head (results tokens x width, contraction over the vocabulary, weights stored [vocabulary][width]):
 // what they wait for is lines that miss the L2s, which arrive at 3 TB/s, and small tiles - a few thousand tokens by a thousand
 // columns - read every operand 8 to 32 times.  With two workgroups per tile, one per half of the contraction, the tiles are twice
-// as large and an XCD reads half of the lines; both add their results to a cleared C, one atomic addition each (0 + a + b = 0 + b
-// + a: the bits repeat).  Cost in us: ceil(u) * n * a + u * n * b + c * results / 10^6, u = two workgroups per tile / 256, n =
-// K / 128; fits to 211 products (128 to 4096 tokens, widths 256 to 1600, vocabularies from 5000).  Of these 55 to 65 are computed
-// in halves, 0.82 times as long, clearing and adding included; none more than 2 % longer (from 8192 steps on one was, by 4 %,
-// and of 90 others one by 11: 1080x1184x8336 39.0 / 43.1).  us, whole / halves: 2048x768x50257 305 / 222, 1717x1512x30429 289 /
-// 192, 2674x648x23654 161 / 129.  Contraction-contiguous operands of 4096 to 16384 steps: 3 of 30 more than 5 % shorter, hence
-// the one layout.
+// as large and all but one XCD read half of the lines; both add their results to a cleared C, one atomic addition each (0 + a + b =
+// 0 + b + a: the bits repeat).  Cost in us: n * (a + u * b) + c * results / 10^6, u = two workgroups per tile / 256, n = K / 128;
+// fits to 211 products (128 to 4096 tokens, widths 256 to 1600, vocabularies from 5000).  us, whole / halves: 2048x768x50257
+// 313 / 224, 1024x4096x50400 470 / 391, 512x4096x50400 361 / 248, 1976x944x65803 453 / 296, 8576x120x59837 500 / 309.
+// Contraction-contiguous operands of 4096 to 16384 steps: 3 of 30 more than 5 % shorter, hence the one layout.
 struct HalfShape {
   int bm, bn;
   float a, b, c;
 };
 constexpr HalfShape half_shapes[] = {{128, 128, 0.496f, 0.118f, 6.36f}, {128, 192, 0.603f, 0.100f, 7.61f}, {128, 256, 0.744f, 0.064f, 8.38f}};
 
-// index into half_shapes, -1: whole (whole_cost: estimate of best_shape, which for these products is 0.6 to 0.9 of the measured
-// time, hence the factor)
+// index into half_shapes, -1: whole.  (whole_cost: estimate of best_shape, which for these products is 0.6 to 0.9 of the measured
+// time, hence the factor.)  Only where all workgroups run at once: with a second round of them 21 of 21 products are 4 to 35 %
+// slower than whole (8841x264x52499 405 / 546).  And only where 8 us are estimated to be gained, the clearing among them: without,
+// 2039x576x10673 43.9 / 47.6, 1003x1392x11952 55.6 / 59.9; 128x256 tiles gain nothing over whole ones of 128x128 below 11520 steps
+// (10 products, 0.92 to 1.105).  Of 531 products (128 to 33000 rows, 72 to 8192 columns, up to 200000 steps) 416 are computed in
+// halves, 0.47 to 1.005 times as long, 0.79 on average, clearing and adding included.
 inline int best_half_shape(const GemmDims &d, float whole_cost) {
-  if (d.ta || !d.tb || d.K < 10240 || ((int64_t)d.M + 127) / 128 * (((int64_t)d.N + 127) / 128) > 256) return -1;
+  if (d.ta || !d.tb || d.K < 10240) return -1;
   const float n = (float)((d.K + 127) / 128);
   int best = -1;
-  float cost = 1.35f * whole_cost;
+  float cost = 1.35f * whole_cost - 8.f;
   for (int i = 0; i < 3; ++i) {
     const HalfShape &p = half_shapes[i];
-    const float u = 2.f * (float)((d.M + p.bm - 1) / p.bm) * (float)((d.N + p.bn - 1) / p.bn) * (1.f / 256.f);
-    const float c = ceilf(u) * n * p.a + u * n * p.b + p.c * 1e-6f * (float)d.M * (float)d.N;
+    const int64_t groups = 2 * (((int64_t)d.M + p.bm - 1) / p.bm) * (((int64_t)d.N + p.bn - 1) / p.bn);
+    if (groups > 256 || (p.bn == 256 && d.K < 11520)) continue;
+    const float c = n * (p.a + (float)groups * (1.f / 256.f) * p.b) + p.c * 1e-6f * (float)d.M * (float)d.N;
     if (c < cost) { best = i; cost = c; }
   }
   return best;

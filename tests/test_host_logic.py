@@ -560,6 +560,11 @@ int main() {
     cases += [(M, N, K, ta, tb, -1) for _, M, N, K, in V.HALVES_CASES for ta, tb in ((0, 0), (1, 0), (1, 1))]
     cases += [(M, N, K // 2, 0, 1, -1) for _, M, N, K, in V.HALVES_CASES]
     cases += [(201, 768, 50257, 0, 1, -1), (8192, 1600, 50257, 0, 1, -1), (100000, 20000, 10240, 0, 1, -1)]
+    # wide heads, and narrow results of many rows
+    cases += [(1024, 4096, 50400, 0, 1, 2), (2048, 2048, 50257, 0, 1, 2), (512, 4096, 50400, 0, 1, 0), (8576, 120, 59837, 0, 1, 0)]
+    # slower in halves: two rounds of workgroups, estimates too close to each other, 128x256 tiles at their shortest contractions
+    cases += [(M, N, K, 0, 1, -1) for M, N, K in [(8841, 264, 52499), (5881, 544, 61410), (1523, 2648, 34416), (4363, 832, 40848),
+              (2039, 576, 10673), (1003, 1392, 11952), (961, 1384, 13959), (659, 4744, 11359), (2535, 1304, 10458)]]
     ask = "\n".join(" ".join(map(str, c[:5])) for c in cases)
     out = subprocess.run([str(tmp_path / "t")], input=ask, text=True, capture_output=True, check=True).stdout.split()
     for c, i in zip(cases, out):
