@@ -669,7 +669,7 @@ __device__ __forceinline__ void attn_bwd_dkv(const bf16_t *__restrict__ qkv, con
 }
 
 template <int DH, int RW, int KW, int TK, bool DIRECT>
-__global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
+__global__ __launch_bounds__(64 * RW * KW, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const bf16_t *__restrict__ qkv,
                                                                    const bf16_t *__restrict__ d_o,
                                                                    const float *__restrict__ lse,
                                                                    const float *__restrict__ dsum, bf16_t *__restrict__ dqkv,
@@ -680,7 +680,7 @@ __global__ __launch_bounds__(64 * RW * KW, 2) void attn_bwd_dkv_kernel(const bf1
 }
 
 // D alone, where part 2 does not sum it: 16 bytes of dO and O per lane, samples blockIdx.y, + gridDim.y, ...  Bound: HBM, and a
-// launch (2.5 us; 33 MB of B 4, H 16, T 2048, dh 128 about 9).
+// launch (us, traced: 13 for the 52 MB of B 8, H 25, T 512, dh 128 or T 1024, dh 64; 5.3 for 6 MB).
 template <int DH>
 __global__ __launch_bounds__(256) void attn_dsum_kernel(const bf16_t *__restrict__ o, const bf16_t *__restrict__ d_o,
                                                         float *__restrict__ dsum, int B, int T, int H) {
@@ -697,18 +697,28 @@ __global__ __launch_bounds__(256) void attn_dsum_kernel(const bf16_t *__restrict
 }
 
 // ---------------------------------------------------------------------------
-// backward, both parts in one launch: 2 * pairs blocks per row block, those of part 2, which take longer, first.  Bound: at a few
-// hundred row blocks the chain of tiles of a block, 0.6 to 0.9 us per 64 rows, which the other part's blocks now share the CUs
-// with; at thousands the matrix pipes, as for the parts alone, less the tails of two launches.  us, two launches / one: B 4,
-// H 12, T 512, dh 64 23.9 / 18.7, B 1, H 12, T 512 19.7 / 13.2, B 8, H 25, T 1024 143 / 133, dh 128 B 1, H 16, T 512 35 / 24.
-// At head width 64 three blocks share a CU (168 registers) unless they sum D (213 to 243: two); at 128 two, with 5 to 41
-// registers spilled.
+// backward, both parts in one launch: 2 * pairs blocks per row block, those of part 2, which take longer, first; MIXED: see
+// attn_bwd_place.  Bound: at a few hundred row blocks the chain of tiles of a block, 0.6 to 0.9 us per 64 rows, which the other
+// part's blocks now share the CUs with; at thousands the matrix pipes, as for the parts alone, less the tails of two launches, until
+// both parts' tensors no longer fit the caches together (attn_bwd_mode).  us, two launches / one: B 4, H 12, T 512, dh 64 23.4 /
+// 18.7, B 1, H 12, T 512 19.7 / 13.2, B 8, H 25, T 1024 143 / 133, dh 128 B 1, H 16, T 512 35 / 24; mixed H 16, T 3792, dh 64
+// 142 / 131 (151 in the other order).
+// At head width 64 three blocks share a CU (168 registers; off the 16-byte grid one form spills 4) unless they sum D (213 to 249
+// registers: two); at 128 two, with 2 to 10 registers spilled, 41 where they sum D.  (Another spelling of the loop's last statement,
+// with 4 instead of 10 spilled, made the two-group form 3 to 8 % slower.)
 // ---------------------------------------------------------------------------
-template <int DH, int RW, int KW, int TK, bool DIRECT, bool OWN_D, int OCC>
+template <int DH, int RW, int KW, int TK, bool DIRECT, bool OWN_D, int OCC, bool MIXED>
 __global__ __launch_bounds__(64 * RW * KW, OCC) void attn_bwd_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ o,
                                                                const bf16_t *__restrict__ d_o, const float *__restrict__ lse,
                                                                float *__restrict__ dsum, bf16_t *__restrict__ dqkv, int T, int H,
                                                                int d, int nb, int pairs, float scale) {
+  if constexpr (MIXED) {
+    const AttnBwdPlace at = attn_bwd_place(blockIdx.y * gridDim.x + blockIdx.x, pairs);
+    if (at.rb >= nb) return;
+    if (at.dq) attn_bwd_dq<DH, RW, KW, TK, DIRECT, OWN_D>(qkv, o, d_o, lse, dsum, dqkv, T, H, d, at.z, nb - 1 - at.rb, scale);
+    else attn_bwd_dkv<DH, RW, KW, TK, DIRECT, OWN_D>(qkv, o, d_o, lse, dsum, dqkv, T, H, d, at.z, at.rb, scale);
+    return;
+  }
   int z, rb;
   if (!block_place(2 * pairs, nb, z, rb)) return;
   if (z < pairs) attn_bwd_dkv<DH, RW, KW, TK, DIRECT, OWN_D>(qkv, o, d_o, lse, dsum, dqkv, T, H, d, z, rb, scale);
@@ -727,20 +737,20 @@ static constexpr size_t attn_lds(int dh, int rw, int kw, int tk, int nacc, int e
 }
 
 // (a row of the grid holds at most 2^32 threads)
-#define HYDRA_ATTN(KERN_, PARTS_, LDS_, ...)                                       \
+#define HYDRA_ATTN(KERN_, BLOCKS_, LDS_, ...)                                      \
   do {                                                                             \
     auto kern = KERN_;                                                             \
     static OncePerGpu once;                                                        \
     const hipError_t attr = allow_lds(once, (const void *)kern, LDS_);             \
     if (attr != hipSuccess) return attr;                                           \
-    const uint32_t blocks = (uint32_t)nb * B * H * PARTS_, gx = blocks < (1u << 22) ? blocks : 1u << 22; \
+    const uint32_t blocks = BLOCKS_, gx = blocks < (1u << 22) ? blocks : 1u << 22; \
     hipLaunchKernelGGL(kern, dim3(gx, (blocks + gx - 1) / gx), dim3(64 * RW * KW), LDS_, s, __VA_ARGS__); \
   } while (0)
 
 template <int DH, int RW, int KW, int TK, bool DIRECT>
 static hipError_t attn_fwd(const bf16_t *qkv, bf16_t *o, float *lse, int B, int H, int T, hipStream_t s) {
   const int nb = (T + 32 * RW - 1) / (32 * RW), d = H * DH;
-  HYDRA_ATTN((attn_fwd_kernel<DH, RW, KW, TK, DIRECT>), 1, attn_lds(DH, RW, KW, TK, DH / 32, 2, 0), qkv, o, lse, T, H, d, nb, B * H,
+  HYDRA_ATTN((attn_fwd_kernel<DH, RW, KW, TK, DIRECT>), (uint32_t)nb * B * H, attn_lds(DH, RW, KW, TK, DH / 32, 2, 0), qkv, o, lse, T, H, d, nb, B * H,
              LOG2E / sqrtf((float)DH));
   return hipGetLastError();
 }
@@ -751,17 +761,19 @@ static hipError_t attn_bwd(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o
   const int nb = (T + 32 * RW - 1) / (32 * RW), d = H * DH;
   const float scale = 1.0f / sqrtf((float)DH);
   constexpr size_t lds_dkv = attn_lds(DH, RW, KW, TK, DH / 16, 0, KW * 2 * 2 * TK * 4);
+  const uint32_t blocks1 = (uint32_t)nb * B * H;  // of one part
   if constexpr (MODE != BWD_TWO) {  // see attn_bwd_mode
-    if constexpr (MODE == BWD_ONE_AFTER_D) {
+    constexpr bool OWN_D = MODE == BWD_ONE || MODE == BWD_MIXED, MIXED = MODE == BWD_MIXED || MODE == BWD_MIXED_AFTER_D;
+    if constexpr (!OWN_D) {
       const uint32_t lanes = (uint32_t)T * H * (DH / 8);  // of a sample
       hipLaunchKernelGGL((attn_dsum_kernel<DH>), dim3((lanes + 255) / 256, B < 32768 ? B : 32768), dim3(256), 0, s, o, d_o, dsum, B, T, H);
     }
-    HYDRA_ATTN((attn_bwd_kernel<DH, RW, KW, TK, DIRECT, MODE == BWD_ONE, MODE == BWD_ONE || DH == 128 ? 2 : 3>), 2, lds_dkv, qkv, o, d_o,
-               lse, dsum, dqkv, T, H, d, nb, B * H, scale);
+    HYDRA_ATTN((attn_bwd_kernel<DH, RW, KW, TK, DIRECT, OWN_D, OWN_D || DH == 128 ? 2 : 3, MIXED>), MIXED ? attn_bwd_grid(blocks1) : 2 * blocks1,
+               lds_dkv, qkv, o, d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale);
   } else {
-    HYDRA_ATTN((attn_bwd_dq_kernel<DH, RW, KW, TK, DIRECT>), 1, attn_lds(DH, RW, KW, TK, DH / 32, 0, 0), qkv, o, d_o, lse, dsum,
+    HYDRA_ATTN((attn_bwd_dq_kernel<DH, RW, KW, TK, DIRECT>), blocks1, attn_lds(DH, RW, KW, TK, DH / 32, 0, 0), qkv, o, d_o, lse, dsum,
                dqkv, T, H, d, nb, B * H, scale);
-    HYDRA_ATTN((attn_bwd_dkv_kernel<DH, RW, KW, TK, DIRECT>), 1, lds_dkv, qkv, d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale);
+    HYDRA_ATTN((attn_bwd_dkv_kernel<DH, RW, KW, TK, DIRECT>), blocks1, lds_dkv, qkv, d_o, lse, dsum, dqkv, T, H, d, nb, B * H, scale);
   }
   return hipGetLastError();
 }
@@ -783,7 +795,9 @@ static hipError_t attn_bwd_form(const bf16_t *qkv, const bf16_t *o, const bf16_t
   if (mode == M_) return attn_bwd<DH, f.rw, f.kw, f.tk, M_, DIRECT>(qkv, o, d_o, lse, dsum, dqkv, B, H, T, s)
   if constexpr (DH == 64 || F == 1) HYDRA_MODE(BWD_ONE);
   if constexpr (DH == 128 || F == 0 || F == 2) HYDRA_MODE(BWD_ONE_AFTER_D);
-  if constexpr (DH == 128 && F == 0) HYDRA_MODE(BWD_TWO);
+  if constexpr (DH == 64 && (F == 0 || F == 2)) HYDRA_MODE(BWD_MIXED);
+  if constexpr (F < 3) HYDRA_MODE(BWD_MIXED_AFTER_D);
+  if constexpr (F == 0 || (DH == 64 && F == 1)) HYDRA_MODE(BWD_TWO);
 #undef HYDRA_MODE
   return hipErrorInvalidValue;
 }

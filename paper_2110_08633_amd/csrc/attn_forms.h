@@ -72,9 +72,11 @@ inline int attn_form_fwd(int dh, int pairs, int T) {
 // head width 64, backward: a sequence of one 64-row tile is one step of the first form and two of the others (B 4, H 12, T 56
 // 9.4 / 9.9), up to 32 rows it is one of each and the smaller block is done sooner (7.9 / 6.8)
 inline int attn_form_bwd(int dh, int pairs, int T) {
-  if (dh == 64 && T > 32 && T <= 64) return 0;
-  return dh == 64 ? best_attn_form(attn_forms_bwd64, dh, pairs, T, 0.954f)
-                  : best_attn_form(attn_forms_bwd128, dh, pairs, T, 0.95f);
+  if (dh == 64) return T > 32 && T <= 64 ? 0 : best_attn_form(attn_forms_bwd64, dh, pairs, T, 0.954f);
+  const int form = best_attn_form(attn_forms_bwd128, dh, pairs, T, 0.95f);
+  // head width 128, thousands of 64-row blocks of a few tiles: in one launch those lose what two had (B 27, H 32, T 408 397 / 441,
+  // B 28, H 16, T 576 298 / 318), two of 128-row blocks do not (361 and 277)
+  return form == 1 && ((int64_t)T + 63) / 64 * pairs >= (T > 512 ? 2500 : T >= 256 ? 4500 : INT64_MAX) ? 0 : form;
 }
 
 // The launches of the backward pass, whose two parts are dQ and dK/dV: two (part 2 reads the D = rowsum(dO * O) that part 1
@@ -83,23 +85,63 @@ inline int attn_form_bwd(int dh, int pairs, int T) {
 // long as the other's, and have room for both at once: two / one, us: B 4, H 12, T 512, dh 64 23.9 / 18.7; B 1, H 12, T 1024
 // 30.3 / 24.6; B 2, H 4, T 64 9.0 / 5.4; B 8, H 25, T 1024 143 / 133; B 1, H 16, T 1024, dh 128 57 / 44.  Over 340 random calls
 // of 16 to 2048 positions form and mode are within 2 % of the best at head width 64, over 310 within 2 % at 128.
-enum AttnBwdMode { BWD_TWO, BWD_ONE, BWD_ONE_AFTER_D };
+enum AttnBwdMode { BWD_TWO, BWD_ONE, BWD_ONE_AFTER_D, BWD_MIXED, BWD_MIXED_AFTER_D };
 constexpr AttnBwdMode attn_bwd_mode(int dh, int form, int pairs, int T) {
   const int rows = 32 * (dh == 64 ? attn_forms_bwd64[form] : attn_forms_bwd128[form]).rw;
   const int64_t blocks = ((int64_t)T + rows - 1) / rows * pairs;  // of each part
+  // long sequences, and each part's blocks of a row a multiple of 8 or both parts' a divisor of it: see attn_bwd_place
+  const bool lopsided = T > 2048 && (pairs % 8 == 0 || pairs == 4 || pairs < 3);
   if (dh == 64) {
+    // Two launches remain where the tensors (a KB per position and pair) exceed the 256 MB cache and both parts would fetch them at
+    // once: B 8, H 32, T 3792 1824 us, in one 2089; T 2656 923 / 982; B 4, H 32, T 2216 329 / 342; B 44, H 16, T 936 470 / 481; not
+    // for short sequences, whose tiles are read again soon (B 28, H 16, T 656 203 / 178).
+    if (form == 0 && T >= 800 && (int64_t)pairs * T >= (T > 2048 ? 240000 : T >= 1200 ? 320000 : 600000)) return BWD_TWO;
+    if (form == 1) {
+      // thousands of single tiles, of which a CU takes more while they are of part 1 alone (T 16, 9376 blocks 71.6 / 77.4 in one)
+      if (T <= 32) return blocks > (T <= 16 ? 4096 : 6000) ? BWD_TWO : BWD_ONE;
+      // the 256 MB cache as above (B 109, H 16, T 448 509 / mixed 539)
+      if (T >= 384 && (int64_t)pairs * T >= 600000) return BWD_TWO;
+      // one / mixed after D: 1476 blocks 35 / 37, 1580 42 / 43, 2448 55 / 50, 7200 296 / 249, two launches 258
+      return blocks > 1536 ? BWD_MIXED_AFTER_D : BWD_ONE;
+    }
     // Summing D takes registers: two such blocks fit a CU, of the others three.  With more blocks than the chip holds that is
     // worth the 2.5 us of the launch before (us, one / after D, 64-row blocks of two groups: 512 blocks 18.2 / 18.9, 640 29.9 /
-    // 28.5, 1056 50.5 / 44.6; 128-row: 525 32.7 / 33.9, 672 54 / 50.5); not for blocks of one group with 32-row tiles (B 8, H 25,
-    // T 256 23.5 / 26.7), and 64-row tiles shared by two groups are for few blocks anyway.
-    return blocks > 512 && (form == 0 || form == 2) ? BWD_ONE_AFTER_D : BWD_ONE;
+    // 28.5, 1056 50.5 / 44.6; 128-row: 525 32.7 / 33.9, 672 54 / 50.5); 64-row tiles shared by two groups are for few blocks anyway.
+    const bool after = blocks > 512 && form != 3;
+    // H 16, T 3792 150 / mixed 126 (two launches 139), T 2904 89 / 79 (85), B 2, H 2, T 7944 190 / 160 (185)
+    if (lopsided && form != 3) return after ? BWD_MIXED_AFTER_D : BWD_MIXED;
+    return after ? BWD_ONE_AFTER_D : BWD_ONE;
   }
-  // Head width 128: with D to sum 40 registers are spilled, which only sequences of a tile or two do not feel (T 24 7.2 / 8.3 us,
-  // T 64 11.1 / 11.1, T 128 16.6 / 15.1).  Two launches remain where 128-row blocks abound: D is summed beside part 1's other
-  // work, and nobody waits for a chain (B 4, H 16, T 2048 271 us, after D 282; B 4, H 32, T 944 160 / 164; with fewer blocks B 3,
-  // H 25, T 1584, 975 blocks, 224 / 218, B 8, H 25, T 512, 800 blocks 106 / 98).
-  if (form == 0 && blocks >= 1000) return BWD_TWO;
-  return form == 1 && T <= 48 ? BWD_ONE : BWD_ONE_AFTER_D;
+  // Head width 128: with D to sum 40 registers are spilled, which only few sequences of one tile do not feel (64 of T 24 7.4 / after
+  // D 8.2 us, 256 of T 16 9.1 / 8.6).  Two launches remain where 128-row blocks abound: D is summed beside part 1's other work, and
+  // nobody waits for a chain (B 4, H 16, T 2048 271 us, after D 282; B 4, H 12, T 2224, 864 blocks, 249 / 258; with fewer blocks
+  // B 3, H 25, T 1584, 975, 224 / 218, B 8, H 25, T 512, 800, 106 / 98).
+  if (form == 0 && blocks >= (T > 2048 ? 850 : 1000)) return BWD_TWO;
+  if (form == 1) {
+    if (T <= 32 && blocks <= 256) return BWD_ONE;
+    // thousands of short sequences, whose tiles both parts then fetch once: after D / mixed (two launches) 3008 of T 64 161 / 136
+    // (159), 9376 of T 16 136 / 126 (127), 1300 of T 40 47 / 44 (51); at T 536 136 / 143.  (700 to 1000 blocks of one tile are left 2
+    // to 9 % slower than in two launches: 996 of T 40 36.7 / 33.6.)
+    return T <= 48 || (blocks > 1024 && T <= 512) ? BWD_MIXED_AFTER_D : BWD_ONE_AFTER_D;
+  }
+  // H 16, T 3416 248 / mixed 202 (two launches 211), B 2, H 4, T 11944 1091 / 1000 (1013); others B 2, H 3, T 5632 209 / 234
+  return lopsided && blocks > 512 ? BWD_MIXED_AFTER_D : BWD_ONE_AFTER_D;
 }
+
+// The mixed launch of both parts: block id -> part, pair of sample and head, row block.  (In the other one all pairs' dK/dV blocks
+// of a row come before their dQ blocks.)  Ids go round-robin to the 8 XCDs and from there round-robin to the groups of CUs: with
+// 16 pairs, say, half of the CUs see the longer dK/dV blocks alone.  Here ids 16 q + x and 16 q + 8 + x are both parts of one
+// pair's row block, which thus share an XCD's L2, in the order of the Thue-Morse sequence: whatever power of two the CUs are taken
+// in, each gets as many of one part as of the other.  Not for few rounds of blocks, where the longest had better be first (B 7,
+// H 32, T 248, dh 128 49.6 / 54.7).
+struct AttnBwdPlace {
+  bool dq;
+  int z, rb;
+};
+constexpr AttnBwdPlace attn_bwd_place(uint32_t id, uint32_t pairs) {
+  const uint32_t k = id >> 3, m = (k >> 1) * 8 + (id & 7), rb = m / pairs;
+  return {(__builtin_popcount(k) & 1) != 0, (int)(m - rb * pairs), (int)rb};
+}
+constexpr uint32_t attn_bwd_grid(uint32_t row_blocks) { return (row_blocks + 7) / 8 * 16; }
 
 }  // namespace hydra

@@ -642,13 +642,62 @@ int main() {
 ''')
     subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2110_08633_amd", "csrc"),
                            str(src), "-o", str(tmp_path / "t")])
-    ask = "\n".join(f"{dh} {B * H} {T}" for B, H, T, dh, _, _ in V.ATT_BWD_CASES + [(32768 + 5, 1, 56, 128, 1, 2)])
+    cases = V.ATT_BWD_CASES + [(32768 + 5, 1, 56, 128, 1, 4)]
+    # each measured slower with a launch it was once given (head width, pairs, T, form, launches): sequences that are long, thousands
+    # of short ones
+    cases += [(p, 1, T, dh, f, m) for dh, p, T, f, m in [
+        (64, 256, 3792, 0, 0), (64, 256, 2656, 0, 0), (64, 704, 936, 0, 0), (64, 1744, 448, 1, 0), (64, 9376, 16, 1, 0), (64, 2416, 264, 1, 4),
+        (64, 16, 3792, 0, 3), (64, 8, 8024, 0, 3), (64, 4, 7944, 2, 3), (64, 16, 2904, 2, 4), (64, 100, 5248, 0, 0),
+        (128, 16, 3416, 2, 4), (128, 16, 2904, 2, 4), (128, 8, 11944, 0, 4), (128, 48, 2224, 0, 0), (128, 864, 408, 0, 0), (128, 448, 576, 0, 0),
+        (128, 4224, 32, 1, 4), (128, 9376, 16, 1, 4), (128, 3008, 64, 1, 4), (128, 512, 24, 1, 4)]]
+    # and with one that the others take now
+    cases += [(p, 1, T, dh, f, m) for dh, p, T, f, m in [
+        (64, 48, 512, 2, 1), (64, 224, 176, 1, 1), (64, 6, 6032, 2, 2), (64, 2720, 24, 1, 1), (128, 64, 2048, 0, 0), (128, 224, 248, 0, 2),
+        (128, 6, 5632, 2, 2), (128, 25, 2112, 2, 2), (128, 228, 536, 1, 2)]]
+    ask = "\n".join(f"{dh} {B * H} {T}" for B, H, T, dh, _, _ in cases)
     out = subprocess.run([str(tmp_path / "t")], input=ask, text=True, capture_output=True, check=True).stdout.split("\n")
-    for c, line in zip(V.ATT_BWD_CASES + [(32768 + 5, 1, 56, 128, 1, 2)], out):
+    for c, line in zip(cases, out):
         assert c[4:] == tuple(map(int, line.split())), (c, line)
     # every kernel that attention.hip builds
-    assert {c[3:] for c in V.ATT_BWD_CASES} == {(64, f, 1) for f in range(4)} | {(64, f, 2) for f in (0, 2)} | {
-        (128, 0, 0), (128, 0, 2), (128, 1, 1), (128, 1, 2), (128, 2, 2)}
+    built = {(64, 0): (0, 1, 2, 3, 4), (64, 1): (0, 1, 4), (64, 2): (1, 2, 3, 4), (64, 3): (1,), (128, 0): (0, 2, 4), (128, 1): (1, 2, 4),
+             (128, 2): (2, 4)}
+    assert {c[3:] for c in V.ATT_BWD_CASES} == {(dh, f, m) for (dh, f), ms in built.items() for m in ms}
+
+
+def test_attention_backward_mixed_launch_places_every_block_once(tmp_path):
+    """Both parts of every row block of every pair; the two parts of one in the same XCD, as many of one part as of the other in
+    every aligned run of an XCD's blocks and, over long runs, at every power of two."""
+    src = tmp_path / "t.cpp"
+    src.write_text(r'''
+#include "attn_forms.h"
+#include <cstdio>
+#include <set>
+#include <tuple>
+using namespace hydra;
+int main() {
+  for (uint32_t pairs : {1, 2, 3, 4, 7, 8, 12, 16, 25, 64, 100})
+    for (uint32_t nb : {1, 2, 3, 17, 65}) {
+      std::set<std::tuple<bool, int, int>> seen;
+      for (uint32_t id = 0; id < attn_bwd_grid(pairs * nb); ++id) {
+        const AttnBwdPlace a = attn_bwd_place(id, pairs), b = attn_bwd_place(id ^ 8, pairs);
+        if (a.z < 0 || a.z >= (int)pairs || a.rb < 0) return 1;
+        if (a.dq == b.dq || a.z != b.z || a.rb != b.rb) return 2;
+        if (a.rb < (int)nb && !seen.insert({a.dq, a.z, a.rb}).second) return 3;
+      }
+      if (seen.size() != 2 * pairs * nb) return 4;
+    }
+  for (uint32_t step = 1; step <= 32; step *= 2)
+    for (uint32_t first = 0; first < step; ++first) {
+      int dq = 0;
+      for (uint32_t k = first; k < 64 * step; k += step) dq += attn_bwd_place(k * 8, 16).dq;
+      if (dq != 32) return 5;
+    }
+  return 0;
+}
+''')
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2110_08633_amd", "csrc"),
+                           str(src), "-o", str(tmp_path / "t")])
+    assert subprocess.run([str(tmp_path / "t")]).returncode == 0
 
 
 def test_cross_entropy_threads_per_row(tmp_path):
