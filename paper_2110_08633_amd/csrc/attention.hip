@@ -168,8 +168,8 @@ __device__ __forceinline__ bool block_place(int pairs, int nb, int &z, int &rb) 
 // tiles g, g + KW, ... and the partial results are merged through LDS at the end
 // (launches that would leave CUs without work; which form when: attn_forms.h).
 // Bound: per 64 keys and wavefront 1024 clocks of MFMAs at head width 128 (512 at 64) and 960 of vector ALU, which overlap
-// only between the wavefronts of a SIMD; counters at B 4, H 16, T 2048, dh 128: matrix pipes 0.47 busy, vector ALU 0.51,
-// LDS 0.24 (with tiles of 64 keys and two blocks per CU 0.43, 0.41, 0.22).  That launch, in a row of such: 82 us with tiles
+// only between the wavefronts of a SIMD; counters at B 4, H 16, T 2048, dh 128: matrix pipes 0.44 busy, vector ALU 0.48,
+// LDS 0.22 (with tiles of 64 keys and two blocks per CU 0.43, 0.41, 0.22).  That launch, in a row of such: 82 us with tiles
 // of 64 keys, 79 with 32, whose LDS lets three blocks share a CU (165 registers; held to 128 for a fourth block it spills:
 // 132 us).  Measured without gain: tiles two and three ahead, raised wavefront priority around the MFMAs, MFMAs and
 // exponentials interleaved by scheduling directives (spills).
@@ -607,8 +607,8 @@ __device__ __forceinline__ void attn_bwd_dkv(const bf16_t *__restrict__ qkv, con
     if (i0 + TK - 1 >= kr0 && i0 < T) {  // else no query of the tile comes after a key of this wavefront
       // one half tile at a time: unrolled, the two halves' results do not fit the 256 registers two wavefronts per SIMD
       // leave at head width 128 (the two backward kernels at B 4, H 16, T 2048, dh 128: 289 -> 270 us).  Even so one register
-      // is spilled there with tiles of 64 rows, three or four with 32 (8 to 20 bytes of scratch per lane; two and four off the
-      // 16-byte grid); at head width 64 none
+      // is spilled there where part 2 has a launch of its own (8 bytes of scratch per lane; two off the 16-byte grid); for one
+      // launch of both parts see attn_bwd_kernel
 #pragma unroll 1
       for (int nt = 0; nt < NT; ++nt) {
         f32x16_t s, dp;
@@ -797,7 +797,7 @@ static hipError_t attn_bwd_form(const bf16_t *qkv, const bf16_t *o, const bf16_t
   if constexpr (DH == 128 || F == 0 || F == 2) HYDRA_MODE(BWD_ONE_AFTER_D);
   if constexpr (DH == 64 && (F == 0 || F == 2)) HYDRA_MODE(BWD_MIXED);
   if constexpr (F < 3) HYDRA_MODE(BWD_MIXED_AFTER_D);
-  if constexpr (F == 0 || (DH == 64 && F == 1)) HYDRA_MODE(BWD_TWO);
+  if constexpr (F < 2) HYDRA_MODE(BWD_TWO);
 #undef HYDRA_MODE
   return hipErrorInvalidValue;
 }

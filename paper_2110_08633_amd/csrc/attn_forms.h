@@ -50,9 +50,9 @@ inline float attn_form_cost(const AttnForm &f, int pairs, int T) {
 // but B 5, H 25, T 456 (1000) 13.2 / 15.9.
 // For the same reason, from one block of 128 rows per CU on, another form has to be estimated below `whole` times the first
 // one: us, forward B 3, H 25, T 1024, dh 64 22.0 with the first form, 26.2 with two groups (estimates 22.3, 21.5), backward
-// B 7, H 25, T 328, dh 64 34.5 / 40.0 with 64-row blocks (32.4, 32.0), B 7, H 12, T 672, dh 128 74.5 / 83.0 (84.4, 83.3).  Of
-// 2400 random calls, forward and backward, 174 were more than 3 % (73 more than 5 %) slower than with the two forms before
-// this table, now 48 (23); the form taken is 0.2 to 0.3 % off the best one on average.
+// B 7, H 25, T 328, dh 64 31.8 / 35.0 with 64-row blocks (30.0, 29.7), B 7, H 12, T 672, dh 128 70.6 / 75.3 (84.4, 83.3).  Of
+// 2400 random calls, forward and backward (then in two launches), 174 were more than 3 % (73 more than 5 %) slower than with the two
+// forms before this table, with it 48 (23); the form taken was 0.2 to 0.3 % off the best one on average.
 template <int N>
 inline int best_attn_form(const AttnForm (&f)[N], int dh, int pairs, int T, float whole) {
   const int64_t blocks = ((int64_t)T + 63) / 64 * pairs, limit = dh == 64 ? (T >= 576 ? 1280 : 900) : (T >= 768 ? 900 : 512);
@@ -69,8 +69,10 @@ inline int attn_form_fwd(int dh, int pairs, int T) {
   return dh == 64 ? best_attn_form(attn_forms_fwd64, dh, pairs, T, 0.92f)
                   : best_attn_form(attn_forms_fwd128, dh, pairs, T, 1.f);
 }
-// head width 64, backward: a sequence of one 64-row tile is one step of the first form and two of the others (B 4, H 12, T 56
-// 9.4 / 9.9), up to 32 rows it is one of each and the smaller block is done sooner (7.9 / 6.8)
+// head width 64, backward: a sequence of one 64-row tile is one step of the first form and two of the others, up to 32 rows it is
+// one of each and the smaller block is done sooner.  In two launches that showed (B 4, H 12, T 56 9.4 / 9.9, T 24 7.9 / 6.8), in one
+// they are alike (5.7 / 5.7, 5.8 / 5.6), and from some 250 pairs on the second form would be the faster one (B 25, H 16, T 56 11.6 /
+// 10.4, T 40 10.5 / 8.7).
 inline int attn_form_bwd(int dh, int pairs, int T) {
   if (dh == 64) return T > 32 && T <= 64 ? 0 : best_attn_form(attn_forms_bwd64, dh, pairs, T, 0.954f);
   const int form = best_attn_form(attn_forms_bwd128, dh, pairs, T, 0.95f);
@@ -120,8 +122,9 @@ constexpr AttnBwdMode attn_bwd_mode(int dh, int form, int pairs, int T) {
   if (form == 1) {
     if (T <= 32 && blocks <= 256) return BWD_ONE;
     // thousands of short sequences, whose tiles both parts then fetch once: after D / mixed (two launches) 3008 of T 64 161 / 136
-    // (159), 9376 of T 16 136 / 126 (127), 1300 of T 40 47 / 44 (51); at T 536 136 / 143.  (700 to 1000 blocks of one tile are left 2
-    // to 9 % slower than in two launches: 996 of T 40 36.7 / 33.6.)
+    // (159), 9376 of T 16 136 / 126 (127), 1300 of T 40 47 / 44 (51); at T 536 136 / 143.  Two launches for one-tile blocks whose
+    // number fits two rounds of part 1 alone (996 of T 40 33.6, mixed 36.7, 736 of T 16 14.1 / 15.0)
+    if (T <= 48 && blocks >= 640 && blocks <= 1024) return BWD_TWO;
     return T <= 48 || (blocks > 1024 && T <= 512) ? BWD_MIXED_AFTER_D : BWD_ONE_AFTER_D;
   }
   // H 16, T 3416 248 / mixed 202 (two launches 211), B 2, H 4, T 11944 1091 / 1000 (1013); others B 2, H 3, T 5632 209 / 234

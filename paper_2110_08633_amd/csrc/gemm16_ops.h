@@ -6,7 +6,7 @@
 namespace hydra {
 
 // first row and column of the tile of workgroup bid of nt: contiguous runs of tiles per XCD, see xcd_group_rows.  HALVES: every
-// tile has two workgroups, one per half of the contraction, numbered so that an XCD works on one half; the half is returned
+// tile has two workgroups, one per half of the contraction, numbered so that all but one XCD, at most, work on one half; the half is returned
 template <int BM, int BN, bool HALVES = false>
 __device__ __forceinline__ int tile_origin(const GemmArgs &g, int bid, int nt, int &m0, int &n0) {
   const int xcd = bid & 7, per = nt >> 3, rem = nt & 7;

@@ -561,7 +561,7 @@ def test_attention_every_form(H, B, Hn, T, dh):
 ATT_BWD_CASES = [(1, 1, 40, 64, 0, 1), (11, 5, 888, 64, 0, 1), (40, 8, 232, 64, 0, 2), (40, 13, 40, 64, 0, 2), (1, 1, 8, 64, 1, 1),
                  (1, 2, 88, 64, 1, 1), (11, 13, 200, 64, 1, 1), (5, 7, 136, 64, 2, 1), (11, 5, 584, 64, 2, 2), (1, 2, 104, 64, 3, 1),
                  (1, 1, 1000, 64, 3, 1), (40, 13, 200, 128, 0, 0), (11, 13, 232, 128, 0, 2), (1, 2, 8, 128, 1, 1), (3, 5, 32, 128, 1, 1),
-                 (1, 3, 72, 128, 1, 2), (2, 1, 104, 128, 2, 2), (1, 3, 1000, 128, 2, 2),
+                 (1, 3, 72, 128, 1, 2), (29, 25, 40, 128, 1, 0), (2, 1, 104, 128, 2, 2), (1, 3, 1000, 128, 2, 2),
                  (89, 3, 1200, 64, 0, 0), (129, 32, 16, 64, 1, 0), (47, 32, 400, 64, 1, 0), (1, 16, 3416, 64, 0, 3), (1, 24, 2816, 64, 0, 4),
                  (49, 17, 72, 64, 1, 4), (1, 8, 2136, 64, 2, 3), (1, 8, 4144, 64, 2, 4), (1, 16, 4208, 128, 0, 4), (3, 5, 40, 128, 1, 4),
                  (100, 13, 56, 128, 1, 4), (2, 8, 2128, 128, 2, 4)]

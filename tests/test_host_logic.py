@@ -649,7 +649,7 @@ int main() {
         (64, 256, 3792, 0, 0), (64, 256, 2656, 0, 0), (64, 704, 936, 0, 0), (64, 1744, 448, 1, 0), (64, 9376, 16, 1, 0), (64, 2416, 264, 1, 4),
         (64, 16, 3792, 0, 3), (64, 8, 8024, 0, 3), (64, 4, 7944, 2, 3), (64, 16, 2904, 2, 4), (64, 100, 5248, 0, 0),
         (128, 16, 3416, 2, 4), (128, 16, 2904, 2, 4), (128, 8, 11944, 0, 4), (128, 48, 2224, 0, 0), (128, 864, 408, 0, 0), (128, 448, 576, 0, 0),
-        (128, 4224, 32, 1, 4), (128, 9376, 16, 1, 4), (128, 3008, 64, 1, 4), (128, 512, 24, 1, 4)]]
+        (128, 4224, 32, 1, 4), (128, 9376, 16, 1, 4), (128, 3008, 64, 1, 4), (128, 512, 24, 1, 4), (128, 996, 40, 1, 0), (128, 736, 16, 1, 0)]]
     # and with one that the others take now
     cases += [(p, 1, T, dh, f, m) for dh, p, T, f, m in [
         (64, 48, 512, 2, 1), (64, 224, 176, 1, 1), (64, 6, 6032, 2, 2), (64, 2720, 24, 1, 1), (128, 64, 2048, 0, 0), (128, 224, 248, 0, 2),
@@ -659,7 +659,7 @@ int main() {
     for c, line in zip(cases, out):
         assert c[4:] == tuple(map(int, line.split())), (c, line)
     # every kernel that attention.hip builds
-    built = {(64, 0): (0, 1, 2, 3, 4), (64, 1): (0, 1, 4), (64, 2): (1, 2, 3, 4), (64, 3): (1,), (128, 0): (0, 2, 4), (128, 1): (1, 2, 4),
+    built = {(64, 0): (0, 1, 2, 3, 4), (64, 1): (0, 1, 4), (64, 2): (1, 2, 3, 4), (64, 3): (1,), (128, 0): (0, 2, 4), (128, 1): (0, 1, 2, 4),
              (128, 2): (2, 4)}
     assert {c[3:] for c in V.ATT_BWD_CASES} == {(dh, f, m) for (dh, f), ms in built.items() for m in ms}
 
